@@ -402,6 +402,39 @@ int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K)
     return NGEMM_KERNEL_TILE_64;
 }
 
+// Pack and column sums.  kbytes: bytes of a column that exist, Kp: bytes of a packed one.
+// Columns of up to 2 KiB: one workgroup of 512 threads per panel walks the whole column, so the sums are
+// stored and no launch has to clear them (us, against parts of 512 bytes with a clearing launch: 64 x 64
+// 5.4 -> 3.9, 768 x 768 5.9 -> 4.1, 4096 columns of 2048 7.8 -> 6.9).  Longer columns: workgroups of 256
+// threads, sums added to cleared memory; parts of one block (512 bytes) for the 8-bit operand (4096 columns of
+// 4096: 9.9 against 10.5 with two), of two for the 16-bit one, the second on its way while the first is turned
+// (4096 columns of 8192 bytes 13.7 against 16.0).  A workgroup per whole long column leaves compute units idle
+// (1024 columns of 8192 bytes: 17 us in the place of 8).
+template <int ELEM, int NT, int PER>
+ngemm_status launch_pack_blocks(const uint8_t *B, int64_t ldb_bytes, int64_t kbytes, int64_t N, int64_t Kp, int64_t Np, uint32_t b_xor,
+                                uint8_t *packed, int32_t *colsum, hipStream_t st)
+{
+    constexpr int KB = 2 * NT;
+    const int64_t panels = Np / 32, nblocks = (Kp + KB - 1) / KB, nparts = (nblocks + PER - 1) / PER;
+    if (panels * nparts > 0x7fffffff) return NGEMM_ERR_BAD_SHAPE;
+    if (nparts != 1) {                               // several parts add up, and K = 0 has no block that would store
+        hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)((Np + 255) / 256)), dim3(256), 0, st, colsum, (int)Np);
+        if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
+        if (nparts == 0) return NGEMM_OK;
+    }
+    hipLaunchKernelGGL((pack_b_kernel<NT, ELEM, PER>), dim3((unsigned)(panels * nparts)), dim3(NT), 0, st, B, ldb_bytes, kbytes, (int)N,
+                       (int)(Kp / 32), (int)nblocks, (int)nparts, b_xor, packed, colsum);
+    return hipGetLastError() == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+}
+
+template <int ELEM>
+ngemm_status launch_pack(const uint8_t *B, int64_t ldb_bytes, int64_t kbytes, int64_t N, int64_t Kp, int64_t Np, uint32_t b_xor,
+                         uint8_t *packed, int32_t *colsum, hipStream_t st)
+{
+    if (Kp <= 2048) return launch_pack_blocks<ELEM, 512, 2>(B, ldb_bytes, kbytes, N, Kp, Np, b_xor, packed, colsum, st);
+    return launch_pack_blocks<ELEM, 256, ELEM>(B, ldb_bytes, kbytes, N, Kp, Np, b_xor, packed, colsum, st);
+}
+
 int workgroup_budget(const ngemm_ctx *ctx)
 {
     const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
@@ -837,16 +870,9 @@ static ngemm_status pack_common(ngemm_ctx *ctx, int64_t K, int64_t N, const int8
         if (!g.ok) { delete d; return NGEMM_ERR_DEVICE; }
         hipStream_t st = (hipStream_t)hip_stream;
         int32_t *colsum = (int32_t *)((uint8_t *)packed_dev + Kp * Np);
-        hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)((Np + 255) / 256)), dim3(256), 0, st, colsum, (int)Np);
-        if (hipGetLastError() != hipSuccess) { delete d; return NGEMM_ERR_DEVICE; }
-        if (Kp > 0) {
-            const int64_t kblocks = (Kp + kPackKBytes - 1) / kPackKBytes;
-            const int64_t nwg = (Np / 32) * kblocks;
-            if (nwg > 0x7fffffff) { delete d; return NGEMM_ERR_BAD_SHAPE; }
-            hipLaunchKernelGGL(pack_b_kernel, dim3((unsigned)nwg), dim3(256), 0, st, B_dev, ldb, (int)K, (int)N,
-                               (int)Kp, (int)kblocks, b_shift ? 0x80808080u : 0u, (uint8_t *)packed_dev, colsum);
-            if (hipGetLastError() != hipSuccess) { delete d; return NGEMM_ERR_DEVICE; }
-        }
+        const ngemm_status ls = launch_pack<1>((const uint8_t *)B_dev, ldb, K, N, Kp, Np, b_shift ? 0x80808080u : 0u,
+                                               (uint8_t *)packed_dev, colsum, st);
+        if (ls != NGEMM_OK) { delete d; return ls; }
     }
     *out = d;
     return NGEMM_OK;
@@ -996,18 +1022,8 @@ ngemm_status ngemm_pack_b_s16(ngemm_ctx *ctx, int64_t K, int64_t N, const int16_
         if (!g.ok) { delete d; return NGEMM_ERR_DEVICE; }
         hipStream_t st = (hipStream_t)hip_stream;
         int32_t *colsum = (int32_t *)((uint8_t *)packed_dev + Kp * Np);
-        hipLaunchKernelGGL(rowsum_s16_kernel, dim3((unsigned)((Np + 3) / 4)), dim3(256), 0, st, B_dev, ldb, (int)N,
-                           (int)Np, (int)K, colsum);
-        if (hipGetLastError() != hipSuccess) { delete d; return NGEMM_ERR_DEVICE; }
-        if (Kp > 0) {
-            const int64_t nslices = Kp / 64;                       // 32-element slices
-            const int64_t nchunks = (Np / 32) * nslices * 64;
-            const int64_t nwg = (nchunks + 255) / 256;
-            if (nwg > 0x7fffffff) { delete d; return NGEMM_ERR_BAD_SHAPE; }
-            hipLaunchKernelGGL(pack_b_s16_kernel, dim3((unsigned)nwg), dim3(256), 0, st, B_dev, ldb, (int)K, (int)N,
-                               (int)nslices, nchunks, (uint8_t *)packed_dev);
-            if (hipGetLastError() != hipSuccess) { delete d; return NGEMM_ERR_DEVICE; }
-        }
+        const ngemm_status ls = launch_pack<2>((const uint8_t *)B_dev, 2 * ldb, 2 * K, N, Kp, Np, 0u, (uint8_t *)packed_dev, colsum, st);
+        if (ls != NGEMM_OK) { delete d; return ls; }
     }
     *out = d;
     return NGEMM_OK;

@@ -72,16 +72,68 @@ __device__ __forceinline__ v4i load16_any(const uint8_t *p)
     return v;
 }
 
-// First `valid` (0..15) bytes of a 16-byte chunk, the rest zero; never reads past p + valid.
+// First `valid` (0..15) bytes of NC 16-byte chunks `step` bytes apart, the rest zero; never reads outside
+// [p, p + valid) of a chunk.  Two overlapping loads of 8 (4) bytes, the second one ending with the last valid
+// byte and shifted down to where it belongs, in the place of a load per byte; the chunks' loads are independent.
+template <int NC>
+__device__ __forceinline__ void load16_partials(const uint8_t *p, int64_t step, int valid, v4i (&v)[NC])
+{
+    uint64_t lo[NC], hi[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) lo[i] = hi[i] = 0;
+    if (valid >= 8) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            __builtin_memcpy(&lo[i], p + i * step, 8);
+            __builtin_memcpy(&hi[i], p + i * step + valid - 8, 8);
+        }
+        // bytes 8 .. valid - 1 are the upper valid - 8 bytes of the second load
+#pragma unroll
+        for (int i = 0; i < NC; ++i) hi[i] = valid > 8 ? hi[i] >> (8 * (16 - valid)) : 0;
+    } else if (valid >= 4) {
+        uint32_t a[NC], b[NC];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            __builtin_memcpy(&a[i], p + i * step, 4);
+            __builtin_memcpy(&b[i], p + i * step + valid - 4, 4);
+        }
+#pragma unroll
+        for (int i = 0; i < NC; ++i) lo[i] = (uint64_t)a[i] | (uint64_t)b[i] << (8 * (valid - 4));
+    } else if (valid > 0) {
+        // bytes 0, valid / 2 and valid - 1: all there are
+        uint32_t a[NC], b[NC], c[NC];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            a[i] = p[i * step];
+            b[i] = p[i * step + (valid >> 1)];
+            c[i] = p[i * step + valid - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < NC; ++i) lo[i] = a[i] | b[i] << (8 * (valid >> 1)) | c[i] << (8 * (valid - 1));
+    }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        v[i].x = (int)(uint32_t)lo[i]; v[i].y = (int)(uint32_t)(lo[i] >> 32);
+        v[i].z = (int)(uint32_t)hi[i]; v[i].w = (int)(uint32_t)(hi[i] >> 32);
+    }
+}
 __device__ __forceinline__ v4i load16_partial(const uint8_t *p, int valid)
 {
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    v4i v[1];
+    load16_partials<1>(p, 0, valid, v);
+    return v[0];
+}
+
+// All ones in the bytes of a 16-byte chunk from byte n (0..16) on, zero before it.
+__device__ __forceinline__ v4i bytes_from(int n)
+{
+    v4i m;
 #pragma unroll
-    for (int b = 0; b < 16; ++b)
-        if (b < valid) w[b >> 2] |= (uint32_t)p[b] << (8 * (b & 3));
-    v4i v;
-    v.x = (int)w[0]; v.y = (int)w[1]; v.z = (int)w[2]; v.w = (int)w[3];
-    return v;
+    for (int q = 0; q < 4; ++q) {
+        const int vb = n - 4 * q;
+        m[q] = vb <= 0 ? -1 : (vb >= 4 ? 0 : (int)(0xffffffffu << (8 * vb)));
+    }
+    return m;
 }
 
 // u8 -> s8 shift of 16 packed bytes: a xor 0x80 == a - 128 read as signed (mask 0x80808080);
@@ -167,15 +219,17 @@ __device__ __forceinline__ int wave_sum(int v)
 }
 
 // ---- pack: column-major B -> fragment order, zero padded, with column sums --------------------
-// One workgroup per (32-column panel, 512 bytes of K = 16 fragments).  Global reads follow the
-// columns (32 consecutive lanes read 512 contiguous bytes of one column), the block is turned
-// in LDS (row pitch 512 + 16 bytes: conflict-free both ways), and the 16 KiB of fragments leave as
-// one contiguous run.  Column sums: every 16-byte chunk is summed with a dot-product-with-ones,
-// the 32 lanes sharing a column are added across lanes (the one horizontal reduction of the
-// path; Sec. 2.1 phase 3) and one integer atomic per column and workgroup goes to colsum, which
-// zero_i32_kernel has cleared beforehand (integer adds: the result does not depend on the order).
-constexpr int kPackKBytes = 512;
-
+// One workgroup per (32-column panel, part of K); it walks its part in blocks of 2 * NT bytes of K per
+// column.  Global reads follow the columns (consecutive lanes read one column's contiguous bytes), the
+// block is turned in LDS (row pitch + 16 bytes: conflict-free both ways) while the next one is on its way
+// from memory, and its fragments leave as one contiguous run.  Column sums: a thread holds chunks of the
+// same four columns in every block, so it adds up its bytes over all of them (a dot product with ones per
+// word); the threads that share a column are added across lanes once at the end (the one horizontal
+// reduction of the path; Sec. 2.1 phase 3).  A part that covers all of K stores the sums; with several
+// parts each adds its share to colsum, which zero_i32_kernel has cleared beforehand (integer adds: the
+// result does not depend on the order).
+// ELEM = 1: 8-bit operand; ELEM = 2: int16 operand, separated into its byte planes on the way out of LDS
+// (see the 16-bit section), column sums of b - 128.
 __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t *__restrict__ dst, int n)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -194,56 +248,134 @@ __global__ __launch_bounds__(256) void zero_c_kernel(int32_t *__restrict__ C, in
         if (col + t < N) dst[t] = 0;
 }
 
-__global__ __launch_bounds__(256) void pack_b_kernel(const int8_t *__restrict__ B, int64_t ldb, int K, int N,
-                                                     int Kp, int kblocks, uint32_t b_xor,
-                                                     uint8_t *__restrict__ packed, int32_t *__restrict__ colsum)
+// kbytes: bytes of a column that exist (K * ELEM); nblocks: blocks of 2 * NT bytes in a padded column;
+// a part takes PER of them.
+template <int NT, int ELEM, int PER>
+__global__ __launch_bounds__(NT) void pack_b_kernel(const uint8_t *__restrict__ B, int64_t ldb_bytes, int64_t kbytes, int N,
+                                                    int nfrag, int nblocks, int nparts, uint32_t b_xor,
+                                                    uint8_t *__restrict__ packed, int32_t *__restrict__ colsum)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t turn[32 * (kPackKBytes + 16)];
+    constexpr int KB = 2 * NT, CPC = KB / 16, PITCH = KB + 16;      // bytes of K per block, chunks per column
+    constexpr int NCOL = NT / CPC;                                  // columns the threads cover at a time (8)
+    __shared__ __attribute__((aligned(16))) uint8_t turn[32 * PITCH];
     const int tid = threadIdx.x;
-    const int pnl = blockIdx.x / kblocks, kblk = blockIdx.x % kblocks;
-    const int nslices = Kp / 32;
-    const int k_base = kblk * kPackKBytes;
+    const int pnl = blockIdx.x / nparts, part = blockIdx.x - pnl * nparts;
+    const int kc = tid % CPC, jl = tid / CPC;                       // this thread's chunk and (first) column of a block
+    const int blk0 = part * PER, blk1 = blk0 + PER < nblocks ? blk0 + PER : nblocks;
+
+    const uint8_t *src0 = B + ((int64_t)pnl * 32 + jl) * ldb_bytes + kc * 16;
+    const bool all_cols = (int64_t)pnl * 32 + 32 <= N;
+    v4i v[4];
+    auto load = [&](int blk) {
+        const uint8_t *src = src0 + (int64_t)blk * KB;
+        if (all_cols && (int64_t)(blk + 1) * KB <= kbytes) {        // the block lies inside the matrix: no tests
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid + 256 * i;                     // chunk: column c/32 of the panel, k-chunk c%32
-        const int jl = c >> 5, kc = c & 31;
-        const int j = pnl * 32 + jl, k0 = k_base + kc * 16;
-        v4i v = {0, 0, 0, 0};
-        if (j < N && k0 < K) {
-            const uint8_t *src = (const uint8_t *)B + (int64_t)j * ldb + k0;
-            v = (k0 + 16 <= K) ? load16_any(src) : load16_partial(src, K - k0);
-            if (b_xor) {
-                // unsigned B: shift the bytes that exist to signed; the padding stays zero
-                const int nb = K - k0;
-                int *w = (int *)&v;
+            for (int i = 0; i < 4; ++i) {
+                v[i] = load16_any(src);
+                if (ELEM == 1) v[i] = shift_u8_to_s8(v[i], b_xor);
+                src += NCOL * ldb_bytes;
+            }
+        } else {
+            const int64_t left = kbytes - ((int64_t)blk * KB + kc * 16);
+            const int ncols = (N - (pnl * 32 + jl) + NCOL - 1) / NCOL;      // of this thread's four, those that exist
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int vb = nb - 4 * q;
-                    const uint32_t m = vb >= 4 ? 0xffffffffu : (vb <= 0 ? 0u : (1u << (8 * vb)) - 1u);
-                    w[q] ^= (int)(b_xor & m);
+            for (int i = 0; i < 4; ++i) v[i] = v4i{0, 0, 0, 0};
+            if (left >= 16) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i < ncols) v[i] = load16_any(src + i * NCOL * ldb_bytes);
+            } else if (left > 0) {                      // the end of the columns
+                if (ncols >= 4) {
+                    load16_partials<4>(src, NCOL * ldb_bytes, (int)left, v);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (i < ncols) v[i] = load16_partial(src + i * NCOL * ldb_bytes, (int)left);
+                }
+            }
+            if (ELEM == 1 && b_xor && left > 0) {       // unsigned B: the bytes that exist are shifted, the padding stays zero
+                const v4i keep = left >= 16 ? v4i{-1, -1, -1, -1} : ~bytes_from((int)left);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i < ncols) v[i] = shift_u8_to_s8(v[i], b_xor) & keep;
+            }
+        }
+    };
+    // ELEM = 2: the sums are of b - 128; 128 for every element of this part of a column that exists
+    const int64_t mine = (kbytes < (int64_t)blk1 * KB ? kbytes : (int64_t)blk1 * KB) - (int64_t)blk0 * KB;
+    const uint32_t shift = ELEM == 2 && mine > 0 ? (uint32_t)(64 * mine) : 0u;
+    int sum[4] = {0, 0, 0, 0};
+    load(blk0);
+#pragma unroll 1
+    for (int blk = blk0; blk < (PER == 1 ? blk0 + 1 : blk1); ++blk) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (ELEM == 1) {
+                sum[i] = __builtin_amdgcn_sdot4(v[i].x, 0x01010101, sum[i], false);
+                sum[i] = __builtin_amdgcn_sdot4(v[i].y, 0x01010101, sum[i], false);
+                sum[i] = __builtin_amdgcn_sdot4(v[i].z, 0x01010101, sum[i], false);
+                sum[i] = __builtin_amdgcn_sdot4(v[i].w, 0x01010101, sum[i], false);
+            } else {
+                const int *w = (const int *)&v[i];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sum[i] += (int)(int16_t)(w[q] & 0xffff) + (w[q] >> 16);
+            }
+            *(v4i *)(turn + (jl + NCOL * i) * PITCH + kc * 16) = v[i];
+            if (PER == 1 || blk + 1 == blk1) {
+                // the sum is complete: added up over the CPC consecutive threads that share the column and sent,
+                // while the next column's chunk is still on its way and ahead of the last block's fragments
+                static_assert(CPC <= 64, "the threads of a column lie in one wavefront");
+                int s = sum[i];
+#pragma unroll
+                for (int off = CPC / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+                if (kc == 0) {
+                    const int j = pnl * 32 + jl + NCOL * i;
+                    const int32_t t = j < N ? (int32_t)((uint32_t)s - shift) : 0;
+                    if (nparts == 1) colsum[j] = t;
+                    else if (t != 0) atomicAdd(colsum + j, t);
                 }
             }
         }
-        *(v4i *)(turn + jl * (kPackKBytes + 16) + kc * 16) = v;
-        // column sum of this chunk, then over the 32 lanes that hold the same column
-        int s = __builtin_amdgcn_sdot4(v.x, 0x01010101, 0, false);
-        s = __builtin_amdgcn_sdot4(v.y, 0x01010101, s, false);
-        s = __builtin_amdgcn_sdot4(v.z, 0x01010101, s, false);
-        s = __builtin_amdgcn_sdot4(v.w, 0x01010101, s, false);
+        __syncthreads();
+        if (PER > 1 && blk + 1 < blk1) load(blk + 1);
+        if (ELEM == 1) {
 #pragma unroll
-        for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        if ((tid & 31) == 0 && j < N && s != 0) atomicAdd(colsum + j, s);
-    }
-    __syncthreads();
+            for (int i = 0; i < 4; ++i) {
+                const int o = tid + NT * i;                     // output chunk: fragment o/64 of the block, lane o%64
+                const int s = o >> 6, l = o & 63;
+                const int slice = blk * (KB / 32) + s;
+                if (slice < nfrag) {
+                    const v4i f = *(const v4i *)(turn + (l & 31) * PITCH + (2 * s + (l >> 5)) * 16);
+                    *(v4i *)(packed + ((int64_t)pnl * nfrag + slice) * kFragBytes + l * 16) = f;
+                }
+            }
+        } else {
+            const int64_t K = kbytes / 2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int o = tid + 256 * i;                     // output chunk: fragment o/64 of the block, lane o%64
-        const int s = o >> 6, l = o & 63;
-        const int slice = kblk * (kPackKBytes / 32) + s;
-        if (slice < nslices) {
-            const v4i v = *(const v4i *)(turn + (l & 31) * (kPackKBytes + 16) + (2 * s + (l >> 5)) * 16);
-            *(v4i *)(packed + ((int64_t)pnl * nslices + slice) * kFragBytes + l * 16) = v;
+            for (int i = 0; i < 2; ++i) {
+                const int o = tid + NT * i;                     // lane o%64 of both planes of slice o/64 of the block
+                const int s = o >> 6, l = o & 63;
+                const int slice = blk * (KB / 64) + s;
+                if (2 * slice < nfrag) {
+                    const uint8_t *src = turn + (l & 31) * PITCH + (4 * s + 2 * (l >> 5)) * 16;
+                    const v4i c[2] = {*(const v4i *)src, *(const v4i *)(src + 16)};
+                    const int64_t left = K - ((int64_t)slice * 32 + 16 * (l >> 5));      // elements that exist
+                    const int nb = pnl * 32 + (l & 31) < N ? (int)(left < 0 ? 0 : left < 16 ? left : 16) : 0;
+                    v4i h, w;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t lo = (uint32_t)c[q >> 1][2 * (q & 1)], hi = (uint32_t)c[q >> 1][2 * (q & 1) + 1];
+                        h[q] = (int)__builtin_amdgcn_perm(hi, lo, 0x07050301u);
+                        w[q] = (int)(__builtin_amdgcn_perm(hi, lo, 0x06040200u) ^ 0x80808080u);
+                    }
+                    if (nb < 16) w &= ~bytes_from(nb);      // the padding of the low plane stays zero
+                    uint8_t *dst = packed + ((int64_t)pnl * nfrag + 2 * slice) * kFragBytes + l * 16;
+                    *(v4i *)dst = h;
+                    *(v4i *)(dst + kFragBytes) = w;
+                }
+            }
         }
+        if (PER > 1) __syncthreads();                           // the block has left LDS
     }
 }
 
@@ -2213,38 +2345,6 @@ __global__ __launch_bounds__(256) void rowsum_s16_kernel(const int16_t *__restri
     }
     s = wave_sum(s);
     if (lane == 0) out[i] = s;
-}
-
-// Pack of the int16 operand.  One thread per (panel, 32-element slice, lane of the fragment): it reads
-// its 16 elements and writes 16 bytes into each plane.
-__global__ __launch_bounds__(256) void pack_b_s16_kernel(const int16_t *__restrict__ B, int64_t ldb, int K, int N,
-                                                         int nslices, int64_t nchunks, uint8_t *__restrict__ packed)
-{
-    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= nchunks) return;
-    const int l = (int)(id & 63);
-    const int64_t f = id >> 6;                           // (panel, slice)
-    const int s = (int)(f % nslices);
-    const int64_t pnl = f / nslices;
-    const int64_t j = pnl * 32 + (l & 31);
-    const int k0 = s * 32 + (l >> 5) * 16;
-    uint32_t hi[4] = {0u, 0u, 0u, 0u}, lo[4] = {0u, 0u, 0u, 0u};
-    if (j < N) {
-        const int16_t *src = B + j * ldb + k0;
-#pragma unroll
-        for (int n = 0; n < 16; ++n)
-            if (k0 + n < K) {
-                const uint32_t v = (uint32_t)(uint16_t)src[n];
-                hi[n >> 2] |= (v >> 8) << (8 * (n & 3));
-                lo[n >> 2] |= ((v & 255u) ^ 0x80u) << (8 * (n & 3));
-            }
-    }
-    v4i h, w;
-    h.x = (int)hi[0]; h.y = (int)hi[1]; h.z = (int)hi[2]; h.w = (int)hi[3];
-    w.x = (int)lo[0]; w.y = (int)lo[1]; w.z = (int)lo[2]; w.w = (int)lo[3];
-    uint8_t *dst = packed + (f * 2) * kFragBytes + l * 16;
-    *(v4i *)dst = h;
-    *(v4i *)(dst + kFragBytes) = w;
 }
 
 struct S16Cfg {
