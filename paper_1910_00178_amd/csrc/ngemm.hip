@@ -435,6 +435,36 @@ ngemm_status launch_pack(const uint8_t *B, int64_t ldb_bytes, int64_t kbytes, in
     return launch_pack_blocks<ELEM, 256, ELEM>(B, ldb_bytes, kbytes, N, Kp, Np, b_xor, packed, colsum, st);
 }
 
+// Forms of the kernel that splits K over a workgroup's wavefronts (gemm_wavek_kernel): tile in units of
+// 32 x 32, wavefronts, ring depth.
+template <int TM_, int TN_, int NW_, int RING_>
+struct WaveKForm {
+    static constexpr int TM = TM_, TN = TN_, NW = NW_, RING = RING_;
+};
+using WaveK11 = WaveKForm<1, 1, 4, 4>;       // 64 KiB of LDS: two workgroups per compute unit
+using WaveK12 = WaveKForm<1, 2, 4, 3>;       // 72 KiB
+using WaveK22 = WaveKForm<2, 2, 2, 4>;       // 64 KiB
+
+template <class F, int ELEM, bool REQUANT, bool ROWS>
+hipError_t launch_wavek(const GemmParams &p0, hipStream_t st)
+{
+    GemmParams p = p0;
+    p.tiles_m = (p.M + F::TM * 32 - 1) / (F::TM * 32);
+    p.tiles_n = (p.N + F::TN * 32 - 1) / (F::TN * 32);
+    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
+                       dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, p);
+    return hipGetLastError();
+}
+
+template <class F, int ELEM, bool REQUANT, bool ROWS>
+hipError_t allow_big_lds_wavek()
+{
+    constexpr int lds = WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes;
+    if (lds <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute((const void *)gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+}
+
 int workgroup_budget(const ngemm_ctx *ctx)
 {
     const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
@@ -709,7 +739,8 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
             hipFuncSetAttribute((const void *)gemm_tile_x64_kernel<false, true, true, 6>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 X64Cfg::kLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void *)gemm_s16_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                S16Cfg::kLdsBytes) != hipSuccess) {
+                                S16Cfg::kLdsBytes) != hipSuccess ||
+            allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess) {
             delete c;
             return NGEMM_ERR_DEVICE;
         }
@@ -1059,24 +1090,41 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     p.ldc = ldc;
     p.M = (int)M; p.N = (int)B->N; p.K = (int)B->K; p.Kp = (int)B->Kp;
     p.npanels = (int)(B->Np / 32);
-    p.tiles_m = (int)((M + 127) / 128);
-    p.tiles_n = (int)((B->N + 127) / 128);
     // sum (a-za)(b-zb) = sum (a-128)(b-128) + (128-za) colsum'[j] - (zb-128) rowsum'[i] - (zb-128)(128-za) K
     p.za_term = (uint32_t)(128 - a_zero_point);
     p.zb = (uint32_t)(b_zero_point - 128);
     p.kconst = 0u - (uint32_t)(b_zero_point - 128) * (uint32_t)(128 - a_zero_point) * (uint32_t)B->K;
     p.nxcd = ctx->num_xcd;
-    if (B->K > 0) {
+    // Small outputs run the kernel that splits K over a workgroup's wavefronts (no row-sum launch, tiles small
+    // enough to spread over the compute units): 32 x 32 tiles while there is a compute unit for each, 32 x 64 up
+    // to two per unit, 64 x 64 up to two per unit while 128 x 128 tiles would fill less than half of the units;
+    // larger ones, and what a K of less than two stages leaves to them, the 128 x 128 kernel.  us, against the
+    // 128 x 128 kernel: 16 x 4096 x 4096 8.9 / 47, 64 x 4096 x 4096 10.6 / 47, 512 x 768 x 768 5.9 / 15.5,
+    // 1024^3 10.5 / 18.9, 512 x 3072 x 768 11.6 / 16.7, 1024 x 2048 x 1024 14.0 / 19.0, but 1024 x 3072 x 1024
+    // 24.8 / 19.6 and 1536^3 27 / 24.9.
+    const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((B->N + bn - 1) / bn); };
+    hipError_t e;
+    if (tiles(32, 32) <= cus) {
+        e = launch_wavek<WaveK11, 2, false, true>(p, st);
+    } else if (tiles(32, 64) <= 2 * cus) {
+        e = launch_wavek<WaveK12, 2, false, true>(p, st);
+    } else if (B->K < S16Cfg::kMinK || (tiles(64, 64) <= 2 * cus && tiles(128, 128) * 2 <= cus)) {
+        e = launch_wavek<WaveK22, 2, false, true>(p, st);
+    } else {
+        p.tiles_m = (int)((M + 127) / 128);
+        p.tiles_n = (int)((B->N + 127) / 128);
         int32_t *rs = (int32_t *)workspace_dev;
         hipLaunchKernelGGL(rowsum_s16_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, A_dev, lda, (int)M,
                            (int)M, (int)B->K, rs);
         if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
         p.rowsum = rs;
+        const int ntiles = p.tiles_m * p.tiles_n, budget = workgroup_budget(ctx);
+        hipLaunchKernelGGL(gemm_s16_tile_kernel, dim3((unsigned)(ntiles < budget ? ntiles : budget)), dim3(256),
+                           S16Cfg::kLdsBytes, st, p);
+        e = hipGetLastError();
     }
-    const int ntiles = p.tiles_m * p.tiles_n, budget = workgroup_budget(ctx);
-    hipLaunchKernelGGL(gemm_s16_tile_kernel, dim3((unsigned)(ntiles < budget ? ntiles : budget)), dim3(256),
-                       S16Cfg::kLdsBytes, st, p);
-    return hipGetLastError() == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+    return e == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
 }
 
 size_t ngemm_unpacked_workspace_bytes(int64_t M, int64_t N, int64_t K)

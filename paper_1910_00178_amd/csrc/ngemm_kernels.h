@@ -2355,6 +2355,7 @@ struct S16Cfg {
     static constexpr int kPatchRow = 64 * 4 + 16;          // epilogue patch: 16 rows of 64 int32, padded
     static constexpr int kPatchBytes = 16 * kPatchRow;     // per wavefront
     static constexpr int kLdsBytes = NSTAGE * kStageBytes;
+    static constexpr int kMinK = 128;                      // two full stages: the pipelined loop starts the sums
     static_assert(4 * kPatchBytes <= kLdsBytes, "epilogue patches fit the ring");
     static_assert((NSTAGE - 2) * kLoadsPerStage <= 63, "vmcnt range");
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
@@ -2465,7 +2466,7 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 
         if (tile != w) __syncthreads();                  // the previous tile's LDS traffic is over
 
-        if (nfull > 0) {
+        {                                                // K >= 128: there are at least two full stages
 #pragma unroll
             for (int s = 0; s < NSTAGE - 1; ++s)
 #pragma unroll
@@ -2517,10 +2518,8 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 
         // What is left of K: an odd last full stage and / or a partial one.  Guarded register loads of A,
         // the zero-padded planes of B (a slice the pack does not hold counts as zero), into the first
-        // buffer in the stage's layout; no pipelining.  Without a pipelined part (K < 128) the first of them
-        // starts the sums; K = 0 leaves a stage of zeros to do that.
-        bool started = nfull > 0;
-        for (int ts = nfull; ts < (nstages > 0 ? nstages : 1); ++ts) {
+        // buffer in the stage's layout; no pipelining.
+        for (int ts = nfull; ts < nstages; ++ts) {
             const int kbase = ts * 128;                  // bytes into a row of A
             __syncthreads();
 #pragma unroll
@@ -2540,14 +2539,8 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int wd = 0; wd < 4; ++wd) split_word(i, wd);
-            if (started) {
 #pragma unroll
-                for (int m = 0; m < 64; ++m) mma(IntC<0>{}, IntC<0>{}, m);
-            } else {
-#pragma unroll
-                for (int m = 0; m < 64; ++m) mma(IntC<0>{}, IntC<1>{}, m);
-            }
-            started = true;
+            for (int m = 0; m < 64; ++m) mma(IntC<0>{}, IntC<0>{}, m);
         }
 
         __syncthreads();                                 // every wavefront is done with the stage buffers
@@ -2625,6 +2618,315 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
                         }
                     }
                 }
+            }
+        }
+    }
+}
+
+// ---- small outputs: K split over the wavefronts of a workgroup ---------------------------------
+// For outputs of few tiles.  There every compute unit works on one tile, and what bounds the launch is the
+// unit's own path: bytes from L2, then bytes through LDS, then waits at barriers.  Here each of the NW
+// wavefronts computes the whole (32 TM) x (32 TN) tile over its own share of K (steps of 64 bytes, dealt out
+// in turn), so every byte that is copied into LDS is read from it once instead of twice, by the wavefront
+// that copied it: the rings are private and the main loop has no barrier.  The partial tiles meet in LDS at
+// the end, where every thread adds the NW values of four columns and finishes them: whole row pieces leave.
+// Small tiles (32 x 32, 32 x 64, 64 x 32) spread an output that has few of the larger ones over more compute
+// units.
+// ELEM = 1: 8-bit operands; a step is two matrix ops per block.  ELEM = 2: 16-bit operands in byte planes (see
+// the 16-bit section); a step is 32 elements: A's bytes are separated behind the LDS read, four matrix ops per
+// block into three accumulators (ah*bl' and al'*bh share a weight and a sum).
+// ROWS: the row sums a zero-point of B needs are added up from the fragments as they pass (no wavefront sums
+// what another one does, in contrast to the kernels whose wavefronts share rows).
+// Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
+// 4096 47 -> 8.7 (3.8 TB/s of B's planes), 64 x 4096 x 4096 47 -> 10.7, 512 x 768 x 768 15.5 -> 6.1, 1024^3
+// 18.9 -> 10.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
+// and 7.1 on the second and third of them.
+template <int TM, int TN, int NW, int RING>
+struct WaveKCfg {
+    static constexpr int kThreads = NW * 64;
+    static constexpr int kLoadsPerStep = 2 * (TM + TN);
+    static constexpr int kStepBytes = kLoadsPerStep * 1024;
+    static constexpr int kWaveBytes = RING * kStepBytes;
+    static constexpr int kPitch = TN * 32 + 4;             // int32 per row of a partial tile, padded
+    static constexpr int kPartBytes = TM * 32 * kPitch * 4;
+    static constexpr int kEpiBytes = NW * (kPartBytes + TM * 32 * 4);
+    static constexpr int kLdsBytes = NW * kWaveBytes > kEpiBytes ? NW * kWaveBytes : kEpiBytes;
+    static_assert((RING - 1) * kLoadsPerStep <= 63, "vmcnt range");
+    static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
+    static_assert(RING >= 3, "copies in flight");
+};
+
+// p.A / p.lda in bytes, rows 16-byte aligned; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
+// count tiles of 32 TM x 32 TN.
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS>
+__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
+{
+    using Cfg = WaveKCfg<TM, TN, NW, RING>;
+    constexpr int LPS = Cfg::kLoadsPerStep, NT = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nfrag = p.Kp / 32;                         // fragments per panel
+    const int kbytes = p.K * ELEM;
+    const int nfull = kbytes / 64;                       // full steps, all wavefronts together
+    const int cnt = nfull > wave ? (nfull - wave + NW - 1) / NW : 0;      // this wavefront's: wave, wave + NW, ...
+    int tm, tn;
+    tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
+    const int m0 = tm * (TM * 32), n0 = tn * (TN * 32);
+
+    // copies of a step: 16-row blocks of A (row t of the block, chunk c in slot 4 t + (c + t / 4) % 4), then
+    // the two fragments of each panel of B as they lie in the pack
+    const int t16 = lane >> 2, a_chunk = ((lane & 3) - (t16 >> 2)) & 3;
+    const uint8_t *a_src[2 * TM], *b_src[TN];
+#pragma unroll
+    for (int i = 0; i < 2 * TM; ++i) {
+        int grow = m0 + 16 * i + t16;
+        grow = grow < p.M ? grow : p.M - 1;              // rows past M: read a valid row, never stored
+        a_src[i] = p.A + (int64_t)grow * p.lda + a_chunk * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        int pnl = n0 / 32 + j;
+        pnl = pnl < p.npanels ? pnl : p.npanels - 1;     // panels past N: read a valid panel, never stored
+        b_src[j] = p.Bp + ((int64_t)pnl * nfrag) * kFragBytes + lane * 16;
+    }
+    uint8_t *ring = lds + wave * Cfg::kWaveBytes;
+    auto dma_step = [&](int t, int slot) {
+        const int g = (t < cnt ? t : cnt - 1) * NW + wave;       // past the end: a copy nobody reads
+        uint8_t *dst = ring + slot * Cfg::kStepBytes;
+#pragma unroll
+        for (int i = 0; i < 2 * TM; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + (int64_t)g * 64), (lptr_t)(dst + i * 1024), 16, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 2 * TN; ++j)
+            __builtin_amdgcn_global_load_lds((gptr_t)(b_src[j >> 1] + (int64_t)g * (2 * kFragBytes) + (j & 1) * kFragBytes),
+                                             (lptr_t)(dst + (2 * TM + j) * 1024), 16, 0, 0);
+    };
+    // fragments of a step: A block i, part x (8-bit: 32-byte half x of the step; 16-bit: chunk x of the lane's
+    // 32 bytes), B panel j, part x (half / plane)
+    v4i fa[2][TM][2], fb[2][TN][2];
+    int a_off[2];
+    {
+        const int r = lane & 31, t = r & 15, h = lane >> 5;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int c = ELEM == 1 ? 2 * x + h : 2 * h + x;
+            a_off[x] = (r >> 4) * 1024 + (4 * t + ((c + (t >> 2)) & 3)) * 16;
+        }
+    }
+    auto read_frags = [&](auto set, int slot) {
+        constexpr int S = decltype(set)::value;
+        const uint8_t *base = ring + slot * Cfg::kStepBytes;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[S][i][x] = *(const v4i *)(base + i * 2048 + a_off[x]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[S][j][x] = *(const v4i *)(base + (2 * TM + 2 * j + x) * 1024 + lane * 16);
+        }
+    };
+    v16i acc[NACC][TM][TN];
+#pragma unroll
+    for (int q = 0; q < NACC; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[q][i][j][r] = 0;
+    int rs[TM], rs_h[TM];                                // this lane's share of the row sums (16-bit: low, high planes)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) { rs[i] = 0; rs_h[i] = 0; }
+    auto dot = [](const v4i &a, int s) {
+        s = __builtin_amdgcn_sdot4(a.x, 0x01010101, s, false);
+        s = __builtin_amdgcn_sdot4(a.y, 0x01010101, s, false);
+        s = __builtin_amdgcn_sdot4(a.z, 0x01010101, s, false);
+        return __builtin_amdgcn_sdot4(a.w, 0x01010101, s, false);
+    };
+    // packed operand first: lane l of a result block holds, for row l % 32, the four consecutive columns
+    // 8 q + 4 (l / 32) .. + 3 in registers 4 q .. 4 q + 3
+    auto compute = [&](auto set) {
+        constexpr int S = decltype(set)::value;
+        if constexpr (ELEM == 1) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const v4i a = shift_u8_to_s8(fa[S][i][x], p.a_xor);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[0][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[S][j][x], a, acc[0][i][j], 0, 0, 0);
+                    if (ROWS) rs[i] = dot(a, rs[i]);
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                v4i ah, al;
+#pragma unroll
+                for (int wd = 0; wd < 4; ++wd) {
+                    const v4i c = fa[S][i][wd >> 1];
+                    const uint32_t lo = (uint32_t)((wd & 1) ? c.z : c.x), hi = (uint32_t)((wd & 1) ? c.w : c.y);
+                    ah[wd] = (int)__builtin_amdgcn_perm(hi, lo, 0x07050301u);
+                    al[wd] = (int)(__builtin_amdgcn_perm(hi, lo, 0x06040200u) ^ 0x80808080u);
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    acc[0][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[S][j][0], ah, acc[0][i][j], 0, 0, 0);
+                    acc[1][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[S][j][1], ah, acc[1][i][j], 0, 0, 0);
+                    acc[2][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[S][j][1], al, acc[2][i][j], 0, 0, 0);
+                    acc[1][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[S][j][0], al, acc[1][i][j], 0, 0, 0);
+                }
+                if (ROWS) {
+                    rs_h[i] = dot(ah, rs_h[i]);
+                    rs[i] = dot(al, rs[i]);
+                }
+            }
+        }
+    };
+
+    // The column terms of this thread's four output columns: asked for now, needed after the loop.
+    constexpr int CG = TN * 8;                           // groups of four columns per row
+    static_assert(NT % CG == 0, "a thread keeps its columns");
+    const int col = n0 + 4 * (tid % CG);
+    uint32_t ct[4] = {0u, 0u, 0u, 0u}, zbv[4] = {p.zb, p.zb, p.zb, p.zb};
+    float sc[4] = {p.scale, p.scale, p.scale, p.scale};
+    if (col < p.N) {
+        const int4 cs = *(const int4 *)(p.colsum + col);             // colsum is padded to 32 columns
+        ct[0] = p.za_term * (uint32_t)cs.x; ct[1] = p.za_term * (uint32_t)cs.y;
+        ct[2] = p.za_term * (uint32_t)cs.z; ct[3] = p.za_term * (uint32_t)cs.w;
+        if (REQUANT) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (col + q < p.N) {
+                    if (p.bias_vec) ct[q] += (uint32_t)p.bias_vec[col + q];
+                    if (p.zb_vec) zbv[q] = (uint32_t)p.zb_vec[col + q];
+                    if (p.scale_vec) sc[q] = p.scale_vec[col + q];
+                }
+        }
+    }
+    if (cnt > 0) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < RING; ++t) dma_step(t, t);
+        wait_vmcnt<(RING - 1) * LPS>();                  // step 0 has landed
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(IntC<0>{}, 0);
+        // Step t: its fragments are in register set t % 2 (waited for, so its slot is free); the fragments of
+        // step t + 1 are read while its matrix ops run, step t + RING is requested into its slot.
+        auto body = [&](auto set, auto other, int t) {
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0): the fragments of step t are in registers
+            wait_vmcnt<(RING - 2) * LPS>();              // step t + 1 has landed
+            __builtin_amdgcn_sched_barrier(0);
+            read_frags(other, (t + 1) % RING);
+            dma_step(t + RING, t % RING);
+            compute(set);
+        };
+        int t = 0;
+        for (; t + 1 < cnt; t += 2) {
+            body(IntC<0>{}, IntC<1>{}, t);
+            body(IntC<1>{}, IntC<0>{}, t + 1);
+        }
+        if (t < cnt) body(IntC<0>{}, IntC<1>{}, t);
+    }
+    wait_vmcnt<0>();                                     // drain the copies nobody reads
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_sched_barrier(0);
+    // the partial step at the end of K: guarded register loads into slot 0 by the wavefront whose turn it is
+    // (the pack is zero padded to whole steps)
+    if (nfull * 64 < kbytes && wave == nfull % NW) {
+        const int kbase = nfull * 64;
+#pragma unroll
+        for (int i = 0; i < 2 * TM; ++i) {
+            const int valid = kbytes - (kbase + a_chunk * 16);
+            const uint8_t *src = a_src[i] + kbase;
+            *(v4i *)(ring + i * 1024 + lane * 16) = valid >= 16 ? load16_any(src) : load16_partial(src, valid < 0 ? 0 : valid);
+        }
+#pragma unroll
+        for (int j = 0; j < 2 * TN; ++j)
+            *(v4i *)(ring + (2 * TM + j) * 1024 + lane * 16) =
+                *(const v4i *)(b_src[j >> 1] + (int64_t)nfull * (2 * kFragBytes) + (j & 1) * kFragBytes);
+        read_frags(IntC<0>{}, 0);
+        compute(IntC<0>{});
+    }
+
+    __syncthreads();                                     // every wavefront is done with its ring
+    int *part = (int *)(lds + wave * Cfg::kPartBytes);
+    int *rsx = (int *)(lds + NW * Cfg::kPartBytes);      // [wave][row of the tile]
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v4i o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 4 * q + e;
+                    if constexpr (ELEM == 1) o[e] = acc[0][i][j][r];
+                    else o[e] = (int)(((uint32_t)acc[0][i][j][r] << 16) + ((uint32_t)acc[1][i][j][r] << 8) + (uint32_t)acc[2][i][j][r]);
+                }
+                *(v4i *)(part + (i * 32 + (lane & 31)) * Cfg::kPitch + j * 32 + 8 * q + 4 * (lane >> 5)) = o;
+            }
+        if (ROWS) {
+            const int v = ELEM == 1 ? rs[i] : 256 * rs_h[i] + rs[i];
+            const int both = v + __shfl_xor(v, 32, 64);              // the halves of a step sit in lanes l and l ^ 32
+            if (lane < 32) rsx[wave * (TM * 32) + i * 32 + lane] = both;
+        }
+    }
+    __syncthreads();
+    // the zero fill of the partial step counts as -128 per element of a shifted operand: taken out again
+    const int filled = (kbytes + 63) / 64 * 64 - kbytes;
+    const uint32_t pad = ELEM == 2 ? 64u * (uint32_t)filled : (p.a_xor ? 128u * (uint32_t)filled : 0u);
+    const bool c_vec_ok = REQUANT ? ((((uintptr_t)p.C | (uintptr_t)p.ldc) & 3) == 0) : true;
+    const bool small_zc = REQUANT && p.zc > -8388608 && p.zc < 8388608;
+    constexpr int RSTEP = NT / CG;                       // rows the workgroup finishes at a time
+#pragma unroll
+    for (int r0 = 0; r0 < TM * 32; r0 += RSTEP) {
+        const int lr = r0 + tid / CG, row = m0 + lr;
+        if (lr >= TM * 32 || row >= p.M || col >= p.N) continue;
+        const int *src = (const int *)lds + lr * Cfg::kPitch + 4 * (tid % CG);
+        uint32_t v[4] = {0u, 0u, 0u, 0u};
+        uint32_t rsum = pad;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const v4i t = *(const v4i *)(src + w * (Cfg::kPartBytes / 4));
+            v[0] += (uint32_t)t.x; v[1] += (uint32_t)t.y; v[2] += (uint32_t)t.z; v[3] += (uint32_t)t.w;
+            if (ROWS) rsum += (uint32_t)rsx[w * (TM * 32) + lr];
+        }
+        if (!ROWS) rsum = 0u;
+        if (REQUANT) {
+            int32_t c[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] = (int32_t)(v[q] + ct[q] - zbv[q] * (rsum + p.rconst));
+            uint32_t bw;
+            if (small_zc) {
+                const float zcf = (float)p.zc;
+                bw = requant4_u8_small_zc(c, float4{sc[0], sc[1], sc[2], sc[3]}, zcf, p.relu ? zcf : -3.402823466e38f);
+            } else {
+                bw = (uint32_t)requant_u8(c[0], sc[0], p.zc, p.relu) | ((uint32_t)requant_u8(c[1], sc[1], p.zc, p.relu) << 8) |
+                     ((uint32_t)requant_u8(c[2], sc[2], p.zc, p.relu) << 16) | ((uint32_t)requant_u8(c[3], sc[3], p.zc, p.relu) << 24);
+            }
+            uint8_t *dst = (uint8_t *)p.C + (int64_t)row * p.ldc + col;
+            if (col + 3 < p.N && c_vec_ok) {
+                *(uint32_t *)dst = bw;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (col + q < p.N) dst[q] = (uint8_t)(bw >> (8 * q));
+            }
+        } else {
+            const uint32_t rt = p.kconst - p.zb * rsum;
+            v4i o;
+            o.x = (int)(v[0] + ct[0] + rt); o.y = (int)(v[1] + ct[1] + rt);
+            o.z = (int)(v[2] + ct[2] + rt); o.w = (int)(v[3] + ct[3] + rt);
+            int32_t *dst = (int32_t *)p.C + (int64_t)row * p.ldc + col;
+            if (col + 3 < p.N) {
+                put4<false>(dst, o);
+            } else {
+                dst[0] = o.x;
+                if (col + 1 < p.N) dst[1] = o.y;
+                if (col + 2 < p.N) dst[2] = o.z;
             }
         }
     }
