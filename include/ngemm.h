@@ -56,7 +56,8 @@ typedef enum {
 enum {
     NGEMM_KERNEL_AUTO = -1,
     NGEMM_KERNEL_SKINNY = 0,     /* split-K streaming kernel, M <= 32 only                */
-    NGEMM_KERNEL_TILE_64 = 1,    /* 64 x 64 workgroup tile                                */
+    NGEMM_KERNEL_TILE_64 = 1,    /* 64 x 64 workgroup tile (both: smaller tiles, K split over the wavefronts of a
+                                    workgroup, for outputs of few tiles with 16-byte aligned rows of A)       */
     NGEMM_KERNEL_TILE_128 = 2,   /* 128 x 128 workgroup tile                              */
     NGEMM_KERNEL_TILE_256 = 3,   /* 256 x 256 workgroup tile (throughput configuration)   */
     NGEMM_KERNEL_SPLIT_K = 4,    /* 64 x 64 tiles, K split over workgroups; int32 outputs */

@@ -368,21 +368,22 @@ hipError_t launch_skinny(const GemmParams &p, bool requant, int num_cus, hipStre
 // the 128 x 128 one when every unit still gets a workgroup, else 64 x 64 (measured on 18 shapes
 // from 16 x 512 x 512 to 4096^3: the smallest tile wins as long as the larger ones leave units
 // idle; ngemm_tune_u8s8s32 settles the borderline cases by measurement).
-constexpr int64_t kSplitMinK = 4096;
+constexpr int64_t kSplitMinK = 9216;
 int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K)
 {
     auto tiles = [&](int64_t b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-    // Few tiles and a long K: spread K over the idle units.  The launch that clears C and the
-    // atomic adds have to pay off: measured on 48 shapes, the split wins from K = 4096 on up to 48
-    // tiles of 64 x 64, from 8192 up to 96, from 12288 up to 128; against the streaming kernel
-    // (M <= 32) from K = 8192 while the output has at most 32 such tiles (N <= 2048).
+    // Few tiles and a long K: spread K over the idle units.  The launch that clears C and the atomic adds have
+    // to pay off: measured on 48 shapes, the split wins from K = 8192 on up to 96 tiles of 64 x 64 and from
+    // 12288 up to 128, and against the kernel that splits K over a workgroup's wavefronts (wavek_form) from
+    // about K = 9000 on: its time is 3 us + 0.56 us per 1024 bytes of K, the split's about 8 us (u8 output 9):
+    // 64 x 64 x 8192 7.6 / 8.1, 128 x 1024 x 8192 9.3 / 11.3, 64 x 64 x 16384 12.1 / 8.1 us.
     const int64_t t64 = tiles(64), step = 3 * cus / 16;
     if (M <= kSkinnyMaxM) {
-        if (K >= 2 * kSplitMinK && t64 * 8 <= cus) return NGEMM_KERNEL_SPLIT_K;
+        if (K >= kSplitMinK && t64 * 8 <= cus) return NGEMM_KERNEL_SPLIT_K;
         return NGEMM_KERNEL_SKINNY;
     }
-    if (t64 * 2 <= cus && K >= kSplitMinK * ((t64 + step - 1) / step)) return NGEMM_KERNEL_SPLIT_K;
+    if (t64 * 2 <= cus && K >= kSplitMinK && K >= 4096 * ((t64 + step - 1) / step)) return NGEMM_KERNEL_SPLIT_K;
     const int64_t t192 = ((M + 191) / 192) * ((N + 255) / 256);
     // The large tiles pay off from 0.7 of the compute units filled with K >= 512 (4096 x 4096 x 256: 16.5 / 15.0), from 0.5 with K >= 1024,
     // from 0.4 with K >= 2048: their fill and epilogue want stages to spread over (us, large against
@@ -398,7 +399,8 @@ int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K)
     }
     // (1536^3, 144 tiles of 128 x 128: 10.0 us against 10.6 us with 64 x 64 tiles; 1024^3, 64 tiles: 7.9
     // against 5.5; 1536 x 1536 x 512: 6.9 against 6.4)
-    if (tiles(128) >= cus || (tiles(128) * 5 >= cus * 2 && K >= 1024)) return NGEMM_KERNEL_TILE_128;
+    // Not for M <= 64, which would leave half of every tile empty (64 x 16384 x 4096 18.6 / 14.5 us).
+    if (M > 64 && (tiles(128) >= cus || (tiles(128) * 5 >= cus * 2 && K >= 1024))) return NGEMM_KERNEL_TILE_128;
     return NGEMM_KERNEL_TILE_64;
 }
 
@@ -443,7 +445,9 @@ struct WaveKForm {
 };
 using WaveK11 = WaveKForm<1, 1, 4, 4>;       // 64 KiB of LDS: two workgroups per compute unit
 using WaveK12 = WaveKForm<1, 2, 4, 3>;       // 72 KiB
-using WaveK22 = WaveKForm<2, 2, 2, 4>;       // 64 KiB
+using WaveK22 = WaveKForm<2, 2, 2, 4>;       // 64 KiB (16-bit operands)
+using WaveK11Short = WaveKForm<1, 1, 2, 4>;  // 32 KiB: five workgroups per compute unit
+using WaveK22Long = WaveKForm<2, 2, 4, 3>;   // 96 KiB: one
 
 template <class F, int ELEM, bool REQUANT, bool ROWS>
 hipError_t launch_wavek(const GemmParams &p0, hipStream_t st)
@@ -463,6 +467,62 @@ hipError_t allow_big_lds_wavek()
     if (lds <= 64 * 1024) return hipSuccess;
     return hipFuncSetAttribute((const void *)gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+}
+
+template <class F>
+hipError_t allow_big_lds_wavek_u8()
+{
+    hipError_t e = allow_big_lds_wavek<F, 1, false, false>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, false, true>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, true, false>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, true, true>();
+    return e;
+}
+
+// The form that serves an 8-bit problem with aligned rows of A (10 TM + TN of its tile, 1 for WaveK11Short), or
+// 0: the skinny and 64 x 64 kernels are faster.  us in a graph, this kernel / the others (at z: with a zero-point
+// of B, whose row sums cost the others more):
+//  * a 32 x 32 tile per compute unit at most: 64 x 4096 x 4096 7.0 / 10.2 (z 7.1 / 12.5), 33 x 4096 x 1024
+//    3.8 / 5.2, 16 x 4096 x 4096 6.0 / 8.2, 1 x 4096 x 16384 12.3 / 21;
+//  * M <= 32 and more panels than that: two wavefronts per panel while the weight is at most 64 MiB (32 x 16384
+//    x 4096 13.1 / 21.8, 16 x 32768 x 1024 8.8 / 11.8, 1 x 16384 x 4096 12.5 / 12.7); beyond it two panels per
+//    workgroup for M > 8 (32 x 16384 x 8192 26 / 41, 16 x 32768 x 4096 27 / 28.8), but not for the widest and
+//    deepest (32 x 32768 x 8192 60 / 51), which stream;
+//  * 32 x 64 tiles, one per compute unit at most: 128 x 4096 x 4096 8.5 / 10.4, 512 x 768 x 3072 7.1 / 8.6,
+//    512 x 768 x 768 4.4 / 5.1;
+//  * a K of up to 1024 and up to three 32 x 32 tiles per unit: 1024 x 768 x 768 5.0 / 5.5, 700 x 900 x 600
+//    6.3 / 6.5; at four tiles per unit (1024 x 1024 x 256 4.6 / 4.4) and below K = 256 it is a tie or a loss;
+//  * 64 x 64 tiles with row sums and a long K: 256 x 4096 x 4096 z 11.8 / 13.7, 384 x 2048 x 2048 z 8.3 / 9.0.
+int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const int64_t t32 = tiles(32, 32), t64 = tiles(64, 64);
+    if (t32 <= cus) return 11;
+    if (M <= kSkinnyMaxM) {
+        if (N * K <= (64ll << 20)) return t32 <= 4 * cus ? 1 : 0;
+        return M > 8 && (K <= 4096 || t32 <= 2 * cus) ? 12 : 0;
+    }
+    if (tiles(32, 64) <= cus) return 12;
+    if (K >= 256 && K <= 1024 && t32 <= 3 * cus && t64 <= cus) return 1;
+    if (rows && K > 1024 && t64 <= cus) return 22;
+    return 0;
+}
+
+template <class F>
+hipError_t launch_wavek_u8(const GemmParams &p, bool requant, bool rows, hipStream_t st)
+{
+    if (requant) return rows ? launch_wavek<F, 1, true, true>(p, st) : launch_wavek<F, 1, true, false>(p, st);
+    return rows ? launch_wavek<F, 1, false, true>(p, st) : launch_wavek<F, 1, false, false>(p, st);
+}
+
+hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool rows, hipStream_t st)
+{
+    switch (form) {
+    case 1: return launch_wavek_u8<WaveK11Short>(p, requant, rows, st);
+    case 11: return launch_wavek_u8<WaveK11>(p, requant, rows, st);
+    case 12: return launch_wavek_u8<WaveK12>(p, requant, rows, st);
+    default: return launch_wavek_u8<WaveK22Long>(p, requant, rows, st);
+    }
 }
 
 int workgroup_budget(const ngemm_ctx *ctx)
@@ -581,6 +641,12 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
         if (a.requant && !part_ws) parts = 1;
         if (parts < 2) kernel = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     }
+    const bool rows_needed = a.needs_rowsum() && B->K > 0;
+    // outputs of few tiles, aligned rows: K split over the wavefronts of a workgroup
+    if (kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64) {
+        const int form = dma_ok ? wavek_form(a.M, B->N, B->K, rows_needed, device_cus) : 0;
+        if (form != 0) return launch_wavek_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+    }
     // at most one tile per compute unit and a K worth pipelining: the long-pipeline variants
     const bool deep64 = kernel == NGEMM_KERNEL_TILE_64 && dma_ok && B->K >= 512 &&
                         ((a.M + 63) / 64) * ((B->N + 63) / 64) <= (int64_t)device_cus;
@@ -590,7 +656,6 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
     // sums themselves; the 256 x 256 kernels read them from a pass of their own
     const bool rows_in_kernel = kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_SPLIT_K ||
                                 kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128;
-    const bool rows_needed = a.needs_rowsum() && B->K > 0;
     if (rows_needed && !rows_in_kernel) {
         int32_t *rs = (int32_t *)ws;
         hipLaunchKernelGGL(rowsum_a_kernel, dim3((unsigned)((a.M + 3) / 4)), dim3(256), 0, st, a.A, a.lda,
@@ -740,7 +805,8 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
                                 X64Cfg::kLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void *)gemm_s16_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 S16Cfg::kLdsBytes) != hipSuccess ||
-            allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess) {
+            allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess ||
+            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess) {
             delete c;
             return NGEMM_ERR_DEVICE;
         }

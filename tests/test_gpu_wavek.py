@@ -47,3 +47,43 @@ def test_s16_small_outputs(runner, K):
         ng.ngemm_packed_b_free(h)
         assert np.array_equal(got[:M, :N], oracle.gemm_s16s16s32(A, B, za, zb)), (M, N)
         assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), (M, N)
+
+
+# (M, N, K): every form of the 8-bit rule on 256 compute units: 32 x 32 tiles, two wavefronts per tile (M <= 32 and
+# not), 32 x 64 and 64 x 64 tiles, each with ragged rows, columns and partial steps
+U8_CASES = [(1, 1, 1), (33, 31, 63), (64, 70, 64), (5, 300, 65), (31, 100, 129), (33, 33, 511), (70, 129, 4097), (300, 500, 200),
+            (32, 9000, 70), (7, 10001, 200), (600, 700, 300), (1000, 600, 257), (520, 1000, 64), (100, 5100, 90), (500, 1900, 1100)]
+
+
+@pytest.mark.parametrize("case", U8_CASES, ids=str)
+def test_u8_small_outputs(runner, case):
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N, K = case
+    rng = np.random.default_rng(M * 7 + N * 3 + K)
+    A = rng.integers(0, 256, size=(M, K), dtype=np.uint8)
+    B = rng.integers(-128, 128, size=(N, K), dtype=np.int8)
+    handle, packed = runner.pack(B)
+    pad = -K % 16
+    for za, zb, ldc_pad in ((0, 0, 0), (131, 0, 1), (255, -128, 0), (7, 5, 2)):
+        assert np.array_equal(runner.run(A, handle, N, za, zb, lda_pad=pad, ldc_pad=ldc_pad), oracle.gemm_u8s8s32(A, B, za, zb)), (za, zb)
+        assert np.array_equal(runner.run(A, handle, N, za, zb, scale=0.0007, zc=99, lda_pad=pad, ldc_pad=ldc_pad),
+                              oracle.gemm_u8s8u8_requant(A, B, za, zb, 0.0007, 99)), (za, zb)
+    # per-column scales, bias, zero-points and ReLU; signed A
+    scale = rng.uniform(0.0003, 0.001, N).astype(np.float32)
+    bias, zbv = rng.integers(-9999, 9999, N).astype(np.int32), rng.integers(-128, 128, N).astype(np.int32)
+    lda = K + pad
+    Ah = np.full((M, lda), 201, np.uint8)
+    Ah[:, :K] = A
+    Ad, sd, bd, zd = (torch.from_numpy(x).cuda() for x in (Ah, scale, bias, zbv))
+    wsb = ng.ngemm_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    C8 = torch.empty((M, N), dtype=torch.uint8, device="cuda")
+    for zc, relu in ((3, True), (1 << 24, False)):          # the second takes the 64-bit form of the arithmetic
+        ng.ngemm_run_u8s8u8_requant_channel(runner.ctx, M, Ad, lda, 77, handle, 0, zd, sd, bd, relu, zc, C8, N, ws, wsb)
+        want = oracle.gemm_u8s8u8_requant_channel(A, B, 77, 0, scale, zc, zb_vec=zbv, bias=bias, relu=relu)
+        assert np.array_equal(C8.cpu().numpy(), want), (zc, relu)
+    C = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    ng.ngemm_run_s8s8s32(runner.ctx, M, Ad, lda, -5, handle, 9, C, N, ws, wsb)
+    assert np.array_equal(C.cpu().numpy(), oracle.gemm_s8s8s32(A.view(np.int8), B, -5, 9))
+    ng.ngemm_packed_b_free(handle)
