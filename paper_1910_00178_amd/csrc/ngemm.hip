@@ -144,7 +144,13 @@ hipError_t launch_tile_dma(const GemmParams &p0, bool requant, int num_cus, hipS
     dim3 grid((unsigned)nwg), block(WGM * WGN * 64);
     const size_t smem = Cfg::kLdsBytes;
     const RawB none{nullptr, 0};
-    if (rawb) {      // unpacked B: int32 output only
+    if (rawb) {      // unpacked B: int32 output only; `rows`: the sums of both operands are formed in the kernel
+        if constexpr (BM < 256) {
+            if (rows) {
+                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, true, true>), grid, block, smem, st, p, *rawb);
+                return hipGetLastError();
+            }
+        }
         hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, true>), grid, block, smem, st, p, *rawb);
         return hipGetLastError();
     }
@@ -449,23 +455,23 @@ using WaveK22 = WaveKForm<2, 2, 2, 4>;       // 64 KiB (16-bit operands)
 using WaveK11Short = WaveKForm<1, 1, 2, 4>;  // 32 KiB: five workgroups per compute unit
 using WaveK22Long = WaveKForm<2, 2, 4, 3>;   // 96 KiB: one
 
-template <class F, int ELEM, bool REQUANT, bool ROWS>
-hipError_t launch_wavek(const GemmParams &p0, hipStream_t st)
+template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false>
+hipError_t launch_wavek(const GemmParams &p0, hipStream_t st, const RawB &rawb = RawB{nullptr, 0})
 {
     GemmParams p = p0;
     p.tiles_m = (p.M + F::TM * 32 - 1) / (F::TM * 32);
     p.tiles_n = (p.N + F::TN * 32 - 1) / (F::TN * 32);
-    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
-                       dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, p);
+    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
+                       dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, p, rawb);
     return hipGetLastError();
 }
 
-template <class F, int ELEM, bool REQUANT, bool ROWS>
+template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false>
 hipError_t allow_big_lds_wavek()
 {
     constexpr int lds = WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes;
     if (lds <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute((const void *)gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS>,
+    return hipFuncSetAttribute((const void *)gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
@@ -476,6 +482,8 @@ hipError_t allow_big_lds_wavek_u8()
     if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, false, true>();
     if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, true, false>();
     if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, true, true>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, false, false, true>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, false, true, true>();
     return e;
 }
 
@@ -523,6 +531,31 @@ hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool r
     case 12: return launch_wavek_u8<WaveK12>(p, requant, rows, st);
     default: return launch_wavek_u8<WaveK22Long>(p, requant, rows, st);
     }
+}
+
+// The forms that read B from the caller's storage.
+template <class F>
+hipError_t launch_wavek_raw(const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
+{
+    return rows ? launch_wavek<F, 1, false, true, true>(p, st, rawb) : launch_wavek<F, 1, false, false, true>(p, st, rawb);
+}
+
+hipError_t launch_wavek_raw_form(int form, const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
+{
+    switch (form) {
+    case 1: return launch_wavek_raw<WaveK11Short>(p, rows, rawb, st);
+    case 11: return launch_wavek_raw<WaveK11>(p, rows, rawb, st);
+    case 12: return launch_wavek_raw<WaveK12>(p, rows, rawb, st);
+    default: return launch_wavek_raw<WaveK22Long>(p, rows, rawb, st);
+    }
+}
+
+// Unpacked B.  There is no long-pipeline form of the 64 x 64 kernel for it, so the 64 x 64 form serves a long K
+// without row sums too (200 x 4096 x 4096 12.1 us against 17.4), and the other way for M <= 32 packs B first.
+int wavek_raw_form(int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    const int form = wavek_form(M, N, K, true, cus);
+    return form == 0 && M <= kSkinnyMaxM ? 12 : form;
 }
 
 int workgroup_budget(const ngemm_ctx *ctx)
@@ -1213,14 +1246,16 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     if (lda < K || ldb < K || ldc < N) return NGEMM_ERR_BAD_SHAPE;
     if (!workspace_dev || ((uintptr_t)workspace_dev & 15u) != 0) return NGEMM_ERR_INVALID_ARG;
     if (workspace_bytes < ngemm_unpacked_workspace_bytes(M, N, K)) return NGEMM_ERR_BUFFER_TOO_SMALL;
-    // Rows of both operands 16-byte aligned and an output that takes a tile kernel: no pack pass.
-    // The tile kernel reads B from the caller's storage with the same copies as A; only the column
-    // sums are computed beforehand (the row-sum kernel applied to B's [N x K] storage).
+    // Rows of both operands 16-byte aligned: no pack pass.  The kernels read B from the caller's storage with the
+    // same copies as A; all but the 256 x 256 ones form the sums of its columns themselves.
     int kernel = ctx->force_kernel == NGEMM_KERNEL_AUTO ? choose_kernel(ctx, M, N, K) : ctx->force_kernel;
     if (kernel == NGEMM_KERNEL_SPLIT_K)                                     // the K split reads a packed B only
         kernel = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     const bool aligned = (((uintptr_t)A_dev | (uintptr_t)lda | (uintptr_t)B_dev | (uintptr_t)ldb) & 15) == 0;
-    if (aligned && K > 0 && kernel != NGEMM_KERNEL_SKINNY) {
+    const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+    const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || (kernel == NGEMM_KERNEL_SKINNY && M <= kSkinnyMaxM);   // M > 32: refused below
+    const int form = aligned && K > 0 && small_kernel ? wavek_raw_form(M, N, K, cus) : 0;
+    if (aligned && K > 0 && (form != 0 || kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return NGEMM_ERR_DEVICE;
         hipStream_t st = (hipStream_t)hip_stream;
@@ -1234,20 +1269,28 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
         int32_t *rowsum = (int32_t *)((uint8_t *)workspace_dev + round_up(shape.Np * 4, 256));
         p.Bp = nullptr;
         p.colsum = colsum;
-        hipLaunchKernelGGL(rowsum_a_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, st, (const uint8_t *)B_dev,
-                           ldb, (int)N, (int)K, 0u, colsum);
-        if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
-        if (b_zero_point != 0) {
+        const RawB rawb{(const uint8_t *)B_dev, ldb};
+        if (form != 0)
+            return launch_wavek_raw_form(form, p, b_zero_point != 0, rawb, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+        // The sums of B's columns (without weight at a_zero_point = 128) and of A's rows (at b_zero_point = 0): the
+        // 64 x 64 and 128 x 128 kernels form them, the larger ones read them from passes of their own.
+        const bool sums = p.za_term != 0 || b_zero_point != 0;
+        const bool sums_in_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128;
+        if (p.za_term != 0 && !sums_in_kernel) {
+            hipLaunchKernelGGL(rowsum_a_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, st, (const uint8_t *)B_dev,
+                               ldb, (int)N, (int)K, 0u, colsum);
+            if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
+        }
+        if (b_zero_point != 0 && !sums_in_kernel) {
             hipLaunchKernelGGL(rowsum_a_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, A_dev, lda, (int)M,
                                (int)K, p.a_xor, rowsum);
             if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
             p.rowsum = rowsum;
         }
-        const RawB rawb{(const uint8_t *)B_dev, ldb};
         const int budget = workgroup_budget(ctx);
         hipError_t e;
-        if (kernel == NGEMM_KERNEL_TILE_64) e = launch_tile_dma<64, 64, 2, 2>(p, false, budget, st, &rawb);
-        else if (kernel == NGEMM_KERNEL_TILE_128) e = launch_tile_dma<128, 128, 2, 2>(p, false, budget, st, &rawb);
+        if (kernel == NGEMM_KERNEL_TILE_64) e = launch_tile_dma<64, 64, 2, 2>(p, false, budget, st, &rawb, sums);
+        else if (kernel == NGEMM_KERNEL_TILE_128) e = launch_tile_dma<128, 128, 2, 2>(p, false, budget, st, &rawb, sums);
         else if (K >= X64Cfg::kMinK && x64_offsets_fit(256, lda, K) && x64_offsets_fit(256, ldb, K)) {
             p.tiles_m = (int)((M + 255) / 256);
             p.tiles_n = (int)((N + 255) / 256);

@@ -1225,7 +1225,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
         tile_of_block(tile, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
         const int m0 = tm * BM, n0 = tn * BN;
         static_assert(BN <= Cfg::kThreads, "a thread per column of the tile");
-        const EpiCols ec = epi_load_cols<TN, BN, REQUANT>(p, n0, wn, lane, tid);   // the epilogue's column terms, early
+        constexpr bool COLS = BRAW && ROWS;
+        EpiCols ec;                                      // the epilogue's column terms, early
+        if (!COLS) ec = epi_load_cols<TN, BN, REQUANT>(p, n0, wn, lane, tid);
 
         // Loader: this lane's source addresses for the blocks its wavefront copies.
         const uint8_t *a_src[AI];
@@ -1298,6 +1300,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
         int rs[TM];                                    // this lane's share of the row sums (row lane % 32 of block i)
 #pragma unroll
         for (int i = 0; i < TM; ++i) rs[i] = 0;
+        int csum[TN];                                  // COLS: of the column sums (column lane % 32 of block j)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) csum[j] = 0;
         auto mma_one = [&](int slot, int i, int j) {
             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[slot][j], fa[slot][i], acc[i][j], 0, 0, 0);
             if (ROWS && j == 0) {
@@ -1306,6 +1311,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
                 rs[i] = __builtin_amdgcn_sdot4(a.y, 0x01010101, rs[i], false);
                 rs[i] = __builtin_amdgcn_sdot4(a.z, 0x01010101, rs[i], false);
                 rs[i] = __builtin_amdgcn_sdot4(a.w, 0x01010101, rs[i], false);
+            }
+            if (COLS && i == 0) {
+                const v4i b = fb[slot][j];
+                csum[j] = __builtin_amdgcn_sdot4(b.x, 0x01010101, csum[j], false);
+                csum[j] = __builtin_amdgcn_sdot4(b.y, 0x01010101, csum[j], false);
+                csum[j] = __builtin_amdgcn_sdot4(b.z, 0x01010101, csum[j], false);
+                csum[j] = __builtin_amdgcn_sdot4(b.w, 0x01010101, csum[j], false);
             }
         };
 
@@ -1432,6 +1444,17 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
             for (int i = 0; i < TM; ++i) rs_reg[i] = (uint32_t)(rs[i] + __shfl_xor(rs[i], 32, 64)) + pad;
         }
         const uint32_t *rsp = ROWS ? rs_reg : nullptr;
+        if (COLS) {
+            // the tile's column sums through LDS (behind the patches) to the lanes that store the columns
+            int *cs_lds = (int *)(lds + NW * kXposeBytes<TN>);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int both = csum[j] + __shfl_xor(csum[j], 32, 64);
+                if (wm == 0 && lane < 32) cs_lds[(wn * TN + j) * 32 + lane] = both;
+            }
+            __syncthreads();
+            ec.cs = *(const int4 *)(cs_lds + wn * TN * 32 + 4 * (lane % (TN * 8)));      // past N: never stored
+        }
         // every practical output zero-point takes the binary32 form of the requantising arithmetic
         if (REQUANT && p.zc > -8388608 && p.zc < 8388608)
             tile_epilogue<TM, TN, BN, REQUANT, true>(p, acc, m0, n0, wm, wn, lane, tid, Cfg::kThreads,
@@ -2637,6 +2660,9 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 // block into three accumulators (ah*bl' and al'*bh share a weight and a sum).
 // ROWS: the row sums a zero-point of B needs are added up from the fragments as they pass (no wavefront sums
 // what another one does, in contrast to the kernels whose wavefronts share rows).
+// BRAW: B is the caller's unpacked [N x K] storage with aligned rows.  It has the shape of A, so its tile is
+// copied and read as A's is, and the column sums are added up from its fragments as the row sums are: one launch
+// in the place of two or three (us: 1 x 4096 x 1024 11.2 -> 4.0, 16 x 4096 x 4096 16.2 -> 6.7, 64 x 2304 x 1664 12.9 -> 4.5).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
 // 4096 47 -> 8.7 (3.8 TB/s of B's planes), 64 x 4096 x 4096 47 -> 10.7, 512 x 768 x 768 15.5 -> 6.1, 1024^3
 // 18.9 -> 10.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
@@ -2649,7 +2675,7 @@ struct WaveKCfg {
     static constexpr int kWaveBytes = RING * kStepBytes;
     static constexpr int kPitch = TN * 32 + 4;             // int32 per row of a partial tile, padded
     static constexpr int kPartBytes = TM * 32 * kPitch * 4;
-    static constexpr int kEpiBytes = NW * (kPartBytes + TM * 32 * 4);
+    static constexpr int kEpiBytes = NW * (kPartBytes + (TM + TN) * 32 * 4);
     static constexpr int kLdsBytes = NW * kWaveBytes > kEpiBytes ? NW * kWaveBytes : kEpiBytes;
     static_assert((RING - 1) * kLoadsPerStep <= 63, "vmcnt range");
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
@@ -2658,9 +2684,10 @@ struct WaveKCfg {
 
 // p.A / p.lda in bytes, rows 16-byte aligned; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
 // count tiles of 32 TM x 32 TN.
-template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS>
-__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false>
+__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p, const RawB rawb)
 {
+    static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
     using Cfg = WaveKCfg<TM, TN, NW, RING>;
     constexpr int LPS = Cfg::kLoadsPerStep, NT = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -2677,7 +2704,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
     // copies of a step: 16-row blocks of A (row t of the block, chunk c in slot 4 t + (c + t / 4) % 4), then
     // the two fragments of each panel of B as they lie in the pack
     const int t16 = lane >> 2, a_chunk = ((lane & 3) - (t16 >> 2)) & 3;
-    const uint8_t *a_src[2 * TM], *b_src[TN];
+    constexpr int NB = BRAW ? 2 * TN : TN;
+    const uint8_t *a_src[2 * TM], *b_src[NB];
 #pragma unroll
     for (int i = 0; i < 2 * TM; ++i) {
         int grow = m0 + 16 * i + t16;
@@ -2685,11 +2713,22 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
         a_src[i] = p.A + (int64_t)grow * p.lda + a_chunk * 16;
     }
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        int pnl = n0 / 32 + j;
-        pnl = pnl < p.npanels ? pnl : p.npanels - 1;     // panels past N: read a valid panel, never stored
-        b_src[j] = p.Bp + ((int64_t)pnl * nfrag) * kFragBytes + lane * 16;
+    for (int j = 0; j < NB; ++j) {
+        if (BRAW) {
+            int gcol = n0 + 16 * j + t16;
+            gcol = gcol < p.N ? gcol : p.N - 1;          // columns past N: read a valid one, never stored
+            b_src[j] = rawb.B + (int64_t)gcol * rawb.ldb + a_chunk * 16;
+        } else {
+            int pnl = n0 / 32 + j;
+            pnl = pnl < p.npanels ? pnl : p.npanels - 1; // panels past N: read a valid panel, never stored
+            b_src[j] = p.Bp + ((int64_t)pnl * nfrag) * kFragBytes + lane * 16;
+        }
     }
+    // memory of copy j (0 .. 2 TN - 1) of B's part of full step g
+    auto b_mem = [&](int j, int g) {
+        if constexpr (BRAW) return b_src[j] + (int64_t)g * 64;
+        else return b_src[j >> 1] + (int64_t)g * (2 * kFragBytes) + (j & 1) * kFragBytes;
+    };
     uint8_t *ring = lds + wave * Cfg::kWaveBytes;
     auto dma_step = [&](int t, int slot) {
         const int g = (t < cnt ? t : cnt - 1) * NW + wave;       // past the end: a copy nobody reads
@@ -2699,8 +2738,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
             __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + (int64_t)g * 64), (lptr_t)(dst + i * 1024), 16, 0, 0);
 #pragma unroll
         for (int j = 0; j < 2 * TN; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)(b_src[j >> 1] + (int64_t)g * (2 * kFragBytes) + (j & 1) * kFragBytes),
-                                             (lptr_t)(dst + (2 * TM + j) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)b_mem(j, g), (lptr_t)(dst + (2 * TM + j) * 1024), 16, 0, 0);
     };
     // fragments of a step: A block i, part x (8-bit: 32-byte half x of the step; 16-bit: chunk x of the lane's
     // 32 bytes), B panel j, part x (half / plane)
@@ -2722,7 +2760,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
 #pragma unroll
             for (int i = 0; i < TM; ++i) fa[S][i][x] = *(const v4i *)(base + i * 2048 + a_off[x]);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) fb[S][j][x] = *(const v4i *)(base + (2 * TM + 2 * j + x) * 1024 + lane * 16);
+            for (int j = 0; j < TN; ++j)
+                fb[S][j][x] = BRAW ? *(const v4i *)(base + (TM + j) * 2048 + a_off[x])
+                                   : *(const v4i *)(base + (2 * TM + 2 * j + x) * 1024 + lane * 16);
         }
     };
     v16i acc[NACC][TM][TN];
@@ -2737,6 +2777,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
     int rs[TM], rs_h[TM];                                // this lane's share of the row sums (16-bit: low, high planes)
 #pragma unroll
     for (int i = 0; i < TM; ++i) { rs[i] = 0; rs_h[i] = 0; }
+    int csum[TN];                                        // BRAW: of the column sums (column l % 32 of panel j)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) csum[j] = 0;
     auto dot = [](const v4i &a, int s) {
         s = __builtin_amdgcn_sdot4(a.x, 0x01010101, s, false);
         s = __builtin_amdgcn_sdot4(a.y, 0x01010101, s, false);
@@ -2749,7 +2792,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
         constexpr int S = decltype(set)::value;
         if constexpr (ELEM == 1) {
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
+            for (int x = 0; x < 2; ++x) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     const v4i a = shift_u8_to_s8(fa[S][i][x], p.a_xor);
@@ -2758,6 +2801,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
                         acc[0][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[S][j][x], a, acc[0][i][j], 0, 0, 0);
                     if (ROWS) rs[i] = dot(a, rs[i]);
                 }
+                if (BRAW) {
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) csum[j] = dot(fb[S][j][x], csum[j]);
+                }
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
@@ -2790,7 +2838,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
     const int col = n0 + 4 * (tid % CG);
     uint32_t ct[4] = {0u, 0u, 0u, 0u}, zbv[4] = {p.zb, p.zb, p.zb, p.zb};
     float sc[4] = {p.scale, p.scale, p.scale, p.scale};
-    if (col < p.N) {
+    if (!BRAW && col < p.N) {
         const int4 cs = *(const int4 *)(p.colsum + col);             // colsum is padded to 32 columns
         ct[0] = p.za_term * (uint32_t)cs.x; ct[1] = p.za_term * (uint32_t)cs.y;
         ct[2] = p.za_term * (uint32_t)cs.z; ct[3] = p.za_term * (uint32_t)cs.w;
@@ -2843,9 +2891,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
             *(v4i *)(ring + i * 1024 + lane * 16) = valid >= 16 ? load16_any(src) : load16_partial(src, valid < 0 ? 0 : valid);
         }
 #pragma unroll
-        for (int j = 0; j < 2 * TN; ++j)
-            *(v4i *)(ring + (2 * TM + j) * 1024 + lane * 16) =
-                *(const v4i *)(b_src[j >> 1] + (int64_t)nfull * (2 * kFragBytes) + (j & 1) * kFragBytes);
+        for (int j = 0; j < 2 * TN; ++j) {
+            v4i v;
+            if (BRAW) {
+                const int valid = kbytes - (kbase + a_chunk * 16);
+                v = valid >= 16 ? load16_any(b_mem(j, nfull)) : load16_partial(b_mem(j, nfull), valid < 0 ? 0 : valid);
+            } else {
+                v = *(const v4i *)b_mem(j, nfull);
+            }
+            *(v4i *)(ring + (2 * TM + j) * 1024 + lane * 16) = v;
+        }
         read_frags(IntC<0>{}, 0);
         compute(IntC<0>{});
     }
@@ -2853,6 +2908,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
     __syncthreads();                                     // every wavefront is done with its ring
     int *part = (int *)(lds + wave * Cfg::kPartBytes);
     int *rsx = (int *)(lds + NW * Cfg::kPartBytes);      // [wave][row of the tile]
+    int *csx = rsx + NW * TM * 32;                       // [wave][column of the tile]
+    if (BRAW) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int both = csum[j] + __shfl_xor(csum[j], 32, 64);
+            if (lane < 32) csx[wave * (TN * 32) + j * 32 + lane] = both;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -2875,6 +2938,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p)
         }
     }
     __syncthreads();
+    if (BRAW) {                                          // columns past N: never stored
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int4 cs = *(const int4 *)(csx + w * (TN * 32) + 4 * (tid % CG));
+            ct[0] += p.za_term * (uint32_t)cs.x; ct[1] += p.za_term * (uint32_t)cs.y;
+            ct[2] += p.za_term * (uint32_t)cs.z; ct[3] += p.za_term * (uint32_t)cs.w;
+        }
+    }
     // the zero fill of the partial step counts as -128 per element of a shifted operand: taken out again
     const int filled = (kbytes + 63) / 64 * 64 - kbytes;
     const uint32_t pad = ELEM == 2 ? 64u * (uint32_t)filled : (p.a_xor ? 128u * (uint32_t)filled : 0u);

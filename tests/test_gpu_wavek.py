@@ -87,3 +87,47 @@ def test_u8_small_outputs(runner, case):
     ng.ngemm_run_s8s8s32(runner.ctx, M, Ad, lda, -5, handle, 9, C, N, ws, wsb)
     assert np.array_equal(C.cpu().numpy(), oracle.gemm_s8s8s32(A.view(np.int8), B, -5, 9))
     ng.ngemm_packed_b_free(handle)
+
+
+# Unpacked B: the forms above on the caller's storage, and the 64 x 64 (1100 x 1600) and 128 x 128 (1600 x 1700 with a
+# long K) tiles that form both operands' sums
+RAW_CASES = [(1, 1, 1), (33, 31, 63), (31, 100, 129), (300, 500, 200), (32, 9000, 70), (7, 10001, 200), (600, 700, 300),
+             (500, 1900, 1100), (1100, 1600, 100), (1111, 1601, 64), (1600, 1700, 1041), (30, 17000, 4100)]
+
+
+@pytest.mark.parametrize("case", RAW_CASES, ids=str)
+def test_unpacked_sums_in_kernel(runner, case):
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N, K = case
+    rng = np.random.default_rng(M * 5 + N * 3 + K)
+    pitch = (K + 15) // 16 * 16 + 16
+    Ah, Bh = rng.integers(0, 256, size=(M, pitch), dtype=np.uint8), rng.integers(-128, 128, size=(N, pitch), dtype=np.int8)
+    A, B = np.ascontiguousarray(Ah[:, :K]), np.ascontiguousarray(Bh[:, :K])
+    Ad, Bd = torch.from_numpy(Ah).cuda(), torch.from_numpy(Bh).cuda()
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, K)
+    ws = torch.full((wsb,), 0xC3, dtype=torch.uint8, device="cuda")
+    for za, zb in ((128, 0), (0, 0), (128, -7), (200, 127)):
+        C = torch.full((M + 1, N + 1), -7, dtype=torch.int32, device="cuda")
+        ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, Ad, pitch, za, Bd, pitch, zb, C, N + 1, ws, wsb)
+        got = C.cpu().numpy()
+        want = oracle.gemm_u8s8s32(A, B, za, zb)
+        assert np.array_equal(got[:M, :N], want), (za, zb)
+        assert (got[M:] == -7).all() and (got[:, N:] == -7).all()
+
+
+def test_forced_skinny_stays_refused_beyond_its_rows(runner):
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N, K = 33, 64, 64
+    A = torch.zeros((M, K), dtype=torch.uint8, device="cuda")
+    B = torch.zeros((N, K), dtype=torch.int8, device="cuda")
+    C = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    runner.set_kernel(ng.NGEMM_KERNEL_SKINNY)
+    try:
+        with pytest.raises(ng.NgemmError):
+            ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, A, K, 0, B, K, 0, C, N, ws, wsb)
+    finally:
+        runner.set_kernel(ng.NGEMM_KERNEL_AUTO)
