@@ -369,13 +369,16 @@ hipError_t launch_skinny(const GemmParams &p, bool requant, int num_cus, hipStre
     return hipGetLastError();
 }
 
+// Rows that copies into LDS can fetch: 16-byte aligned.
+inline bool rows_aligned(const void *A, int64_t lda) { return (((uintptr_t)A | (uintptr_t)lda) & 15) == 0; }
+
 // Shape heuristic: the 256 x 256 configuration when it fills at least half of the compute units
 // (3072^3, 144 tiles: 35 us against 47 us with 128 x 128; 2048 x 4096 x 1024, 128 tiles: a tie),
 // the 128 x 128 one when every unit still gets a workgroup, else 64 x 64 (measured on 18 shapes
 // from 16 x 512 x 512 to 4096^3: the smallest tile wins as long as the larger ones leave units
 // idle; ngemm_tune_u8s8s32 settles the borderline cases by measurement).
 constexpr int64_t kSplitMinK = 9216;
-int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K)
+int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, bool aligned)
 {
     auto tiles = [&](int64_t b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
@@ -397,6 +400,14 @@ int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K)
     // 13.4 / 12.1, 2304^3 20.8 / 22.5, 2560^3 24.0 / 26.6).
     const int64_t big = tiles(256) > t192 ? tiles(256) : t192;
     if ((big * 10 >= cus * 7 && K >= 512) || (big * 2 >= cus && K >= 1024) || (big * 5 >= cus * 2 && K >= 2048)) {
+        if (!aligned) {
+            // The 256 x 256 tiles are staged through registers then and pay off only when they fill most of every
+            // round of compute units; else 128 x 128 tiles, which also form the row sums (us, 128 / 256, zero-point
+            // of B: 2047 x 3071 x 1537, 96 tiles of 256 25.8 / 40.5, 3001 x 3003 x 1001, 144 tiles 29.1 / 34.3,
+            // 4097^3, 289 tiles 129 / 145, 8191 x 4095 x 2047, 512 tiles 128 / 115).
+            const int64_t rounds = (tiles(256) + cus - 1) / cus;
+            return tiles(256) * 100 < 58 * rounds * cus ? NGEMM_KERNEL_TILE_128 : NGEMM_KERNEL_TILE_256;
+        }
         // rounds of resident workgroups times the rows of a tile: 192 x 256 tiles when they fill more of the
         // compute units for less time (3072^3: 144 tiles of 256 rows against 192 of 192, one round each;
         // 2560^3: 100 against 140, 29.3 us against 24.0 us, 128 x 128 tiles 26.6 us)
@@ -454,14 +465,15 @@ using WaveK12 = WaveKForm<1, 2, 4, 3>;       // 72 KiB
 using WaveK22 = WaveKForm<2, 2, 2, 4>;       // 64 KiB (16-bit operands)
 using WaveK11Short = WaveKForm<1, 1, 2, 4>;  // 32 KiB: five workgroups per compute unit
 using WaveK22Long = WaveKForm<2, 2, 4, 3>;   // 96 KiB: one
+using WaveK12Short = WaveKForm<1, 2, 2, 4>;  // 48 KiB (A through registers)
 
-template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false>
+template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false>
 hipError_t launch_wavek(const GemmParams &p0, hipStream_t st, const RawB &rawb = RawB{nullptr, 0})
 {
     GemmParams p = p0;
     p.tiles_m = (p.M + F::TM * 32 - 1) / (F::TM * 32);
     p.tiles_n = (p.N + F::TN * 32 - 1) / (F::TN * 32);
-    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
+    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW, AREG>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
                        dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, p, rawb);
     return hipGetLastError();
 }
@@ -531,6 +543,34 @@ hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool r
     case 12: return launch_wavek_u8<WaveK12>(p, requant, rows, st);
     default: return launch_wavek_u8<WaveK22Long>(p, requant, rows, st);
     }
+}
+
+// Rows of A with any alignment (A through registers).  us in a graph, this kernel / the others:
+//  * M > 8 and a 32 x 32 tile per compute unit at most: 64 x 4096 x 4097 9.9 / 23.7, 32 x 4096 x 4097 9.8 / 18.5,
+//    64 x 1024 x 1025 5.2 / 6.1; up to eight rows the skinny kernel's direct loads of A cost little (1 x 4096 x 1025
+//    4.3 / 4.3, 2 x 300 x 8191 12.8 / 10.3);
+//  * 32 x 64 tiles of two wavefronts: M <= 32 beyond that (16 x 32767 x 2047 14.4 / 19.4, 16 x 16384 x 4097 15.6 /
+//    22.6), one per unit (128 x 4096 x 4097 13.8 / 23.8, 256 x 1025 x 1025 6.3 / 6.7), two per unit with a long K
+//    (256 x 4096 x 4097 16.8 / 24.2, 48 x 16384 x 2049 12.0 / 14.6, but 200 x 4096 x 1001 8.1 / 6.8).
+int wavek_areg_form(int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (M <= 8) return 0;
+    if (tiles(32, 32) <= cus) return 11;
+    if (M <= kSkinnyMaxM || tiles(32, 64) <= cus || (K >= 2048 && tiles(32, 64) <= 2 * cus)) return 12;
+    return 0;
+}
+
+template <class F>
+hipError_t launch_wavek_areg(const GemmParams &p, bool requant, bool rows, hipStream_t st)
+{
+    if (requant) return rows ? launch_wavek<F, 1, true, true, false, true>(p, st) : launch_wavek<F, 1, true, false, false, true>(p, st);
+    return rows ? launch_wavek<F, 1, false, true, false, true>(p, st) : launch_wavek<F, 1, false, false, false, true>(p, st);
+}
+
+hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, bool rows, hipStream_t st)
+{
+    return form == 11 ? launch_wavek_areg<WaveK11>(p, requant, rows, st) : launch_wavek_areg<WaveK12Short>(p, requant, rows, st);
 }
 
 // The forms that read B from the caller's storage.
@@ -607,7 +647,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, int *kernel_ou
     if (k == NGEMM_KERNEL_AUTO) {
         for (const ngemm_ctx::Tuned &t : ctx->tuned)
             if (t.M == a.M && t.N == a.B->N && t.K == a.B->K) k = t.kernel;
-        if (k == NGEMM_KERNEL_AUTO) k = choose_kernel(ctx, a.M, a.B->N, a.B->K);
+        if (k == NGEMM_KERNEL_AUTO) k = choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda));
     }
     if (k == NGEMM_KERNEL_SKINNY && a.M > kSkinnyMaxM) return NGEMM_ERR_INVALID_ARG;
     *kernel_out = k;
@@ -660,7 +700,7 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
     const ngemm_packed_b *B = a.B;
     if (a.M == 0 || B->N == 0) return NGEMM_OK;
     GemmParams p = make_params(a, nxcd);
-    const bool dma_ok = (((uintptr_t)a.A | (uintptr_t)a.lda) & 15) == 0;
+    const bool dma_ok = rows_aligned(a.A, a.lda);
     int kchunk = 0, parts = 1;
     int32_t *part_ws = nullptr;
     if (kernel == NGEMM_KERNEL_SPLIT_K) {
@@ -675,8 +715,12 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
         if (parts < 2) kernel = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     }
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
-    // outputs of few tiles, aligned rows: K split over the wavefronts of a workgroup
+    // outputs of few tiles: K split over the wavefronts of a workgroup
     if (kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64) {
+        if (!dma_ok) {
+            const int form = wavek_areg_form(a.M, B->N, B->K, device_cus);
+            if (form != 0) return launch_wavek_areg_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+        }
         const int form = dma_ok ? wavek_form(a.M, B->N, B->K, rows_needed, device_cus) : 0;
         if (form != 0) return launch_wavek_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
     }
@@ -1248,7 +1292,7 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     if (workspace_bytes < ngemm_unpacked_workspace_bytes(M, N, K)) return NGEMM_ERR_BUFFER_TOO_SMALL;
     // Rows of both operands 16-byte aligned: no pack pass.  The kernels read B from the caller's storage with the
     // same copies as A; all but the 256 x 256 ones form the sums of its columns themselves.
-    int kernel = ctx->force_kernel == NGEMM_KERNEL_AUTO ? choose_kernel(ctx, M, N, K) : ctx->force_kernel;
+    int kernel = ctx->force_kernel == NGEMM_KERNEL_AUTO ? choose_kernel(ctx, M, N, K, rows_aligned(A_dev, lda)) : ctx->force_kernel;
     if (kernel == NGEMM_KERNEL_SPLIT_K)                                     // the K split reads a packed B only
         kernel = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     const bool aligned = (((uintptr_t)A_dev | (uintptr_t)lda | (uintptr_t)B_dev | (uintptr_t)ldb) & 15) == 0;

@@ -2663,6 +2663,9 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 // BRAW: B is the caller's unpacked [N x K] storage with aligned rows.  It has the shape of A, so its tile is
 // copied and read as A's is, and the column sums are added up from its fragments as the row sums are: one launch
 // in the place of two or three (us: 1 x 4096 x 1024 11.2 -> 4.0, 16 x 4096 x 4096 16.2 -> 6.7, 64 x 2304 x 1664 12.9 -> 4.5).
+// AREG: rows of A with any alignment, which copies into LDS cannot fetch: A comes through registers (two steps on
+// their way, written into the ring two steps before they are read); everything else stays (64 x 4096 x 4097
+// 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
 // 4096 47 -> 8.7 (3.8 TB/s of B's planes), 64 x 4096 x 4096 47 -> 10.7, 512 x 768 x 768 15.5 -> 6.1, 1024^3
 // 18.9 -> 10.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
@@ -2682,9 +2685,9 @@ struct WaveKCfg {
     static_assert(RING >= 3, "copies in flight");
 };
 
-// p.A / p.lda in bytes, rows 16-byte aligned; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
+// p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
 // count tiles of 32 TM x 32 TN.
-template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false>
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false>
 __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p, const RawB rawb)
 {
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
@@ -2730,15 +2733,33 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
         else return b_src[j >> 1] + (int64_t)g * (2 * kFragBytes) + (j & 1) * kFragBytes;
     };
     uint8_t *ring = lds + wave * Cfg::kWaveBytes;
-    auto dma_step = [&](int t, int slot) {
-        const int g = (t < cnt ? t : cnt - 1) * NW + wave;       // past the end: a copy nobody reads
-        uint8_t *dst = ring + slot * Cfg::kStepBytes;
+    auto step_of = [&](int t) { return (t < cnt ? t : cnt - 1) * NW + wave; };       // past the end: copies nobody reads
+    auto dma_a = [&](int t, int slot) {
+        const int g = step_of(t);
 #pragma unroll
         for (int i = 0; i < 2 * TM; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + (int64_t)g * 64), (lptr_t)(dst + i * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + (int64_t)g * 64),
+                                             (lptr_t)(ring + slot * Cfg::kStepBytes + i * 1024), 16, 0, 0);
+    };
+    auto dma_b = [&](int t, int slot) {
+        const int g = step_of(t);
 #pragma unroll
         for (int j = 0; j < 2 * TN; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)b_mem(j, g), (lptr_t)(dst + (2 * TM + j) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)b_mem(j, g), (lptr_t)(ring + slot * Cfg::kStepBytes + (2 * TM + j) * 1024), 16, 0, 0);
+    };
+    // AREG: A of step t waits in register set t % 2
+    static_assert(!AREG || RING == 4, "a step's register set is free again when the step four on is requested");
+    v4i va[2][2 * TM];
+    auto load_a = [&](auto set, int t) {
+        constexpr int S = decltype(set)::value;
+        const int g = step_of(t);
+#pragma unroll
+        for (int i = 0; i < 2 * TM; ++i) va[S][i] = load16_any(a_src[i] + (int64_t)g * 64);
+    };
+    auto write_a = [&](auto set, int slot) {
+        constexpr int S = decltype(set)::value;
+#pragma unroll
+        for (int i = 0; i < 2 * TM; ++i) *(v4i *)(ring + slot * Cfg::kStepBytes + i * 1024 + lane * 16) = va[S][i];
     };
     // fragments of a step: A block i, part x (8-bit: 32-byte half x of the step; 16-bit: chunk x of the lane's
     // 32 bytes), B panel j, part x (half / plane)
@@ -2854,9 +2875,24 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
     }
     if (cnt > 0) {
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (AREG) {
+            load_a(IntC<0>{}, 0);
+            load_a(IntC<1>{}, 1);
 #pragma unroll
-        for (int t = 0; t < RING; ++t) dma_step(t, t);
-        wait_vmcnt<(RING - 1) * LPS>();                  // step 0 has landed
+            for (int t = 0; t < RING; ++t) dma_b(t, t);
+            write_a(IntC<0>{}, 0);
+            write_a(IntC<1>{}, 1);
+            load_a(IntC<0>{}, 2);
+            load_a(IntC<1>{}, 3);
+            wait_vmcnt<(RING - 1) * 2 * TN + 4 * TM>();  // step 0 has landed: younger are B of steps 1 .. 3, A of 2 and 3
+        } else {
+#pragma unroll
+            for (int t = 0; t < RING; ++t) {
+                dma_a(t, t);
+                dma_b(t, t);
+            }
+            wait_vmcnt<(RING - 1) * LPS>();              // step 0 has landed
+        }
         __builtin_amdgcn_sched_barrier(0);
         read_frags(IntC<0>{}, 0);
         // Step t: its fragments are in register set t % 2 (waited for, so its slot is free); the fragments of
@@ -2867,7 +2903,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
             wait_vmcnt<(RING - 2) * LPS>();              // step t + 1 has landed
             __builtin_amdgcn_sched_barrier(0);
             read_frags(other, (t + 1) % RING);
-            dma_step(t + RING, t % RING);
+            if constexpr (AREG) {
+                write_a(set, (t + 2) % RING);            // A of step t + 2, requested two steps ago
+                load_a(set, t + RING);
+            } else {
+                dma_a(t + RING, t % RING);
+            }
+            dma_b(t + RING, t % RING);
             compute(set);
         };
         int t = 0;

@@ -52,11 +52,13 @@ def test_s16_small_outputs(runner, K):
 # (M, N, K): every form of the 8-bit rule on 256 compute units: 32 x 32 tiles, two wavefronts per tile (M <= 32 and
 # not), 32 x 64 and 64 x 64 tiles, each with ragged rows, columns and partial steps
 U8_CASES = [(1, 1, 1), (33, 31, 63), (64, 70, 64), (5, 300, 65), (31, 100, 129), (33, 33, 511), (70, 129, 4097), (300, 500, 200),
-            (32, 9000, 70), (7, 10001, 200), (600, 700, 300), (1000, 600, 257), (520, 1000, 64), (100, 5100, 90), (500, 1900, 1100)]
+            (32, 9000, 70), (7, 10001, 200), (600, 700, 300), (1000, 600, 257), (520, 1000, 64), (100, 5100, 90), (500, 1900, 1100),
+            (9, 33, 300), (40, 16000, 2049)]
 
 
+@pytest.mark.parametrize("pitch", ["padded", "tight"])
 @pytest.mark.parametrize("case", U8_CASES, ids=str)
-def test_u8_small_outputs(runner, case):
+def test_u8_small_outputs(runner, case, pitch):
     import torch
     import paper_1910_00178_amd as ng
     M, N, K = case
@@ -64,7 +66,7 @@ def test_u8_small_outputs(runner, case):
     A = rng.integers(0, 256, size=(M, K), dtype=np.uint8)
     B = rng.integers(-128, 128, size=(N, K), dtype=np.int8)
     handle, packed = runner.pack(B)
-    pad = -K % 16
+    pad = -K % 16 if pitch == "padded" else (1 if K % 16 == 0 else 0)      # tight: rows of any alignment
     for za, zb, ldc_pad in ((0, 0, 0), (131, 0, 1), (255, -128, 0), (7, 5, 2)):
         assert np.array_equal(runner.run(A, handle, N, za, zb, lda_pad=pad, ldc_pad=ldc_pad), oracle.gemm_u8s8s32(A, B, za, zb)), (za, zb)
         assert np.array_equal(runner.run(A, handle, N, za, zb, scale=0.0007, zc=99, lda_pad=pad, ldc_pad=ldc_pad),
