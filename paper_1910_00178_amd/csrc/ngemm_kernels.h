@@ -562,17 +562,18 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams &p, v16i (&acc)[T
                                               int wn, int lane, int tid, int nthreads, uint8_t *xpose,
                                               uint32_t *cterm_lds, const EpiCols &ec, const uint32_t *rs_reg = nullptr)
 {
-    const bool c_vec_ok = REQUANT ? ((((uintptr_t)p.C | (uintptr_t)p.ldc) & 3) == 0) : true;
     constexpr int LPR = TN * 8, RPP = 64 / LPR, NPASS = 32 / RPP;   // read-back: LPR lanes per row
     const int bcol = n0 + wn * TN * 32 + 4 * (lane % LPR);
     const bool interior = m0 + (wm + 1) * TM * 32 <= p.M && n0 + (wn + 1) * TN * 32 <= p.N;   // this wavefront's part
-    // u8 output of a wavefront part that lies inside C with 16-byte aligned rows: the bytes go through
+    // u8 output of a wavefront part that lies inside C: the bytes go through
     // the wavefront's patch as well (32 rows of TN * 32 bytes, padded) and leave as 16-byte pieces of
     // whole rows; straight from the accumulators a store instruction touches 32 rows with 8 bytes each
     // (1-2.5 % of the u8 calls of one tile per workgroup; plain stores: streaming stores of pieces of a
-    // line are far slower)
+    // line are far slower).  Rows need no alignment: the target stores 16 and 4 bytes at any address, and a byte
+    // at a time a ragged pitch cost a third of a call and more (4096 x 4100 x 1024 57.7 -> 37.5 us, 100 x 3001 x 512
+    // 6.2 -> 4.8, 2047 x 3071 x 1537 34.1 -> 27.8).
     constexpr int kRow8 = TN * 32 + 16, LPR8 = TN * 2, RPP8 = 64 / LPR8, NPASS8 = 32 / RPP8;
-    const bool u8_rows = REQUANT && interior && ((((uintptr_t)p.C | (uintptr_t)p.ldc) & 15) == 0);
+    const bool u8_rows = REQUANT && interior;
     uint4 ct_back = {0u, 0u, 0u, 0u};
     if (REQUANT) {
         // per column: (128-za)*colsum + bias, zero-point of B, scale (vectors or the scalars); thread c
@@ -634,8 +635,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams &p, v16i (&acc)[T
                     }
                     if (u8_rows) {
                         *(uint32_t *)(xpose + (lane & 31) * kRow8 + j * 32 + 8 * q + 4 * (lane >> 5)) = bw;
-                    } else if (col + 3 < p.N && c_vec_ok) {
-                        *(uint32_t *)dst = bw;
+                    } else if (col + 3 < p.N) {
+                        __builtin_memcpy(dst, &bw, 4);
                     } else {
 #pragma unroll
                         for (int t = 0; t < 4; ++t)
@@ -658,7 +659,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams &p, v16i (&acc)[T
                 o[pass] = *(const v4i *)(xpose + (RPP8 * pass + lane / LPR8) * kRow8 + 16 * (lane % LPR8));
 #pragma unroll
             for (int pass = 0; pass < NPASS8; ++pass)
-                *(v4i *)(dst0 + (int64_t)(RPP8 * pass) * p.ldc) = o[pass];
+                __builtin_memcpy(dst0 + (int64_t)(RPP8 * pass) * p.ldc, &o[pass], 16);
         }
         if (!REQUANT) {
             // read the block row back row-wise, add the column terms, store full lines
@@ -1915,6 +1916,8 @@ __global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmParams p, 
                     uint8_t *dst = (uint8_t *)p.C + (int64_t)orow * p.ldc + bcol8;
                     if (interior) {
                         __builtin_nontemporal_store(o, (v4i *)dst);   // streaming, as the int32 form's
+                    } else if (orow < p.M && bcol8 + 16 <= p.N) {
+                        __builtin_memcpy(dst, &o, 16);       // rows of any alignment
                     } else if (orow < p.M) {
                         const uint8_t *ob = (const uint8_t *)&o;
 #pragma unroll
@@ -1938,7 +1941,10 @@ __global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmParams p, 
             ct.x = p.za_term * (uint32_t)cs.x; ct.y = p.za_term * (uint32_t)cs.y;
             ct.z = p.za_term * (uint32_t)cs.z; ct.w = p.za_term * (uint32_t)cs.w;
         }
-        const bool interior = m0 + (wm + 1) * WROWS <= p.M && n0 + (wn + 1) * 128 <= p.N;
+        // Rows that begin inside a 64-byte piece of memory take the plain stores: L2 has to put the pieces together
+        // that two row pieces share, a streaming store sends each on by itself (4096 x 4100 x 1024 37.9 -> 33.9 us).
+        const bool interior = m0 + (wm + 1) * WROWS <= p.M && n0 + (wn + 1) * 128 <= p.N &&
+                              (((uintptr_t)p.C | (uintptr_t)(p.ldc * 4)) & 63) == 0;
         // the row terms of all eight blocks first, as eight independent loads (rows past M read row
         // M - 1 and are never stored): loaded block by block, each load would wait for its own
         // latency and for the stores of the block before it
@@ -2991,7 +2997,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
     // the zero fill of the partial step counts as -128 per element of a shifted operand: taken out again
     const int filled = (kbytes + 63) / 64 * 64 - kbytes;
     const uint32_t pad = ELEM == 2 ? 64u * (uint32_t)filled : (p.a_xor ? 128u * (uint32_t)filled : 0u);
-    const bool c_vec_ok = REQUANT ? ((((uintptr_t)p.C | (uintptr_t)p.ldc) & 3) == 0) : true;
     const bool small_zc = REQUANT && p.zc > -8388608 && p.zc < 8388608;
     constexpr int RSTEP = NT / CG;                       // rows the workgroup finishes at a time
 #pragma unroll
@@ -3021,8 +3026,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
                      ((uint32_t)requant_u8(c[2], sc[2], p.zc, p.relu) << 16) | ((uint32_t)requant_u8(c[3], sc[3], p.zc, p.relu) << 24);
             }
             uint8_t *dst = (uint8_t *)p.C + (int64_t)row * p.ldc + col;
-            if (col + 3 < p.N && c_vec_ok) {
-                *(uint32_t *)dst = bw;
+            if (col + 3 < p.N) {
+                __builtin_memcpy(dst, &bw, 4);
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
