@@ -399,7 +399,9 @@ int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, bool al
     // 128 x 128 tiles: 3072 x 3072 x 512 13.2 / 15.0, 2560 x 2560 x 512 10.8 / 9.6, 2176 x 2176 x 1024
     // 13.4 / 12.1, 2304^3 20.8 / 22.5, 2560^3 24.0 / 26.6).
     const int64_t big = tiles(256) > t192 ? tiles(256) : t192;
-    if ((big * 10 >= cus * 7 && K >= 512) || (big * 2 >= cus && K >= 1024) || (big * 5 >= cus * 2 && K >= 2048)) {
+    // Only where 128 x 128 tiles would not give every unit one at most (256 x 16384 x 4096, 64 tiles of 256 rows or 128
+    // of 192, half of them rows that do not exist: 35.2 us, 128 x 128 tiles 26).
+    if (tiles(128) > cus && ((big * 10 >= cus * 7 && K >= 512) || (big * 2 >= cus && K >= 1024) || (big * 5 >= cus * 2 && K >= 2048))) {
         if (!aligned) {
             // The 256 x 256 tiles are staged through registers then and pay off only when they fill most of every
             // round of compute units; else 128 x 128 tiles, which also form the row sums (us, 128 / 256, zero-point
@@ -408,16 +410,22 @@ int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, bool al
             const int64_t rounds = (tiles(256) + cus - 1) / cus;
             return tiles(256) * 100 < 58 * rounds * cus ? NGEMM_KERNEL_TILE_128 : NGEMM_KERNEL_TILE_256;
         }
+        // The large tiles take what is left of K behind their even number of stages without pipelining, 4 us and
+        // more per tile; 128 x 128 tiles that all are resident at once (two per unit) lose less by it (us, 128 against
+        // the large ones: 2047 x 3071 x 1537 23.1 / 24.3, u8 23.4 / 27.6; 700 x 8000 x 1500 20.4 / 22.1, u8 21.1 / 26.7;
+        // 1000 x 7000 x 3000 33.4 / 34.0, u8 34.0 / 35.9; 2304 x 2304 x 2304, whole stages 24.2 / 22.0).
+        if (K % 64 != 0 && tiles(128) <= 2 * cus) return NGEMM_KERNEL_TILE_128;
         // rounds of resident workgroups times the rows of a tile: 192 x 256 tiles when they fill more of the
         // compute units for less time (3072^3: 144 tiles of 256 rows against 192 of 192, one round each;
         // 2560^3: 100 against 140, 29.3 us against 24.0 us, 128 x 128 tiles 26.6 us)
         const int64_t r256 = (tiles(256) + cus - 1) / cus * 256, r192 = (t192 + cus - 1) / cus * 192;
         return r192 < r256 ? NGEMM_KERNEL_TILE_192 : NGEMM_KERNEL_TILE_256;
     }
-    // (1536^3, 144 tiles of 128 x 128: 10.0 us against 10.6 us with 64 x 64 tiles; 1024^3, 64 tiles: 7.9
-    // against 5.5; 1536 x 1536 x 512: 6.9 against 6.4)
+    // (us, 128 x 128 against 64 x 64 tiles, inputs changing from call to call: 1536^3, 144 tiles of 128 x 128 12.2 /
+    // 12.7, 1024 x 2048 x 2048, 128 tiles 13.7 / 13.0 and with a zero-point or u8 output 15.0 / 13.3; at K = 4096
+    // 1408 x 1408, 121 tiles, 18.8 / 20.3; 1024^3, 64 tiles: 7.9 / 5.5; 1536 x 1536 x 512: 6.9 / 6.4)
     // Not for M <= 64, which would leave half of every tile empty (64 x 16384 x 4096 18.6 / 14.5 us).
-    if (M > 64 && (tiles(128) >= cus || (tiles(128) * 5 >= cus * 2 && K >= 1024))) return NGEMM_KERNEL_TILE_128;
+    if (M > 64 && (tiles(128) >= cus || (tiles(128) * 20 >= cus * 11 && K >= 1024) || (tiles(128) * 5 >= cus * 2 && K >= 4096))) return NGEMM_KERNEL_TILE_128;
     return NGEMM_KERNEL_TILE_64;
 }
 
@@ -465,6 +473,7 @@ using WaveK12 = WaveKForm<1, 2, 4, 3>;       // 72 KiB
 using WaveK22 = WaveKForm<2, 2, 2, 4>;       // 64 KiB (16-bit operands)
 using WaveK11Short = WaveKForm<1, 1, 2, 4>;  // 32 KiB: five workgroups per compute unit
 using WaveK22Long = WaveKForm<2, 2, 4, 3>;   // 96 KiB: one
+using WaveK24 = WaveKForm<2, 4, 4, 3>;       // 144 KiB: one
 using WaveK12Short = WaveKForm<1, 2, 2, 4>;  // 48 KiB (A through registers)
 
 template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false>
@@ -512,6 +521,9 @@ hipError_t allow_big_lds_wavek_u8()
 //    512 x 768 x 768 4.4 / 5.1;
 //  * a K of up to 1024 and up to three 32 x 32 tiles per unit: 1024 x 768 x 768 5.0 / 5.5, 700 x 900 x 600
 //    6.3 / 6.5; at four tiles per unit (1024 x 1024 x 256 4.6 / 4.4) and below K = 256 it is a tie or a loss;
+//  * 64 x 128 tiles, one per compute unit at most, and a long K, in the place of 128 x 128 tiles on half of the units or
+//    of two rounds of 64 x 64: 512 x 4096 x 4096 16.8 / 19.3 (z 18.0 / 21.9), 128 x 16384 x 4096 18.1 / 20.2 (z 20.4 /
+//    23.0); at K = 2048 it is a tie (1024 x 2048 x 2048 12.0 / 11.9);
 //  * 64 x 64 tiles with row sums and a long K: 256 x 4096 x 4096 z 11.8 / 13.7, 384 x 2048 x 2048 z 8.3 / 9.0.
 int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
 {
@@ -525,6 +537,7 @@ int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
     if (tiles(32, 64) <= cus) return 12;
     if (K >= 256 && K <= 1024 && t32 <= 3 * cus && t64 <= cus) return 1;
     if (rows && K > 1024 && t64 <= cus) return 22;
+    if (K >= 3072 && t64 > cus && tiles(64, 128) <= cus) return 24;
     return 0;
 }
 
@@ -541,6 +554,7 @@ hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool r
     case 1: return launch_wavek_u8<WaveK11Short>(p, requant, rows, st);
     case 11: return launch_wavek_u8<WaveK11>(p, requant, rows, st);
     case 12: return launch_wavek_u8<WaveK12>(p, requant, rows, st);
+    case 24: return launch_wavek_u8<WaveK24>(p, requant, rows, st);
     default: return launch_wavek_u8<WaveK22Long>(p, requant, rows, st);
     }
 }
@@ -586,6 +600,7 @@ hipError_t launch_wavek_raw_form(int form, const GemmParams &p, bool rows, const
     case 1: return launch_wavek_raw<WaveK11Short>(p, rows, rawb, st);
     case 11: return launch_wavek_raw<WaveK11>(p, rows, rawb, st);
     case 12: return launch_wavek_raw<WaveK12>(p, rows, rawb, st);
+    case 24: return launch_wavek_raw<WaveK24>(p, rows, rawb, st);
     default: return launch_wavek_raw<WaveK22Long>(p, rows, rawb, st);
     }
 }
@@ -716,13 +731,13 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
     }
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
     // outputs of few tiles: K split over the wavefronts of a workgroup
-    if (kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64) {
+    if (kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64 || (kernel == NGEMM_KERNEL_TILE_128 && dma_ok)) {
         if (!dma_ok) {
             const int form = wavek_areg_form(a.M, B->N, B->K, device_cus);
             if (form != 0) return launch_wavek_areg_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
         const int form = dma_ok ? wavek_form(a.M, B->N, B->K, rows_needed, device_cus) : 0;
-        if (form != 0) return launch_wavek_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+        if (form != 0 && (kernel != NGEMM_KERNEL_TILE_128 || form == 24)) return launch_wavek_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
     }
     // at most one tile per compute unit and a K worth pipelining: the long-pipeline variants
     const bool deep64 = kernel == NGEMM_KERNEL_TILE_64 && dma_ok && B->K >= 512 &&
@@ -883,7 +898,7 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
             hipFuncSetAttribute((const void *)gemm_s16_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 S16Cfg::kLdsBytes) != hipSuccess ||
             allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess ||
-            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess) {
+            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess) {
             delete c;
             return NGEMM_ERR_DEVICE;
         }
@@ -1297,8 +1312,9 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
         kernel = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     const bool aligned = (((uintptr_t)A_dev | (uintptr_t)lda | (uintptr_t)B_dev | (uintptr_t)ldb) & 15) == 0;
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-    const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || (kernel == NGEMM_KERNEL_SKINNY && M <= kSkinnyMaxM);   // M > 32: refused below
-    const int form = aligned && K > 0 && small_kernel ? wavek_raw_form(M, N, K, cus) : 0;
+    const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128 || (kernel == NGEMM_KERNEL_SKINNY && M <= kSkinnyMaxM);   // M > 32: refused below
+    int form = aligned && K > 0 && small_kernel ? wavek_raw_form(M, N, K, cus) : 0;
+    if (kernel == NGEMM_KERNEL_TILE_128 && form != 24) form = 0;
     if (aligned && K > 0 && (form != 0 || kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return NGEMM_ERR_DEVICE;

@@ -50,10 +50,10 @@ def test_s16_small_outputs(runner, K):
 
 
 # (M, N, K): every form of the 8-bit rule on 256 compute units: 32 x 32 tiles, two wavefronts per tile (M <= 32 and
-# not), 32 x 64 and 64 x 64 tiles, each with ragged rows, columns and partial steps
+# not), 32 x 64, 64 x 64 and 64 x 128 tiles, each with ragged rows, columns and partial steps
 U8_CASES = [(1, 1, 1), (33, 31, 63), (64, 70, 64), (5, 300, 65), (31, 100, 129), (33, 33, 511), (70, 129, 4097), (300, 500, 200),
             (32, 9000, 70), (7, 10001, 200), (600, 700, 300), (1000, 600, 257), (520, 1000, 64), (100, 5100, 90), (500, 1900, 1100),
-            (9, 33, 300), (40, 16000, 2049)]
+            (9, 33, 300), (40, 16000, 2049), (300, 4000, 3100), (1000, 1300, 3073)]
 
 
 @pytest.mark.parametrize("pitch", ["padded", "tight"])
@@ -94,7 +94,7 @@ def test_u8_small_outputs(runner, case, pitch):
 # Unpacked B: the forms above on the caller's storage, and the 64 x 64 (1100 x 1600) and 128 x 128 (1600 x 1700 with a
 # long K) tiles that form both operands' sums
 RAW_CASES = [(1, 1, 1), (33, 31, 63), (31, 100, 129), (300, 500, 200), (32, 9000, 70), (7, 10001, 200), (600, 700, 300),
-             (500, 1900, 1100), (1100, 1600, 100), (1111, 1601, 64), (1600, 1700, 1041), (30, 17000, 4100)]
+             (500, 1900, 1100), (1100, 1600, 100), (1111, 1601, 64), (1600, 1700, 1041), (30, 17000, 4100), (300, 4000, 3100)]
 
 
 @pytest.mark.parametrize("case", RAW_CASES, ids=str)
