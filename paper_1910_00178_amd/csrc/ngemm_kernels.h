@@ -384,18 +384,17 @@ __global__ __launch_bounds__(NT) void pack_b_kernel(const uint8_t *__restrict__ 
 // ones, then across the lanes.
 __device__ __forceinline__ int row_sum_shifted(const uint8_t *row, int K, int lane, uint32_t mask)
 {
-    int s = 0;
-    for (int k = lane * 16; k < K; k += 64 * 16) {
-        v4i v = (k + 16 <= K) ? load16_any(row + k) : load16_partial(row + k, K - k);
-        v = shift_u8_to_s8(v, mask);
-        if (k + 16 > K && mask) {
-            // bytes past K were zero before the shift: take their -128 back out
-            s += 128 * (k + 16 - K);
-        }
+    int s = 0, k = lane * 16;
+    auto add = [&](const v4i &v) {
         s = __builtin_amdgcn_sdot4(v.x, 0x01010101, s, false);
         s = __builtin_amdgcn_sdot4(v.y, 0x01010101, s, false);
         s = __builtin_amdgcn_sdot4(v.z, 0x01010101, s, false);
         s = __builtin_amdgcn_sdot4(v.w, 0x01010101, s, false);
+    };
+    for (; k + 16 <= K; k += 64 * 16) add(shift_u8_to_s8(load16_any(row + k), mask));
+    if (k < K) {                                         // the row's last, partial chunk: one lane's
+        add(shift_u8_to_s8(load16_partial(row + k, K - k), mask));
+        if (mask) s += 128 * (k + 16 - K);               // bytes past K were zero before the shift: their -128 back out
     }
     return wave_sum(s);
 }
