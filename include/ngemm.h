@@ -56,8 +56,7 @@ typedef enum {
 enum {
     NGEMM_KERNEL_AUTO = -1,
     NGEMM_KERNEL_SKINNY = 0,     /* split-K streaming kernel, M <= 32 only                */
-    NGEMM_KERNEL_TILE_64 = 1,    /* 64 x 64 workgroup tile (both: smaller tiles, K split over the wavefronts of a
-                                    workgroup, for outputs of few tiles with 16-byte aligned rows of A)       */
+    NGEMM_KERNEL_TILE_64 = 1,    /* 64 x 64 workgroup tile                                */
     NGEMM_KERNEL_TILE_128 = 2,   /* 128 x 128 workgroup tile                              */
     NGEMM_KERNEL_TILE_256 = 3,   /* 256 x 256 workgroup tile (throughput configuration)   */
     NGEMM_KERNEL_SPLIT_K = 4,    /* 64 x 64 tiles, K split over workgroups; int32 outputs */
@@ -86,7 +85,10 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal);
 ngemm_status ngemm_destroy(ngemm_ctx *ctx);
 
 /* Force one kernel for the run calls (NGEMM_KERNEL_*), or NGEMM_KERNEL_AUTO for
- * the shape heuristic.  Forcing NGEMM_KERNEL_SKINNY with M > 32 makes the run
+ * the shape heuristic.  For outputs of few tiles the heuristic also has a kernel that splits K
+ * over the wavefronts of a workgroup, in the place of the streaming kernel, the 64 x 64 and the
+ * 128 x 128 tiles; a forced kernel is always the one that runs.  The calls on 16-bit operands
+ * follow the heuristic whatever is forced.  Forcing NGEMM_KERNEL_SKINNY with M > 32 makes the run
  * call return NGEMM_ERR_INVALID_ARG.  NGEMM_KERNEL_SPLIT_K serves outputs with so few
  * 64 x 64 tiles that most compute units would idle: K is cut into parts of at least 1024
  * bytes, one workgroup per tile and part; C is cleared by a launch of its own and the parts
@@ -105,7 +107,9 @@ ngemm_status ngemm_set_kernel(ngemm_ctx *ctx, int kernel);
  * and remember the fastest for later run calls of any entry point with the same (M, N, K) on
  * this context while the kernel choice is NGEMM_KERNEL_AUTO.  Arguments as for
  * ngemm_run_u8s8s32.  The call waits for the stream; it belongs to set-up, next to the pack.
- * *best_kernel (may be NULL) receives the NGEMM_KERNEL_* value.  A context is not meant to be
+ * *best_kernel (may be NULL) receives the fastest NGEMM_KERNEL_* value, one that ngemm_set_kernel
+ * takes; where the kernel that splits K over the wavefronts of a workgroup is faster still, the
+ * later run calls take that.  A context is not meant to be
  * tuned and used from several threads at once.
  */
 ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M,

@@ -34,7 +34,8 @@ struct ngemm_ctx {
     // kernels found fastest by ngemm_tune_u8s8s32, by shape; consulted before the shape heuristic
     struct Tuned {
         int64_t M, N, K;
-        int kernel;
+        int kernel;          // the fastest of NGEMM_KERNEL_*
+        bool wavek;          // the kernel that splits K over a workgroup's wavefronts was faster still
     };
     std::vector<Tuned> tuned;
 };
@@ -587,6 +588,15 @@ hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, b
     return form == 11 ? launch_wavek_areg<WaveK11>(p, requant, rows, st) : launch_wavek_areg<WaveK12Short>(p, requant, rows, st);
 }
 
+// The form that takes the place of `kernel` (the streaming kernel, 64 x 64 tiles, 128 x 128 tiles with aligned rows), or 0.
+int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, int64_t cus)
+{
+    const bool small = kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64;
+    if (!aligned) return small ? wavek_areg_form(M, N, K, cus) : 0;
+    const int form = small || kernel == NGEMM_KERNEL_TILE_128 ? wavek_form(M, N, K, rows, cus) : 0;
+    return small || form == 24 ? form : 0;
+}
+
 // The forms that read B from the caller's storage.
 template <class F>
 hipError_t launch_wavek_raw(const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
@@ -640,7 +650,15 @@ struct RunArgs {
     bool needs_rowsum() const { return zb != 0 || zb_vec != nullptr; }
 };
 
-ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, int *kernel_out)
+// What serves a call: one of NGEMM_KERNEL_*, and whether the kernel that splits K over a workgroup's wavefronts may
+// take its place where its rules have a form for the call.  It may for the automatic choice and for shapes whose
+// tuning found it faster; a kernel that the caller asked for is the one that runs.
+struct Route {
+    int kernel;
+    bool wavek;
+};
+
+ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
 {
     if (!ctx_ok(ctx) || !pack_ok(a.B)) return NGEMM_ERR_INVALID_ARG;
     if (a.B->device != ctx->device) return NGEMM_ERR_INVALID_ARG;
@@ -653,19 +671,26 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, int *kernel_ou
         if (!std::isfinite(a.scale) || a.scale < 0x1p-30f || a.scale > 0x1p30f) return NGEMM_ERR_INVALID_ARG;
     }
     if (a.M == 0 || a.B->N == 0) {
-        *kernel_out = NGEMM_KERNEL_AUTO;
+        *route = Route{NGEMM_KERNEL_AUTO, false};
         return NGEMM_OK;
     }
     if (!a.C || (!a.A && a.B->K > 0)) return NGEMM_ERR_INVALID_ARG;
     if (a.lda < a.B->K || a.ldc < a.B->N) return NGEMM_ERR_BAD_SHAPE;
-    int k = ctx->force_kernel;
-    if (k == NGEMM_KERNEL_AUTO) {
+    Route r{ctx->force_kernel, false};
+    const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+    if (r.kernel == NGEMM_KERNEL_AUTO) {
         for (const ngemm_ctx::Tuned &t : ctx->tuned)
-            if (t.M == a.M && t.N == a.B->N && t.K == a.B->K) k = t.kernel;
-        if (k == NGEMM_KERNEL_AUTO) k = choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda));
+            if (t.M == a.M && t.N == a.B->N && t.K == a.B->K) {
+                r = Route{t.kernel, false};
+                const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
+                // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
+                if (t.wavek && wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus) != 0)
+                    r = Route{small, true};
+            }
+        if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda)), true};
     }
-    if (k == NGEMM_KERNEL_SKINNY && a.M > kSkinnyMaxM) return NGEMM_ERR_INVALID_ARG;
-    *kernel_out = k;
+    if (r.kernel == NGEMM_KERNEL_SKINNY && a.M > kSkinnyMaxM) return NGEMM_ERR_INVALID_ARG;
+    *route = r;
     return NGEMM_OK;
 }
 
@@ -709,13 +734,14 @@ GemmParams make_params(const RunArgs &a, int nxcd)
 
 // Launches one validated GEMM; `ws` must hold rowsum_bytes(M) when zb != 0.  What lies beyond those
 // bytes serves the K split for its partial results when there is enough of it.
-ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cus, int nxcd, void *ws, size_t ws_bytes,
+ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_cus, int nxcd, void *ws, size_t ws_bytes,
                         hipStream_t st)
 {
     const ngemm_packed_b *B = a.B;
     if (a.M == 0 || B->N == 0) return NGEMM_OK;
     GemmParams p = make_params(a, nxcd);
     const bool dma_ok = rows_aligned(a.A, a.lda);
+    int kernel = route.kernel;
     int kchunk = 0, parts = 1;
     int32_t *part_ws = nullptr;
     if (kernel == NGEMM_KERNEL_SPLIT_K) {
@@ -731,13 +757,13 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
     }
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
     // outputs of few tiles: K split over the wavefronts of a workgroup
-    if (kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64 || (kernel == NGEMM_KERNEL_TILE_128 && dma_ok)) {
-        if (!dma_ok) {
-            const int form = wavek_areg_form(a.M, B->N, B->K, device_cus);
-            if (form != 0) return launch_wavek_areg_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+    if (route.wavek) {
+        const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, device_cus);
+        if (form != 0) {
+            const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, st)
+                                         : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
+            return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
-        const int form = dma_ok ? wavek_form(a.M, B->N, B->K, rows_needed, device_cus) : 0;
-        if (form != 0 && (kernel != NGEMM_KERNEL_TILE_128 || form == 24)) return launch_wavek_form(form, p, a.requant, rows_needed, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
     }
     // at most one tile per compute unit and a K worth pipelining: the long-pipeline variants
     const bool deep64 = kernel == NGEMM_KERNEL_TILE_64 && dma_ok && B->K >= 512 &&
@@ -808,11 +834,9 @@ ngemm_status launch_run(const RunArgs &a, int kernel, int num_cus, int device_cu
     return e == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
 }
 
-ngemm_status run_common(ngemm_ctx *ctx, const RunArgs &a, void *ws, size_t ws_bytes, void *stream)
+// A validated call on a given kernel.
+ngemm_status run_route(ngemm_ctx *ctx, const RunArgs &a, Route route, void *ws, size_t ws_bytes, void *stream)
 {
-    int kernel;
-    ngemm_status s = validate_run(ctx, a, &kernel);
-    if (s != NGEMM_OK) return s;
     if (a.M == 0 || a.B->N == 0) return NGEMM_OK;
     if (a.needs_rowsum() && a.B->K > 0) {
         if (!ws) return NGEMM_ERR_INVALID_ARG;
@@ -822,8 +846,15 @@ ngemm_status run_common(ngemm_ctx *ctx, const RunArgs &a, void *ws, size_t ws_by
     if (ws && ws_bytes > 0 && ((uintptr_t)ws & 15u) != 0) return NGEMM_ERR_INVALID_ARG;
     DeviceGuard g(ctx->device);
     if (!g.ok) return NGEMM_ERR_DEVICE;
-    return launch_run(a, kernel, workgroup_budget(ctx), ctx->num_cus > 0 ? ctx->num_cus : 256, ctx->num_xcd, ws, ws_bytes,
+    return launch_run(a, route, workgroup_budget(ctx), ctx->num_cus > 0 ? ctx->num_cus : 256, ctx->num_xcd, ws, ws_bytes,
                       (hipStream_t)stream);
+}
+
+ngemm_status run_common(ngemm_ctx *ctx, const RunArgs &a, void *ws, size_t ws_bytes, void *stream)
+{
+    Route route;
+    const ngemm_status s = validate_run(ctx, a, &route);
+    return s == NGEMM_OK ? run_route(ctx, a, route, ws, ws_bytes, stream) : s;
 }
 
 }  // namespace
@@ -932,9 +963,9 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
     if (!ctx_ok(ctx) || !pack_ok(B)) return NGEMM_ERR_INVALID_ARG;
     RunArgs a{M, A_dev, lda, a_zero_point, b_zero_point, B, C_dev, ldc, false, 1.0f, 0};
     const int saved = ctx->force_kernel;
-    int dummy;
+    Route checked;
     ctx->force_kernel = NGEMM_KERNEL_TILE_64;         // valid for every shape: checks the arguments
-    ngemm_status s = validate_run(ctx, a, &dummy);
+    ngemm_status s = validate_run(ctx, a, &checked);
     ctx->force_kernel = saved;
     if (s != NGEMM_OK) return s;
     if (M == 0 || B->N == 0 || B->K == 0) return NGEMM_OK;   // nothing to measure
@@ -947,23 +978,27 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
         (void)hipEventDestroy(e0);
         return NGEMM_ERR_DEVICE;
     }
-    const int candidates[6] = {NGEMM_KERNEL_SKINNY, NGEMM_KERNEL_TILE_64, NGEMM_KERNEL_TILE_128, NGEMM_KERNEL_TILE_256,
-                               NGEMM_KERNEL_SPLIT_K, NGEMM_KERNEL_TILE_192};
+    const bool dma_ok = rows_aligned(A_dev, lda);
+    const int small = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
+    // the last one: the kernel that splits K over a workgroup's wavefronts, in the place of the kernel for small outputs
+    const Route candidates[7] = {{NGEMM_KERNEL_SKINNY, false}, {NGEMM_KERNEL_TILE_64, false}, {NGEMM_KERNEL_TILE_128, false},
+                                 {NGEMM_KERNEL_TILE_256, false}, {NGEMM_KERNEL_SPLIT_K, false}, {NGEMM_KERNEL_TILE_192, false},
+                                 {small, true}};
     int best = NGEMM_KERNEL_AUTO;
+    bool best_wavek = false;
     float best_ms = 0.0f;
     s = NGEMM_OK;
-    for (int c = 0; c < 6 && s == NGEMM_OK; ++c) {
-        const int k = candidates[c];
+    for (int c = 0; c < 7 && s == NGEMM_OK; ++c) {
+        const int k = candidates[c].kernel;
         if (k == NGEMM_KERNEL_SKINNY && M > kSkinnyMaxM) continue;
         // a tile far larger than the output cannot win: skip what would leave most of it empty
         if ((k == NGEMM_KERNEL_TILE_256 || k == NGEMM_KERNEL_TILE_192) && (M <= 64 || B->N <= 64)) continue;
         if (k == NGEMM_KERNEL_SPLIT_K) {
             // only where it would really split (else it is the 64 x 64 candidate once more)
             int kchunk = 0;
-            const bool dma_ok = (((uintptr_t)A_dev | (uintptr_t)lda) & 15) == 0;
             if (!dma_ok || splitk_parts(M, B->N, B->K, workgroup_budget(ctx), &kchunk) < 2) continue;
         }
-        ctx->force_kernel = k;
+        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, ctx->num_cus > 0 ? ctx->num_cus : 256) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
         const int warm = 5, reps = 50, rounds = 3;
@@ -971,7 +1006,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
         for (int round = 0; round < rounds && s == NGEMM_OK; ++round) {
             for (int r = (round == 0 ? 0 : warm); r < warm + reps && s == NGEMM_OK; ++r) {
                 if (r == warm && hipEventRecord(e0, st) != hipSuccess) s = NGEMM_ERR_DEVICE;
-                if (s == NGEMM_OK) s = run_common(ctx, a, workspace_dev, workspace_bytes, hip_stream);
+                if (s == NGEMM_OK) s = run_route(ctx, a, candidates[c], workspace_dev, workspace_bytes, hip_stream);
             }
             float t = 0.0f;
             if (s == NGEMM_OK && (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
@@ -980,11 +1015,11 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
             if (round == 0 || t < ms) ms = t;
         }
         if (s == NGEMM_OK && (best == NGEMM_KERNEL_AUTO || ms < best_ms)) {
-            best = k;
+            if (candidates[c].wavek) best_wavek = true;      // `best` stays the fastest that a caller can force
+            else best = k;
             best_ms = ms;
         }
     }
-    ctx->force_kernel = saved;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (s != NGEMM_OK) return s;
@@ -992,12 +1027,13 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
     for (ngemm_ctx::Tuned &t : ctx->tuned)
         if (t.M == M && t.N == B->N && t.K == B->K) {
             t.kernel = best;
+            t.wavek = best_wavek;
             found = true;
         }
     if (!found) {
         try {
             if (ctx->tuned.size() >= 4096) ctx->tuned.erase(ctx->tuned.begin());
-            ctx->tuned.push_back(ngemm_ctx::Tuned{M, B->N, B->K, best});
+            ctx->tuned.push_back(ngemm_ctx::Tuned{M, B->N, B->K, best, best_wavek});
         } catch (...) {
             return NGEMM_ERR_DEVICE;               // out of host memory: measured, but not remembered
         }
@@ -1312,8 +1348,9 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
         kernel = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     const bool aligned = (((uintptr_t)A_dev | (uintptr_t)lda | (uintptr_t)B_dev | (uintptr_t)ldb) & 15) == 0;
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-    const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128 || (kernel == NGEMM_KERNEL_SKINNY && M <= kSkinnyMaxM);   // M > 32: refused below
-    int form = aligned && K > 0 && small_kernel ? wavek_raw_form(M, N, K, cus) : 0;
+    const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128 || kernel == NGEMM_KERNEL_SKINNY;
+    // the kernel that splits K over a workgroup's wavefronts: of the automatic choice only
+    int form = aligned && K > 0 && small_kernel && ctx->force_kernel == NGEMM_KERNEL_AUTO ? wavek_raw_form(M, N, K, cus) : 0;
     if (kernel == NGEMM_KERNEL_TILE_128 && form != 24) form = 0;
     if (aligned && K > 0 && (form != 0 || kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
@@ -1387,8 +1424,8 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
     for (int t = 0; t < count; ++t) {
         const ngemm_problem &q = problems[t];
         RunArgs a{q.M, q.A_dev, q.lda, q.a_zero_point, q.b_zero_point, q.B, q.C_dev, q.ldc, false, 1.0f, 0};
-        int kernel;
-        ngemm_status s = validate_run(ctx, a, &kernel);
+        Route route;
+        ngemm_status s = validate_run(ctx, a, &route);
         if (s != NGEMM_OK) return s;
     }
     DeviceGuard g(ctx->device);

@@ -1,0 +1,159 @@
+"""Which kernel a call launches: the calls are captured into a graph that is never run, and the names and grids of the
+graph's kernel nodes are looked at.  A kernel that a caller forced is the one that runs, so the tests that force a
+kernel run the kernel they name."""
+import ctypes
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")                 # before the library: both then use torch's HIP runtime
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class _KernelNode(ctypes.Structure):                     # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+@pytest.fixture(scope="module")
+def launches():
+    """launches(call) -> [(kernel name, workgroups)] of what call(stream) launches; nothing is executed."""
+    import paper_1910_00178_amd as ng
+    hip = ctypes.CDLL(ng.LIB_PATH)                       # the HIP runtime that the library itself is bound to
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    demangle = ctypes.CDLL("libstdc++.so.6").__cxa_demangle
+    demangle.restype = ctypes.c_char_p
+    stream = torch.cuda.Stream()
+
+    def ok(code):
+        assert code == 0, code
+
+    def run(call):
+        st, graph, n = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t(0)
+        ok(hip.hipStreamBeginCapture(st, 2))             # relaxed
+        try:
+            call(stream)
+        finally:
+            ended = hip.hipStreamEndCapture(st, ctypes.byref(graph))
+        ok(ended)
+        ok(hip.hipGraphGetNodes(graph, None, ctypes.byref(n)))
+        nodes = (ctypes.c_void_p * n.value)()
+        ok(hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)))
+        out = []
+        for node in nodes:
+            p = _KernelNode()
+            ok(hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)))
+            name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), st)
+            full = demangle(name, None, None, None) or name
+            out.append((full.decode().replace("void ", "").split("(")[0].replace("ngemm::", ""), p.grid.x))
+        ok(hip.hipGraphDestroy(graph))
+        return out
+
+    return run
+
+
+class Problem:
+    """Operands of one 8-bit product (contents do not matter: nothing is run)."""
+
+    def __init__(self, ctx, M, N, K, pitch=None):
+        import paper_1910_00178_amd as ng
+        self.ng, self.ctx, self.M, self.N, self.K = ng, ctx, M, N, K
+        self.lda = pitch or (K + 15) // 16 * 16
+        self.A = torch.zeros((M, self.lda), dtype=torch.uint8, device="cuda")
+        self.B = torch.zeros((N, self.lda), dtype=torch.int8, device="cuda")
+        nb = ng.ngemm_packed_b_bytes(K, N)
+        self.packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        self.h = ng.ngemm_pack_b(ctx, K, N, self.B, self.lda, self.packed, nb)
+        self.C = torch.empty((M, N), dtype=torch.int32, device="cuda")
+        self.wsb = ng.ngemm_workspace_bytes(M, N, K)
+        self.ws = torch.empty(self.wsb, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+
+    def run(self, zb=0):
+        return lambda st: self.ng.ngemm_run_u8s8s32(self.ctx, self.M, self.A, self.lda, 7, self.h, zb, self.C, self.N, self.ws, self.wsb, st)
+
+    def run_u8(self, zb=0):
+        return lambda st: self.ng.ngemm_run_u8s8u8_requant(self.ctx, self.M, self.A, self.lda, 7, self.h, zb, 0.01, 3, self.C, 4 * self.N,
+                                                           self.ws, self.wsb, st)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_1910_00178_amd as ng
+    c = ng.ngemm_create(0)
+    yield c
+    ng.ngemm_destroy(c)
+
+
+# (kernel, M, N, K, pitch, zero-point of B, what runs): shapes that the automatic choice gives to the kernel that splits K
+# over wavefronts
+FORCED = [
+    ("SKINNY", 16, 4096, 1024, None, 0, "gemm_skinny_kernel<false, 1>"),
+    ("SKINNY", 17, 32840, 2112, None, 3, "gemm_skinny_kernel<false, 4>"),
+    ("SKINNY", 9, 65600, 2048, None, 3, "gemm_stream_skinny_kernel<false>"),
+    ("SKINNY", 20, 4096, 1025, 1025, 3, "gemm_skinny_kernel<false, 1>"),
+    ("TILE_64", 64, 4096, 4096, None, 0, "gemm_tile_deep_kernel<1, 4, 4, false, 0, false>"),
+    ("TILE_64", 64, 4096, 4096, None, 3, "gemm_tile_deep_kernel<1, 4, 4, false, 0, true>"),
+    ("TILE_64", 300, 200, 200, None, 3, "gemm_tile_dma_kernel<64, 64, 2, 2, 4, false, false, true>"),
+    ("TILE_64", 64, 1000, 4097, 4097, 3, "gemm_tile_kernel<64, 64, 2, 2, 64, false, true>"),
+    ("TILE_128", 512, 4096, 4096, None, 3, "gemm_tile_deep_kernel<2, 2, 4, false, 0, true>"),
+    ("SPLIT_K", 40, 4000, 3000, None, 0, "gemm_tile_deep_kernel<1, 4, 4, false, 1, false>"),
+    # what a forced K split cannot serve: the 64 x 64 tiles, the streaming kernel
+    ("SPLIT_K", 64, 1000, 1024, None, 3, "gemm_tile_deep_kernel<1, 4, 4, false, 0, true>"),
+    ("SPLIT_K", 16, 1000, 1024, None, 3, "gemm_skinny_kernel<false, 1>"),
+]
+
+
+@pytest.mark.parametrize("case", FORCED, ids=str)
+def test_a_forced_kernel_is_the_one_that_runs(ctx, launches, case):
+    import paper_1910_00178_amd as ng
+    kernel, M, N, K, pitch, zb, want = case
+    p = Problem(ctx, M, N, K, pitch)
+    ng.ngemm_set_kernel(ctx, getattr(ng, "NGEMM_KERNEL_" + kernel))
+    try:
+        got = launches(p.run(zb))
+    finally:
+        ng.ngemm_set_kernel(ctx, ng.NGEMM_KERNEL_AUTO)
+    assert got[-1][0] == want, got
+    automatic = launches(p.run(zb))
+    assert [name.split("<")[0] for name, _ in automatic] == ["gemm_wavek_kernel"], automatic
+    ng.ngemm_packed_b_free(p.h)
+
+
+@pytest.mark.parametrize("M,kernel,want", [(16, "SKINNY", "gemm_skinny_kernel<"), (500, "TILE_64", "gemm_tile_dma_kernel<64, 64,"),
+                                           (500, "TILE_128", "gemm_tile_dma_kernel<128, 128,")])
+def test_a_forced_kernel_on_unpacked_operands(ctx, launches, M, kernel, want):
+    import paper_1910_00178_amd as ng
+    N, K = 700, 1024
+    p = Problem(ctx, M, N, K)
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    call = lambda st: ng.ngemm_run_u8s8s32_unpacked(ctx, M, N, K, p.A, p.lda, 7, p.B, p.lda, 3, p.C, N, ws, wsb, st)
+    ng.ngemm_set_kernel(ctx, getattr(ng, "NGEMM_KERNEL_" + kernel))
+    try:
+        got = launches(call)
+    finally:
+        ng.ngemm_set_kernel(ctx, ng.NGEMM_KERNEL_AUTO)
+    assert got[-1][0].startswith(want), got
+    assert [name.split("<")[0] for name, _ in launches(call)] == ["gemm_wavek_kernel"]
+    ng.ngemm_packed_b_free(p.h)
+
+
+def test_tuning_chooses_among_all_of_them(ctx, launches):
+    """The tuner reports a kernel that can be forced, and where the kernel that splits K over wavefronts beat it by far
+    (64 x 4096 x 4096: 7 us against 10 and more) later calls take that one."""
+    import paper_1910_00178_amd as ng
+    own = ng.ngemm_create(0)
+    p = Problem(own, 64, 4096, 4096)
+    best = ng.ngemm_tune_u8s8s32(own, p.M, p.A, p.lda, 7, p.h, 3, p.C, p.N, p.ws, p.wsb)
+    assert best in (ng.NGEMM_KERNEL_TILE_64, ng.NGEMM_KERNEL_TILE_128, ng.NGEMM_KERNEL_SPLIT_K)
+    assert ng.ngemm_tuned_kernel(own, p.M, p.N, p.K) == best
+    assert launches(p.run(3))[0][0].startswith("gemm_wavek_kernel<"), best
+    ng.ngemm_set_kernel(own, best)
+    assert not any(name.startswith("gemm_wavek_kernel<") for name, _ in launches(p.run(3)))
+    ng.ngemm_packed_b_free(p.h)
+    ng.ngemm_destroy(own)
