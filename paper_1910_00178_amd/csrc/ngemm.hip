@@ -477,23 +477,23 @@ using WaveK22Long = WaveKForm<2, 2, 4, 3>;   // 96 KiB: one
 using WaveK24 = WaveKForm<2, 4, 4, 3>;       // 144 KiB: one
 using WaveK12Short = WaveKForm<1, 2, 2, 4>;  // 48 KiB (A through registers)
 
-template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false>
+template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false>
 hipError_t launch_wavek(const GemmParams &p0, hipStream_t st, const RawB &rawb = RawB{nullptr, 0})
 {
     GemmParams p = p0;
     p.tiles_m = (p.M + F::TM * 32 - 1) / (F::TM * 32);
     p.tiles_n = (p.N + F::TN * 32 - 1) / (F::TN * 32);
-    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW, AREG>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
+    hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW, AREG, NT>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
                        dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, p, rawb);
     return hipGetLastError();
 }
 
-template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false>
+template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false, bool NT = false>
 hipError_t allow_big_lds_wavek()
 {
     constexpr int lds = WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes;
     if (lds <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute((const void *)gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW>,
+    return hipFuncSetAttribute((const void *)gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW, false, NT>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
@@ -509,15 +509,64 @@ hipError_t allow_big_lds_wavek_u8()
     return e;
 }
 
-// The form that serves an 8-bit problem with aligned rows of A (10 TM + TN of its tile, 1 for WaveK11Short), or
-// 0: the skinny and 64 x 64 kernels are faster.  us in a graph, this kernel / the others (at z: with a zero-point
-// of B, whose row sums cost the others more):
+template <class F>
+hipError_t allow_big_lds_wavek_nt()
+{
+    hipError_t e = allow_big_lds_wavek<F, 1, false, false, false, true>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, false, true, false, true>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, true, false, false, true>();
+    if (e == hipSuccess) e = allow_big_lds_wavek<F, 1, true, true, false, true>();
+    return e;
+}
+
+// M <= 32, aligned rows: the form (10 TM + TN of its tile, 1 for WaveK11Short), or 0: the streaming kernel is faster.  A weight
+// may be read again and again from cache or come from memory on every call, so the lines lie where neither loses much:
+// us in a graph, one weight / three in turn / 768 MiB of them in turn (every byte from memory), streaming kernel,
+// then this one (copies as wavek_nt says):
+//  * a 32 x 32 tile per compute unit at most: 16 x 1024 x 1024 3.68 / 3.59 / 3.98, 3.23 / 3.14 / 3.71; 8 x 8192 x 4096
+//    6.7 / 8.2 / 8.9, 5.9 / 7.3 / 8.0.  Two wavefronts are enough up to K = 512 (1 x 4096 x 512 3.42 with four, 3.35 with two);
+//  * up to two tiles per unit and up to eight rows: 1 x 16384 x 1024 4.2 / 5.0 / 5.6, 4.0 / 5.0 / 5.7, but 1 x 16384 x 4096
+//    10.6 / 11.6 / 12.7, 10.7 / 12.0 / 13.2 and 8 x 16384 x 2048 5.9 / 7.1 / 7.8, 5.7 / 7.5 / 8.2: half of what this kernel copies
+//    is A.  More rows: 16 x 16384 x 4096 13.3 / 13.8 / 14.6, 11.1 / 12.5 / 13.5; two panels per workgroup from K = 2048
+//    on (32 x 16384 x 2048 6.5 / 8.4 / 10.4 with one, 6.0 / 8.6 / 9.6 with two; 16 x 16384 x 512 3.5 / 3.4 / 4.7 and 3.7 / 3.6 / 4.9);
+//  * more tiles and up to 64 MiB of weight: 8 x 32768 x 1024 8.8 / 10.8 / 11.6, 6.0 / 8.3 / 9.9; 1 x 32768 x 2048
+//    12.5 / 13.1 / 14.1, 12.3 / 13.2 / 14.2; not for a few rows and the shortest K (1 x 32768 x 256 4.0 / 3.9 / 4.8, 4.0 / 3.9 / 5.2; 1 x 32768 x 300
+//    4.8 / 5.1 / 5.9, 4.4 / 4.9 / 7.0; at 512 it is 7.6 / 8.2 (in cache, from memory), 4.4 / 6.8);
+//  * larger ones, more than eight rows: 32 x 32768 x 4096 27.3 / 28.2 / 29.8, 22.3 / 27.9 / 28.7, but not the widest and deepest
+//    (32 x 32768 x 8192 51, 60), and up to 16 rows only if the last round of units is nearly full (16 x 24576 x 4096, 1.5 rounds,
+//    18.9 / 19.7 / 20.6, 17.7 / 22.6 / 23.4; 16 x 32768 x 4096, two rounds, 26.7 / 28.9 / 29.6, 21.4 / 26.3 / 27.3).
+int wavek_skinny_form(int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    const int64_t t32 = (N + 31) / 32;
+    if (t32 <= cus) return K <= 512 ? 1 : 11;
+    if (t32 <= 2 * cus) return M <= 8 && K > 1024 ? 0 : K >= 2048 ? 12 : 1;
+    if (N * K <= (64ll << 20)) return t32 > 4 * cus || (M <= 4 && K <= 320) ? 0 : 1;
+    const int64_t wgs = (N + 63) / 64, rounds = (wgs + cus - 1) / cus;
+    if (M <= 16 && wgs * 10 < rounds * cus * 8) return 0;
+    return M > 8 && K <= 4096 ? 12 : 0;
+}
+
+// Whether that form copies B non-temporally.  From memory this is always faster (1 x 4096 x 1024 3.73 against 4.39 us,
+// 16 x 16384 x 4096 13.5 / 15.1), but a weight that the next call could have found in cache is not kept there (three in
+// turn, us, non-temporal / plain: 16 x 4096 x 4096 6.6 / 5.7, 32 x 8192 x 8192 15.6 / 13.0).  Weights of up to 8 MiB
+// stay in cache all the same (8 x 4096 x 2048 3.58 / 3.58; from memory 4.7 / 5.4).  Beyond, where most units stream and the plain
+// copies lose to the streaming kernel (three in turn and from memory, non-temporal / plain / streaming kernel):
+// 8 x 8192 x 2048 4.9 / 5.5 / 5.5 and 5.4 / 6.1 / 6.1, 8 x 8192 x 4096 7.3 / 7.7 / 8.2 and 8.0 / 9.1 / 8.9, 16 x 16384 x 2048
+// 7.7 / 8.1 / 7.8 and 8.4 / 9.3 / 8.6, 1 x 32768 x 2048 13.2 / 12.2 / 13.1 and 14.2 / 16.6 / 14.1.
+bool wavek_nt(int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    if (M > kSkinnyMaxM) return false;
+    const int64_t t32 = (N + 31) / 32;
+    if (N * K <= (8ll << 20)) return true;
+    if (M > 16) return false;
+    if (t32 <= cus) return 2 * t32 > cus && (N * K <= (16ll << 20) || M <= 8);
+    return N * K <= (64ll << 20) && (t32 <= 2 * cus || (M <= 4 && K >= 2048));
+}
+
+// The form that serves an 8-bit problem with aligned rows of A, or 0: the other kernels are faster.  us in a graph, this
+// kernel / the others (at z: with a zero-point of B, whose row sums cost the others more):
 //  * a 32 x 32 tile per compute unit at most: 64 x 4096 x 4096 7.0 / 10.2 (z 7.1 / 12.5), 33 x 4096 x 1024
-//    3.8 / 5.2, 16 x 4096 x 4096 6.0 / 8.2, 1 x 4096 x 16384 12.3 / 21;
-//  * M <= 32 and more panels than that: two wavefronts per panel while the weight is at most 64 MiB (32 x 16384
-//    x 4096 13.1 / 21.8, 16 x 32768 x 1024 8.8 / 11.8, 1 x 16384 x 4096 12.5 / 12.7); beyond it two panels per
-//    workgroup for M > 8 (32 x 16384 x 8192 26 / 41, 16 x 32768 x 4096 27 / 28.8), but not for the widest and
-//    deepest (32 x 32768 x 8192 60 / 51), which stream;
+//    3.8 / 5.2;
 //  * 32 x 64 tiles, one per compute unit at most: 128 x 4096 x 4096 8.5 / 10.4, 512 x 768 x 3072 7.1 / 8.6,
 //    512 x 768 x 768 4.4 / 5.1;
 //  * a K of up to 1024 and up to three 32 x 32 tiles per unit: 1024 x 768 x 768 5.0 / 5.5, 700 x 900 x 600
@@ -530,11 +579,8 @@ int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const int64_t t32 = tiles(32, 32), t64 = tiles(64, 64);
+    if (M <= kSkinnyMaxM) return wavek_skinny_form(M, N, K, cus);
     if (t32 <= cus) return 11;
-    if (M <= kSkinnyMaxM) {
-        if (N * K <= (64ll << 20)) return t32 <= 4 * cus ? 1 : 0;
-        return M > 8 && (K <= 4096 || t32 <= 2 * cus) ? 12 : 0;
-    }
     if (tiles(32, 64) <= cus) return 12;
     if (K >= 256 && K <= 1024 && t32 <= 3 * cus && t64 <= cus) return 1;
     if (rows && K > 1024 && t64 <= cus) return 22;
@@ -542,15 +588,20 @@ int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
     return 0;
 }
 
-template <class F>
+template <class F, bool NT = false>
 hipError_t launch_wavek_u8(const GemmParams &p, bool requant, bool rows, hipStream_t st)
 {
-    if (requant) return rows ? launch_wavek<F, 1, true, true>(p, st) : launch_wavek<F, 1, true, false>(p, st);
-    return rows ? launch_wavek<F, 1, false, true>(p, st) : launch_wavek<F, 1, false, false>(p, st);
+    if (requant) return rows ? launch_wavek<F, 1, true, true, false, false, NT>(p, st) : launch_wavek<F, 1, true, false, false, false, NT>(p, st);
+    return rows ? launch_wavek<F, 1, false, true, false, false, NT>(p, st) : launch_wavek<F, 1, false, false, false, false, NT>(p, st);
 }
 
-hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool rows, hipStream_t st)
+hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool rows, bool nt, hipStream_t st)
 {
+    if (nt) {
+        if (form == 1) return launch_wavek_u8<WaveK11Short, true>(p, requant, rows, st);
+        if (form == 11) return launch_wavek_u8<WaveK11, true>(p, requant, rows, st);
+        if (form == 12) return launch_wavek_u8<WaveK12, true>(p, requant, rows, st);
+    }
     switch (form) {
     case 1: return launch_wavek_u8<WaveK11Short>(p, requant, rows, st);
     case 11: return launch_wavek_u8<WaveK11>(p, requant, rows, st);
@@ -760,7 +811,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
     if (route.wavek) {
         const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, device_cus);
         if (form != 0) {
-            const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, st)
+            const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
             return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
@@ -929,7 +980,7 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
             hipFuncSetAttribute((const void *)gemm_s16_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 S16Cfg::kLdsBytes) != hipSuccess ||
             allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess ||
-            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess) {
+            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_nt<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess) {
             delete c;
             return NGEMM_ERR_DEVICE;
         }

@@ -1165,6 +1165,7 @@ __device__ __forceinline__ void wait_vmcnt()
 }
 
 typedef const __attribute__((address_space(1))) void *gptr_t;
+constexpr int kCopyNT = 2;                              // cache policy of a copy into LDS: non-temporal
 typedef __attribute__((address_space(3))) void *lptr_t;
 
 // An operand B that was not packed: the caller's int8 [N x K] storage (column j = ldb-strided row of
@@ -2671,6 +2672,7 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 // AREG: rows of A with any alignment, which copies into LDS cannot fetch: A comes through registers (two steps on
 // their way, written into the ring two steps before they are read); everything else stays (64 x 4096 x 4097
 // 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).
+// NT: non-temporal copies of B, for weights that are read once (the rule that chooses it has the figures).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
 // 4096 47 -> 8.7 (3.8 TB/s of B's planes), 64 x 4096 x 4096 47 -> 10.7, 512 x 768 x 768 15.5 -> 6.1, 1024^3
 // 18.9 -> 10.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
@@ -2692,12 +2694,12 @@ struct WaveKCfg {
 
 // p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
 // count tiles of 32 TM x 32 TN.
-template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false>
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false>
 __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p, const RawB rawb)
 {
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
     using Cfg = WaveKCfg<TM, TN, NW, RING>;
-    constexpr int LPS = Cfg::kLoadsPerStep, NT = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
+    constexpr int LPS = Cfg::kLoadsPerStep, NTHREADS = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2750,7 +2752,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
         const int g = step_of(t);
 #pragma unroll
         for (int j = 0; j < 2 * TN; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)b_mem(j, g), (lptr_t)(ring + slot * Cfg::kStepBytes + (2 * TM + j) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)b_mem(j, g), (lptr_t)(ring + slot * Cfg::kStepBytes + (2 * TM + j) * 1024), 16, 0, NT ? kCopyNT : 0);
     };
     // AREG: A of step t waits in register set t % 2
     static_assert(!AREG || RING == 4, "a step's register set is free again when the step four on is requested");
@@ -2860,7 +2862,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
 
     // The column terms of this thread's four output columns: asked for now, needed after the loop.
     constexpr int CG = TN * 8;                           // groups of four columns per row
-    static_assert(NT % CG == 0, "a thread keeps its columns");
+    static_assert(NTHREADS % CG == 0, "a thread keeps its columns");
     const int col = n0 + 4 * (tid % CG);
     uint32_t ct[4] = {0u, 0u, 0u, 0u}, zbv[4] = {p.zb, p.zb, p.zb, p.zb};
     float sc[4] = {p.scale, p.scale, p.scale, p.scale};
@@ -2878,6 +2880,18 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
                 }
         }
     }
+    // The partial step at the end of K belongs to one wavefront.  Its part of B (the pack is zero padded to whole
+    // steps): with NT, a weight that comes from memory, asked for behind the ring's first copies, because after the loop it
+    // would be one more trip there (1 x 4096 x 1000 5.07 -> 4.77 us; loads younger than a step's copies only make its wait
+    // longer).  From cache that costs 0.05 us more than it saves.
+    static_assert(!NT || (!BRAW && !AREG), "packed B, aligned rows of A");
+    v4i tail_b[2 * TN];
+    auto load_tail = [&]() {
+        if (nfull * 64 < kbytes && wave == nfull % NW) {
+#pragma unroll
+            for (int j = 0; j < 2 * TN; ++j) tail_b[j] = *(const v4i *)b_mem(j, nfull);
+        }
+    };
     if (cnt > 0) {
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (AREG) {
@@ -2896,6 +2910,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
                 dma_a(t, t);
                 dma_b(t, t);
             }
+            if constexpr (NT) load_tail();
             wait_vmcnt<(RING - 1) * LPS>();              // step 0 has landed
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -2923,6 +2938,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
             body(IntC<1>{}, IntC<0>{}, t + 1);
         }
         if (t < cnt) body(IntC<0>{}, IntC<1>{}, t);
+    } else if constexpr (NT) {
+        load_tail();
     }
     wait_vmcnt<0>();                                     // drain the copies nobody reads
     __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -2944,7 +2961,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
                 const int valid = kbytes - (kbase + a_chunk * 16);
                 v = valid >= 16 ? load16_any(b_mem(j, nfull)) : load16_partial(b_mem(j, nfull), valid < 0 ? 0 : valid);
             } else {
-                v = *(const v4i *)b_mem(j, nfull);
+                v = NT ? tail_b[j] : *(const v4i *)b_mem(j, nfull);
             }
             *(v4i *)(ring + (2 * TM + j) * 1024 + lane * 16) = v;
         }
@@ -2997,7 +3014,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
     const int filled = (kbytes + 63) / 64 * 64 - kbytes;
     const uint32_t pad = ELEM == 2 ? 64u * (uint32_t)filled : (p.a_xor ? 128u * (uint32_t)filled : 0u);
     const bool small_zc = REQUANT && p.zc > -8388608 && p.zc < 8388608;
-    constexpr int RSTEP = NT / CG;                       // rows the workgroup finishes at a time
+    constexpr int RSTEP = NTHREADS / CG;                 // rows the workgroup finishes at a time
 #pragma unroll
     for (int r0 = 0; r0 < TM * 32; r0 += RSTEP) {
         const int lr = r0 + tid / CG, row = m0 + lr;

@@ -157,3 +157,33 @@ def test_tuning_chooses_among_all_of_them(ctx, launches):
     assert not any(name.startswith("gemm_wavek_kernel<") for name, _ in launches(p.run(3)))
     ng.ngemm_packed_b_free(p.h)
     ng.ngemm_destroy(own)
+
+
+# M <= 32 (M, N, K, what runs): which calls stream a weight, measured with the weight in cache and in memory: from memory the
+# plain copies of the kernel that splits K over wavefronts lose up to 20 % to the streaming kernel
+SKINNY = [
+    (1, 4096, 1024, "gemm_wavek_kernel<1, 1, 1, 4, 4, false, false, false, false, true>"),       # non-temporal copies (the last)
+    (16, 1024, 512, "gemm_wavek_kernel<1, 1, 1, 2, 4, false, false, false, false, true>"),
+    (16, 4096, 4096, "gemm_wavek_kernel<1, 1, 1, 4, 4, false, false, false, false, false>"),
+    (8, 8192, 4096, "gemm_wavek_kernel<1, 1, 1, 4, 4, false, false, false, false, true>"),
+    (16, 8192, 4096, "gemm_wavek_kernel<1, 1, 1, 4, 4, false, false, false, false, false>"),
+    (8, 16384, 1024, "gemm_wavek_kernel<1, 1, 1, 2, 4, false, false, false, false, true>"),
+    (8, 16384, 2048, "gemm_skinny_kernel<false, 1>"),
+    (16, 16384, 2048, "gemm_wavek_kernel<1, 1, 2, 4, 3, false, false, false, false, true>"),
+    (32, 16384, 2048, "gemm_wavek_kernel<1, 1, 2, 4, 3, false, false, false, false, false>"),
+    (4, 32768, 256, "gemm_skinny_kernel<false, 1>"),
+    (4, 32768, 2048, "gemm_wavek_kernel<1, 1, 1, 2, 4, false, false, false, false, true>"),
+    (8, 32768, 2048, "gemm_wavek_kernel<1, 1, 1, 2, 4, false, false, false, false, false>"),
+    (16, 24576, 4096, "gemm_skinny_kernel<false, 1>"),
+    (16, 32768, 4096, "gemm_wavek_kernel<1, 1, 2, 4, 3, false, false, false, false, false>"),
+]
+
+
+@pytest.mark.parametrize("case", SKINNY, ids=str)
+def test_weights_from_memory(ctx, launches, case):
+    import paper_1910_00178_amd as ng
+    M, N, K, want = case
+    p = Problem(ctx, M, N, K)
+    got = launches(p.run())
+    assert [name for name, _ in got] == [want], got
+    ng.ngemm_packed_b_free(p.h)

@@ -53,7 +53,9 @@ def test_s16_small_outputs(runner, K):
 # not), 32 x 64, 64 x 64 and 64 x 128 tiles, each with ragged rows, columns and partial steps
 U8_CASES = [(1, 1, 1), (33, 31, 63), (64, 70, 64), (5, 300, 65), (31, 100, 129), (33, 33, 511), (70, 129, 4097), (300, 500, 200),
             (32, 9000, 70), (7, 10001, 200), (600, 700, 300), (1000, 600, 257), (520, 1000, 64), (100, 5100, 90), (500, 1900, 1100),
-            (9, 33, 300), (40, 16000, 2049), (300, 4000, 3100), (1000, 1300, 3073)]
+            (9, 33, 300), (40, 16000, 2049), (300, 4000, 3100), (1000, 1300, 3073),
+            # M <= 32 with non-temporal copies of B, the partial step asked for early: four and two wavefronts, 32 x 64 tiles
+            (3, 4000, 777), (16, 300, 1000), (30, 8190, 1000), (7, 9000, 900), (13, 10000, 2100), (20, 8200, 2500), (2, 17000, 2049)]
 
 
 @pytest.mark.parametrize("pitch", ["padded", "tight"])
