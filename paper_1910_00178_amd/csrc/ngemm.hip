@@ -611,18 +611,24 @@ hipError_t launch_wavek_form(int form, const GemmParams &p, bool requant, bool r
     }
 }
 
-// Rows of A with any alignment (A through registers).  us in a graph, this kernel / the others:
-//  * M > 8 and a 32 x 32 tile per compute unit at most: 64 x 4096 x 4097 9.9 / 23.7, 32 x 4096 x 4097 9.8 / 18.5,
-//    64 x 1024 x 1025 5.2 / 6.1; up to eight rows the skinny kernel's direct loads of A cost little (1 x 4096 x 1025
-//    4.3 / 4.3, 2 x 300 x 8191 12.8 / 10.3);
+// Rows of A with any alignment (A through registers).  us in a graph, this kernel / the others; where there are three pairs
+// for one weight / three in turn / every byte from memory, as above:
+//  * up to eight rows the skinny kernel's direct loads of A cost little (1 x 4096 x 1025 4.3 / 4.3, 2 x 300 x 8191 12.8 / 10.3);
+//    up to 16 that holds for one tile per unit and a K of up to 1500 (12 x 8191 x 1025 5.5 / 4.9, 5.4 / 5.1, 7.1 / 5.8;
+//    16 x 4096 x 513 4.5 / 4.2, 4.4 / 4.1, 5.6 / 4.5; 16 x 4096 x 2047 6.0 / 6.7, 5.9 / 7.1, 8.1 / 7.5; 16 x 16384 x 1025
+//    5.6 / 7.3, 7.5 / 7.9, 9.0 / 8.0), and below 12 for two (9 x 16384 x 4097 14.4 / 15.3, 14.3 / 14.7, 19.5 / 15.6; 12 rows
+//    15.0 / 18.0, 14.9 / 17.5, 20.4 / 18.5);
+//  * a 32 x 32 tile per compute unit at most: 64 x 4096 x 4097 9.9 / 23.7, 32 x 4096 x 4097 9.8 / 18.5,
+//    64 x 1024 x 1025 5.2 / 6.1;
 //  * 32 x 64 tiles of two wavefronts: M <= 32 beyond that (16 x 32767 x 2047 14.4 / 19.4, 16 x 16384 x 4097 15.6 /
 //    22.6), one per unit (128 x 4096 x 4097 13.8 / 23.8, 256 x 1025 x 1025 6.3 / 6.7), two per unit with a long K
 //    (256 x 4096 x 4097 16.8 / 24.2, 48 x 16384 x 2049 12.0 / 14.6, but 200 x 4096 x 1001 8.1 / 6.8).
 int wavek_areg_form(int64_t M, int64_t N, int64_t K, int64_t cus)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    if (M <= 8) return 0;
-    if (tiles(32, 32) <= cus) return 11;
+    const int64_t t32 = tiles(32, 32);
+    if (M <= 8 || (M <= 16 && K <= 1500 && t32 <= cus) || (M < 12 && t32 > cus && t32 <= 2 * cus)) return 0;
+    if (t32 <= cus) return 11;
     if (M <= kSkinnyMaxM || tiles(32, 64) <= cus || (K >= 2048 && tiles(32, 64) <= 2 * cus)) return 12;
     return 0;
 }

@@ -187,3 +187,26 @@ def test_weights_from_memory(ctx, launches, case):
     got = launches(p.run())
     assert [name for name, _ in got] == [want], got
     ng.ngemm_packed_b_free(p.h)
+
+
+# rows of A that are not 16-byte aligned, 9 .. 32 of them
+UNALIGNED = [
+    (16, 4096, 513, "gemm_skinny_kernel<false, 1>"),
+    (16, 1024, 1025, "gemm_skinny_kernel<false, 1>"),
+    (16, 4096, 2047, "gemm_wavek_kernel<1, 1, 1, 4, 4, false, false, false, true, false>"),
+    (17, 4096, 513, "gemm_wavek_kernel<1, 1, 1, 4, 4, false, false, false, true, false>"),
+    (16, 16384, 1025, "gemm_wavek_kernel<1, 1, 2, 2, 4, false, false, false, true, false>"),
+    (9, 16384, 4097, "gemm_skinny_kernel<false, 1>"),
+    (12, 16384, 4097, "gemm_wavek_kernel<1, 1, 2, 2, 4, false, false, false, true, false>"),
+    (9, 32767, 2047, "gemm_wavek_kernel<1, 1, 2, 2, 4, false, false, false, true, false>"),
+]
+
+
+@pytest.mark.parametrize("case", UNALIGNED, ids=str)
+def test_unaligned_rows(ctx, launches, case):
+    import paper_1910_00178_amd as ng
+    M, N, K, want = case
+    p = Problem(ctx, M, N, K, pitch=K)
+    got = launches(p.run())
+    assert [name for name, _ in got] == [want], got
+    ng.ngemm_packed_b_free(p.h)
