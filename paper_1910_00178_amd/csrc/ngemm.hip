@@ -378,22 +378,27 @@ inline bool rows_aligned(const void *A, int64_t lda) { return (((uintptr_t)A | (
 // the 128 x 128 one when every unit still gets a workgroup, else 64 x 64 (measured on 18 shapes
 // from 16 x 512 x 512 to 4096^3: the smallest tile wins as long as the larger ones leave units
 // idle; ngemm_tune_u8s8s32 settles the borderline cases by measurement).
-constexpr int64_t kSplitMinK = 9216;
-int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, bool aligned)
+int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, bool aligned, bool requant)
 {
     auto tiles = [&](int64_t b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     // Few tiles and a long K: spread K over the idle units.  The launch that clears C and the atomic adds have
-    // to pay off: measured on 48 shapes, the split wins from K = 8192 on up to 96 tiles of 64 x 64 and from
-    // 12288 up to 128, and against the kernel that splits K over a workgroup's wavefronts (wavek_form) from
-    // about K = 9000 on: its time is 3 us + 0.56 us per 1024 bytes of K, the split's about 8 us (u8 output 9):
-    // 64 x 64 x 8192 7.6 / 8.1, 128 x 1024 x 8192 9.3 / 11.3, 64 x 64 x 16384 12.1 / 8.1 us.
+    // to pay off: against 64 x 64 tiles (48 shapes) the split wins from K = 8192 on up to 96 of them and from 12288 up to
+    // 128.  Against the kernel that splits K over a workgroup's wavefronts (wavek_form) it depends on where the weight
+    // is (us, that kernel / the split, the same weight in cache, then every byte from memory):
+    //   64 x 1024 x 6144 5.5 / 7.1 and 10.5 / 9.4, x 8192 6.3 / 7.4 and 12.9 / 9.6, x 9216 6.8 / 7.7 and 14.1 / 10.0
+    //   256 x 256 x 8192 8.6 / 8.7 and 11.1 / 9.8, x 9216 9.4 / 8.8 and 12.1 / 10.0, x 16384 9.7 / 10.0 (u8 10.2 / 10.6)
+    //   32 x 2048 x 8192 6.3 / 7.5 and 14.2 / 9.8; u8 outputs, whose partial sums go through the workspace:
+    //   64 x 256 x 8192 6.5 / 8.4 and 12.7 / 10.6, 64 x 64 x 8192 6.5 / 8.1 and 8.6 / 8.9
+    // so int32 outputs of up to a quarter of a 32 x 32 tile per unit split from K = 8192 on and u8 ones and larger ones
+    // (64 x 2048 x 8192 7.2 / 9.5 and 13.6 / 11.8, x 9216 9.1 / 9.7 and 14.8 / 11.6; 512 x 256 x 9216 9.3 / 10.7 and 10.8 / 11.0) from 9216.
+    const int64_t split_min_k = tiles(32) * 4 <= cus && !requant ? 8192 : 9216;
     const int64_t t64 = tiles(64), step = 3 * cus / 16;
     if (M <= kSkinnyMaxM) {
-        if (K >= kSplitMinK && t64 * 8 <= cus) return NGEMM_KERNEL_SPLIT_K;
+        if (K >= split_min_k && t64 * 8 <= cus) return NGEMM_KERNEL_SPLIT_K;
         return NGEMM_KERNEL_SKINNY;
     }
-    if (t64 * 2 <= cus && K >= kSplitMinK && K >= 4096 * ((t64 + step - 1) / step)) return NGEMM_KERNEL_SPLIT_K;
+    if (t64 * 2 <= cus && K >= split_min_k && K >= 4096 * ((t64 + step - 1) / step)) return NGEMM_KERNEL_SPLIT_K;
     const int64_t t192 = ((M + 191) / 192) * ((N + 255) / 256);
     // The large tiles pay off from 0.7 of the compute units filled with K >= 512 (4096 x 4096 x 256: 16.5 / 15.0), from 0.5 with K >= 1024,
     // from 0.4 with K >= 2048: their fill and epilogue want stages to spread over (us, large against
@@ -744,7 +749,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 if (t.wavek && wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus) != 0)
                     r = Route{small, true};
             }
-        if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda)), true};
+        if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.requant), true};
     }
     if (r.kernel == NGEMM_KERNEL_SKINNY && a.M > kSkinnyMaxM) return NGEMM_ERR_INVALID_ARG;
     *route = r;
@@ -1400,7 +1405,7 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     if (workspace_bytes < ngemm_unpacked_workspace_bytes(M, N, K)) return NGEMM_ERR_BUFFER_TOO_SMALL;
     // Rows of both operands 16-byte aligned: no pack pass.  The kernels read B from the caller's storage with the
     // same copies as A; all but the 256 x 256 ones form the sums of its columns themselves.
-    int kernel = ctx->force_kernel == NGEMM_KERNEL_AUTO ? choose_kernel(ctx, M, N, K, rows_aligned(A_dev, lda)) : ctx->force_kernel;
+    int kernel = ctx->force_kernel == NGEMM_KERNEL_AUTO ? choose_kernel(ctx, M, N, K, rows_aligned(A_dev, lda), false) : ctx->force_kernel;
     if (kernel == NGEMM_KERNEL_SPLIT_K)                                     // the K split reads a packed B only
         kernel = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     const bool aligned = (((uintptr_t)A_dev | (uintptr_t)lda | (uintptr_t)B_dev | (uintptr_t)ldb) & 15) == 0;

@@ -210,3 +210,18 @@ def test_unaligned_rows(ctx, launches, case):
     got = launches(p.run())
     assert [name for name, _ in got] == [want], got
     ng.ngemm_packed_b_free(p.h)
+
+
+# K split over workgroups: from K = 8192 on for int32 outputs of few tiles (weights from memory: 64 x 1024 x 8192 12.9 us without)
+SPLIT = [(64, 1024, 8192, False, True), (64, 1024, 8128, False, False), (64, 1024, 8192, True, False), (64, 1024, 9216, True, True),
+         (32, 2048, 8192, False, True), (64, 2048, 8192, False, False), (64, 2048, 9216, False, True)]
+
+
+@pytest.mark.parametrize("M,N,K,u8,split", SPLIT)
+def test_k_split(ctx, launches, M, N, K, u8, split):
+    import paper_1910_00178_amd as ng
+    p = Problem(ctx, M, N, K)
+    got = launches(p.run_u8() if u8 else p.run())
+    want = ["gemm_tile_deep_kernel", "splitk_reduce_kernel"] if u8 else ["zero_c_kernel", "gemm_tile_deep_kernel"]
+    assert [name.split("<")[0] for name, _ in got] == (want if split else ["gemm_wavek_kernel"]), got
+    ng.ngemm_packed_b_free(p.h)
