@@ -427,11 +427,16 @@ int choose_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, bool al
         const int64_t r256 = (tiles(256) + cus - 1) / cus * 256, r192 = (t192 + cus - 1) / cus * 192;
         return r192 < r256 ? NGEMM_KERNEL_TILE_192 : NGEMM_KERNEL_TILE_256;
     }
-    // (us, 128 x 128 against 64 x 64 tiles, inputs changing from call to call: 1536^3, 144 tiles of 128 x 128 12.2 /
-    // 12.7, 1024 x 2048 x 2048, 128 tiles 13.7 / 13.0 and with a zero-point or u8 output 15.0 / 13.3; at K = 4096
-    // 1408 x 1408, 121 tiles, 18.8 / 20.3; 1024^3, 64 tiles: 7.9 / 5.5; 1536 x 1536 x 512: 6.9 / 6.4)
+    // (us, 128 x 128 against 64 x 64 tiles; 1536^3, 144 tiles of 128 x 128, inputs changing from call to call, 12.2 / 12.7;
+    // the same inputs: 1408 x 1408, 121 tiles, K = 1024 8.3 / 7.1, 2048 11.7 / 10.9, 3072 15.7 / 14.3 (the kernel behind TILE_64
+    // there splits K over wavefronts); 1024 x 2048 x 2048, 128 tiles 11.9 / 10.8 and with a zero-point or u8 output 13.6 / 11.9;
+    // 1024^3, 64 tiles 7.9 / 5.5; 1536 x 1536 x 512 6.9 / 6.4.  Once 64 x 64 tiles need a third round of two per unit the larger ones
+    // win from K = 2560 on: 1536 x 1408, 132 tiles, 14.4 / 15.4, u8 16.0 / 15.9, 3584 16.6 / 19.4, u8 18.3 / 20.1; 1400 x 1500 x 2048
+    // 12.6 / 12.7 and u8 14.2 / 12.9.)
     // Not for M <= 64, which would leave half of every tile empty (64 x 16384 x 4096 18.6 / 14.5 us).
-    if (M > 64 && (tiles(128) >= cus || (tiles(128) * 20 >= cus * 11 && K >= 1024) || (tiles(128) * 5 >= cus * 2 && K >= 4096))) return NGEMM_KERNEL_TILE_128;
+    if (M > 64 && (tiles(128) >= cus || (tiles(128) * 20 >= cus * 11 && K >= 1024) || (tiles(128) * 5 >= cus * 2 && K >= 4096) ||
+                   (t64 > 2 * cus && tiles(128) * 2 >= cus && K >= 2560)))
+        return NGEMM_KERNEL_TILE_128;
     return NGEMM_KERNEL_TILE_64;
 }
 

@@ -225,3 +225,17 @@ def test_k_split(ctx, launches, M, N, K, u8, split):
     want = ["gemm_tile_deep_kernel", "splitk_reduce_kernel"] if u8 else ["zero_c_kernel", "gemm_tile_deep_kernel"]
     assert [name.split("<")[0] for name, _ in got] == (want if split else ["gemm_wavek_kernel"]), got
     ng.ngemm_packed_b_free(p.h)
+
+
+# 128 x 128 tiles where 64 x 64 ones need a third round of two per compute unit and K is long (1536 x 1408 x 3584: 16.6 / 19.4 us)
+THIRD_ROUND = [(1536, 1408, 2560, "gemm_tile_deep_kernel<2, 2, 4, false, 0, false>"), (1536, 1408, 2048, "gemm_tile_dma_kernel<64, 64, 2, 2, 4, false, false, false>"),
+               (1472, 1408, 3584, "gemm_wavek_kernel<1, 2, 4, 4, 3, false, false, false, false, false>")]
+
+
+@pytest.mark.parametrize("case", THIRD_ROUND, ids=str)
+def test_third_round_of_small_tiles(ctx, launches, case):
+    import paper_1910_00178_amd as ng
+    M, N, K, want = case
+    p = Problem(ctx, M, N, K)
+    assert [name for name, _ in launches(p.run())] == [want]
+    ng.ngemm_packed_b_free(p.h)
