@@ -122,9 +122,13 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M,
 /* The kernel remembered for a shape by ngemm_tune_u8s8s32, or NGEMM_KERNEL_AUTO if none. */
 ngemm_status ngemm_tuned_kernel(const ngemm_ctx *ctx, int64_t M, int64_t N, int64_t K, int *kernel);
 
-/* Cap the number of persistent workgroups the large-tile kernel launches (0 = one per compute
- * unit, the default).  For sharing the device with other work, and for tests that want many
- * tiles per workgroup on a small problem. */
+/* Cap the number of persistent workgroups of a launch (0 = one per compute unit, the default).
+ * For sharing the device with other work, and for tests that want many tiles per workgroup on a
+ * small problem.  It holds for the kernels that walk tiles: 192 x 256 and 256 x 256 tiles, the
+ * 16-bit products, the K split, and the 64 x 64 and 128 x 128 tiles with 16-byte aligned rows
+ * of A (which count two or four workgroups for one where that many fit a compute unit).  Calls
+ * with M <= 32 on 8-bit operands, rows of A of other alignment, batched calls and the helper
+ * launches (pack, row sums, clearing, the sum of a K split's parts) are not capped. */
 ngemm_status ngemm_set_max_workgroups(ngemm_ctx *ctx, int max_workgroups);
 
 /*

@@ -370,6 +370,12 @@ hipError_t launch_skinny(const GemmParams &p, bool requant, int num_cus, hipStre
     return hipGetLastError();
 }
 
+int workgroup_budget(const ngemm_ctx *ctx)
+{
+    const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+    return (ctx->max_workgroups > 0 && ctx->max_workgroups < cus) ? ctx->max_workgroups : cus;
+}
+
 // Rows that copies into LDS can fetch: 16-byte aligned.
 inline bool rows_aligned(const void *A, int64_t lda) { return (((uintptr_t)A | (uintptr_t)lda) & 15) == 0; }
 
@@ -655,13 +661,23 @@ hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, b
     return form == 11 ? launch_wavek_areg<WaveK11>(p, requant, rows, st) : launch_wavek_areg<WaveK12Short>(p, requant, rows, st);
 }
 
+// Whether a form's workgroups, one per tile, keep within a caller's cap (budget < cus).  Up to 32 rows they need not: the
+// streaming kernels, in whose place they run there, launch a workgroup per panel as well.
+bool wavek_fits(int form, int64_t M, int64_t N, int64_t budget, int64_t cus)
+{
+    if (budget >= cus || M <= kSkinnyMaxM) return true;
+    const int64_t bm = form == 1 ? 32 : form / 10 * 32, bn = form == 1 ? 32 : form % 10 * 32;
+    return ((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= budget;
+}
+
 // The form that takes the place of `kernel` (the streaming kernel, 64 x 64 tiles, 128 x 128 tiles with aligned rows), or 0.
-int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, int64_t cus)
+// budget: workgroups that the caller allows (the kernels for unaligned rows launch one per tile whichever runs).
+int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, int64_t cus, int64_t budget)
 {
     const bool small = kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64;
     if (!aligned) return small ? wavek_areg_form(M, N, K, cus) : 0;
     const int form = small || kernel == NGEMM_KERNEL_TILE_128 ? wavek_form(M, N, K, rows, cus) : 0;
-    return small || form == 24 ? form : 0;
+    return (small || form == 24) && wavek_fits(form, M, N, budget, cus) ? form : 0;
 }
 
 // The forms that read B from the caller's storage.
@@ -688,12 +704,6 @@ int wavek_raw_form(int64_t M, int64_t N, int64_t K, int64_t cus)
 {
     const int form = wavek_form(M, N, K, true, cus);
     return form == 0 && M <= kSkinnyMaxM ? 12 : form;
-}
-
-int workgroup_budget(const ngemm_ctx *ctx)
-{
-    const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-    return (ctx->max_workgroups > 0 && ctx->max_workgroups < cus) ? ctx->max_workgroups : cus;
 }
 
 struct RunArgs {
@@ -751,7 +761,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 r = Route{t.kernel, false};
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
-                if (t.wavek && wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus) != 0)
+                if (t.wavek && wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0)
                     r = Route{small, true};
             }
         if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.requant), true};
@@ -825,7 +835,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
     // outputs of few tiles: K split over the wavefronts of a workgroup
     if (route.wavek) {
-        const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, device_cus);
+        const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, device_cus, num_cus);
         if (form != 0) {
             const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
@@ -1065,7 +1075,8 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
             int kchunk = 0;
             if (!dma_ok || splitk_parts(M, B->N, B->K, workgroup_budget(ctx), &kchunk) < 2) continue;
         }
-        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, ctx->num_cus > 0 ? ctx->num_cus : 256) == 0) continue;
+        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, ctx->num_cus > 0 ? ctx->num_cus : 256,
+                                                workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
         const int warm = 5, reps = 50, rounds = 3;
@@ -1363,14 +1374,24 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     // 128 x 128 kernel: 16 x 4096 x 4096 8.9 / 47, 64 x 4096 x 4096 10.6 / 47, 512 x 768 x 768 5.9 / 15.5,
     // 1024^3 10.5 / 18.9, 512 x 3072 x 768 11.6 / 16.7, 1024 x 2048 x 1024 14.0 / 19.0, but 1024 x 3072 x 1024
     // 24.8 / 19.6 and 1536^3 27 / 24.9.
-    const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+    // Under a caller's cap only those whose workgroups, one per tile, keep within it; the 128 x 128 kernel and, below its K,
+    // the looping form walk several tiles per workgroup.
+    const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256, budget = workgroup_budget(ctx);
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((B->N + bn - 1) / bn); };
+    auto fits = [&](int64_t n) { return budget >= cus || n <= budget; };
     hipError_t e;
-    if (tiles(32, 32) <= cus) {
+    if (tiles(32, 32) <= cus && fits(tiles(32, 32))) {
         e = launch_wavek<WaveK11, 2, false, true>(p, st);
-    } else if (tiles(32, 64) <= 2 * cus) {
+    } else if (tiles(32, 64) <= 2 * cus && fits(tiles(32, 64))) {
         e = launch_wavek<WaveK12, 2, false, true>(p, st);
-    } else if (B->K < S16Cfg::kMinK || (tiles(64, 64) <= 2 * cus && tiles(128, 128) * 2 <= cus)) {
+    } else if (B->K < S16Cfg::kMinK && !fits(tiles(64, 64))) {
+        p.tiles_m = (int)((M + 63) / 64);
+        p.tiles_n = (int)((B->N + 63) / 64);
+        const RawB none{nullptr, 0};
+        hipLaunchKernelGGL((gemm_wavek_kernel<2, 2, 2, WaveK22::NW, WaveK22::RING, false, true, false, false, false, true>), dim3((unsigned)budget),
+                           dim3(WaveK22::NW * 64), (WaveKCfg<2, 2, WaveK22::NW, WaveK22::RING>::kLdsBytes), st, p, none);
+        e = hipGetLastError();
+    } else if (B->K < S16Cfg::kMinK || (tiles(64, 64) <= 2 * cus && tiles(128, 128) * 2 <= cus && fits(tiles(64, 64)))) {
         e = launch_wavek<WaveK22, 2, false, true>(p, st);
     } else {
         p.tiles_m = (int)((M + 127) / 128);
@@ -1380,7 +1401,7 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
                            (int)M, (int)B->K, rs);
         if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
         p.rowsum = rs;
-        const int ntiles = p.tiles_m * p.tiles_n, budget = workgroup_budget(ctx);
+        const int64_t ntiles = (int64_t)p.tiles_m * p.tiles_n;
         hipLaunchKernelGGL(gemm_s16_tile_kernel, dim3((unsigned)(ntiles < budget ? ntiles : budget)), dim3(256),
                            S16Cfg::kLdsBytes, st, p);
         e = hipGetLastError();
@@ -1418,7 +1439,7 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128 || kernel == NGEMM_KERNEL_SKINNY;
     // the kernel that splits K over a workgroup's wavefronts: of the automatic choice only
     int form = aligned && K > 0 && small_kernel && ctx->force_kernel == NGEMM_KERNEL_AUTO ? wavek_raw_form(M, N, K, cus) : 0;
-    if (kernel == NGEMM_KERNEL_TILE_128 && form != 24) form = 0;
+    if ((kernel == NGEMM_KERNEL_TILE_128 && form != 24) || !wavek_fits(form, M, N, workgroup_budget(ctx), cus)) form = 0;
     if (aligned && K > 0 && (form != 0 || kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return NGEMM_ERR_DEVICE;

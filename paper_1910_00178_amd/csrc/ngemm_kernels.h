@@ -2673,6 +2673,7 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 // their way, written into the ring two steps before they are read); everything else stays (64 x 4096 x 4097
 // 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).
 // NT: non-temporal copies of B, for weights that are read once (the rule that chooses it has the figures).
+// LOOP: fewer workgroups than tiles, for a caller that caps them (the others launch a workgroup per tile).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
 // 4096 47 -> 8.7 (3.8 TB/s of B's planes), 64 x 4096 x 4096 47 -> 10.7, 512 x 768 x 768 15.5 -> 6.1, 1024^3
 // 18.9 -> 10.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
@@ -2694,7 +2695,8 @@ struct WaveKCfg {
 
 // p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
 // count tiles of 32 TM x 32 TN.
-template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false>
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
+          bool LOOP = false>
 __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p, const RawB rawb)
 {
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
@@ -2707,8 +2709,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
     const int kbytes = p.K * ELEM;
     const int nfull = kbytes / 64;                       // full steps, all wavefronts together
     const int cnt = nfull > wave ? (nfull - wave + NW - 1) / NW : 0;      // this wavefront's: wave, wave + NW, ...
+    int tile = blockIdx.x;
+    do {                                                 // (one pass but for LOOP; to the end of the kernel)
     int tm, tn;
-    tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
+    tile_of_block(tile, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
     const int m0 = tm * (TM * 32), n0 = tn * (TN * 32);
 
     // copies of a step: 16-row blocks of A (row t of the block, chunk c in slot 4 t + (c + t / 4) % 4), then
@@ -3063,7 +3067,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
                 if (col + 2 < p.N) dst[2] = o.z;
             }
         }
-    }
+    }    if (LOOP) __syncthreads();                           // the partial tiles are read: the next tile's copies may land
+    tile += gridDim.x;
+    } while (LOOP && tile < p.tiles_m * p.tiles_n);
 }
 
 // ---- skinny-M kernel (M <= 32) --------------------------------------------------------------

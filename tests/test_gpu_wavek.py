@@ -49,6 +49,46 @@ def test_s16_small_outputs(runner, K):
         assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), (M, N)
 
 
+# Under a cap on workgroups: the 128 x 128 kernel and, below two of its stages, the looping form, several tiles each.  Without
+# one, outputs of more than a tile per compute unit: what is left of K behind the pipelined stages of 64 elements (an odd
+# full stage, a partial one, both, neither), ragged rows and columns, values at both ends of the type.
+S16_LARGE_K = [128, 129, 191, 192, 209, 257, 320]
+S16_LARGE = [(300, 400, K, 3) for K in [1, 40, 127] + S16_LARGE_K] + [(M, N, K, 0) for M, N in ((1500, 1700), (2049, 2111)) for K in S16_LARGE_K]
+
+
+@pytest.mark.parametrize("M,N,K,cap", S16_LARGE)
+def test_s16_large_tile_kernel_and_caps(runner, M, N, K, cap):
+    import torch
+    import paper_1910_00178_amd as ng
+    rng = np.random.default_rng(M + K)
+    A = rng.integers(-32768, 32768, size=(M, K)).astype(np.int16)
+    B = rng.integers(-32768, 32768, size=(N, K)).astype(np.int16)
+    A[::3], B[1::4] = np.where(A[::3] < 0, -32768, 32767), np.where(B[1::4] < 0, -32768, 32767)
+    lda = (K + 7) // 8 * 8
+    Ah = np.full((M, lda), 7777, np.int16)
+    Ah[:, :K] = A
+    Ad, Bd = torch.from_numpy(Ah.reshape(-1)[:(M - 1) * lda + K].copy()).cuda(), torch.from_numpy(B).cuda()
+    nb = ng.ngemm_packed_b_bytes_s16(K, N)
+    packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    h = ng.ngemm_pack_b_s16(runner.ctx, K, N, Bd, K, packed, nb)
+    wsb = ng.ngemm_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    C = torch.full((M + 1, N + 3), -7, dtype=torch.int32, device="cuda")
+    za, zb = int(rng.integers(-32768, 32768)), int(rng.integers(-32768, 32768))
+    ng.ngemm_set_max_workgroups(runner.ctx, cap)
+    try:
+        ng.ngemm_run_s16s16s32(runner.ctx, M, Ad, lda, za, h, zb, C, N + 3, ws, wsb)
+        got = C.cpu().numpy()
+    finally:
+        ng.ngemm_set_max_workgroups(runner.ctx, 0)
+    ng.ngemm_packed_b_free(h)
+    # exact in 64 bits (|sum| < 2^41), then the low 32; float64 products of 16-bit values and sums below 2^53 are exact
+    want = ((A.astype(np.float64) - za) @ (B.astype(np.float64) - zb).T).astype(np.int64).astype(np.int32)
+    assert np.array_equal(want[::97], oracle.gemm_s16s16s32(np.ascontiguousarray(A[::97]), B, za, zb))
+    assert np.array_equal(got[:M, :N], want)
+    assert (got[M:] == -7).all() and (got[:, N:] == -7).all()
+
+
 # (M, N, K): every form of the 8-bit rule on 256 compute units: 32 x 32 tiles, two wavefronts per tile (M <= 32 and
 # not), 32 x 64, 64 x 64 and 64 x 128 tiles, each with ragged rows, columns and partial steps
 U8_CASES = [(1, 1, 1), (33, 31, 63), (64, 70, 64), (5, 300, 65), (31, 100, 129), (33, 33, 511), (70, 129, 4097), (300, 500, 200),
