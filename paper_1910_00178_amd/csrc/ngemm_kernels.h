@@ -213,9 +213,10 @@ __device__ __forceinline__ void store_out(const GemmParams &p, int row, int col,
 
 __device__ __forceinline__ int wave_sum(int v)
 {
+    uint32_t u = (uint32_t)v;                            // sums wrap
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    for (int off = 32; off > 0; off >>= 1) u += (uint32_t)__shfl_xor((int)u, off, 64);
+    return (int)u;
 }
 
 // ---- pack: column-major B -> fragment order, zero padded, with column sums --------------------
@@ -318,19 +319,19 @@ __global__ __launch_bounds__(NT) void pack_b_kernel(const uint8_t *__restrict__ 
             } else {
                 const int *w = (const int *)&v[i];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) sum[i] += (int)(int16_t)(w[q] & 0xffff) + (w[q] >> 16);
+                for (int q = 0; q < 4; ++q) sum[i] = (int)((uint32_t)sum[i] + (uint32_t)((int)(int16_t)(w[q] & 0xffff) + (w[q] >> 16)));
             }
             *(v4i *)(turn + (jl + NCOL * i) * PITCH + kc * 16) = v[i];
             if (PER == 1 || blk + 1 == blk1) {
                 // the sum is complete: added up over the CPC consecutive threads that share the column and sent,
                 // while the next column's chunk is still on its way and ahead of the last block's fragments
                 static_assert(CPC <= 64, "the threads of a column lie in one wavefront");
-                int s = sum[i];
+                uint32_t s = (uint32_t)sum[i];
 #pragma unroll
-                for (int off = CPC / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+                for (int off = CPC / 2; off > 0; off >>= 1) s += (uint32_t)__shfl_xor((int)s, off, 64);
                 if (kc == 0) {
                     const int j = pnl * 32 + jl + NCOL * i;
-                    const int32_t t = j < N ? (int32_t)((uint32_t)s - shift) : 0;
+                    const int32_t t = j < N ? (int32_t)(s - shift) : 0;
                     if (nparts == 1) colsum[j] = t;
                     else if (t != 0) atomicAdd(colsum + j, t);
                 }
@@ -1450,7 +1451,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
             int *cs_lds = (int *)(lds + NW * kXposeBytes<TN>);
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int both = csum[j] + __shfl_xor(csum[j], 32, 64);
+                const int both = (int)((uint32_t)csum[j] + (uint32_t)__shfl_xor(csum[j], 32, 64));
                 if (wm == 0 && lane < 32) cs_lds[(wn * TN + j) * 32 + lane] = both;
             }
             __syncthreads();
@@ -2358,7 +2359,7 @@ __global__ __launch_bounds__(256) void rowsum_s16_kernel(const int16_t *__restri
 {
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= rows_out) return;
-    int s = 0;
+    uint32_t s = 0;
     if (i < rows_valid) {
         const int16_t *row = X + (int64_t)i * ldx;
         for (int k = lane * 8; k < K; k += 64 * 8) {
@@ -2366,14 +2367,14 @@ __global__ __launch_bounds__(256) void rowsum_s16_kernel(const int16_t *__restri
                 int16_t v[8];
                 __builtin_memcpy(v, row + k, 16);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) s += (int)v[t] - 128;
+                for (int t = 0; t < 8; ++t) s += (uint32_t)((int)v[t] - 128);
             } else {
-                for (int t = 0; k + t < K; ++t) s += (int)row[k + t] - 128;
+                for (int t = 0; k + t < K; ++t) s += (uint32_t)((int)row[k + t] - 128);
             }
         }
     }
-    s = wave_sum(s);
-    if (lane == 0) out[i] = s;
+    const int sum = wave_sum((int)s);
+    if (lane == 0) out[i] = sum;
 }
 
 struct S16Cfg {
@@ -2980,7 +2981,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
     if (BRAW) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int both = csum[j] + __shfl_xor(csum[j], 32, 64);
+            const int both = (int)((uint32_t)csum[j] + (uint32_t)__shfl_xor(csum[j], 32, 64));
             if (lane < 32) csx[wave * (TN * 32) + j * 32 + lane] = both;
         }
     }
@@ -3000,8 +3001,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
                 *(v4i *)(part + (i * 32 + (lane & 31)) * Cfg::kPitch + j * 32 + 8 * q + 4 * (lane >> 5)) = o;
             }
         if (ROWS) {
-            const int v = ELEM == 1 ? rs[i] : 256 * rs_h[i] + rs[i];
-            const int both = v + __shfl_xor(v, 32, 64);              // the halves of a step sit in lanes l and l ^ 32
+            const uint32_t v = ELEM == 1 ? (uint32_t)rs[i] : 256u * (uint32_t)rs_h[i] + (uint32_t)rs[i];
+            const int both = (int)(v + (uint32_t)__shfl_xor((int)v, 32, 64));    // the halves of a step sit in lanes l and l ^ 32
             if (lane < 32) rsx[wave * (TM * 32) + i * 32 + lane] = both;
         }
     }

@@ -89,6 +89,36 @@ def test_s16_large_tile_kernel_and_caps(runner, M, N, K, cap):
     assert (got[M:] == -7).all() and (got[:, N:] == -7).all()
 
 
+# Row and column sums beyond 2^31, which wrap like everything else: the pack's, the small-output kernel's and, under a cap,
+# the row-sum launch of the 128 x 128 kernel
+@pytest.mark.parametrize("cap", [0, 2])
+def test_s16_sums_wrap(runner, cap):
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N, K = 290, 270, 70000
+    rng = np.random.default_rng(cap)
+    A, B = np.full((M, K), -32768, np.int16), np.full((N, K), 32767, np.int16)
+    A[::2], B[::3] = rng.integers(-32768, 32768, size=A[::2].shape), rng.integers(-32768, 32768, size=B[::3].shape)
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    nb = ng.ngemm_packed_b_bytes_s16(K, N)
+    packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    h = ng.ngemm_pack_b_s16(runner.ctx, K, N, Bd, K, packed, nb)
+    wsb = ng.ngemm_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    C = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    ng.ngemm_set_max_workgroups(runner.ctx, cap)
+    try:
+        ng.ngemm_run_s16s16s32(runner.ctx, M, Ad, K, 12345, h, -23456, C, N, ws, wsb)
+        got = C.cpu().numpy()
+    finally:
+        ng.ngemm_set_max_workgroups(runner.ctx, 0)
+    ng.ngemm_packed_b_free(h)
+    # float64: every product below 2^33 and every sum below 2^50 is exact
+    want = ((A.astype(np.float64) - 12345) @ (B.astype(np.float64) + 23456).T).astype(np.int64).astype(np.int32)
+    assert abs(A[1].astype(np.int64).sum()) > 2 ** 31 and B[1].astype(np.int64).sum() > 2 ** 31
+    assert np.array_equal(got, want)
+
+
 # (M, N, K): every form of the 8-bit rule on 256 compute units: 32 x 32 tiles, two wavefronts per tile (M <= 32 and
 # not), 32 x 64, 64 x 64 and 64 x 128 tiles, each with ragged rows, columns and partial steps
 U8_CASES = [(1, 1, 1), (33, 31, 63), (64, 70, 64), (5, 300, 65), (31, 100, 129), (33, 33, 511), (70, 129, 4097), (300, 500, 200),
