@@ -475,7 +475,8 @@ template <int ELEM>
 ngemm_status launch_pack(const uint8_t *B, int64_t ldb_bytes, int64_t kbytes, int64_t N, int64_t Kp, int64_t Np, uint32_t b_xor,
                          uint8_t *packed, int32_t *colsum, hipStream_t st)
 {
-    if (Kp <= 2048) return launch_pack_blocks<ELEM, 512, 2>(B, ldb_bytes, kbytes, N, Kp, Np, b_xor, packed, colsum, st);
+    // (the runtime takes less than 2^32 threads in a launch: the widest operands need the smaller workgroups)
+    if (Kp <= 2048 && Np / 32 * 512 < (1ll << 32)) return launch_pack_blocks<ELEM, 512, 2>(B, ldb_bytes, kbytes, N, Kp, Np, b_xor, packed, colsum, st);
     return launch_pack_blocks<ELEM, 256, ELEM>(B, ldb_bytes, kbytes, N, Kp, Np, b_xor, packed, colsum, st);
 }
 

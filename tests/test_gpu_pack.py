@@ -48,3 +48,26 @@ def test_pack_layout(kind, K):
         assert np.array_equal(got[:n], layout(B[:, :K], 128 if kind == "u8" else 0)), (N, gap)
         assert (got[n:] == 0xA5).all(), "written past the packed buffer"
     ng.ngemm_destroy(ctx)
+
+
+def test_widest_operand():
+    """2^28 columns and more: as many panels as workgroups of 512 threads would need 2^32 threads for, and packed bytes far beyond
+    4 GiB.  Columns on both sides of that mark against the header's definition."""
+    import torch
+    import paper_1910_00178_amd as ng
+    N, K = (1 << 28) + 7, 3
+    ctx = ng.ngemm_create(0)
+    B = torch.randint(-128, 128, (N, K), dtype=torch.int8, device="cuda")
+    n = ng.ngemm_packed_b_bytes(K, N)
+    packed = torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda")
+    h = ng.ngemm_pack_b(ctx, K, N, B, K, packed, n)
+    torch.cuda.synchronize()
+    ng.ngemm_packed_b_free(h)
+    Np = -(-N // 32) * 32
+    for first in (0, 1 << 26, (1 << 28) - 32, 1 << 28):          # a panel of 32 columns: two fragments of 1 KiB
+        cols = B[first:first + 32].cpu().numpy()
+        want = layout(cols, 0)
+        assert np.array_equal(packed[first * 64:first * 64 + 2048].cpu().numpy(), want[:2048]), first
+        at = Np * 64 + 4 * first
+        assert np.array_equal(packed[at:at + 128].cpu().numpy(), want[2048:]), first
+    ng.ngemm_destroy(ctx)
