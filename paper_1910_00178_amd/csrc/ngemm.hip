@@ -1372,8 +1372,8 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     // enough to spread over the compute units): 32 x 32 tiles while there is a compute unit for each, 32 x 64 up
     // to two per unit, 64 x 64 up to two per unit while 128 x 128 tiles would fill less than half of the units;
     // larger ones, and what a K of less than two stages leaves to them, the 128 x 128 kernel.  us, against the
-    // 128 x 128 kernel: 16 x 4096 x 4096 8.9 / 47, 64 x 4096 x 4096 10.6 / 47, 512 x 768 x 768 5.9 / 15.5,
-    // 1024^3 10.5 / 18.9, 512 x 3072 x 768 11.6 / 16.7, 1024 x 2048 x 1024 14.0 / 19.0, but 1024 x 3072 x 1024
+    // 128 x 128 kernel: 16 x 4096 x 4096 8.5 / 45.6, 64 x 4096 x 4096 11.1 / 46.0, 512 x 768 x 768 5.8 / 15.0,
+    // 1024^3 9.8 / 17.6, 512 x 3072 x 768 11.5 / 15.4, 1024 x 2048 x 1024 14.0 / 17.8, but 1024 x 3072 x 1024
     // 24.8 / 19.6 and 1536^3 27 / 24.9.
     // Under a caller's cap only those whose workgroups, one per tile, keep within it; the 128 x 128 kernel and, below its K,
     // the looping form walk several tiles per workgroup.
@@ -1399,7 +1399,7 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
         p.tiles_n = (int)((B->N + 127) / 128);
         int32_t *rs = (int32_t *)workspace_dev;
         hipLaunchKernelGGL(rowsum_s16_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, A_dev, lda, (int)M,
-                           (int)M, (int)B->K, rs);
+                           (int)B->K, rs);
         if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
         p.rowsum = rs;
         const int64_t ntiles = (int64_t)p.tiles_m * p.tiles_n;

@@ -2352,25 +2352,22 @@ __global__ __launch_bounds__(64 * kReduceWaves) void splitk_reduce_kernel(const 
 // panel contiguous over K; zero padded to (K rounded up to 32) x (N rounded up to 32).  A's bytes are
 // separated after the LDS read by byte permutes.
 
-// Row sums of an int16 matrix minus 128 per element: out[i] = sum_k (X[i][k] - 128), rows >= rows_valid
-// give 0.  One wavefront per row.
-__global__ __launch_bounds__(256) void rowsum_s16_kernel(const int16_t *__restrict__ X, int64_t ldx, int rows_valid,
-                                                         int rows_out, int K, int32_t *__restrict__ out)
+// Row sums of an int16 matrix minus 128 per element: out[i] = sum_k (X[i][k] - 128).  One wavefront per row.
+__global__ __launch_bounds__(256) void rowsum_s16_kernel(const int16_t *__restrict__ X, int64_t ldx, int rows, int K,
+                                                         int32_t *__restrict__ out)
 {
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= rows_out) return;
+    if (i >= rows) return;
     uint32_t s = 0;
-    if (i < rows_valid) {
-        const int16_t *row = X + (int64_t)i * ldx;
-        for (int k = lane * 8; k < K; k += 64 * 8) {
-            if (k + 8 <= K) {
-                int16_t v[8];
-                __builtin_memcpy(v, row + k, 16);
+    const int16_t *row = X + (int64_t)i * ldx;
+    for (int k = lane * 8; k < K; k += 64 * 8) {
+        if (k + 8 <= K) {
+            int16_t v[8];
+            __builtin_memcpy(v, row + k, 16);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) s += (uint32_t)((int)v[t] - 128);
-            } else {
-                for (int t = 0; k + t < K; ++t) s += (uint32_t)((int)row[k + t] - 128);
-            }
+            for (int t = 0; t < 8; ++t) s += (uint32_t)((int)v[t] - 128);
+        } else {
+            for (int t = 0; k + t < K; ++t) s += (uint32_t)((int)row[k + t] - 128);
         }
     }
     const int sum = wave_sum((int)s);
@@ -2660,8 +2657,8 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 // in turn), so every byte that is copied into LDS is read from it once instead of twice, by the wavefront
 // that copied it: the rings are private and the main loop has no barrier.  The partial tiles meet in LDS at
 // the end, where every thread adds the NW values of four columns and finishes them: whole row pieces leave.
-// Small tiles (32 x 32, 32 x 64, 64 x 32) spread an output that has few of the larger ones over more compute
-// units.
+// Small tiles (32 x 32, 32 x 64; 64 x 64 and 64 x 128 where there are more) spread an output that has few of the
+// larger ones over more compute units.
 // ELEM = 1: 8-bit operands; a step is two matrix ops per block.  ELEM = 2: 16-bit operands in byte planes (see
 // the 16-bit section); a step is 32 elements: A's bytes are separated behind the LDS read, four matrix ops per
 // block into three accumulators (ah*bl' and al'*bh share a weight and a sum).
@@ -2669,15 +2666,16 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 // what another one does, in contrast to the kernels whose wavefronts share rows).
 // BRAW: B is the caller's unpacked [N x K] storage with aligned rows.  It has the shape of A, so its tile is
 // copied and read as A's is, and the column sums are added up from its fragments as the row sums are: one launch
-// in the place of two or three (us: 1 x 4096 x 1024 11.2 -> 4.0, 16 x 4096 x 4096 16.2 -> 6.7, 64 x 2304 x 1664 12.9 -> 4.5).
+// in the place of two or three (us in a graph: 1 x 4096 x 1024 10.9 -> 3.4, 16 x 4096 x 4096 17.1 -> 5.1, 64 x 2304 x 1664
+// 9.0 -> 4.0 and, every byte of B from memory, 12.2 -> 4.3, 18.8 -> 8.4, 12.0 -> 5.8).
 // AREG: rows of A with any alignment, which copies into LDS cannot fetch: A comes through registers (two steps on
 // their way, written into the ring two steps before they are read); everything else stays (64 x 4096 x 4097
 // 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).
 // NT: non-temporal copies of B, for weights that are read once (the rule that chooses it has the figures).
 // LOOP: fewer workgroups than tiles, for a caller that caps them (the others launch a workgroup per tile).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
-// 4096 47 -> 8.7 (3.8 TB/s of B's planes), 64 x 4096 x 4096 47 -> 10.7, 512 x 768 x 768 15.5 -> 6.1, 1024^3
-// 18.9 -> 10.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
+// 4096 45.6 -> 8.5 (3.9 TB/s of B's planes), 64 x 4096 x 4096 46.0 -> 11.1, 512 x 768 x 768 15.0 -> 5.8, 1024^3
+// 17.6 -> 9.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
 // and 7.1 on the second and third of them.
 template <int TM, int TN, int NW, int RING>
 struct WaveKCfg {
