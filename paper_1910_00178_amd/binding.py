@@ -227,7 +227,8 @@ def ngemm_run_u8s8s32_static(ctx, M, A_dev, lda, a_zero_point, B, b_zero_point, 
 
 def ngemm_tune_u8s8s32(ctx, M, A_dev, lda, a_zero_point, B, b_zero_point, C_dev, ldc,
                        workspace_dev=None, workspace_bytes=0, hip_stream=None):
-    """Returns the NGEMM_KERNEL_* value found fastest (and remembered) for this shape."""
+    """Returns the NGEMM_KERNEL_* value found fastest for this shape, one that ngemm_set_kernel takes; what later calls
+    take is remembered in the context."""
     best = _int(-1)
     _check(_lib.ngemm_tune_u8s8s32(ctx, int(M), _dev(A_dev), int(lda), int(a_zero_point), B, int(b_zero_point),
                                    _dev(C_dev), int(ldc), _dev(workspace_dev), int(workspace_bytes),
