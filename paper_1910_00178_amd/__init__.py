@@ -5,14 +5,36 @@ that `paper_1910_00178_amd.build` can (re)compile the library without loading a 
 There is no fallback: a missing or unloadable library raises.
 """
 import importlib
+import types
 
 _binding = None
+_found = set()           # names of the binding that this module holds as well
+
+
+class _Binding(types.ModuleType):
+    """The binding's module: a name that is set or deleted there is looked up again here, all of them after a reload."""
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        for n in list(_found) if name == "__spec__" else [name]:       # a reload begins by setting it
+            _forget(n)
+
+    def __delattr__(self, name):
+        super().__delattr__(name)
+        _forget(name)
+
+
+def _forget(name):
+    if name in _found:
+        _found.discard(name)
+        globals().pop(name, None)
 
 
 def _load():
     global _binding
     if _binding is None:
         _binding = importlib.import_module(".binding", __name__)
+        _binding.__class__ = _Binding
     return _binding
 
 
@@ -22,7 +44,9 @@ def __getattr__(name):
     if name in ("build", "workloads", "binding"):
         return importlib.import_module("." + name, __name__)
     value = getattr(_load(), name)
-    globals()[name] = value          # found without this function from now on (it costs 0.2 us a call)
+    if not name.startswith("_"):
+        globals()[name] = value      # found without this function from now on (it costs 0.2 us a call)
+        _found.add(name)
     return value
 
 

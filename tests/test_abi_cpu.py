@@ -1,6 +1,7 @@
 """CPU-side checks of the boundary: the library loads, exports every symbol the header
 declares, and its pure host functions follow the documented sizes.  No compute calls."""
 import ctypes
+import importlib
 import os
 import re
 
@@ -79,3 +80,18 @@ def test_unpack_helper_inverts_documented_layout():
     back, pad_zero, colsum = unpack_packed(raw, K, N)
     assert np.array_equal(back, B) and pad_zero
     assert np.array_equal(colsum[:N], B.astype(np.int64).sum(1))
+
+
+def test_package_follows_its_binding(monkeypatch):
+    """A name of the binding is the same through the package, also when it is replaced after its first use."""
+    import paper_1910_00178_amd as ng
+    from paper_1910_00178_amd import binding
+    real = ng.ngemm_packed_b_bytes
+    assert real is binding.ngemm_packed_b_bytes and ng.ngemm_packed_b_bytes is real
+    monkeypatch.setattr(binding, "ngemm_packed_b_bytes", lambda K, N: -5)
+    assert ng.ngemm_packed_b_bytes(3, 4) == -5
+    monkeypatch.undo()
+    assert ng.ngemm_packed_b_bytes is real
+    again = importlib.reload(binding)
+    assert ng.ngemm_packed_b_bytes is again.ngemm_packed_b_bytes is not real
+    assert ng.NGEMM_KERNEL_TILE_64 == 1 and ng.__name__ == "paper_1910_00178_amd" and ng.__spec__ is not None
