@@ -3,6 +3,7 @@
 // ngemm_kernels.h; there is no CPU fallback.
 #include "ngemm.h"
 #include "ngemm_kernels.h"
+#include "ngemm_mid.h"
 
 #include <hip/hip_runtime.h>
 #include <cmath>
@@ -35,7 +36,7 @@ struct ngemm_ctx {
     struct Tuned {
         int64_t M, N, K;
         int kernel;          // the fastest of NGEMM_KERNEL_*
-        bool wavek;          // the kernel that splits K over a workgroup's wavefronts was faster still
+        bool wavek;          // what only the automatic choice launches (gemm_wavek_kernel, gemm_mid_kernel) was faster still
     };
     std::vector<Tuned> tuned;
 };
@@ -681,6 +682,114 @@ int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, boo
     return (small || form == 24) && wavek_fits(form, M, N, budget, cus) ? form : 0;
 }
 
+// Forms of gemm_mid_kernel.
+using Mid256 = MidCfg<4, 4, 2, 4, 6>;        // 128 x 256, eight wavefronts, 144 KiB of LDS: one workgroup per compute unit
+using Mid192 = MidCfg<4, 6, 2, 2, 4>;        // 128 x 192, 80 KiB: two
+using Mid128 = MidCfg<4, 4, 2, 2, 4>;        // 128 x 128, 64 KiB
+using Mid64x192 = MidCfg<2, 6, 2, 2, 4>;     // 64 KiB
+using Mid64x128 = MidCfg<2, 4, 2, 2, 6>;     // 72 KiB
+
+template <class C>
+hipError_t launch_mid(const GemmParams &p0, bool requant, bool rows, bool aligned, hipStream_t st)
+{
+    GemmParams p = p0;
+    p.tiles_m = (p.M + C::BM - 1) / C::BM;
+    p.tiles_n = (p.N + C::BN - 1) / C::BN;
+    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(C::kThreads);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, C::kLdsBytes, st, p);
+        return hipGetLastError();
+    };
+    if (aligned) {
+        if (requant) return rows ? go(gemm_mid_kernel<C, true, true, false>) : go(gemm_mid_kernel<C, true, false, false>);
+        return rows ? go(gemm_mid_kernel<C, false, true, false>) : go(gemm_mid_kernel<C, false, false, false>);
+    }
+    if (requant) return rows ? go(gemm_mid_kernel<C, true, true, true>) : go(gemm_mid_kernel<C, true, false, true>);
+    return rows ? go(gemm_mid_kernel<C, false, true, true>) : go(gemm_mid_kernel<C, false, false, true>);
+}
+
+hipError_t launch_mid_form(int form, const GemmParams &p, bool requant, bool rows, bool aligned, hipStream_t st)
+{
+    switch (form) {
+    case 1: return launch_mid<Mid64x128>(p, requant, rows, aligned, st);
+    case 2: return launch_mid<Mid64x192>(p, requant, rows, aligned, st);
+    case 3: return launch_mid<Mid128>(p, requant, rows, aligned, st);
+    case 4: return launch_mid<Mid192>(p, requant, rows, aligned, st);
+    default: return launch_mid<Mid256>(p, requant, rows, aligned, st);
+    }
+}
+
+template <class C>
+hipError_t allow_big_lds_mid()
+{
+    if (C::kLdsBytes <= 64 * 1024) return hipSuccess;
+    const void *forms[] = {
+        (const void *)gemm_mid_kernel<C, false, false, false>, (const void *)gemm_mid_kernel<C, false, true, false>,
+        (const void *)gemm_mid_kernel<C, true, false, false>,  (const void *)gemm_mid_kernel<C, true, true, false>,
+        (const void *)gemm_mid_kernel<C, false, false, true>,  (const void *)gemm_mid_kernel<C, false, true, true>,
+        (const void *)gemm_mid_kernel<C, true, false, true>,   (const void *)gemm_mid_kernel<C, true, true, true>,
+    };
+    for (const void *f : forms) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// The form of gemm_mid_kernel that serves an 8-bit problem in the place of the tiled kernels, or 0.  1420 shapes were timed with every
+// form and with the kernels before (M, N, K up to 8192, odd sizes among them, aligned and unaligned rows, int32 and u8 outputs, with and
+// without a zero-point of B):
+//  * outputs of more than 0.55 x 128 x 128 tiles per compute unit: 1.17 x faster on average, unaligned rows 1.15 x; below K = 640 only from a tile per
+//    unit on (2240 x 960 x 512 7.0 us before, 8.0 here; 2048 x 4096 x 256 9.7 and 9.4);
+//  * from two 64 x 64 tiles per two units on with a long K where the kernels before pay extra: row sums, u8 outputs, K of no whole stages,
+//    unaligned rows (1.1 x; 1088 x 1413 x 2112 z 12.5 / 11.0).  Plain int32 problems there are a tie or a loss.
+// Not where 256 or 192 x 256 tiles fill their rounds of units to 0.85 and more and K is whole pairs of stages or long: those read half the
+// bytes per matrix op (4736 x 3072 x 768 19.2 us, here 21.7; 4096 x 4096 x 1024 25.4 / 27.2; 8192^3 bound by power).
+// Which form: the least time by a model with constants (ns) that were fitted to those shapes; its choices are within 1.5 % of the best form on
+// average.  n tiles that a unit works through (rounds of resident workgroups counted whole) cost `stage` per stage and `tile`
+// each, all the tiles together their share of the chip's (`flow`, `out`), a workgroup alone on its unit `lone_stage`, `lone` on top.
+int mid_form(int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
+{
+    if (M <= kSkinnyMaxM || K < 64 || budget < cus) return 0;          // (a workgroup per tile: not under a caller's cap)
+    if (!x64_offsets_fit(256, lda, K) || !x64_offsets_fit(9, 32 * round_up(K, 64), 0)) return 0;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const bool plain = aligned && !rows && !requant && K % 64 == 0;
+    if (!(tiles(128, 128) * 20 > cus * 11 && (K >= 640 || tiles(128, 128) > cus)) && !(!plain && tiles(64, 64) > cus && K >= 1536)) return 0;
+    if (aligned && K >= 512 && (K % 128 < 64 || K >= 2048))
+        for (int64_t bm : {256, 192}) {
+            const int64_t t = tiles(bm, 256), rounds = (t + cus - 1) / cus;
+            if (t * 20 >= 17 * rounds * cus) return 0;
+        }
+    struct Form {
+        int id, bm, bn, per_cu;
+        int64_t fixed, stage, tile, flow, out, lone_stage, lone;
+    };
+    constexpr Form forms[2][5] = {{{1, 64, 128, 2, 2650, 139, 1287, 38, 315, -10, 2084},
+                                  {2, 64, 192, 2, 3002, 176, 1083, 38, 1132, 9, 1022},
+                                  {3, 128, 128, 2, 2577, 192, 1841, 76, 822, 16, 1132},
+                                  {4, 128, 192, 2, 2219, 257, 2758, 79, 1525, 14, 2067},
+                                  {5, 128, 256, 1, 1793, 313, 4811, 189, 1919, 0, 0}},
+                                 // rows of A through registers
+                                 {{1, 64, 128, 2, 3485, 166, 1110, 39, 312, 22, 1600},
+                                  {2, 64, 192, 2, 3371, 181, 2221, 70, -227, 43, 874},
+                                  {3, 128, 128, 2, 2813, 261, 2873, 56, -99, 54, 1119},
+                                  {4, 128, 192, 2, 2760, 375, 2079, 12, 2048, 41, 2773},
+                                  {5, 128, 256, 1, 3345, 397, 3102, 90, 2557, 0, 0}}};
+    int best = 0;
+    int64_t least = 0;
+    const int64_t nst = (K + 63) / 64;
+    for (const Form &f : forms[aligned ? 0 : 1]) {
+        const int64_t t = tiles(f.bm, f.bn), whole = t / (cus * f.per_cu), rest = t - whole * cus * f.per_cu;
+        const int64_t n = whole * f.per_cu + (rest + cus - 1) / cus;
+        const int64_t cost = f.fixed + n * (f.stage * nst + f.tile) + t * (f.flow * nst + f.out) / cus + (n == 1 ? f.lone_stage * nst + f.lone : 0);
+        if (best == 0 || cost < least) {
+            best = f.id;
+            least = cost;
+        }
+    }
+    return best;
+}
+
 // The forms that read B from the caller's storage.
 template <class F>
 hipError_t launch_wavek_raw(const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
@@ -728,9 +837,9 @@ struct RunArgs {
     bool needs_rowsum() const { return zb != 0 || zb_vec != nullptr; }
 };
 
-// What serves a call: one of NGEMM_KERNEL_*, and whether the kernel that splits K over a workgroup's wavefronts may
-// take its place where its rules have a form for the call.  It may for the automatic choice and for shapes whose
-// tuning found it faster; a kernel that the caller asked for is the one that runs.
+// What serves a call: one of NGEMM_KERNEL_*, and whether the kernels that have no number, the one that splits K over a
+// workgroup's wavefronts and gemm_mid_kernel, may take its place where their rules have a form for the call.  They may for the automatic
+// choice and for shapes whose tuning found them faster; a kernel that the caller asked for is the one that runs.
 struct Route {
     int kernel;
     bool wavek;
@@ -762,7 +871,8 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 r = Route{t.kernel, false};
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
-                if (t.wavek && wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0)
+                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0 ||
+                                mid_form(a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0))
                     r = Route{small, true};
             }
         if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.requant), true};
@@ -834,7 +944,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
         if (parts < 2) kernel = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
     }
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
-    // outputs of few tiles: K split over the wavefronts of a workgroup
+    // outputs of few tiles: K split over the wavefronts of a workgroup; of many: the kernel of tiles between those of the others
     if (route.wavek) {
         const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, device_cus, num_cus);
         if (form != 0) {
@@ -842,6 +952,8 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
             return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
+        const int mid = kernel == NGEMM_KERNEL_SPLIT_K ? 0 : mid_form(a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
+        if (mid != 0) return launch_mid_form(mid, p, a.requant, rows_needed, dma_ok, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
     }
     // at most one tile per compute unit and a K worth pipelining: the long-pipeline variants
     const bool deep64 = kernel == NGEMM_KERNEL_TILE_64 && dma_ok && B->K >= 512 &&
@@ -1007,7 +1119,9 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
             hipFuncSetAttribute((const void *)gemm_s16_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 S16Cfg::kLdsBytes) != hipSuccess ||
             allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess ||
-            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_nt<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess) {
+            allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_nt<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess ||
+            allow_big_lds_mid<Mid256>() != hipSuccess || allow_big_lds_mid<Mid192>() != hipSuccess || allow_big_lds_mid<Mid128>() != hipSuccess ||
+            allow_big_lds_mid<Mid64x192>() != hipSuccess || allow_big_lds_mid<Mid64x128>() != hipSuccess) {
             delete c;
             return NGEMM_ERR_DEVICE;
         }
@@ -1058,7 +1172,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
     }
     const bool dma_ok = rows_aligned(A_dev, lda);
     const int small = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
-    // the last one: the kernel that splits K over a workgroup's wavefronts, in the place of the kernel for small outputs
+    // the last one: what the automatic choice puts in the place of the kernel for small outputs (gemm_wavek_kernel, gemm_mid_kernel)
     const Route candidates[7] = {{NGEMM_KERNEL_SKINNY, false}, {NGEMM_KERNEL_TILE_64, false}, {NGEMM_KERNEL_TILE_128, false},
                                  {NGEMM_KERNEL_TILE_256, false}, {NGEMM_KERNEL_SPLIT_K, false}, {NGEMM_KERNEL_TILE_192, false},
                                  {small, true}};
@@ -1076,8 +1190,9 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
             int kchunk = 0;
             if (!dma_ok || splitk_parts(M, B->N, B->K, workgroup_budget(ctx), &kchunk) < 2) continue;
         }
-        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, ctx->num_cus > 0 ? ctx->num_cus : 256,
-                                                workgroup_budget(ctx)) == 0) continue;
+        const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, cus, workgroup_budget(ctx)) == 0 &&
+            mid_form(M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
         const int warm = 5, reps = 50, rounds = 3;

@@ -1,0 +1,85 @@
+"""gemm_mid_kernel against the oracle, in all its forms: edges of its tiles (64 and 128 rows, 128 to 256 columns), K of one stage (64 bytes),
+of fewer stages than its ring, of partial stages and of a last chunk that ends inside 16 bytes, rows of A with any alignment (the
+allocation ends with the last row), each output and operand type."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_routes import Problem, ctx, launches  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+W64x128, W64x192, W128, W192, W256 = "2, 4, 2, 2, 6", "2, 6, 2, 2, 4", "4, 4, 2, 2, 4", "4, 6, 2, 2, 4", "4, 4, 2, 4, 6"
+# (M, N, K, pitch of A: 0 = K, which form)
+SHAPES = [(802, 4624, 64, 64, W64x128), (387, 2314, 1537, 1552, W64x128), (802, 4624, 79, 0, W64x128), (1100, 1300, 1663, 0, W64x128),
+          (4727, 774, 65, 80, W64x192), (386, 4727, 650, 656, W64x192), (385, 4755, 641, 0, W64x192), (1701, 1537, 1600, 1603, W64x192),
+          (4712, 1185, 64, 64, W128), (3279, 775, 700, 704, W128), (2918, 1314, 643, 0, W128),
+          (4524, 1935, 65, 80, W192), (2725, 3339, 193, 208, W192), (3490, 2519, 77, 0, W192), (2368, 4629, 343, 0, W192),
+          (1824, 3322, 774, 784, W256), (3268, 1799, 131, 0, W256), (1930, 3100, 1000, 1001, W256)]
+
+
+@pytest.fixture(scope="module")
+def runner():
+    from gpu_util import Runner
+    r = Runner()
+    yield r
+    r.close()
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=str)
+def test_forms_against_the_oracle(runner, ctx, launches, case):  # noqa: F811
+    M, N, K, pitch, form = case
+    import paper_1910_00178_amd as ng
+    p = Problem(ctx, M, N, K, pitch or K)
+    got = launches(p.run())
+    want = "gemm_mid_kernel<MidCfg<%s>, false, false, %s>" % (form, "true" if (pitch or K) % 16 else "false")
+    assert [name for name, _ in got] == [want], got
+    ng.ngemm_packed_b_free(p.h)
+    rng = np.random.default_rng(M * 7 + K)
+    A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(N, K), dtype=np.int8)
+    A[::5], B[1::7] = 255, -128
+    h, _ = runner.pack(B)
+    pad = (pitch or K) - K
+    for za, zb, ldc_pad in ((7, 0, 0), (200, -5, 3)):
+        C = oracle.gemm_u8s8s32(A, B, za, zb)
+        assert np.array_equal(runner.run(A, h, N, za=za, zb=zb, lda_pad=pad, ldc_pad=ldc_pad), C)
+        scale = np.float32(60.0 / np.sqrt(K) / 5000)
+        assert np.array_equal(runner.run(A, h, N, za=za, zb=zb, scale=float(scale), zc=128, lda_pad=pad, ldc_pad=ldc_pad),
+                              oracle.requant_s32u8(C, float(scale), 128))
+    ng.ngemm_packed_b_free(h)
+
+
+@pytest.mark.parametrize("K,pitch", [(700, 704), (701, 701)])
+def test_other_operands_and_per_column_terms(runner, K, pitch):
+    """Signed A and unsigned B with zero-points, a zero-point, bias and scale per column, a zero-point of C beyond binary32."""
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N = 1500, 1605
+    rng = np.random.default_rng(K)
+    ctx = runner.ctx                                         # noqa: F811
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+    def rows(x):
+        full = np.full((x.shape[0], pitch), 99, x.dtype)
+        full[:, :K] = x
+        return dev(full.reshape(-1)[:(x.shape[0] - 1) * pitch + K])
+    Au, As = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(M, K), dtype=np.int8)
+    Bs, Bu = rng.integers(-128, 128, size=(N, K), dtype=np.int8), rng.integers(0, 256, size=(N, K), dtype=np.uint8)
+    nb = ng.ngemm_packed_b_bytes(K, N)
+    ps, pu = (torch.empty(nb, dtype=torch.uint8, device="cuda") for _ in range(2))
+    hs, hu = ng.ngemm_pack_b(ctx, K, N, dev(Bs), K, ps, nb), ng.ngemm_pack_b_u8(ctx, K, N, dev(Bu), K, pu, nb)
+    wsb = ng.ngemm_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    C = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    ng.ngemm_run_s8s8s32(ctx, M, rows(As), pitch, -5, hs, 9, C, N, ws, wsb)
+    assert np.array_equal(C.cpu().numpy(), oracle.gemm_s8s8s32(As, Bs, -5, 9))
+    ng.ngemm_run_u8u8s32(ctx, M, rows(Au), pitch, 131, hu, 120, C, N, ws, wsb)
+    assert np.array_equal(C.cpu().numpy(), oracle.gemm_u8u8s32(Au, Bu, 131, 120))
+    zbv, bias = rng.integers(-8, 9, N).astype(np.int32), rng.integers(-3000, 3000, N).astype(np.int32)
+    scale = (rng.random(N) * 1e-3 + 1e-4).astype(np.float32)
+    D = torch.empty((M, N), dtype=torch.uint8, device="cuda")
+    for zc, relu in ((128, False), (-(1 << 30), False), (3, True)):
+        ng.ngemm_run_u8s8u8_requant_channel(ctx, M, rows(Au), pitch, 128, hs, 0, dev(zbv), dev(scale), dev(bias), int(relu), zc, D, N, ws, wsb)
+        assert np.array_equal(D.cpu().numpy(), oracle.gemm_u8s8u8_requant_channel(Au, Bs, 128, 0, scale, zc, zb_vec=zbv, bias=bias, relu=relu))
+    ng.ngemm_packed_b_free(hs)
+    ng.ngemm_packed_b_free(hu)
