@@ -739,27 +739,23 @@ hipError_t allow_big_lds_mid()
 // The form of gemm_mid_kernel that serves an 8-bit problem in the place of the tiled kernels, or 0.  1420 shapes were timed with every
 // form and with the kernels before (M, N, K up to 8192, odd sizes among them, aligned and unaligned rows, int32 and u8 outputs, with and
 // without a zero-point of B):
-//  * outputs of more than 0.55 x 128 x 128 tiles per compute unit: 1.17 x faster on average, unaligned rows 1.15 x; below K = 640 only from a tile per
-//    unit on (2240 x 960 x 512 7.0 us before, 8.0 here; 2048 x 4096 x 256 9.7 and 9.4);
-//  * from two 64 x 64 tiles per two units on with a long K where the kernels before pay extra: row sums, u8 outputs, K of no whole stages,
+//  * outputs of more than 0.55 x 128 x 128 tiles per compute unit: 1.17 x faster on average, unaligned rows 1.15 x; a K below 768 only from 0.8
+//    tiles per unit on (3840 x 640 x 704, 150 tiles, 7.6 us before, 8.6 here; at 205 .. 256 tiles 1.08-1.16 x);
+//  * from one 64 x 64 tile per unit on with a long K where the kernels before pay extra: row sums, u8 outputs, K of no whole stages,
 //    unaligned rows (1.1 x; 1088 x 1413 x 2112 z 12.5 / 11.0).  Plain int32 problems there are a tie or a loss.
-// Not where 256 or 192 x 256 tiles fill their rounds of units to 0.85 and more and K is whole pairs of stages or long: those read half the
-// bytes per matrix op (4736 x 3072 x 768 19.2 us, here 21.7; 4096 x 4096 x 1024 25.4 / 27.2; 8192^3 bound by power).
 // Which form: the least time by a model with constants (ns) that were fitted to those shapes; its choices are within 1.5 % of the best form on
 // average.  n tiles that a unit works through (rounds of resident workgroups counted whole) cost `stage` per stage and `tile`
 // each, all the tiles together their share of the chip's (`flow`, `out`), a workgroup alone on its unit `lone_stage`, `lone` on top.
-int mid_form(int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
+// `kernel`: what would run otherwise; the 256- and 192-row tiles, which read half the bytes per matrix op but take a row-sum launch and
+// what is left behind an even number of stages apart, stay by a model of the same kind where it says that they are faster (4736 x 3072 x
+// 768 19.2 us against 21.7, 4096 x 4096 x 1024 25.4 / 27.2, 2662 x 3521 x 2816 z 34.9 / 39.3).
+int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
 {
     if (M <= kSkinnyMaxM || K < 64 || budget < cus) return 0;          // (a workgroup per tile: not under a caller's cap)
     if (!x64_offsets_fit(256, lda, K) || !x64_offsets_fit(9, 32 * round_up(K, 64), 0)) return 0;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const bool plain = aligned && !rows && !requant && K % 64 == 0;
-    if (!(tiles(128, 128) * 20 > cus * 11 && (K >= 640 || tiles(128, 128) > cus)) && !(!plain && tiles(64, 64) > cus && K >= 1536)) return 0;
-    if (aligned && K >= 512 && (K % 128 < 64 || K >= 2048))
-        for (int64_t bm : {256, 192}) {
-            const int64_t t = tiles(bm, 256), rounds = (t + cus - 1) / cus;
-            if (t * 20 >= 17 * rounds * cus) return 0;
-        }
+    if (!(tiles(128, 128) * 20 > cus * 11 && (K >= 768 || tiles(128, 128) * 5 > cus * 4)) && !(!plain && tiles(64, 64) > cus && K >= 1536)) return 0;
     struct Form {
         int id, bm, bn, per_cu;
         int64_t fixed, stage, tile, flow, out, lone_stage, lone;
@@ -786,6 +782,13 @@ int mid_form(int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool ro
             best = f.id;
             least = cost;
         }
+    }
+    if (aligned && (kernel == NGEMM_KERNEL_TILE_256 || kernel == NGEMM_KERNEL_TILE_192)) {
+        const bool t256 = kernel == NGEMM_KERNEL_TILE_256;
+        const int64_t t = tiles(t256 ? 256 : 192, 256), rounds = (t + cus - 1) / cus, odd = K % 128 != 0 ? rounds : 0;
+        const int64_t large = t256 ? -2142 + rounds * (324 * nst + 12043) + t * (244 * nst + 4397) / cus + (rows ? 6211 : 0) + 5828 * odd
+                                   : 3533 + rounds * (283 * nst + 5802) + t * (249 * nst + 3410) / cus + (rows ? 5391 : 0) + 2809 * odd;
+        if (least * 100 > large * 97) return 0;
     }
     return best;
 }
@@ -872,7 +875,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
                 if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0 ||
-                                mid_form(a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0))
+                                mid_form(small, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0))
                     r = Route{small, true};
             }
         if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.requant), true};
@@ -952,7 +955,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
             return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
-        const int mid = kernel == NGEMM_KERNEL_SPLIT_K ? 0 : mid_form(a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
+        const int mid = kernel == NGEMM_KERNEL_SPLIT_K ? 0 : mid_form(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
         if (mid != 0) return launch_mid_form(mid, p, a.requant, rows_needed, dma_ok, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
     }
     // at most one tile per compute unit and a K worth pipelining: the long-pipeline variants
@@ -1192,7 +1195,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
         }
         const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
         if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, cus, workgroup_budget(ctx)) == 0 &&
-            mid_form(M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
+            mid_form(k, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
         const int warm = 5, reps = 50, rounds = 3;

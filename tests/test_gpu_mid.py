@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 W64x128, W64x192, W128, W192, W256 = "2, 4, 2, 2, 6", "2, 6, 2, 2, 4", "4, 4, 2, 2, 4", "4, 6, 2, 2, 4", "4, 4, 2, 4, 6"
 # (M, N, K, pitch of A: 0 = K, which form)
 SHAPES = [(802, 4624, 64, 64, W64x128), (387, 2314, 1537, 1552, W64x128), (802, 4624, 79, 0, W64x128), (1100, 1300, 1663, 0, W64x128),
-          (4727, 774, 65, 80, W64x192), (386, 4727, 650, 656, W64x192), (385, 4755, 641, 0, W64x192), (1701, 1537, 1600, 1603, W64x192),
-          (4712, 1185, 64, 64, W128), (3279, 775, 700, 704, W128), (2918, 1314, 643, 0, W128),
+          (4727, 774, 65, 80, W64x192), (386, 4727, 781, 784, W64x192), (385, 4755, 773, 0, W64x192), (1701, 1537, 1600, 1603, W64x192),
+          (4712, 1185, 64, 64, W128), (3279, 775, 774, 784, W128), (2918, 1314, 643, 0, W128),
           (4524, 1935, 65, 80, W192), (2725, 3339, 193, 208, W192), (3490, 2519, 77, 0, W192), (2368, 4629, 343, 0, W192),
           (1824, 3322, 774, 784, W256), (3268, 1799, 131, 0, W256), (1930, 3100, 1000, 1001, W256)]
 
@@ -49,7 +49,7 @@ def test_forms_against_the_oracle(runner, ctx, launches, case):  # noqa: F811
     ng.ngemm_packed_b_free(h)
 
 
-@pytest.mark.parametrize("K,pitch", [(700, 704), (701, 701)])
+@pytest.mark.parametrize("K,pitch", [(770, 784), (773, 773)])
 def test_other_operands_and_per_column_terms(runner, K, pitch):
     """Signed A and unsigned B with zero-points, a zero-point, bias and scale per column, a zero-point of C beyond binary32."""
     import torch
