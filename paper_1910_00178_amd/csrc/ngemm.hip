@@ -688,6 +688,7 @@ using Mid192 = MidCfg<4, 6, 2, 2, 4>;        // 128 x 192, 80 KiB: two
 using Mid128 = MidCfg<4, 4, 2, 2, 4>;        // 128 x 128, 64 KiB
 using Mid64x192 = MidCfg<2, 6, 2, 2, 4>;     // 64 KiB
 using Mid64x128 = MidCfg<2, 4, 2, 2, 6>;     // 72 KiB
+struct MidGroup : MidCfg<2, 2, 2, 2, 4> { static constexpr int kPerCu = 4; };      // grouped launches
 
 template <class C>
 hipError_t launch_mid(const GemmParams &p0, bool requant, bool rows, bool aligned, hipStream_t st)
@@ -1652,6 +1653,9 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
     grp.unit_start[0] = 0;
     const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     using TCfg = TileCfg<64, 64, 2, 2, 64>;
+    // gemm_group_mid_kernel counts in 32 bits from a tile's first row and panel; a group with a member that has more keeps the kernel
+    // with 64-bit addresses.
+    bool wide = false;
     auto flush = [&]() -> hipError_t {
         if (grp.count == 0) return hipSuccess;
         const unsigned grid = (unsigned)grp.unit_start[grp.count];
@@ -1664,12 +1668,14 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
                 hipLaunchKernelGGL(gemm_group_skinny_kernel, dim3(grid), dim3(64 * nw), (size_t)(nw * 16 * 64 * 4), st, grp);
             } else {
                 const size_t lds = std::max((size_t)TCfg::kLdsBytes, (size_t)(4 * 16 * 64 * 4));
-                hipLaunchKernelGGL((gemm_group_kernel<64, 64, 2, 2, 64>), dim3(grid), dim3(256), lds, st, grp);
+                if (wide) hipLaunchKernelGGL((gemm_group_kernel<64, 64, 2, 2, 64>), dim3(grid), dim3(256), lds, st, grp);
+                else hipLaunchKernelGGL((gemm_group_mid_kernel<MidGroup>), dim3(grid), dim3(256), MidGroup::kLdsBytes, st, grp);
             }
         }
         grp.count = 0;
         grp.first_tile = 0;
         grp.unit_start[0] = 0;
+        wide = false;
         return hipGetLastError();
     };
     // The streaming kernel's group: up to kStreamGroupMax members; unit_start collects panel counts
@@ -1762,6 +1768,7 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
     for (const Pending &m : tile_members) {
         if (grp.count == kGroupMax || grp.unit_start[grp.count] + m.units > kMaxGrid)
             if (flush() != hipSuccess) return NGEMM_ERR_DEVICE;
+        wide = wide || !x64_offsets_fit(256, m.p.lda, m.p.K) || !x64_offsets_fit(9, 32 * (int64_t)m.p.Kp, 0);
         push(m.p, m.units, false);
     }
     for (const Pending &m : stream_members) {

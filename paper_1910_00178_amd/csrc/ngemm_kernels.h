@@ -1070,12 +1070,13 @@ struct GroupParams {
 static_assert(sizeof(GroupMember) == 56, "member record");
 static_assert(sizeof(GroupParams) <= 4096, "kernel argument block");
 
+// The member of a workgroup, found by a wavefront's lanes at once.
 __device__ __forceinline__ int group_find(const GroupParams &g, int bid)
 {
-    int q = 0;
-    for (int t = 1; t < g.count; ++t)
-        if (bid >= g.unit_start[t]) q = t;
-    return q;
+    static_assert(kGroupMax <= 128, "two comparisons per lane");
+    const int lane = threadIdx.x & 63, a = lane + 1, b = lane + 65;
+    const int sa = g.unit_start[a < kGroupMax ? a : kGroupMax], sb = g.unit_start[b < kGroupMax ? b : kGroupMax];
+    return __builtin_popcountll(__ballot(a < g.count && bid >= sa)) + __builtin_popcountll(__ballot(b < g.count && bid >= sb));
 }
 
 // The full parameter set of a member; tiles are counted for BM x BN workgroup tiles.
@@ -1115,9 +1116,7 @@ __device__ __forceinline__ GemmParams group_member_params(const GroupMember &m, 
     return p;
 }
 
-// Register ring of the grouped kernel's tiles: with four sets the batch of 64 odd shapes takes 28.8 us,
-// with one 34.8 (a long-K member's loads no longer wait behind the other members' traffic); stages
-// of 128 bytes instead of 64 gain nothing.
+// Register ring of this grouped kernel's tiles: four sets, so that a long-K member's loads do not wait behind the other members' traffic.
 constexpr int kGroupRing = 4;
 
 // ---- tiled MFMA kernel, direct-to-LDS variant -------------------------------------------------

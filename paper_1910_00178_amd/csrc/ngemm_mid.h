@@ -42,6 +42,7 @@ struct MidCfg {
     static constexpr int kEpi = kEpi32 > kEpi8 ? kEpi32 : kEpi8;
     static constexpr int kLdsBytes = NS * kStage > kEpi ? NS * kStage : kEpi;
     static constexpr int kPerCu = kLdsBytes <= 80 * 1024 || NW == 4 ? 2 : 1;
+    static constexpr int AD = NS % 4 == 0 ? 4 : 3;             // register sets for A of unaligned rows
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
     static_assert(NS >= 3, "ring");
     static_assert(BN % 32 == 0 && BN <= kThreads, "whole panels, a thread per column");
@@ -49,18 +50,26 @@ struct MidCfg {
     static constexpr int kCopyBias = 3 * 1024;                 // lane offsets carry it, the descriptors' bases lack it
 };
 
+// f(IntC<U>) && ... && f(IntC<R - 1>)
+template <int U, int R, class F>
+__device__ __forceinline__ bool all_of(F &&f)
+{
+    if constexpr (U < R) return f(IntC<U>{}) && all_of<U + 1, R>(f);
+    else return true;
+}
+
+// One workgroup tile (`tile` in the XCD-aware order of tile_of_block) of the problem `p`.  K >= 16, AREG: any K.
 template <class C, bool REQUANT, bool ROWS, bool AREG>
-__global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_kernel(const GemmParams p)
+__device__ __forceinline__ void mid_body(const GemmParams &p, int tile, uint8_t *lds)
 {
     constexpr int RM = C::RM, RN = C::RN, WGN = C::WGN, NW = C::NW, NS = C::NS, NM = RM * RN, NT = C::kThreads, NR = RM + RN;
     constexpr int AC = C::AITEMS / NW, BC = C::BITEMS / NW;          // KiB of A and B per wavefront and stage
     constexpr int PER = AC + BC, NC = AREG ? BC : PER;               // vector memory instructions, copies into LDS among them
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     int tm, tn;
-    tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
+    tile_of_block(tile, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     const int nst = p.Kp / 64;                               // stages of 64 bytes of K
     const int nfrag = p.Kp / 32;
@@ -86,10 +95,10 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
         const uint32_t row = (uint32_t)(grow - m0) * (uint32_t)p.lda, bias = AREG ? 0u : (uint32_t)(C::kCopyBias - 1024 * i);
         voff[i] = row + (uint32_t)(a_chunk * 16) + bias;
         const int k0 = klast + a_chunk * 16, valid = p.K - k0;
-        fix[i] = valid > 0 && valid < 16 && grow == p.M - 1;
+        fix[i] = (valid > 0 && valid < 16 && grow == p.M - 1) || (AREG && nst == 1);     // (a row may be shorter than 16 bytes)
         a_last[i] = row + bias + (valid <= 0 || fix[i] ? 0u : (uint32_t)k0);
         fixv[i] = v4i{0, 0, 0, 0};
-        if (fix[i]) fixv[i] = load16_partial(a_tile + row + k0, valid);
+        if (fix[i]) fixv[i] = valid >= 16 ? load16_any(a_tile + row + k0) : load16_partial(a_tile + row + k0, valid < 0 ? 0 : valid);
     }
 #pragma unroll
     for (int i = 0; i < BC; ++i) {
@@ -138,7 +147,7 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lptr_t)(lds + slot * C::kStage + C::kABytes + wave * BC * 1024), 16, voff[I], t * 2048,
                                                      (I - AC) * 1024, 0);
     };
-    constexpr int AD = NS % 4 == 0 ? 4 : 3;                  // AREG: register sets, stage t in set t % AD
+    constexpr int AD = C::AD;                                // AREG: register sets, stage t in set t % AD
     v4i va[AD][AC];
     auto load_a = [&](auto set, int t) {
         constexpr int S = decltype(set)::value;
@@ -246,16 +255,20 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
 
     // ---- prologue ----
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (AREG) static_for<0, AD>([&](auto u) { load_a(u, decltype(u)::value); });
+    if constexpr (AREG) {
+        if (nst > 1) static_for<0, AD>([&](auto u) { load_a(u, decltype(u)::value); });
+    }
 #pragma unroll
     for (int t = 0; t < NS; ++t)
         if (t < nst) static_for<0, NC>([&](auto n) { dma1(n, t, t); });
     if constexpr (AREG) {
         write_a(IntC<0>{}, 0, 0);
-        if (nst > 1) write_a(IntC<1>{}, 1, 1);
-        load_a(IntC<0>{}, AD);
-        load_a(IntC<1>{}, AD + 1);
-        wait_vmcnt<2 * AC>();                                 // (all first copies: once per tile)
+        if (nst > 1) {
+            write_a(IntC<1>{}, 1, 1);
+            load_a(IntC<0>{}, AD);
+            load_a(IntC<1>{}, AD + 1);
+            wait_vmcnt<2 * AC>();
+        } else wait_vmcnt<0>();                                 // (all first copies: once per tile)
     } else {
         if (nst >= NS) wait_vmcnt<(NS - 1) * NC>();
         else wait_vmcnt<0>();
@@ -304,28 +317,50 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
             }
         });
     };
-    auto finish = [&](auto u) {                               // the last stages
+    // AREG: the last stages but one.  As many loads as in the steady loop, so that the waits are counted there as well; what lies past
+    // the end is one address for all lanes.
+    auto finish_areg = [&](auto u) -> bool {
         constexpr int V = decltype(u)::value, X = V & 1, P2 = (V + 2) % AD, S0 = V % NS, S1 = (V + 1) % NS, S2 = (V + 2) % NS;
+        if (t + 1 >= nst) return false;
+        const uint8_t *nxt = lds + S1 * C::kStage;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        wait_vmcnt<(NS - 2 < AD - 1 ? NS - 2 : AD - 1) * PER>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 2 < nst) write_a(IntC<P2>{}, S2, t + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        const int ta = t + 2 + AD, tb = t + NS;
+        static_for<0, PER>([&](auto n) {
+            constexpr int I = decltype(n)::value;
+            if constexpr (I < AC) {
+                const uint32_t at = ta < nst - 1 ? voff[I] + (uint32_t)(ta * 64) : ta == nst - 1 ? a_last[I] : 0u;
+                va[P2][I] = load16_any(a_tile + at);
+            } else {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lptr_t)(lds + S0 * C::kStage + C::kABytes + wave * BC * 1024), 16,
+                                                         tb < nst ? voff[I] : (uint32_t)C::kCopyBias, tb < nst ? tb * 2048 : 0, (I - AC) * 1024, 0);
+            }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        stage(IntC<X>{}, [&](int m) { read_gap(IntC<X ^ 1>{}, nxt, m); });
+        ++t;
+        return true;
+    };
+    auto finish = [&](auto u) {                               // the last stages
+        constexpr int V = decltype(u)::value, X = V & 1, S0 = V % NS, S1 = (V + 1) % NS;
         const uint8_t *nxt = lds + S1 * C::kStage;
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < nst) {
             const int y = nst - 2 - t;                        // stages behind t + 1 on their way
-            if (AREG) wait_vmcnt<0>();
-            else if (y >= NS - 2) wait_vmcnt<(NS - 2) * NC>();
+            if (y >= NS - 2) wait_vmcnt<(NS - 2) * NC>();
             else if (y == 1) wait_vmcnt<NC>();
             else if (NS > 4 && y == 2) wait_vmcnt<2 * NC>();
             else if (NS > 5 && y == 3) wait_vmcnt<3 * NC>();
             else wait_vmcnt<0>();
-            if constexpr (!AREG) {
-                if (fixes && t + 1 == nst - 1) apply_fix(S1);
-                if (ROWS) own_rows(t + 1, S1);
-            }
+            if (fixes && t + 1 == nst - 1) apply_fix(S1);
+            if (ROWS) own_rows(t + 1, S1);
             __builtin_amdgcn_s_waitcnt(0xc07f);
             __builtin_amdgcn_s_barrier();
-            if constexpr (AREG) {
-                if (t + 2 < nst) write_a(IntC<P2>{}, S2, t + 2);
-                load_a(IntC<P2>{}, t + 2 + AD);
-            }
             if (t + NS < nst) static_for<0, NC>([&](auto n) { dma1(n, t + NS, S0); });
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -339,10 +374,17 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
     constexpr int U1 = AREG && NS % AD != 0 ? NS * AD : NS, U = U1 % 2 == 0 ? U1 : 2 * U1, AHEAD = AREG && AD + 2 > NS ? AD + 2 : NS;
     static_assert(U % NS == 0 && U % 2 == 0 && (!AREG || U % AD == 0), "static places and sets");
     for (; t + U - 1 + AHEAD < nst - 1; t += U) static_for<0, U>(steady);
-    while (t < nst) {
-        static_for<0, U>([&](auto u) {
-            if (t < nst) finish(u);
-        });
+    if constexpr (AREG) {
+        while (all_of<0, U>(finish_areg)) {}
+        if (nst == 0) {                                       // (a grouped member of K = 0)
+        } else if ((t & 1) == 0) stage(IntC<0>{}, [](int) {});
+        else stage(IntC<1>{}, [](int) {});
+    } else {
+        while (t < nst) {
+            static_for<0, U>([&](auto u) {
+                if (t < nst) finish(u);
+            });
+        }
     }
 
     // ---- epilogue ----
@@ -489,6 +531,30 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
             }
         }
     }
+}
+
+template <class C, bool REQUANT, bool ROWS, bool AREG>
+__global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_kernel(const GemmParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    mid_body<C, REQUANT, ROWS, AREG>(p, blockIdx.x, lds);
+}
+
+// Grouped launches (see GroupParams): the panels of the skinny members, four wavefronts each, then the tiles of the others, whose rows
+// have any alignment.  Bound by latency: a member of few tiles and a long K lasts as long as its stages, and the short ones are a prologue and an
+// epilogue each, so four workgroups share a unit (64 x 64 tiles, 32 KiB, 128 registers).  The batch of 64 odd shapes (M, N to 4096, K to
+// 3183; 1911 tiles and the panels) in a graph: 19.9 us with the tiles staged through registers, 16.5 here; 128 columns per tile 17.8, two workgroups per
+// unit 17.4, six stages and register sets 18.1.
+template <class C>
+__global__ __launch_bounds__(256, C::kPerCu) void gemm_group_mid_kernel(const GroupParams g)
+{
+    static_assert(C::kThreads == 256, "the skinny members' four wavefronts");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int q = group_find(g, blockIdx.x);
+    const GemmParams p = group_member_params<C::BM, C::BN>(g.prob[q], g.nxcd);
+    const int unit = blockIdx.x - g.unit_start[q];
+    if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, 4 * ((p.M + 7) / 8), (int *)lds);
+    else mid_body<C, false, true, true>(p, unit, lds);
 }
 
 }  // namespace ngemm

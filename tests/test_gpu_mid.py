@@ -83,3 +83,41 @@ def test_other_operands_and_per_column_terms(runner, K, pitch):
         assert np.array_equal(D.cpu().numpy(), oracle.gemm_u8s8u8_requant_channel(Au, Bs, 128, 0, scale, zc, zb_vec=zbv, bias=bias, relu=relu))
     ng.ngemm_packed_b_free(hs)
     ng.ngemm_packed_b_free(hu)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_grouped_tiles(runner, launches, wide):  # noqa: F811
+    """Tiled members of a batch: K of none, one, two ... stages of 64 bytes to well past the ring and its unrolled loop, with and without a
+    last chunk that ends inside 16 bytes, edges of the 64 x 64 tiles, rows of any alignment, a skinny member in front; one member
+    whose rows are too far apart for 32-bit offsets takes the whole group to the kernel with 64-bit addresses."""
+    import torch
+    import paper_1910_00178_amd as ng
+    rng = np.random.default_rng(31)
+    ks = [0, 1, 15, 16, 17, 63, 64, 65, 80, 127, 128, 129, 191, 257, 320, 383, 449, 513, 640, 705, 769, 1000, 1100, 1663]
+    shapes = [((33, 64, 65, 129)[i % 4], (1, 31, 64, 65, 130)[i % 5], k, k + (0, 3, 16)[i % 3]) for i, k in enumerate(ks)]
+    shapes += [(7, 100, 700, 701)] + ([(35, 40, 16, (1 << 24) + 256 * 1024)] if wide else [])
+    items, want, outs, keep, handles = [], [], [], [], []
+    for t, (M, N, K, pitch) in enumerate(shapes):
+        A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(N, K), dtype=np.int8)
+        za, zb = int(rng.integers(0, 256)), 0 if t % 3 == 0 else int(rng.integers(-128, 128))
+        h, packed = runner.pack(B)
+        flat = torch.empty(max(16, (M - 1) * pitch + K), dtype=torch.uint8, device="cuda")          # ends with the last row
+        if K:
+            flat.as_strided((M, K), (pitch, 1)).copy_(torch.from_numpy(A))
+        C = torch.full((M + 1, N + 1), -9, dtype=torch.int32, device="cuda")
+        items.append((M, flat, max(pitch, 1), za, zb, h, C, N + 1))
+        want.append(oracle.gemm_u8s8s32(A, B, za, zb))
+        outs.append(C)
+        keep += [flat, packed]
+        handles.append(h)
+    problems = ng.make_problems(items)
+    got = launches(lambda stream: ng.ngemm_run_batched_u8s8s32(runner.ctx, problems, None, 0, stream.cuda_stream))
+    assert [name.split("<")[0] for name, _ in got] == ["gemm_group_kernel" if wide else "gemm_group_mid_kernel"], got
+    ng.ngemm_run_batched_u8s8s32(runner.ctx, problems)
+    torch.cuda.synchronize()
+    for shape, C, w in zip(shapes, outs, want):
+        c = C.cpu().numpy()
+        assert np.array_equal(c[:-1, :-1], w), shape
+        assert (c[-1] == -9).all() and (c[:, -1] == -9).all(), shape
+    for h in handles:
+        ng.ngemm_packed_b_free(h)
