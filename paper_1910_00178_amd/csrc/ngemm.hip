@@ -1120,7 +1120,9 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
                                 X64Cfg::kLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void *)gemm_tile_x64_kernel<false, true, true, 6>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 X64Cfg::kLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void *)gemm_s16_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void *)gemm_s16_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                S16Cfg::kLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void *)gemm_s16_tile_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 S16Cfg::kLdsBytes) != hipSuccess ||
             allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess ||
             allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_nt<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess ||
@@ -1516,14 +1518,17 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     } else {
         p.tiles_m = (int)((M + 127) / 128);
         p.tiles_n = (int)((B->N + 127) / 128);
-        int32_t *rs = (int32_t *)workspace_dev;
-        hipLaunchKernelGGL(rowsum_s16_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, A_dev, lda, (int)M,
-                           (int)B->K, rs);
-        if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
-        p.rowsum = rs;
-        const int64_t ntiles = (int64_t)p.tiles_m * p.tiles_n;
-        hipLaunchKernelGGL(gemm_s16_tile_kernel, dim3((unsigned)(ntiles < budget ? ntiles : budget)), dim3(256),
-                           S16Cfg::kLdsBytes, st, p);
+        const int64_t ntiles = (int64_t)p.tiles_m * p.tiles_n, grid = ntiles < budget ? ntiles : budget;
+        // the row sums: in the kernel while that costs less (55 ns per stage) than a launch of their own (2.5 us and more)
+        if ((ntiles + grid - 1) / grid * ((B->K + 63) / 64) <= 40) {
+            hipLaunchKernelGGL(gemm_s16_tile_kernel<true>, dim3((unsigned)grid), dim3(256), S16Cfg::kLdsBytes, st, p);
+        } else {
+            int32_t *rs = (int32_t *)workspace_dev;
+            hipLaunchKernelGGL(rowsum_s16_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, A_dev, lda, (int)M, (int)B->K, rs);
+            if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
+            p.rowsum = rs;
+            hipLaunchKernelGGL(gemm_s16_tile_kernel<false>, dim3((unsigned)grid), dim3(256), S16Cfg::kLdsBytes, st, p);
+        }
         e = hipGetLastError();
     }
     return e == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;

@@ -2403,6 +2403,10 @@ struct S16Cfg {
 // plane of B the half (l / 16) % 2 of slice l / 32.
 // With the packed operand first, lane l of a result block holds, for row l % 16 of A's block, the four
 // consecutive columns 4 (l / 16) .. + 3 of B's block.
+// SUMS: the sums of A's rows are formed here, from the byte planes in the gaps between the matrix ops, instead of being read from p.rowsum:
+// saves a launch (3136 x 964 x 192 12.9 us with it, 11.2 without; 3668 x 597 x 320 15.2 / 12.9) but costs about 55 ns per stage
+// (4096^3, 256 stages per unit, 213 / 221).
+template <bool SUMS>
 __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 {
     using Cfg = S16Cfg;
@@ -2478,6 +2482,11 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
             ah[i][wd] = (int)__builtin_amdgcn_perm(hi, lo, 0x07050301u);
             al[i][wd] = (int)(__builtin_amdgcn_perm(hi, lo, 0x06040200u) ^ 0x80808080u);
         };
+        // Row sums, for the zero-point of B: of the unsigned low bytes plus 256 times the high ones (128 up), by lane for row l % 16 of
+        // each block and a quarter of the elements; sums of absolute differences from zero.
+        uint32_t rs[4] = {0u, 0u, 0u, 0u};
+        auto sum_low = [&](int i, int wd) { rs[i] = __builtin_amdgcn_sad_u8((uint32_t)al[i][wd] ^ 0x80808080u, 0u, rs[i]); };
+        auto sum_high = [&](int i, int wd) { rs[i] += __builtin_amdgcn_sad_u8((uint32_t)ah[i][wd] ^ 0x80808080u, 0u, 0u) << 8; };
         // matrix op m (0..63) of a stage: row block m / 16, product (m / 4) % 4, column block m % 4.
         // Packed operand first.  FIRST: the stage that starts the sums (a literal zero: accumulators
         // zeroed ahead of the loop make the compiler shuffle them between registers inside it).
@@ -2524,6 +2533,10 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
                     }
                     if ((m & 15) >= 4 && (m & 15) < 8 && m < 48) split_word((m >> 4) + 1, m & 3);
                     if (m >= 56 && m < 60) split_word(0, m & 3);
+                    if (SUMS && (m >= 48 ? m < 56 : (m & 8) != 0)) {
+                        if (m & 1) sum_high(m >> 4, (m >> 1) & 3);
+                        else sum_low(m >> 4, (m >> 1) & 3);
+                    }
                     // reads 0..5 (A's blocks 0..2), 8, 9 (B's block 0), 6, 7 (A's block 3, whose old chunks
                     // the gaps 36..39 consume), 10..15
                     if (m >= 32 && m < 48) read_one(other, buf_n, m < 38 ? m - 32 : m < 40 ? m - 30 : m < 42 ? m - 34 : m - 32);
@@ -2564,7 +2577,13 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int wd = 0; wd < 4; ++wd) split_word(i, wd);
+                for (int wd = 0; wd < 4; ++wd) {
+                    split_word(i, wd);
+                    if (SUMS) {
+                        sum_low(i, wd);
+                        sum_high(i, wd);
+                    }
+                }
 #pragma unroll
             for (int m = 0; m < 64; ++m) mma(IntC<0>{}, IntC<0>{}, m);
         }
@@ -2592,7 +2611,15 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
         uint32_t row_terms[4];                           // all four first: independent loads
 #pragma unroll
         for (int i = 0; i < 4; ++i) row_terms[i] = p.kconst;
-        if (p.rowsum) {                                  // rows past M read row M - 1 and are never stored
+        if constexpr (SUMS) {                            // (zeros behind the end of K: 0 as low bytes, 128 as high ones, like every element)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t sum = rs[i];
+                sum += (uint32_t)__shfl_xor((int)sum, 16, 64);
+                sum += (uint32_t)__shfl_xor((int)sum, 32, 64);
+                row_terms[i] -= p.zb * (sum - 256u * 128u * 64u * (uint32_t)nstages - 128u * (uint32_t)p.K);
+            }
+        } else if (p.rowsum) {                           // rows past M read row M - 1 and are never stored
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = m0 + wm * 64 + 16 * i + ft;

@@ -121,3 +121,33 @@ def test_grouped_tiles(runner, launches, wide):  # noqa: F811
         assert (c[-1] == -9).all() and (c[:, -1] == -9).all(), shape
     for h in handles:
         ng.ngemm_packed_b_free(h)
+
+
+@pytest.mark.parametrize("M,N,K,in_kernel", [(1541, 1500, 128, True), (1665, 1409, 133, True), (1537, 1537, 191, True), (2047, 2050, 192, True),
+                                             (1600, 1600, 333, True), (1541, 1500, 2560, True), (1541, 1500, 2561, False), (4097, 2049, 1344, False)])
+def test_s16_row_sums(ctx, launches, M, N, K, in_kernel):  # noqa: F811
+    """The 128 x 128 kernel of 16-bit operands forms the row sums itself while a unit works through 40 stages of 64 elements at most: K of an even and an
+    odd number of stages, with a partial one, several tiles per workgroup, extreme values; a launch of their own beyond."""
+    import torch
+    import paper_1910_00178_amd as ng
+    rng = np.random.default_rng(M + K)
+    A, B = (rng.integers(-32768, 32768, size=(n, K)).astype(np.int16) for n in (M, N))
+    A[::3], A[1::9] = -32768, 32767
+    lda = (K + 7) // 8 * 8
+    Ah = np.full((M, lda), 7777, np.int16)
+    Ah[:, :K] = A
+    Ad, Bd = torch.from_numpy(Ah.reshape(-1)[:(M - 1) * lda + K].copy()).cuda(), torch.from_numpy(B).cuda()
+    nb, wsb = ng.ngemm_packed_b_bytes_s16(K, N), ng.ngemm_workspace_bytes(M, N, K)
+    packed, ws = torch.empty(nb, dtype=torch.uint8, device="cuda"), torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    h = ng.ngemm_pack_b_s16(ctx, K, N, Bd, K, packed, nb)
+    C = torch.full((M + 1, N + 3), -7, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    got = launches(lambda st: ng.ngemm_run_s16s16s32(ctx, M, Ad, lda, -321, h, 20000, C, N + 3, ws, wsb, st))
+    assert [name for name, _ in got] == (["gemm_s16_tile_kernel<true>"] if in_kernel else ["rowsum_s16_kernel", "gemm_s16_tile_kernel<false>"]), got
+    ng.ngemm_run_s16s16s32(ctx, M, Ad, lda, -321, h, 20000, C, N + 3, ws, wsb)
+    got = C.cpu().numpy()
+    ng.ngemm_packed_b_free(h)
+    # products below 2^33, sums below 2^45: exact in binary64, then the low 32 bits
+    want = ((A.astype(np.float64) + 321) @ (B.astype(np.float64) - 20000).T).astype(np.int64).astype(np.int32)
+    assert np.array_equal(got[:M, :N], want)
+    assert (got[M:] == -7).all() and (got[:, N:] == -7).all()
