@@ -789,7 +789,7 @@ int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool alig
         const int64_t t = tiles(t256 ? 256 : 192, 256), rounds = (t + cus - 1) / cus, odd = K % 128 != 0 ? rounds : 0;
         const int64_t large = t256 ? -2142 + rounds * (324 * nst + 12043) + t * (244 * nst + 4397) / cus + (rows ? 6211 : 0) + 5828 * odd
                                    : 3533 + rounds * (283 * nst + 5802) + t * (249 * nst + 3410) / cus + (rows ? 5391 : 0) + 2809 * odd;
-        if (least * 100 > large * 97) return 0;
+        if (least * 100 > large * 93) return 0;
     }
     return best;
 }
