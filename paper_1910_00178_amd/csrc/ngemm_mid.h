@@ -21,7 +21,7 @@
 // the shift of A as an exclusive or on LDS (29 cycles each: slower), priorities for one of two workgroups (nothing).
 // us in a graph, before / here: 2048 x 4096 x 1024 with a zero-point 17.8 / 15.9 (128 x 128 tiles of this kernel: 1.1 POP/s, half of the time the
 // launch and 32 MiB of C), 2048 x 3072 x 1536 18.5 / 15.9, 1024 x 3072 x 768 u8 8.9 / 8.0, 1088 x 1413 x 2112 z 12.5 / 11.0; unaligned rows:
-// 2047 x 3071 x 1537 z 23.5 / 22.1, 2368 x 4629 x 1343 37.9 / 33.
+// 2047 x 3071 x 1537 z 23.5 / 21.4 (22.1 while the last stages waited for all loads), 2368 x 4629 x 1343 37.9 / 33.
 #pragma once
 #include "ngemm_kernels.h"
 
