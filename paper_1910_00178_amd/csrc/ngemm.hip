@@ -777,6 +777,7 @@ int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool alig
     const int64_t nst = (K + 63) / 64;
     for (const Form &f : forms[aligned ? 0 : 1]) {
         const int64_t t = tiles(f.bm, f.bn), whole = t / (cus * f.per_cu), rest = t - whole * cus * f.per_cu;
+        if (t * (f.id == 5 ? 512 : 256) >= (1ll << 32)) continue;         // (the runtime takes less than 2^32 threads in a launch)
         const int64_t n = whole * f.per_cu + (rest + cus - 1) / cus;
         const int64_t cost = f.fixed + n * (f.stage * nst + f.tile) + t * (f.flow * nst + f.out) / cus + (n == 1 ? f.lone_stage * nst + f.lone : 0);
         if (best == 0 || cost < least) {

@@ -49,6 +49,17 @@ def test_forms_against_the_oracle(runner, ctx, launches, case):  # noqa: F811
     ng.ngemm_packed_b_free(h)
 
 
+def test_more_tiles_than_a_launch_takes(ctx, launches):  # noqa: F811
+    """A launch takes less than 2^32 threads: a form with 2^24 tiles (128 x 128, here of 184 GB of u8 beside 46 GB of A) is not launched.
+    Captured only: the addresses are those of small buffers that nothing reads."""
+    import paper_1910_00178_amd as ng
+    M, N, K = 715827883, 257, 64
+    p = Problem(ctx, 64, N, K)
+    got = launches(lambda st: ng.ngemm_run_u8s8u8_requant(ctx, M, p.A, K, 7, p.h, 0, 0.01, 3, p.C, N, p.ws, 0, st))
+    assert len(got) == 1 and got[0][1] * (512 if W256 in got[0][0] else 256) < 1 << 32, got
+    ng.ngemm_packed_b_free(p.h)
+
+
 @pytest.mark.parametrize("K,pitch", [(770, 784), (773, 773)])
 def test_other_operands_and_per_column_terms(runner, K, pitch):
     """Signed A and unsigned B with zero-points, a zero-point, bias and scale per column, a zero-point of C beyond binary32."""
