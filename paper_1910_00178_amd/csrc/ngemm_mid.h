@@ -466,10 +466,19 @@ __device__ __forceinline__ void mid_body(const GemmParams &p, int tile, uint8_t 
             if (q < TOTAL && row < p.M && col < p.N) {
                 if (col + 16 <= p.N) {
                     __builtin_memcpy(dst, &o[k], 16);
-                } else {
+                } else {                                      // the last piece of a row: words, then bytes (u8 with a zero-point, bytes only / so:
+                                                              // 5120 x 3901 x 192 22.5 / 20.4 us, 113945 x 29 x 262 22.0 / 19.6)
 #pragma unroll
-                    for (int b = 0; b < 16; ++b)
-                        if (col + b < p.N) dst[b] = (uint8_t)((uint32_t)o[k][b >> 2] >> (8 * (b & 3)));
+                    for (int w = 0; w < 4; ++w) {
+                        const uint32_t v = (uint32_t)o[k][w];
+                        if (col + 4 * w + 4 <= p.N) {
+                            __builtin_memcpy(dst + 4 * w, &v, 4);
+                        } else {
+#pragma unroll
+                            for (int b = 0; b < 3; ++b)
+                                if (col + 4 * w + b < p.N) dst[4 * w + b] = (uint8_t)(v >> (8 * b));
+                        }
+                    }
                 }
             }
         }

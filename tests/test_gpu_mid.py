@@ -49,6 +49,23 @@ def test_forms_against_the_oracle(runner, ctx, launches, case):  # noqa: F811
     ng.ngemm_packed_b_free(h)
 
 
+def test_u8_rows_that_end_inside_16_bytes(runner, ctx, launches):  # noqa: F811
+    """u8 rows of every length modulo 16, to the byte: what follows a row keeps its contents."""
+    import paper_1910_00178_amd as ng
+    M, K, top = 1500, 67, 2336
+    rng = np.random.default_rng(16)
+    A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(top, K), dtype=np.int8)
+    want = oracle.requant_s32u8(oracle.gemm_u8s8s32(A, B, 9, 5), 0.0015, 128)
+    for N in range(top - 16, top + 1):
+        p = Problem(ctx, M, N, K)
+        got = launches(p.run_u8(5))
+        assert len(got) == 1 and got[0][0].startswith("gemm_mid_kernel<"), got
+        ng.ngemm_packed_b_free(p.h)
+        h, _ = runner.pack(B[:N])
+        assert np.array_equal(runner.run(A, h, N, za=9, zb=5, scale=0.0015, zc=128, lda_pad=13, ldc_pad=1), want[:, :N]), N
+        ng.ngemm_packed_b_free(h)
+
+
 def test_more_tiles_than_a_launch_takes(ctx, launches):  # noqa: F811
     """A launch takes less than 2^32 threads: a form with 2^24 tiles (128 x 128, here of 184 GB of u8 beside 46 GB of A) is not launched.
     Captured only: the addresses are those of small buffers that nothing reads."""
