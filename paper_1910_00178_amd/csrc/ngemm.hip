@@ -737,19 +737,66 @@ hipError_t allow_big_lds_mid()
     return hipSuccess;
 }
 
+// Where another kernel stays although the lines of mid_form admit a problem.  80000 shapes were drawn around those lines and beyond the sizes that its
+// model was fitted to (N from 16, M from 33); us before / with gemm_mid_kernel, z: with a zero-point of B, whose row sums cost its forms more.
+// In the place of 64 x 64 tiles (t of them per unit):
+//  * N <= 64, a single column of them: never (28544 x 33 x 960 9.2 / 11.8, 16512 x 39 x 3328 16.6 / 18.8);
+//  * M <= 64, which leaves half of a 128-row tile empty: from a K on that grows with t, longer with z and where K is whole stages, which the 64 x 64
+//    tiles do best (50 x 20272 x 2421, t = 1.2, 14.2 / 12.4; 36 x 27520 x 2176 z, t = 1.7, 13.2 / 14.6; unaligned 47 x 16896 x 1771 14.7 / 11.2,
+//    47 x 45376 x 891 z 11.2 / 12.8); beyond t = 2 without z u8 outputs only (1.03-1.07 x, int32 0.93-1.01 x);
+//  * z, t <= 2: beyond K = 1536 (2432 x 512 x 2112 12.3 / 11.5; K = 1536 itself 0.95 x);
+//  * z, t <= 3: also from 769 on if K is no whole number of stages (1.05 x) or u8 rows are whole tiles (1024 x 2560 x 832 10.0 / 9.1); else
+//    2086 x 1359 x 768 10.1 / 12.0, 642 x 3659 x 960 10.4 / 11.1;
+//  * z, t > 3: not for 256 < K <= 640 and columns that share 64-byte lines of C (0.90-1.02 x), nor K = 512 (0.96 x; 1757 x 1881 x 512 9.8 / 11.2); the
+//    rest 1.02-1.15 x (1885 x 1856 x 283 7.9 / 7.6, 2368 x 1425 x 832 13.0 / 11.8).
+// In the place of 128 x 128 tiles:
+//  * narrow u8 outputs, for which their epilogue skips the columns past N: not N <= 32 and, with z, N < 64, up to K = 1536 (38465 x 19 x 128 6.5 / 7.6,
+//    55276 x 37 x 64 z 7.1 / 7.7; 63872 x 49 x 64 without z 7.8 / 7.2);
+//  * unaligned rows, K < 1024: not N <= 64 nor, with z and up to three tiles per unit, N <= 128, but u8 rows of whole pieces (64128 x 40 x 98 7.9 / 9.3, 48289 x 128 x 397 z
+//    12.2 / 14.9; 60416 x 64 x 108 u8 8.3 / 7.3; from 1024 on 67499 x 64 x 2653 82 / 73);
+//  * z, int32 rows of whole lines, four to five such tiles per unit, whole stages: their third round of two is short (3826 x 5056 x 192 19.4 / 22.1).
+// In the place of 192 x 256 tiles: int32 outputs of N <= 128 without z, up to 1.5 x 128 x 128 tiles per unit and K > 2048 are a stream of A
+// (33280 x 128 x 3392 39.7 / 52.0; beyond 1.5 1.18 x).
+bool mid_stays_out(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, bool requant, int64_t cus)
+{
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const bool whole = K % 64 == 0;
+    if (kernel == NGEMM_KERNEL_TILE_64) {
+        if (N <= 64) return true;
+        if (M <= 64) {
+            if (!aligned) return rows ? K <= (t64 * 2 > cus * 3 ? 1536 : 1024) : t64 > 2 * cus && K <= 1024;
+            if (rows) return K <= (t64 * 2 > cus * 3 ? 2816 : t64 * 4 > cus * 5 ? 2304 : 1536);
+            if (t64 > 2 * cus) return !(requant && (!whole || N % 16 == 0));
+            return K <= (!whole ? 768 : t64 * 2 > cus * 3 ? 2304 : 1024);
+        }
+        if (!rows) return false;
+        if (t64 > 3 * cus) return (K > 256 && K <= 640 && N % 16 != 0) || K == 512;
+        return K <= 1536 && !(t64 > 2 * cus && K > 768 && (!whole || (requant && N % 64 == 0)));
+    }
+    if (kernel == NGEMM_KERNEL_TILE_128) {
+        if (requant && K < 1536 && (N <= 32 || (rows && N < 64))) return true;
+        if (!aligned) return K < 1024 && (N <= 64 || (rows && N <= 128 && t128 <= 3 * cus)) && !(requant && N % 64 == 0);
+        return rows && !requant && whole && K > 64 && N % 16 == 0 && t128 > 4 * cus && t128 <= 5 * cus;
+    }
+    return kernel == NGEMM_KERNEL_TILE_192 && !rows && !requant && N <= 128 && K > 2048 && t128 * 2 <= 3 * cus;
+}
+
 // The form of gemm_mid_kernel that serves an 8-bit problem in the place of the tiled kernels, or 0.  1420 shapes were timed with every
-// form and with the kernels before (M, N, K up to 8192, odd sizes among them, aligned and unaligned rows, int32 and u8 outputs, with and
-// without a zero-point of B):
+// form and with the kernels before (M from 64, N from 256, K up to 8192, odd sizes among them, aligned and unaligned rows, int32 and u8 outputs, with
+// and without a zero-point of B):
 //  * outputs of more than 0.55 x 128 x 128 tiles per compute unit: 1.17 x faster on average, unaligned rows 1.15 x; a K below 768 only from 0.8
 //    tiles per unit on (3840 x 640 x 704, 150 tiles, 7.6 us before, 8.6 here; at 205 .. 256 tiles 1.08-1.16 x);
 //  * from one 64 x 64 tile per unit on with a long K where the kernels before pay extra: row sums, u8 outputs, K of no whole stages,
-//    unaligned rows (1.1 x; 1088 x 1413 x 2112 z 12.5 / 11.0).  Plain int32 problems there are a tie or a loss.
+//    unaligned rows (1.1 x; 1088 x 1413 x 2112 z 12.5 / 11.0).  Plain int32 problems there are a tie or a loss;
+//  * less what mid_stays_out keeps.
 // Which form: the least time by a model with constants (ns) that were fitted to those shapes; its choices are within 1.5 % of the best form on
-// average.  n tiles that a unit works through (rounds of resident workgroups counted whole) cost `stage` per stage and `tile`
-// each, all the tiles together their share of the chip's (`flow`, `out`), a workgroup alone on its unit `lone_stage`, `lone` on top.
+// average, in all four combinations of output type and zero-point.  n tiles that a unit works through (rounds of resident workgroups counted whole)
+// cost `stage` per stage and `tile` each, all the tiles together their share of the chip's (`flow`, `out`), a workgroup alone on its unit
+// `lone_stage`, `lone` on top.
 // `kernel`: what would run otherwise; the 256- and 192-row tiles, which read half the bytes per matrix op but take a row-sum launch and
 // what is left behind an even number of stages apart, stay by a model of the same kind where it says that they are faster (4736 x 3072 x
-// 768 19.2 us against 21.7, 4096 x 4096 x 1024 25.4 / 27.2, 2662 x 3521 x 2816 z 34.9 / 39.3).
+// 768 19.2 us against 21.7, 4096 x 4096 x 1024 25.4 / 27.2, 2662 x 3521 x 2816 z 34.9 / 39.3).  NGEMM_KERNEL_AUTO: a measurement decides, not a comparison
+// with what would run.
 int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
 {
     if (M <= kSkinnyMaxM || K < 64 || budget < cus) return 0;          // (a workgroup per tile: not under a caller's cap)
@@ -757,6 +804,7 @@ int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool alig
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const bool plain = aligned && !rows && !requant && K % 64 == 0;
     if (!(tiles(128, 128) * 20 > cus * 11 && (K >= 768 || tiles(128, 128) * 5 > cus * 4)) && !(!plain && tiles(64, 64) > cus && K >= 1536)) return 0;
+    if (mid_stays_out(kernel, M, N, K, aligned, rows, requant, cus)) return 0;
     struct Form {
         int id, bm, bn, per_cu;
         int64_t fixed, stage, tile, flow, out, lone_stage, lone;
@@ -848,6 +896,7 @@ struct RunArgs {
 struct Route {
     int kernel;
     bool wavek;
+    bool measured = false;    // by the tuner: the rules against `kernel` do not apply
 };
 
 ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
@@ -877,8 +926,9 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
                 if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0 ||
-                                mid_form(small, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0))
-                    r = Route{small, true};
+                                mid_form(NGEMM_KERNEL_AUTO, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus,
+                                         workgroup_budget(ctx)) != 0))
+                    r = Route{small, true, true};
             }
         if (r.kernel == NGEMM_KERNEL_AUTO) r = Route{choose_kernel(ctx, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.requant), true};
     }
@@ -957,7 +1007,8 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
             return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
-        const int mid = kernel == NGEMM_KERNEL_SPLIT_K ? 0 : mid_form(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
+        const int mid = kernel == NGEMM_KERNEL_SPLIT_K ? 0 : mid_form(route.measured ? NGEMM_KERNEL_AUTO : kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed,
+                                                                      a.requant, device_cus, num_cus);
         if (mid != 0) return launch_mid_form(mid, p, a.requant, rows_needed, dma_ok, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
     }
     // at most one tile per compute unit and a K worth pipelining: the long-pipeline variants
@@ -1182,7 +1233,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
     // the last one: what the automatic choice puts in the place of the kernel for small outputs (gemm_wavek_kernel, gemm_mid_kernel)
     const Route candidates[7] = {{NGEMM_KERNEL_SKINNY, false}, {NGEMM_KERNEL_TILE_64, false}, {NGEMM_KERNEL_TILE_128, false},
                                  {NGEMM_KERNEL_TILE_256, false}, {NGEMM_KERNEL_SPLIT_K, false}, {NGEMM_KERNEL_TILE_192, false},
-                                 {small, true}};
+                                 {small, true, true}};
     int best = NGEMM_KERNEL_AUTO;
     bool best_wavek = false;
     float best_ms = 0.0f;
@@ -1199,7 +1250,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
         }
         const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
         if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, cus, workgroup_budget(ctx)) == 0 &&
-            mid_form(k, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
+            mid_form(NGEMM_KERNEL_AUTO, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
         const int warm = 5, reps = 50, rounds = 3;

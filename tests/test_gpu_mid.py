@@ -66,6 +66,34 @@ def test_u8_rows_that_end_inside_16_bytes(runner, ctx, launches):  # noqa: F811
         ng.ngemm_packed_b_free(h)
 
 
+# (M, N, K, pitch of A: 0 = whole 16 bytes, u8 output, zero-point of B, kernel): each line of the rule that gives a call to gemm_mid_kernel, on both sides
+BORDERS = [
+    (28544, 64, 960, 0, False, 0, "gemm_tile_dma_kernel<64, 64,"), (28544, 65, 960, 0, False, 0, "gemm_mid"),
+    (2112, 1300, 768, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"), (2112, 1300, 768, 0, False, 0, "gemm_mid"),
+    (2112, 1300, 1000, 0, False, 3, "gemm_mid"), (1024, 2560, 832, 0, True, 3, "gemm_mid"), (1024, 2561, 832, 0, True, 3, "gemm_tile_dma_kernel<64, 64,"),
+    (1024, 3072, 768, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"), (1757, 1881, 512, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"),
+    (1757, 1881, 641, 0, False, 3, "gemm_mid"), (1757, 1881, 512, 0, False, 0, "gemm_mid"),
+    (1100, 1300, 1536, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"), (1100, 1300, 1537, 0, False, 3, "gemm_mid"),
+    (47, 32253, 960, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"), (64, 17000, 1100, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"),
+    (64, 17000, 1600, 0, False, 3, "gemm_mid"), (65, 8500, 1600, 0, False, 3, "gemm_mid"), (47, 45376, 891, 891, False, 3, "gemm_tile_kernel<64, 64,"),
+    (47, 17000, 1771, 1771, False, 3, "gemm_mid"), (38465, 19, 128, 0, True, 0, "gemm_tile_dma_kernel<128, 128,"),
+    (38465, 49, 128, 0, True, 0, "gemm_mid"), (38465, 49, 128, 0, True, 3, "gemm_tile_dma_kernel<128, 128,"), (38465, 19, 128, 0, False, 0, "gemm_mid"),
+    (48289, 128, 397, 397, False, 3, "gemm_tile_kernel<128, 128,"), (48289, 129, 397, 397, False, 3, "gemm_mid"),
+    (3826, 5056, 192, 0, False, 3, "gemm_tile_dma_kernel<128, 128,"), (3826, 5057, 192, 0, False, 3, "gemm_mid"),
+    (33280, 128, 3392, 0, False, 0, "gemm_tile_x64_kernel<"), (33280, 128, 3392, 0, False, 3, "gemm_mid"),
+]
+
+
+@pytest.mark.parametrize("case", BORDERS, ids=str)
+def test_which_calls_the_kernel_serves(ctx, launches, case):  # noqa: F811
+    import paper_1910_00178_amd as ng
+    M, N, K, pitch, u8, zb, want = case
+    p = Problem(ctx, M, N, K, pitch or None)
+    got = launches(p.run_u8(zb) if u8 else p.run(zb))
+    assert got[-1][0].startswith(want), got
+    ng.ngemm_packed_b_free(p.h)
+
+
 def test_more_tiles_than_a_launch_takes(ctx, launches):  # noqa: F811
     """A launch takes less than 2^32 threads: a form with 2^24 tiles (128 x 128, here of 184 GB of u8 beside 46 GB of A) is not launched.
     Captured only: the addresses are those of small buffers that nothing reads."""
