@@ -179,6 +179,27 @@ def test_grouped_tiles(runner, launches, wide):  # noqa: F811
         ng.ngemm_packed_b_free(h)
 
 
+@pytest.mark.parametrize("shapes,want", [
+    ([(100, 200, 640)], "gemm_group_kernel"), ([(100, 200, 192)], "gemm_group_mid_kernel"), ([(100, 200, 1537)], "gemm_group_mid_kernel"),
+    ([(64, 64, 700)] * 30 + [(16, 500, 3000)], "gemm_group_kernel"), ([(64, 64, 700)] * 30 + [(64, 64, 1600)], "gemm_group_mid_kernel"),
+    ([(1024, 1024, 1024)], "gemm_group_kernel"), ([(1024, 1024, 1025)], "gemm_group_mid_kernel"), ([(1024, 1025, 1024)], "gemm_group_mid_kernel")], ids=str)
+def test_grouped_tiles_of_few_short_chains(runner, launches, shapes, want):  # noqa: F811
+    import torch
+    import paper_1910_00178_amd as ng
+    items, keep, handles = [], [], []
+    for M, N, K in shapes:
+        A, C = torch.zeros((M, K), dtype=torch.uint8, device="cuda"), torch.empty((M, N), dtype=torch.int32, device="cuda")
+        h, packed = runner.pack(np.zeros((N, K), np.int8))
+        items.append((M, A, K, 7, 3, h, C, N))
+        keep += [A, C, packed]
+        handles.append(h)
+    problems = ng.make_problems(items)
+    got = launches(lambda stream: ng.ngemm_run_batched_u8s8s32(runner.ctx, problems, None, 0, stream.cuda_stream))
+    assert [name.split("<")[0] for name, _ in got] == [want], got
+    for h in handles:
+        ng.ngemm_packed_b_free(h)
+
+
 @pytest.mark.parametrize("M,N,K,in_kernel", [(1541, 1500, 128, True), (1665, 1409, 133, True), (1537, 1537, 191, True), (2047, 2050, 192, True),
                                              (1600, 1600, 333, True), (1541, 1500, 2560, True), (1541, 1500, 2561, False), (4097, 2049, 1344, False)])
 def test_s16_row_sums(ctx, launches, M, N, K, in_kernel):  # noqa: F811
