@@ -737,48 +737,53 @@ hipError_t allow_big_lds_mid()
     return hipSuccess;
 }
 
-// Where another kernel stays although the lines of mid_form admit a problem.  80000 shapes were drawn around those lines and beyond the sizes that its
-// model was fitted to (N from 16, M from 33); us before / with gemm_mid_kernel, z: with a zero-point of B, whose row sums cost its forms more.
+// Where another kernel stays although the lines of mid_form admit a problem.  90000 shapes were drawn around those lines and beyond the sizes that its
+// model was fitted to (N from 16, M from 33), 7000 of them with every weight byte from memory as well as from cache; the lines lie where neither
+// loses much.  us before / with gemm_mid_kernel; z: with a zero-point of B, whose row sums cost its forms more.
 // In the place of 64 x 64 tiles (t of them per unit):
 //  * N <= 64, a single column of them: never (28544 x 33 x 960 9.2 / 11.8, 16512 x 39 x 3328 16.6 / 18.8);
-//  * M <= 64, which leaves half of a 128-row tile empty: from a K on that grows with t, longer with z and where K is whole stages, which the 64 x 64
-//    tiles do best (50 x 20272 x 2421, t = 1.2, 14.2 / 12.4; 36 x 27520 x 2176 z, t = 1.7, 13.2 / 14.6; unaligned 47 x 16896 x 1771 14.7 / 11.2,
-//    47 x 45376 x 891 z 11.2 / 12.8); beyond t = 2 without z u8 outputs only (1.03-1.07 x, int32 0.93-1.01 x);
+//  * M <= 64, which leaves half of a 128-row tile empty: from a K on that grows with t and z (without z beyond 768 0.99-1.18 x in cache, 1.09-1.2 x from
+//    memory; with z, t = 1.5 .. 2, K up to 1024 0.89 and 1.03, up to 2304 0.92 and 1.15, beyond 0.99 and 1.14; unaligned 47 x 16896 x 1771
+//    14.7 / 11.2, 47 x 45376 x 891 z 11.2 / 12.8); beyond t = 2 without z u8 outputs only (1.03-1.07 x, int32 0.93-1.01 x);
 //  * z, t <= 2: beyond K = 1536 (2432 x 512 x 2112 12.3 / 11.5; K = 1536 itself 0.95 x);
-//  * z, t <= 3: also from 769 on if K is no whole number of stages (1.05 x) or u8 rows are whole tiles (1024 x 2560 x 832 10.0 / 9.1); else
-//    2086 x 1359 x 768 10.1 / 12.0, 642 x 3659 x 960 10.4 / 11.1;
-//  * z, t > 3: not for 256 < K <= 640 and columns that share 64-byte lines of C (0.90-1.02 x), nor K = 512 (0.96 x; 1757 x 1881 x 512 9.8 / 11.2); the
-//    rest 1.02-1.15 x (1885 x 1856 x 283 7.9 / 7.6, 2368 x 1425 x 832 13.0 / 11.8).
+//  * z, t <= 3: also from 769 on if K is no whole number of stages (1.05 x), u8 rows are whole tiles (1024 x 2560 x 832 10.0 / 9.1) or M <= 256 (in cache
+//    1.0 x, from memory 1.09 x); else 2086 x 1359 x 768 10.1 / 12.0, 642 x 3659 x 960 10.4 / 11.1;
+//  * z, t > 3, M > 256 (from memory 1.18 x): not for 256 < K <= 640 and columns that share 64-byte lines of C (0.90-1.02 x), nor K = 512 (0.96 x;
+//    1757 x 1881 x 512 9.8 / 11.2); the rest 1.02-1.15 x (1885 x 1856 x 283 7.9 / 7.6, 2368 x 1425 x 832 13.0 / 11.8).
 // In the place of 128 x 128 tiles:
 //  * narrow u8 outputs, for which their epilogue skips the columns past N: not N <= 32 and, with z, N < 64, up to K = 1536 (38465 x 19 x 128 6.5 / 7.6,
 //    55276 x 37 x 64 z 7.1 / 7.7; 63872 x 49 x 64 without z 7.8 / 7.2);
-//  * unaligned rows, K < 1024: not N <= 64 nor, with z and up to three tiles per unit, N <= 128, but u8 rows of whole pieces (64128 x 40 x 98 7.9 / 9.3, 48289 x 128 x 397 z
-//    12.2 / 14.9; 60416 x 64 x 108 u8 8.3 / 7.3; from 1024 on 67499 x 64 x 2653 82 / 73);
+//  * unaligned rows, K < 1024: not N <= 64 nor, with z and up to three tiles per unit, N <= 128, but u8 rows of whole pieces (64128 x 40 x 98
+//    7.9 / 9.3, 48289 x 128 x 397 z 12.2 / 14.9; 60416 x 64 x 108 u8 8.3 / 7.3; from 1024 on 67499 x 64 x 2653 82 / 73);
 //  * z, int32 rows of whole lines, four to five such tiles per unit, whole stages: their third round of two is short (3826 x 5056 x 192 19.4 / 22.1).
-// In the place of 192 x 256 tiles: int32 outputs of N <= 128 without z, up to 1.5 x 128 x 128 tiles per unit and K > 2048 are a stream of A
-// (33280 x 128 x 3392 39.7 / 52.0; beyond 1.5 1.18 x).
+// In the place of the larger tiles (t of 128 x 128 per unit):
+//  * 192-row ones, int32 without z, N <= 128, t <= 1.5, K > 2048: a stream of A (33280 x 128 x 3392 39.7 / 52.0; beyond t = 1.5 1.18 x);
+//  * wide short int32 outputs (N >= 8 M), K > 1024, 2 < t <= 3 (192 rows) or, z, 3 < t <= 4 (256 rows): the last round of two tiles per unit is short, and
+//    from memory it waits (320 x 27686 x 1792 z from cache 29.4 / 35.1, from memory 33.1 / 44.4; on average 1.00 and 0.94 x).
 bool mid_stays_out(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, bool requant, int64_t cus)
 {
     const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    const bool whole = K % 64 == 0;
+    const bool whole = K % 64 == 0, above_1_5 = t64 * 2 > cus * 3;
     if (kernel == NGEMM_KERNEL_TILE_64) {
         if (N <= 64) return true;
         if (M <= 64) {
-            if (!aligned) return rows ? K <= (t64 * 2 > cus * 3 ? 1536 : 1024) : t64 > 2 * cus && K <= 1024;
-            if (rows) return K <= (t64 * 2 > cus * 3 ? 2816 : t64 * 4 > cus * 5 ? 2304 : 1536);
-            if (t64 > 2 * cus) return !(requant && (!whole || N % 16 == 0));
-            return K <= (!whole ? 768 : t64 * 2 > cus * 3 ? 2304 : 1024);
+            if (rows) return K <= (aligned ? (above_1_5 ? 2304 : 1536) : above_1_5 ? 1024 : 768);
+            if (t64 <= 2 * cus) return aligned && K <= 768;
+            return aligned ? !(requant && (!whole || N % 16 == 0)) : K <= 1024;
         }
         if (!rows) return false;
-        if (t64 > 3 * cus) return (K > 256 && K <= 640 && N % 16 != 0) || K == 512;
-        return K <= 1536 && !(t64 > 2 * cus && K > 768 && (!whole || (requant && N % 64 == 0)));
+        if (t64 > 3 * cus) return M > 256 && ((K > 256 && K <= 640 && N % 16 != 0) || K == 512);
+        return K <= 1536 && !(t64 > 2 * cus && K > 768 && (!whole || M <= 256 || (requant && N % 64 == 0)));
     }
     if (kernel == NGEMM_KERNEL_TILE_128) {
         if (requant && K < 1536 && (N <= 32 || (rows && N < 64))) return true;
         if (!aligned) return K < 1024 && (N <= 64 || (rows && N <= 128 && t128 <= 3 * cus)) && !(requant && N % 64 == 0);
         return rows && !requant && whole && K > 64 && N % 16 == 0 && t128 > 4 * cus && t128 <= 5 * cus;
     }
-    return kernel == NGEMM_KERNEL_TILE_192 && !rows && !requant && N <= 128 && K > 2048 && t128 * 2 <= 3 * cus;
+    if (requant || (kernel != NGEMM_KERNEL_TILE_192 && kernel != NGEMM_KERNEL_TILE_256) || !aligned) return false;
+    const bool t192 = kernel == NGEMM_KERNEL_TILE_192;
+    if (N >= 8 * M && K > 1024 && (t192 ? t128 > 2 * cus && t128 <= 3 * cus : rows && t128 > 3 * cus && t128 <= 4 * cus)) return true;
+    return t192 && !rows && N <= 128 && K > 2048 && t128 * 2 <= 3 * cus;
 }
 
 // The form of gemm_mid_kernel that serves an 8-bit problem in the place of the tiled kernels, or 0.  1420 shapes were timed with every

@@ -81,6 +81,10 @@ BORDERS = [
     (48289, 128, 397, 397, False, 3, "gemm_tile_kernel<128, 128,"), (48289, 129, 397, 397, False, 3, "gemm_mid"),
     (3826, 5056, 192, 0, False, 3, "gemm_tile_dma_kernel<128, 128,"), (3826, 5057, 192, 0, False, 3, "gemm_mid"),
     (33280, 128, 3392, 0, False, 0, "gemm_tile_x64_kernel<"), (33280, 128, 3392, 0, False, 3, "gemm_mid"),
+    (64, 29000, 800, 0, False, 0, "gemm_mid"), (64, 29000, 768, 0, False, 0, "gemm_tile_dma_kernel<64, 64,"), (64, 29000, 2368, 0, False, 3, "gemm_mid"),
+    (64, 29000, 2304, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"), (256, 9000, 832, 0, False, 3, "gemm_mid"),
+    (320, 9000, 832, 0, False, 3, "gemm_tile_dma_kernel<64, 64,"), (320, 27686, 1792, 0, False, 3, "gemm_tile_x64_kernel<"),
+    (320, 27686, 1792, 0, True, 3, "gemm_mid"), (704, 13149, 1179, 0, False, 0, "gemm_tile_x64_kernel<"),
 ]
 
 
