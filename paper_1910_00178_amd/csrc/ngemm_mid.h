@@ -302,7 +302,7 @@ __device__ __forceinline__ void mid_body(const GemmParams &p, int tile, uint8_t 
             static_for<0, PER>([&](auto n) {
                 constexpr int I = decltype(n)::value;
                 if ((CG + I < NM - 1 ? CG + I : NM - 1) == m) {
-                    if constexpr (AREG && I < AC) va[P2][I] = load16_any(a_tile + (t + V + 2 + AD < nst - 1 ? t + V + 2 + AD : nst - 2) * 64 + voff[I]);
+                    if constexpr (AREG && I < AC) va[P2][I] = load16_any(a_tile + (t + V + 2 + AD) * 64 + voff[I]);
                     else dma1_full(IntC<I - (AREG ? AC : 0)>{}, t + V + NS, S0);
                 }
             });
@@ -370,9 +370,10 @@ __device__ __forceinline__ void mid_body(const GemmParams &p, int tile, uint8_t 
         });
         ++t;
     };
-    // steady while the stages requested are not the last
+    // steady while the stages requested, the rows of A of t + V + 2 + AD among them, are not the last
     constexpr int U1 = AREG && NS % AD != 0 ? NS * AD : NS, U = U1 % 2 == 0 ? U1 : 2 * U1, AHEAD = AREG && AD + 2 > NS ? AD + 2 : NS;
     static_assert(U % NS == 0 && U % 2 == 0 && (!AREG || U % AD == 0), "static places and sets");
+    static_assert(AHEAD >= NS && (!AREG || AHEAD >= AD + 2), "no request past the last stage but one");
     for (; t + U - 1 + AHEAD < nst - 1; t += U) static_for<0, U>(steady);
     if constexpr (AREG) {
         while (all_of<0, U>(finish_areg)) {}
