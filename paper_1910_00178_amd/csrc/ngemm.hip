@@ -664,10 +664,10 @@ hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, b
 }
 
 // Whether a form's workgroups, one per tile, keep within a caller's cap (budget < cus).  Up to 32 rows they need not: the
-// streaming kernels, in whose place they run there, launch a workgroup per panel as well.
+// streaming kernels, in whose place they run there, launch a workgroup per panel as well.  (Form 0, none, has no tiles to count.)
 bool wavek_fits(int form, int64_t M, int64_t N, int64_t budget, int64_t cus)
 {
-    if (budget >= cus || M <= kSkinnyMaxM) return true;
+    if (form == 0 || budget >= cus || M <= kSkinnyMaxM) return true;
     const int64_t bm = form == 1 ? 32 : form / 10 * 32, bn = form == 1 ? 32 : form % 10 * 32;
     return ((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= budget;
 }

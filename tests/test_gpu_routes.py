@@ -267,7 +267,11 @@ CAPPED = [(64, 4096, 4096, "s32", 3, "gemm_tile_deep_kernel<1,", 3), (500, 768, 
           (1024, 768, 768, "s32", 0, "gemm_wavek_kernel<1, 1, 1, 2,", 768), (64, 96, 1000, "s32", 6, "gemm_wavek_kernel<1, 1, 1, 4,", 6),
           (500, 700, 1024, "unpacked", 3, "gemm_tile_dma_kernel<64, 64,", 12), (512, 768, 768, "s16", 2, "gemm_s16_tile_kernel", 2),
           (512, 768, 100, "s16", 2, "gemm_wavek_kernel<2, 2, 2, 2, 4, false, true, false, false, false, true>", 2),
-          (60, 60, 100, "s16", 4, "gemm_wavek_kernel<2, 1, 1, 4,", 4), (512, 768, 768, "s16", 0, "gemm_wavek_kernel<2, 1, 2, 4,", 192)]
+          (60, 60, 100, "s16", 4, "gemm_wavek_kernel<2, 1, 1, 4,", 4), (512, 768, 768, "s16", 0, "gemm_wavek_kernel<2, 1, 2, 4,", 192),
+          # shapes that no form of the kernel that splits K serves (its form 0 was asked how many tiles it has)
+          (1024, 3072, 1000, "s32", 100, "gemm_tile_dma_kernel<64, 64,", 400), (1000, 3000, 300, "u8", 31, "gemm_tile_dma_kernel<64, 64,", 124),
+          (1100, 1300, 1500, "unpacked", 31, "gemm_tile_dma_kernel<64, 64,", 124), (2048, 2048, 200, "unpacked", 31, "gemm_tile_dma_kernel<128, 128,", 62),
+          (3072, 3072, 1024, "unpacked", 50, "gemm_tile_x64_kernel<true", 50)]
 
 
 @pytest.mark.parametrize("case", CAPPED, ids=str)
