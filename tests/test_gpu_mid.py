@@ -15,7 +15,11 @@ SHAPES = [(802, 4624, 64, 64, W64x128), (387, 2314, 1537, 1552, W64x128), (802, 
           (4727, 774, 65, 80, W64x192), (386, 4727, 781, 784, W64x192), (385, 4755, 773, 0, W64x192), (1701, 1537, 1600, 1603, W64x192),
           (4712, 1185, 64, 64, W128), (3279, 775, 774, 784, W128), (2918, 1314, 643, 0, W128),
           (4524, 1935, 65, 80, W192), (2725, 3339, 193, 208, W192), (3490, 2519, 77, 0, W192), (2368, 4629, 343, 0, W192),
-          (1824, 3322, 774, 784, W256), (3268, 1799, 131, 0, W256), (1930, 3100, 1000, 1001, W256)]
+          (1824, 3322, 774, 784, W256), (3268, 1799, 131, 0, W256), (1930, 3100, 1000, 1001, W256),
+          # stages enough for two passes of the steady loop and more, every number of stages modulo its unrolling for the 128 x 192 tiles
+          (2388, 2307, 901, 912, W192), (2242, 2144, 1000, 1008, W192), (2116, 1936, 1025, 1040, W192), (835, 4621, 1100, 1104, W192),
+          (4880, 1737, 901, 0, W192), (4891, 1752, 965, 0, W192), (4875, 1744, 1027, 0, W192), (2882, 1028, 901, 0, W128),
+          (4694, 1168, 1157, 1168, W256), (3279, 1160, 1157, 0, W256)]
 
 
 @pytest.fixture(scope="module")
@@ -26,14 +30,35 @@ def runner():
     r.close()
 
 
+def steady_passes(form, K, aligned):
+    """Passes of the kernel's steady loop: NS stages in the ring, AD register sets for unaligned rows, U stages a pass."""
+    ns, nst, t, n = int(form.split(", ")[-1]), -(-K // 64), 0, 0
+    ad = 4 if ns % 4 == 0 else 3
+    u, ahead = ns if aligned or ns % ad == 0 else ns * ad, ns if aligned else max(ns, ad + 2)
+    u = u if u % 2 == 0 else 2 * u
+    while t + u - 1 + ahead < nst - 1:
+        t, n = t + u, n + 1
+    return n
+
+
+@pytest.mark.parametrize("form", [W64x128, W64x192, W128, W192, W256])
+@pytest.mark.parametrize("aligned", [True, False])
+def test_the_shapes_run_the_steady_loops(form, aligned):
+    mine = [(steady_passes(form, K, aligned), -(-K // 64)) for M, N, K, pitch, f in SHAPES if f == form and ((pitch or K) % 16 == 0) == aligned]
+    assert max(n for n, _ in mine) >= 2, mine
+    if form == W192:
+        assert len({nst % 4 for n, nst in mine if n >= 2}) >= (4 if aligned else 3), mine
+
+
 @pytest.mark.parametrize("case", SHAPES, ids=str)
 def test_forms_against_the_oracle(runner, ctx, launches, case):  # noqa: F811
     M, N, K, pitch, form = case
     import paper_1910_00178_amd as ng
     p = Problem(ctx, M, N, K, pitch or K)
-    got = launches(p.run())
-    want = "gemm_mid_kernel<MidCfg<%s>, false, false, %s>" % (form, "true" if (pitch or K) % 16 else "false")
-    assert [name for name, _ in got] == [want], got
+    for u8, zb in ((False, 0), (False, -5), (True, 0), (True, -5)):
+        got = launches(p.run_u8(zb) if u8 else p.run(zb))
+        want = ["gemm_mid_kernel<MidCfg<%s>, %s>" % (form, ", ".join(str(x).lower() for x in (u8, zb != 0, (pitch or K) % 16 != 0)))]
+        assert [name for name, _ in got] == want, got
     ng.ngemm_packed_b_free(p.h)
     rng = np.random.default_rng(M * 7 + K)
     A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(N, K), dtype=np.int8)
@@ -98,6 +123,44 @@ def test_which_calls_the_kernel_serves(ctx, launches, case):  # noqa: F811
     ng.ngemm_packed_b_free(p.h)
 
 
+def test_where_the_kernels_before_stay(ctx, launches):  # noqa: F811
+    """A cap below the unit count, rows or panels too far apart for 32-bit offsets, and a shape that the time model leaves to the large tiles."""
+    import paper_1910_00178_amd as ng
+    p = Problem(ctx, 1024, 3072, 1000)
+    assert launches(p.run())[0][0].startswith("gemm_mid_kernel<")
+    ng.ngemm_set_max_workgroups(ctx, 100)
+    try:
+        got = launches(p.run())
+    finally:
+        ng.ngemm_set_max_workgroups(ctx, 0)
+    assert got[0][0].startswith("gemm_tile_dma_kernel<64, 64,") and got[0][1] <= 400, got
+    far = (1 << 32) // 255 // 16 * 16                       # captured only: no row but the first is there
+    for lda, name in ((far - 4096, "gemm_mid_kernel<"), (far, "gemm_tile_dma_kernel<64, 64,")):
+        got = launches(lambda st: ng.ngemm_run_u8s8s32(ctx, p.M, p.A, lda, 7, p.h, 0, p.C, p.N, p.ws, p.wsb, st))
+        assert got[0][0].startswith(name), (lda, got)
+    ng.ngemm_packed_b_free(p.h)
+    for shape, name in (((4736, 3072, 768), "gemm_tile_x64_kernel<"), ((2048, 4096, 1024), "gemm_mid_kernel<")):
+        p = Problem(ctx, *shape)
+        assert launches(p.run())[-1][0].startswith(name), shape
+        ng.ngemm_packed_b_free(p.h)
+
+
+def test_a_tuned_shape_takes_what_the_tuner_found(launches):  # noqa: F811
+    """3000 x 3001 x 448 with a zero-point: a fifth faster than any kernel that can be forced.  Later calls of the shape take it, other outputs
+    and zero-points too; what the rule says against 64 x 64 tiles (K of 257 .. 640, columns that share lines of C) does not count then."""
+    import paper_1910_00178_amd as ng
+    own = ng.ngemm_create(0)
+    p = Problem(own, 3000, 3001, 448)
+    best = ng.ngemm_tune_u8s8s32(own, p.M, p.A, p.lda, 7, p.h, 3, p.C, p.N, p.ws, p.wsb)
+    assert best != ng.NGEMM_KERNEL_AUTO and ng.ngemm_tuned_kernel(own, p.M, p.N, p.K) == best
+    tuned = [launches(call)[-1][0] for call in (p.run(3), p.run(0), p.run_u8(3))]
+    assert all(t.startswith("gemm_mid_kernel<") for t in tuned), tuned
+    ng.ngemm_set_kernel(own, best)
+    assert not launches(p.run(3))[-1][0].startswith("gemm_mid_kernel<")
+    ng.ngemm_packed_b_free(p.h)
+    ng.ngemm_destroy(own)
+
+
 def test_more_tiles_than_a_launch_takes(ctx, launches):  # noqa: F811
     """A launch takes less than 2^32 threads: a form with 2^24 tiles (128 x 128, here of 184 GB of u8 beside 46 GB of A) is not launched.
     Captured only: the addresses are those of small buffers that nothing reads."""
@@ -110,7 +173,7 @@ def test_more_tiles_than_a_launch_takes(ctx, launches):  # noqa: F811
 
 
 @pytest.mark.parametrize("K,pitch", [(770, 784), (773, 773)])
-def test_other_operands_and_per_column_terms(runner, K, pitch):
+def test_other_operands_and_per_column_terms(runner, launches, K, pitch):  # noqa: F811
     """Signed A and unsigned B with zero-points, a zero-point, bias and scale per column, a zero-point of C beyond binary32."""
     import torch
     import paper_1910_00178_amd as ng
@@ -131,15 +194,22 @@ def test_other_operands_and_per_column_terms(runner, K, pitch):
     wsb = ng.ngemm_workspace_bytes(M, N, K)
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     C = torch.empty((M, N), dtype=torch.int32, device="cuda")
-    ng.ngemm_run_s8s8s32(ctx, M, rows(As), pitch, -5, hs, 9, C, N, ws, wsb)
+    As_d, Au_d = rows(As), rows(Au)
+
+    def run(call):
+        got = launches(lambda st: call(st))
+        assert len(got) == 1 and got[0][0].startswith("gemm_mid_kernel<"), got
+        call(None)
+    run(lambda st: ng.ngemm_run_s8s8s32(ctx, M, As_d, pitch, -5, hs, 9, C, N, ws, wsb, st))
     assert np.array_equal(C.cpu().numpy(), oracle.gemm_s8s8s32(As, Bs, -5, 9))
-    ng.ngemm_run_u8u8s32(ctx, M, rows(Au), pitch, 131, hu, 120, C, N, ws, wsb)
+    run(lambda st: ng.ngemm_run_u8u8s32(ctx, M, Au_d, pitch, 131, hu, 120, C, N, ws, wsb, st))
     assert np.array_equal(C.cpu().numpy(), oracle.gemm_u8u8s32(Au, Bu, 131, 120))
     zbv, bias = rng.integers(-8, 9, N).astype(np.int32), rng.integers(-3000, 3000, N).astype(np.int32)
     scale = (rng.random(N) * 1e-3 + 1e-4).astype(np.float32)
+    zb_d, scale_d, bias_d = dev(zbv), dev(scale), dev(bias)
     D = torch.empty((M, N), dtype=torch.uint8, device="cuda")
     for zc, relu in ((128, False), (-(1 << 30), False), (3, True)):
-        ng.ngemm_run_u8s8u8_requant_channel(ctx, M, rows(Au), pitch, 128, hs, 0, dev(zbv), dev(scale), dev(bias), int(relu), zc, D, N, ws, wsb)
+        run(lambda st: ng.ngemm_run_u8s8u8_requant_channel(ctx, M, Au_d, pitch, 128, hs, 0, zb_d, scale_d, bias_d, int(relu), zc, D, N, ws, wsb, st))
         assert np.array_equal(D.cpu().numpy(), oracle.gemm_u8s8u8_requant_channel(Au, Bs, 128, 0, scale, zc, zb_vec=zbv, bias=bias, relu=relu))
     ng.ngemm_packed_b_free(hs)
     ng.ngemm_packed_b_free(hu)
