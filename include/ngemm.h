@@ -85,9 +85,11 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal);
 ngemm_status ngemm_destroy(ngemm_ctx *ctx);
 
 /* Force one kernel for the run calls (NGEMM_KERNEL_*), or NGEMM_KERNEL_AUTO for
- * the shape heuristic.  For outputs of few tiles the heuristic also has a kernel that splits K
- * over the wavefronts of a workgroup, in the place of the streaming kernel, the 64 x 64 and the
- * 128 x 128 tiles; a forced kernel is always the one that runs.  The calls on 16-bit operands
+ * the shape heuristic.  The heuristic also has two kernels without a number: for outputs of few
+ * tiles one that splits K over the wavefronts of a workgroup, in the place of the streaming kernel,
+ * the 64 x 64 and the 128 x 128 tiles; for mid-size outputs and rows of A of any alignment one with
+ * tiles from 64 x 128 to 128 x 256, in the place of all tiled kernels (not under a cap of
+ * ngemm_set_max_workgroups).  A forced kernel is always the one that runs.  The calls on 16-bit operands
  * follow the heuristic whatever is forced.  Forcing NGEMM_KERNEL_SKINNY with M > 32 makes the run
  * call return NGEMM_ERR_INVALID_ARG.  NGEMM_KERNEL_SPLIT_K serves outputs with so few
  * 64 x 64 tiles that most compute units would idle: K is cut into parts of at least 1024
@@ -108,8 +110,8 @@ ngemm_status ngemm_set_kernel(ngemm_ctx *ctx, int kernel);
  * this context while the kernel choice is NGEMM_KERNEL_AUTO.  Arguments as for
  * ngemm_run_u8s8s32.  The call waits for the stream; it belongs to set-up, next to the pack.
  * *best_kernel (may be NULL) receives the fastest NGEMM_KERNEL_* value, one that ngemm_set_kernel
- * takes; where the kernel that splits K over the wavefronts of a workgroup is faster still, the
- * later run calls take that.  A context is not meant to be
+ * takes; where one of the heuristic's two kernels without a number (see ngemm_set_kernel) is faster
+ * still, the later run calls take that.  A context is not meant to be
  * tuned and used from several threads at once.
  */
 ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M,

@@ -2404,8 +2404,9 @@ struct S16Cfg {
 // With the packed operand first, lane l of a result block holds, for row l % 16 of A's block, the four
 // consecutive columns 4 (l / 16) .. + 3 of B's block.
 // SUMS: the sums of A's rows are formed here, from the byte planes in the gaps between the matrix ops, instead of being read from p.rowsum:
-// saves a launch (3136 x 964 x 192 12.9 us with it, 11.2 without; 3668 x 597 x 320 15.2 / 12.9) but costs about 55 ns per stage
-// (4096^3, 256 stages per unit, 213 / 221).
+// saves a launch and a pass over A (2.3 us and 0.12 per MB; 3136 x 964 x 192 12.9 us with it, 11.2 without; 3668 x 597 x 320 15.2 / 12.9) but costs
+// about 40 ns per stage and 0.14 us per tile (3800 drawn shapes of 2 to 130 stages per unit; 4096^3, 256 stages, 213 / 221).  The four registers that this form
+// spills are reloaded once per tile, ahead of its loop.
 template <bool SUMS>
 __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
 {
@@ -3276,8 +3277,8 @@ __global__ __launch_bounds__(512) void gemm_group_skinny_kernel(const GroupParam
 // Both kinds of member in one grid (see GroupParams): four wavefronts; a skinny member's panel is
 // summed over K by the four of them, a tile is the 2 x 2 wavefront form of the staged kernel.  The
 // skinny members come first in the grid: the longest of them take as long as the whole launch and
-// have to start with it.  Addresses of 64 bits: for groups with a member whose rows or panels lie too far apart for
-// gemm_group_mid_kernel, which is the faster one (64 odd shapes 16.4 us against 22.0).
+// have to start with it.  For groups with a member whose rows or panels lie too far apart for the 32-bit offsets of gemm_group_mid_kernel, and for
+// groups of few tiles with a short K, on which that one is slower (64 odd shapes in a graph: 16.9 us there, 18.3 here).
 template <int BM, int BN, int WGM, int WGN, int BK>
 __global__ __launch_bounds__(WGM * WGN * 64) void gemm_group_kernel(const GroupParams g)
 {

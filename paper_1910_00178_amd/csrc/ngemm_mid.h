@@ -1,5 +1,5 @@
-// Device kernel for outputs of one to some rounds of workgroups (more 64 x 64 tiles than two per compute unit) and for rows of A
-// with any alignment.  Included only by ngemm.hip.
+// Device kernel for outputs of one to some rounds of workgroups and for rows of A with any alignment; mid_form in ngemm.hip, which alone
+// includes this, says which calls it serves.
 //
 // What bounded such calls: 64 x 64 and 128 x 128 tiles of the older kernels pull 128 bytes per byte of K and tile through a unit's path
 // from L2 (120-155 GB/s) with a barrier per 64 bytes; the 256-row tiles leave units idle (2048 x 4096: 176 tiles of 192 x 256) and
@@ -16,12 +16,13 @@
 //  * AREG: rows of A with any alignment, which copies into LDS cannot fetch, come through registers, AD stages ahead;
 //  * the u8 output is requantised where it lies in the accumulators, with the column terms in registers, and leaves through LDS in
 //    16-byte pieces of whole rows.
-// Time stamps in the loop: no wait for copies to land (0 cycles), 50-150 of a stage's 640-900 cycles at the barrier; 512 are matrix ops.
+// Time stamps in a copy of the loop: no wait for copies to land, 50-150 of a stage's 640-900 cycles at the barrier; 512 are matrix ops (16 of 16 cycles
+// for each of two wavefronts on a SIMD).
 // Tried: stages of 128 bytes (the same), 64 x 128 of a 128 x 256 tile per wavefront (registers spill or move to the accumulation file),
 // the shift of A as an exclusive or on LDS (29 cycles each: slower), priorities for one of two workgroups (nothing).
-// us in a graph, before / here: 2048 x 4096 x 1024 with a zero-point 17.8 / 15.9 (128 x 128 tiles of this kernel: 1.1 POP/s, half of the time the
-// launch and 32 MiB of C), 2048 x 3072 x 1536 18.5 / 15.9, 1024 x 3072 x 768 u8 8.9 / 8.0, 1088 x 1413 x 2112 z 12.5 / 11.0; unaligned rows:
-// 2047 x 3071 x 1537 z 23.5 / 21.4 (22.1 while the last stages waited for all loads), 2368 x 4629 x 1343 37.9 / 33.
+// us in a graph, the kernels before / here: 2048 x 4096 x 1024 with a zero-point 19.9 / 16.6 (128 x 128 tiles of this kernel: 1.0 POP/s, half of the
+// time the launch and 32 MiB of C), 2048 x 3072 x 1536 18.3 / 15.7, 1024 x 3072 x 768 u8 9.0 / 7.7, 1088 x 1413 x 2112 z 12.4 / 11.7; unaligned
+// rows: 2047 x 3071 x 1537 z 24.5 / 22.0, 2368 x 4629 x 1343 36.6 / 27.9.
 #pragma once
 #include "ngemm_kernels.h"
 
@@ -553,8 +554,9 @@ __global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_k
 // Grouped launches (see GroupParams): the panels of the skinny members, four wavefronts each, then the tiles of the others, whose rows
 // have any alignment.  Bound by latency: a member of few tiles and a long K lasts as long as its stages, and the short ones are a prologue and an
 // epilogue each, so four workgroups share a unit (64 x 64 tiles, 32 KiB, 128 registers).  The batch of 64 odd shapes (M, N to 4096, K to
-// 3183; 1911 tiles and the panels) in a graph: 19.9 us with the tiles staged through registers, 16.5 here; 128 columns per tile 17.8, two workgroups per
-// unit 17.4, six stages and register sets 18.1.
+// 3183; 1911 tiles and the panels) in a graph: 18.3 us on gemm_group_kernel, whose tiles are staged through registers, 16.9 here; when this was
+// written, against 16.5: 128 columns per tile 17.8, two workgroups per unit 17.4, six stages and register sets 18.1.  Groups of few tiles and a short K
+// stay with gemm_group_kernel (the launch says which).
 template <class C>
 __global__ __launch_bounds__(256, C::kPerCu) void gemm_group_mid_kernel(const GroupParams g)
 {
