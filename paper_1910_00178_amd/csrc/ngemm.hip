@@ -790,7 +790,8 @@ bool mid_stays_out(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bo
 // form and with the kernels before (M from 64, N from 256, K up to 8192, odd sizes among them, aligned and unaligned rows, int32 and u8 outputs, with
 // and without a zero-point of B):
 //  * outputs of more than 0.55 x 128 x 128 tiles per compute unit: 1.17 x faster on average, unaligned rows 1.15 x; a K below 768 only from 0.8
-//    tiles per unit on (3840 x 640 x 704, 150 tiles, 7.6 us before, 8.6 here; at 205 .. 256 tiles 1.08-1.16 x);
+//    tiles per unit on (1.08-1.16 x there; below it, K = 576 .. 767, 0.92-0.98 x with a zero-point of B, and without one 0.97-1.14 x, aligned rows
+//    of no whole stages most: a line that could be drawn closer);
 //  * from one 64 x 64 tile per unit on with a long K where the kernels before pay extra: row sums, u8 outputs, K of no whole stages,
 //    unaligned rows (1.1 x; 1088 x 1413 x 2112 z 12.5 / 11.0).  Plain int32 problems there are a tie or a loss;
 //  * less what mid_stays_out keeps.
