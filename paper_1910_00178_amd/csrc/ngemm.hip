@@ -104,16 +104,16 @@ hipError_t launch_tile(const GemmParams &p0, bool requant, hipStream_t st, bool 
         static_assert(Cfg::kLdsBytes <= 64 * 1024, "needs no LDS attribute");
         if (rows) {
             if (requant)
-                hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, true, true>), grid, block, smem, st, p);
+                hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, true, true>), grid, block, smem, st, args_of(p));
             else
-                hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, false, true>), grid, block, smem, st, p);
+                hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, false, true>), grid, block, smem, st, args_of(p));
             return hipGetLastError();
         }
     }
     if (requant)
-        hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, true>), grid, block, smem, st, p);
+        hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, true>), grid, block, smem, st, args_of(p));
     else
-        hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, false>), grid, block, smem, st, p);
+        hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN, BK, false>), grid, block, smem, st, args_of(p));
     return hipGetLastError();
 }
 
@@ -145,15 +145,15 @@ hipError_t launch_tile_dma(const GemmParams &p0, bool requant, int num_cus, hipS
     const int nwg = ntiles < num_cus * per_cu ? ntiles : num_cus * per_cu;
     dim3 grid((unsigned)nwg), block(WGM * WGN * 64);
     const size_t smem = Cfg::kLdsBytes;
-    const RawB none{nullptr, 0};
+    const GemmArgs args = rawb ? args_of_raw(p, *rawb, nwg) : args_of(p, nwg);
     if (rawb) {      // unpacked B: int32 output only; `rows`: the sums of both operands are formed in the kernel
         if constexpr (BM < 256) {
             if (rows) {
-                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, true, true>), grid, block, smem, st, p, *rawb);
+                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, true, true>), grid, block, smem, st, args);
                 return hipGetLastError();
             }
         }
-        hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, true>), grid, block, smem, st, p, *rawb);
+        hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, true>), grid, block, smem, st, args);
         return hipGetLastError();
     }
     if constexpr (BM < 256) {
@@ -161,16 +161,16 @@ hipError_t launch_tile_dma(const GemmParams &p0, bool requant, int num_cus, hipS
         static_assert(Cfg::kLdsBytes <= 64 * 1024, "needs no LDS attribute");
         if (rows) {
             if (requant)
-                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, true, false, true>), grid, block, smem, st, p, none);
+                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, true, false, true>), grid, block, smem, st, args);
             else
-                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, false, true>), grid, block, smem, st, p, none);
+                hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false, false, true>), grid, block, smem, st, args);
             return hipGetLastError();
         }
     }
     if (requant)
-        hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, true>), grid, block, smem, st, p, none);
+        hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, true>), grid, block, smem, st, args);
     else
-        hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false>), grid, block, smem, st, p, none);
+        hipLaunchKernelGGL((gemm_tile_dma_kernel<BM, BN, WGM, WGN, NSTAGE, false>), grid, block, smem, st, args);
     return hipGetLastError();
 }
 
@@ -204,15 +204,17 @@ hipError_t launch_tile_deep(const GemmParams &p0, bool requant, bool rows, int n
     p.tiles_m = (p.M + Cfg::BMN - 1) / Cfg::BMN;
     p.tiles_n = (p.N + Cfg::BMN - 1) / Cfg::BMN;
     const int ntiles = p.tiles_m * p.tiles_n;
-    dim3 grid((unsigned)(ntiles < num_cus ? ntiles : num_cus)), block(256);
+    const int nwg = ntiles < num_cus ? ntiles : num_cus;
+    const dim3 grid((unsigned)nwg), block(256);
+    const GemmArgs args = args_of(p, nwg);
     if (requant && rows)
-        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, true, 0, true>), grid, block, Cfg::kLdsBytes, st, p);
+        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, true, 0, true>), grid, block, Cfg::kLdsBytes, st, args);
     else if (requant)
-        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, true>), grid, block, Cfg::kLdsBytes, st, p);
+        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, true>), grid, block, Cfg::kLdsBytes, st, args);
     else if (rows)
-        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, false, 0, true>), grid, block, Cfg::kLdsBytes, st, p);
+        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, false, 0, true>), grid, block, Cfg::kLdsBytes, st, args);
     else
-        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, false>), grid, block, Cfg::kLdsBytes, st, p);
+        hipLaunchKernelGGL((gemm_tile_deep_kernel<T, kDeepSub<T>, kDeepStages, false>), grid, block, Cfg::kLdsBytes, st, args);
     return hipGetLastError();
 }
 
@@ -254,20 +256,23 @@ hipError_t launch_tile_deep_splitk(const GemmParams &p0, int parts, int kchunk, 
     p.kchunk = kchunk;
     p.part_ws = part_ws;
     const int nunits = p.tiles_m * p.tiles_n * parts;
-    dim3 grid((unsigned)(nunits < num_cus ? nunits : num_cus)), block(256);
+    const int nwg = nunits < num_cus ? nunits : num_cus;
+    const dim3 grid((unsigned)nwg), block(256);
+    const GemmArgs args = args_of(p, nwg);
     if (part_ws) {
         if (rows)
-            hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 2, true>), grid, block, Cfg::kLdsBytes, st, p);
+            hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 2, true>), grid, block, Cfg::kLdsBytes, st, args);
         else
-            hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 2, false>), grid, block, Cfg::kLdsBytes, st, p);
+            hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 2, false>), grid, block, Cfg::kLdsBytes, st, args);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        const int nw = parts < kReduceWaves ? parts : kReduceWaves;
         const int64_t lanes = (int64_t)p.M * (splitk_part_pitch(p.N) / 4);
-        const dim3 rgrid((unsigned)((lanes + 63) / 64)), rblock(64 * (parts < kReduceWaves ? parts : kReduceWaves));
+        const dim3 rgrid((unsigned)((lanes + 63) / 64)), rblock(64 * nw);
         if (requant)
-            hipLaunchKernelGGL(splitk_reduce_kernel<true>, rgrid, rblock, 0, st, p, parts);
+            hipLaunchKernelGGL(splitk_reduce_kernel<true>, rgrid, rblock, 0, st, args_of(p, nw));
         else
-            hipLaunchKernelGGL(splitk_reduce_kernel<false>, rgrid, rblock, 0, st, p, parts);
+            hipLaunchKernelGGL(splitk_reduce_kernel<false>, rgrid, rblock, 0, st, args_of(p, nw));
         return hipGetLastError();
     }
     const int64_t segs = (p.N + 1023) / 1024;
@@ -275,9 +280,9 @@ hipError_t launch_tile_deep_splitk(const GemmParams &p0, int parts, int kchunk, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (rows)
-        hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 1, true>), grid, block, Cfg::kLdsBytes, st, p);
+        hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 1, true>), grid, block, Cfg::kLdsBytes, st, args);
     else
-        hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 1, false>), grid, block, Cfg::kLdsBytes, st, p);
+        hipLaunchKernelGGL((gemm_tile_deep_kernel<1, kDeepSub<1>, kDeepStages, false, 1, false>), grid, block, Cfg::kLdsBytes, st, args);
     return hipGetLastError();
 }
 
@@ -303,13 +308,13 @@ hipError_t allow_big_lds_deep()
 }
 
 template <int P>
-void launch_skinny_p(const GemmParams &p, bool requant, int nwaves, int nregs, size_t smem, hipStream_t st)
+void launch_skinny_p(const GemmParams &p, bool requant, int nwaves, size_t smem, hipStream_t st)
 {
     dim3 grid((unsigned)((p.npanels + P - 1) / P)), block(nwaves * 64);
     if (requant)
-        hipLaunchKernelGGL((gemm_skinny_kernel<true, P>), grid, block, smem, st, p, nregs);
+        hipLaunchKernelGGL((gemm_skinny_kernel<true, P>), grid, block, smem, st, args_of(p, nwaves));
     else
-        hipLaunchKernelGGL((gemm_skinny_kernel<false, P>), grid, block, smem, st, p, nregs);
+        hipLaunchKernelGGL((gemm_skinny_kernel<false, P>), grid, block, smem, st, args_of(p, nwaves));
 }
 
 // The streaming kernel (a panel per wavefront, A in LDS) can serve a problem when its A fits the
@@ -347,10 +352,13 @@ hipError_t launch_skinny(const GemmParams &p, bool requant, int num_cus, hipStre
         const int chunk = stream_chunk(p.npanels, num_cus);
         const dim3 grid((unsigned)((p.npanels + chunk - 1) / chunk)), block(kStreamWaves * 64);
         const int smem = stream_launch_lds(p.M, p.Kp, chunk);
+        GemmArgs args = args_of(p);
+        args.kchunk = chunk;
+        args.ksplit = smem;
         if (requant)
-            hipLaunchKernelGGL(gemm_stream_skinny_kernel<true>, grid, block, (size_t)smem, st, p, chunk, smem);
+            hipLaunchKernelGGL(gemm_stream_skinny_kernel<true>, grid, block, (size_t)smem, st, args);
         else
-            hipLaunchKernelGGL(gemm_stream_skinny_kernel<false>, grid, block, (size_t)smem, st, p, chunk, smem);
+            hipLaunchKernelGGL(gemm_stream_skinny_kernel<false>, grid, block, (size_t)smem, st, args);
         return hipGetLastError();
     }
     const int nslices = p.Kp / 32;
@@ -363,11 +371,11 @@ hipError_t launch_skinny(const GemmParams &p, bool requant, int num_cus, hipStre
     // (measured at N = 32768, K = 8192: M = 32 gains 30 % with four panels, M = 16 12 % with two;
     // at N = 16384 a workgroup per panel is still the fastest)
     if (p.M > 16 && p.npanels >= 4 * num_cus)
-        launch_skinny_p<4>(p, requant, nwaves, nregs, smem, st);
+        launch_skinny_p<4>(p, requant, nwaves, smem, st);
     else if (p.M > 4 && p.npanels >= 4 * num_cus)
-        launch_skinny_p<2>(p, requant, nwaves, nregs, smem, st);
+        launch_skinny_p<2>(p, requant, nwaves, smem, st);
     else
-        launch_skinny_p<1>(p, requant, nwaves, nregs, smem, st);
+        launch_skinny_p<1>(p, requant, nwaves, smem, st);
     return hipGetLastError();
 }
 
@@ -496,13 +504,13 @@ using WaveK24 = WaveKForm<2, 4, 4, 3>;       // 144 KiB: one
 using WaveK12Short = WaveKForm<1, 2, 2, 4>;  // 48 KiB (A through registers)
 
 template <class F, int ELEM, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false>
-hipError_t launch_wavek(const GemmParams &p0, hipStream_t st, const RawB &rawb = RawB{nullptr, 0})
+hipError_t launch_wavek(const GemmParams &p0, hipStream_t st, const RawB *rawb = nullptr)
 {
     GemmParams p = p0;
     p.tiles_m = (p.M + F::TM * 32 - 1) / (F::TM * 32);
     p.tiles_n = (p.N + F::TN * 32 - 1) / (F::TN * 32);
     hipLaunchKernelGGL((gemm_wavek_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, ROWS, BRAW, AREG, NT>), dim3((unsigned)(p.tiles_m * p.tiles_n)),
-                       dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, p, rawb);
+                       dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, rawb ? args_of_raw(p, *rawb) : args_of(p));
     return hipGetLastError();
 }
 
@@ -698,7 +706,7 @@ hipError_t launch_mid(const GemmParams &p0, bool requant, bool rows, bool aligne
     p.tiles_n = (p.N + C::BN - 1) / C::BN;
     const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(C::kThreads);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, C::kLdsBytes, st, p);
+        hipLaunchKernelGGL(kernel, grid, block, C::kLdsBytes, st, args_of(p));
         return hipGetLastError();
     };
     if (aligned) {
@@ -853,7 +861,7 @@ int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool alig
 template <class F>
 hipError_t launch_wavek_raw(const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
 {
-    return rows ? launch_wavek<F, 1, false, true, true>(p, st, rawb) : launch_wavek<F, 1, false, false, true>(p, st, rawb);
+    return rows ? launch_wavek<F, 1, false, true, true>(p, st, &rawb) : launch_wavek<F, 1, false, false, true>(p, st, &rawb);
 }
 
 hipError_t launch_wavek_raw_form(int form, const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
@@ -1062,19 +1070,20 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
             p.tiles_m = (p.M + trows - 1) / trows;
             p.tiles_n = (p.N + 255) / 256;
             const int ntiles = p.tiles_m * p.tiles_n;
-            const dim3 grid((unsigned)(ntiles < num_cus ? ntiles : num_cus));
-            const RawB none{nullptr, 0};
+            const int nwg = ntiles < num_cus ? ntiles : num_cus;
+            const dim3 grid((unsigned)nwg);
+            const GemmArgs args = args_of(p, nwg);
             if (trows == 192) {
                 if (a.requant)
-                    hipLaunchKernelGGL((gemm_tile_x64_kernel<false, true, true, 6>), grid, dim3(256), X64Cfg::kLdsBytes, st, p, none);
+                    hipLaunchKernelGGL((gemm_tile_x64_kernel<false, true, true, 6>), grid, dim3(256), X64Cfg::kLdsBytes, st, args);
                 else
-                    hipLaunchKernelGGL((gemm_tile_x64_kernel<false, false, true, 6>), grid, dim3(256), X64Cfg::kLdsBytes, st, p, none);
+                    hipLaunchKernelGGL((gemm_tile_x64_kernel<false, false, true, 6>), grid, dim3(256), X64Cfg::kLdsBytes, st, args);
             } else if (a.requant)
-                hipLaunchKernelGGL((gemm_tile_x64_kernel<false, true>), grid, dim3(256), X64Cfg::kLdsBytes, st, p, none);
+                hipLaunchKernelGGL((gemm_tile_x64_kernel<false, true>), grid, dim3(256), X64Cfg::kLdsBytes, st, args);
             else if (a.a_signed)      // signed A: the form without the u8 -> s8 shift
-                hipLaunchKernelGGL((gemm_tile_x64_kernel<false, false, false>), grid, dim3(256), X64Cfg::kLdsBytes, st, p, none);
+                hipLaunchKernelGGL((gemm_tile_x64_kernel<false, false, false>), grid, dim3(256), X64Cfg::kLdsBytes, st, args);
             else
-                hipLaunchKernelGGL((gemm_tile_x64_kernel<false, false>), grid, dim3(256), X64Cfg::kLdsBytes, st, p, none);
+                hipLaunchKernelGGL((gemm_tile_x64_kernel<false, false>), grid, dim3(256), X64Cfg::kLdsBytes, st, args);
             e = hipGetLastError();
         } else {
             e = dma_ok ? launch_tile_dma<256, 256, 2, 2, kStages256>(p, a.requant, num_cus, st)
@@ -1567,9 +1576,8 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     } else if (B->K < S16Cfg::kMinK && !fits(tiles(64, 64))) {
         p.tiles_m = (int)((M + 63) / 64);
         p.tiles_n = (int)((B->N + 63) / 64);
-        const RawB none{nullptr, 0};
         hipLaunchKernelGGL((gemm_wavek_kernel<2, 2, 2, WaveK22::NW, WaveK22::RING, false, true, false, false, false, true>), dim3((unsigned)budget),
-                           dim3(WaveK22::NW * 64), (WaveKCfg<2, 2, WaveK22::NW, WaveK22::RING>::kLdsBytes), st, p, none);
+                           dim3(WaveK22::NW * 64), (WaveKCfg<2, 2, WaveK22::NW, WaveK22::RING>::kLdsBytes), st, args_of(p, (int)budget));
         e = hipGetLastError();
     } else if (B->K < S16Cfg::kMinK || (tiles(64, 64) <= 2 * cus && tiles(128, 128) * 2 <= cus && fits(tiles(64, 64)))) {
         e = launch_wavek<WaveK22, 2, false, true>(p, st);
@@ -1581,13 +1589,13 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
         // MB of A).  3800 drawn shapes, launch over kernel: up to 8 stages per unit 1.10-1.16 x, 32 1.03, 40 1.025 (0.976 at worst, many short tiles),
         // 64 1.01, 80 1.006, beyond 100 0.99.
         if ((ntiles + grid - 1) / grid * ((B->K + 63) / 64) <= 40) {
-            hipLaunchKernelGGL(gemm_s16_tile_kernel<true>, dim3((unsigned)grid), dim3(256), S16Cfg::kLdsBytes, st, p);
+            hipLaunchKernelGGL(gemm_s16_tile_kernel<true>, dim3((unsigned)grid), dim3(256), S16Cfg::kLdsBytes, st, args_of(p, (int)grid));
         } else {
             int32_t *rs = (int32_t *)workspace_dev;
             hipLaunchKernelGGL(rowsum_s16_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, A_dev, lda, (int)M, (int)B->K, rs);
             if (hipGetLastError() != hipSuccess) return NGEMM_ERR_DEVICE;
             p.rowsum = rs;
-            hipLaunchKernelGGL(gemm_s16_tile_kernel<false>, dim3((unsigned)grid), dim3(256), S16Cfg::kLdsBytes, st, p);
+            hipLaunchKernelGGL(gemm_s16_tile_kernel<false>, dim3((unsigned)grid), dim3(256), S16Cfg::kLdsBytes, st, args_of(p, (int)grid));
         }
         e = hipGetLastError();
     }
@@ -1665,8 +1673,8 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
             p.tiles_m = (int)((M + 255) / 256);
             p.tiles_n = (int)((N + 255) / 256);
             const int ntiles = p.tiles_m * p.tiles_n;
-            hipLaunchKernelGGL(gemm_tile_x64_kernel<true>, dim3((unsigned)(ntiles < budget ? ntiles : budget)), dim3(256),
-                               X64Cfg::kLdsBytes, st, p, rawb);
+            const int nwg = ntiles < budget ? ntiles : budget;
+            hipLaunchKernelGGL(gemm_tile_x64_kernel<true>, dim3((unsigned)nwg), dim3(256), X64Cfg::kLdsBytes, st, args_of_raw(p, rawb, nwg));
             e = hipGetLastError();
         } else e = launch_tile_dma<256, 256, 2, 2, kStages256>(p, false, budget, st, &rawb);
         return e == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
@@ -1730,6 +1738,7 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
                 // few; with several panels per compute unit anyway, fewer wavefronts with more
                 // fragments each spend less on the final sum across wavefronts
                 const unsigned nw = grid >= 8u * cus ? 2 : (grid >= 4u * cus ? 4 : 8);
+                grp.nwaves = (int)nw;
                 hipLaunchKernelGGL(gemm_group_skinny_kernel, dim3(grid), dim3(64 * nw), (size_t)(nw * 16 * 64 * 4), st, grp);
             } else {
                 const size_t lds = std::max((size_t)TCfg::kLdsBytes, (size_t)(4 * 16 * 64 * 4));

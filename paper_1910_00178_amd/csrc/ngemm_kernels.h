@@ -62,6 +62,93 @@ struct GemmParams {
     int nxcd;
 };
 
+// What a launch carries of them: the one argument of every kernel that serves a single product; the rest is rebuilt on the device
+// by a few scalar operations.  The size is what counts: a launch whose arguments (the hidden ones of gridDim and blockDim among
+// them) take more than 112 bytes costs the host 3.5-4.2 us, any smaller one 2.7, whatever the kernel, and calls of small outputs
+// are bound by that (1 x 4096 x 1024 in a loop in C 3.8 -> 3.1 us; GemmParams alone are 168 bytes).  So the grid and the
+// wavefronts of a workgroup are among the fields too, for the kernels that need them.
+struct GemmArgs {
+    const uint8_t *A;
+    int64_t lda;
+    const uint8_t *Bp;       // unpacked B: the caller's storage
+    void *C;
+    int64_t ldc;
+    int M, N, K;
+    int32_t za_term, zb;
+    float scale;
+    int32_t zc;
+    uint32_t flags;          // bit 0: unsigned A, 1: relu, 8 .. 15: XCDs, 16 .. 31: `count`
+    const float *scale_vec;  // unpacked B: its column sums
+    const int32_t *bias_vec, *zb_vec;
+    void *ws;                // the row sums; kernels of a K split: part_ws
+    union {
+        int64_t ldb;         // unpacked B: its pitch
+        struct { int ksplit, kchunk; };
+    };
+};
+static_assert(sizeof(GemmArgs) == 112, "a launch of more than 112 bytes costs the host 0.7-1.4 us more");
+
+// `count`: workgroups of a grid whose workgroups walk tiles, or wavefronts per workgroup, for the kernels that need to know
+inline GemmArgs args_of(const GemmParams &p, int count = 0)
+{
+    GemmArgs a;
+    a.A = p.A; a.lda = p.lda; a.Bp = p.Bp; a.C = p.C; a.ldc = p.ldc;
+    a.M = p.M; a.N = p.N; a.K = p.K;
+    a.za_term = (int32_t)p.za_term; a.zb = (int32_t)p.zb;
+    a.scale = p.scale; a.zc = p.zc;
+    a.flags = (p.a_xor ? 1u : 0u) | (p.relu ? 2u : 0u) | ((uint32_t)p.nxcd & 0xffu) << 8 | (uint32_t)count << 16;
+    a.scale_vec = p.scale_vec; a.bias_vec = p.bias_vec; a.zb_vec = p.zb_vec;
+    a.ws = p.part_ws ? (void *)p.part_ws : (void *)p.rowsum;      // (a K split forms its row sums itself)
+    a.ksplit = p.ksplit; a.kchunk = p.kchunk;
+    return a;
+}
+
+// An operand B that was not packed: the caller's int8 [N x K] storage (column j = ldb-strided row of
+// K contiguous bytes), 16-byte aligned.  It has the shape of A, so the BRAW forms of the kernels below
+// copy and read its tiles exactly as they do A's (Sec. 3.1.1: the case where both matrices are inputs).
+struct RawB {
+    const uint8_t *B;
+    int64_t ldb;
+};
+
+// p.colsum: the sums of its columns where a pass has formed them
+inline GemmArgs args_of_raw(const GemmParams &p, const RawB &raw, int count = 0)
+{
+    GemmArgs a = args_of(p, count);
+    a.Bp = raw.B;
+    a.ldb = raw.ldb;
+    a.scale_vec = (const float *)p.colsum;
+    return a;
+}
+
+__device__ __forceinline__ int count_of(const GemmArgs &a) { return (int)(a.flags >> 16); }
+
+// ELEM: bytes of an element (2: packed as byte planes); tiles are counted for BM x BN.
+template <int ELEM, int BM, int BN, bool BRAW = false, bool SPLITK = false>
+__device__ __forceinline__ GemmParams params_of(const GemmArgs &a)
+{
+    GemmParams p;
+    p.A = a.A; p.lda = a.lda; p.Bp = a.Bp; p.C = a.C; p.ldc = a.ldc;
+    p.M = a.M; p.N = a.N; p.K = a.K;
+    p.Kp = ELEM == 1 ? (a.K + 63) & ~63 : 2 * ((a.K + 31) & ~31);
+    p.npanels = (a.N + 31) >> 5;
+    p.colsum = BRAW ? (const int32_t *)a.scale_vec : (const int32_t *)(a.Bp + (int64_t)p.Kp * ((int64_t)p.npanels * 32));
+    p.rowsum = SPLITK ? nullptr : (const int32_t *)a.ws;
+    p.part_ws = SPLITK ? (int32_t *)a.ws : nullptr;
+    p.tiles_m = (int)((unsigned)(a.M + (BM - 1)) / BM);
+    p.tiles_n = (int)((unsigned)(a.N + (BN - 1)) / BN);
+    p.za_term = (uint32_t)a.za_term; p.zb = (uint32_t)a.zb;
+    p.rconst = p.za_term * (uint32_t)a.K;
+    p.kconst = 0u - p.zb * p.rconst;
+    p.scale = a.scale; p.zc = a.zc;
+    p.scale_vec = BRAW ? nullptr : a.scale_vec; p.bias_vec = a.bias_vec; p.zb_vec = a.zb_vec;
+    p.relu = (int)(a.flags >> 1 & 1u);
+    p.a_xor = (a.flags & 1u) ? 0x80808080u : 0u;
+    p.ksplit = a.ksplit; p.kchunk = a.kchunk;
+    p.nxcd = (int)(a.flags >> 8 & 0xffu);
+    return p;
+}
+
 // ---- small helpers -------------------------------------------------------------------------
 
 // 16 bytes from an address with no alignment promise.
@@ -1035,9 +1122,10 @@ __device__ __forceinline__ void tile_body_staged(const GemmParams &p, int tile, 
 }
 
 template <int BM, int BN, int WGM, int WGN, int BK, bool REQUANT, bool ROWS = false>
-__global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_kernel(const GemmParams p)
+__global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_kernel(const GemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const GemmParams p = params_of<1, BM, BN>(a);
     tile_body_staged<BM, BN, WGM, WGN, BK, REQUANT, ROWS>(p, blockIdx.x, lds);
 }
 
@@ -1063,6 +1151,7 @@ struct GroupParams {
     int count;
     int nxcd;                // XCDs of the device (see GemmParams)
     int first_tile;          // members before it are skinny (units = panels), from it on tiled (units = tiles)
+    int nwaves;              // gemm_group_skinny_kernel: wavefronts of a workgroup
     int unit_start[kGroupMax + 1];
     GroupMember prob[kGroupMax];
 };
@@ -1168,20 +1257,13 @@ typedef const __attribute__((address_space(1))) void *gptr_t;
 constexpr int kCopyNT = 2;                              // cache policy of a copy into LDS: non-temporal
 typedef __attribute__((address_space(3))) void *lptr_t;
 
-// An operand B that was not packed: the caller's int8 [N x K] storage (column j = ldb-strided row of
-// K contiguous bytes), 16-byte aligned.  It has the shape of A, so the BRAW form of the kernel below
-// copies and reads its tiles exactly as it does A's (Sec. 3.1.1: the case where both matrices are inputs).
-struct RawB {
-    const uint8_t *B;
-    int64_t ldb;
-};
-
 // ROWS: the row sums a zero-point of B needs are added up here, from the A fragments behind the matrix
 // op that uses them (no row-sum pass before the kernel); the host takes this form only when the
 // zero-point is there.
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool REQUANT, bool BRAW = false, bool ROWS = false>
-__global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const GemmParams p, const RawB rawb)
+__global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const GemmArgs a)
 {
+    const GemmParams p = params_of<1, BM, BN, BRAW>(a);
     using Cfg = DmaCfg<BM, BN, WGM, WGN, NSTAGE>;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, KS = Cfg::KS, BK = Cfg::BK;
     constexpr int AI = Cfg::kAIters, BI = Cfg::kBIters, NW = Cfg::kWaves;
@@ -1202,7 +1284,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
     // (G = grid size: one workgroup per compute unit when there is enough work; the LDS ring and
     // the 512 registers per lane leave no room for a second one anyway).
     const int ntiles = p.tiles_m * p.tiles_n;
-    const int G = gridDim.x, w = blockIdx.x;
+    const int G = count_of(a), w = blockIdx.x;
 
     const int t16 = lane >> 2;
     const int a_chunk = ((lane & 3) - (t16 >> 2)) & 3;
@@ -1245,7 +1327,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_tile_dma_kernel(const Gem
             if (BRAW) {
                 int gcol = n0 + q * 16 + t16;
                 gcol = gcol < p.N ? gcol : p.N - 1;      // columns past N: read a valid one, never stored
-                b_src[i] = rawb.B + (int64_t)gcol * rawb.ldb + a_chunk * 16;
+                b_src[i] = p.Bp + (int64_t)gcol * a.ldb + a_chunk * 16;
             } else {
                 int pnl = n0 / 32 + (q >> 1);
                 pnl = pnl < p.npanels ? pnl : p.npanels - 1; // panels past N: read a valid panel, never stored
@@ -1520,8 +1602,9 @@ struct X64Cfg {
 // 256 x 256 tiles, where the shorter tile fills more of them for three quarters of the time per tile
 // (Sec. 3.1.1: the tiling is chosen per problem size).
 template <bool BRAW, bool REQUANT = false, bool SHIFT = true, int RB = 8>
-__global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmParams p, const RawB rawb)
+__global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmArgs a)
 {
+    const GemmParams p = params_of<1, RB * 32, 256, BRAW>(a);
     using Cfg = X64Cfg;
     static_assert(RB == 8 || RB == 6, "wavefront tile of 128 or 96 rows");
     constexpr int CPH = RB / 2;                          // copies of A per wavefront and half of a double stage
@@ -1537,7 +1620,7 @@ __global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmParams p, 
     const int nfull = p.K / 64 & ~1;                     // stages of the pipelined loop: an even number
     const int nstages = p.Kp / 64;                       // the one or two after them (full, partial) go unpipelined
     const int ntiles = p.tiles_m * p.tiles_n;
-    const int gsz = gridDim.x, w = blockIdx.x;
+    const int gsz = count_of(a), w = blockIdx.x;
 
     const int ft = lane & 15, fc = lane >> 4;            // fragments: row / column of the block, 16-byte chunk
     // A fragment of a 16-row block: lane l takes row l % 16, chunk l / 16 (+ 4 in the odd position).
@@ -1576,7 +1659,7 @@ __global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmParams p, 
         // lane offset, and the advance along K as a scalar offset, so that a copy costs no vector
         // arithmetic (the host checks that 256 rows of A, and eight panels or 256 columns of B, span
         // less than 4 GiB).  A: copy d of half h takes rows 8 * (4 * CPH * h + CPH * wave + d) .. +7.
-        const uint8_t *b_tile = BRAW ? rawb.B + (int64_t)n0 * rawb.ldb
+        const uint8_t *b_tile = BRAW ? p.Bp + (int64_t)n0 * a.ldb
                                      : p.Bp + (int64_t)(n0 / 32) * nslices * kFragBytes;
         // A wavefront's four copies of one operand go to four consecutive KiB of LDS: the LDS base (M0)
         // is written once for the four, and copy d carries the immediate offset 1024 * d, which the
@@ -1606,7 +1689,7 @@ __global__ __launch_bounds__(256) void gemm_tile_x64_kernel(const GemmParams p, 
             if (BRAW) {
                 int gcol = n0 + q * 16 + t16;
                 gcol = gcol < p.N ? gcol : p.N - 1;      // columns past N: read a valid one, never stored
-                b_voff[i] = (uint32_t)(gcol - n0) * (uint32_t)rawb.ldb + (uint32_t)b_chunk * 16u + bias;
+                b_voff[i] = (uint32_t)(gcol - n0) * (uint32_t)a.ldb + (uint32_t)b_chunk * 16u + bias;
             } else {
                 int pnl = n0 / 32 + (q >> 1);
                 pnl = pnl < p.npanels ? pnl : p.npanels - 1; // panels past N: read a valid panel, never stored
@@ -2036,9 +2119,10 @@ struct DeepCfg {
 // atomic adds; 2 K split, the parts store their partial tiles (row terms taken off already) to
 // p.part_ws and splitk_reduce_kernel forms the output (any output type).
 template <int T, int SUB, int NSTAGE, bool REQUANT, int SPLITK = 0, bool ROWS = false>
-__global__ __launch_bounds__(256) void gemm_tile_deep_kernel(const GemmParams p)
+__global__ __launch_bounds__(256) void gemm_tile_deep_kernel(const GemmArgs a)
 {
     using Cfg = DeepCfg<T, SUB, NSTAGE>;
+    const GemmParams p = params_of<1, Cfg::BMN, Cfg::BMN, false, SPLITK != 0>(a);
     constexpr int BMN = Cfg::BMN, LPS = Cfg::kLoadsPerStage;
     constexpr int NF = 2 * SUB;                          // 32-byte steps of K per stage
     constexpr int NM = T * T;                            // matrix ops per such step
@@ -2055,7 +2139,7 @@ __global__ __launch_bounds__(256) void gemm_tile_deep_kernel(const GemmParams p)
     const int nslices = p.Kp / 32;
     const int ntiles = p.tiles_m * p.tiles_n;
     const int nunits = (SPLITK != 0) ? ntiles * p.ksplit : ntiles;
-    const int gsz = gridDim.x, w = blockIdx.x;
+    const int gsz = count_of(a), w = blockIdx.x;
 
     const int t16 = lane >> 2;
     const int a_chunk = ((lane & 3) - (t16 >> 2)) & 3;
@@ -2293,10 +2377,11 @@ constexpr int kReduceWaves = 16;
 __host__ __device__ inline int64_t splitk_part_pitch(int64_t N) { return (N + 3) & ~(int64_t)3; }
 
 template <bool REQUANT>
-__global__ __launch_bounds__(64 * kReduceWaves) void splitk_reduce_kernel(const GemmParams p, int parts)
+__global__ __launch_bounds__(64 * kReduceWaves) void splitk_reduce_kernel(const GemmArgs a)
 {
     __shared__ uint4 red[kReduceWaves][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const GemmParams p = params_of<1, 64, 64, false, true>(a);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = count_of(a), parts = p.ksplit;
     const int64_t ldp = splitk_part_pitch(p.N), quads = ldp / 4;
     const int64_t u = (int64_t)blockIdx.x * 64 + lane;
     const bool ok = u < (int64_t)p.M * quads;
@@ -2408,8 +2493,9 @@ struct S16Cfg {
 // about 40 ns per stage and 0.14 us per tile (3800 drawn shapes of 2 to 130 stages per unit; 4096^3, 256 stages, 213 / 221).  The four registers that this form
 // spills are reloaded once per tile, ahead of its loop.
 template <bool SUMS>
-__global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
+__global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmArgs a)
 {
+    const GemmParams p = params_of<2, 128, 128>(a);
     using Cfg = S16Cfg;
     constexpr int NSTAGE = Cfg::NSTAGE, LPS = Cfg::kLoadsPerStage;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -2421,7 +2507,7 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmParams p)
     const int nfull = p.K / 64 & ~1;                     // stages of the pipelined loop: an even number
     const int nstages = (p.K + 63) / 64;                 // the one or two after them (full, partial) go unpipelined
     const int ntiles = p.tiles_m * p.tiles_n;
-    const int gsz = gridDim.x, w = blockIdx.x;
+    const int gsz = count_of(a), w = blockIdx.x;
 
     const int ft = lane & 15, fc = lane >> 4;
     const int a_off0 = (wm * 64 + (ft ^ (ft >> 3))) * 128 + ((2 * fc) ^ (ft & 7)) * 16;   // chunk 2 fc of the row; chunk 2 fc + 1: ^ 16
@@ -2723,8 +2809,9 @@ struct WaveKCfg {
 // count tiles of 32 TM x 32 TN.
 template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
           bool LOOP = false>
-__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p, const RawB rawb)
+__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmArgs args)
 {
+    const GemmParams p = params_of<ELEM, TM * 32, TN * 32, BRAW>(args);
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
     using Cfg = WaveKCfg<TM, TN, NW, RING>;
     constexpr int LPS = Cfg::kLoadsPerStep, NTHREADS = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
@@ -2757,7 +2844,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
         if (BRAW) {
             int gcol = n0 + 16 * j + t16;
             gcol = gcol < p.N ? gcol : p.N - 1;          // columns past N: read a valid one, never stored
-            b_src[j] = rawb.B + (int64_t)gcol * rawb.ldb + a_chunk * 16;
+            b_src[j] = p.Bp + (int64_t)gcol * args.ldb + a_chunk * 16;
         } else {
             int pnl = n0 / 32 + j;
             pnl = pnl < p.npanels ? pnl : p.npanels - 1; // panels past N: read a valid panel, never stored
@@ -3094,7 +3181,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
             }
         }
     }    if (LOOP) __syncthreads();                           // the partial tiles are read: the next tile's copies may land
-    tile += gridDim.x;
+    tile += count_of(args);
     } while (LOOP && tile < p.tiles_m * p.tiles_n);
 }
 
@@ -3116,7 +3203,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmParams p,
 // fetches the sums of the 16 rows its accumulator registers belong to, and each wavefront takes zb
 // times its share off its partial sums before they are added up.
 template <bool REQUANT, int P, bool ROWSUM_IN = false>
-__device__ __forceinline__ void skinny_body(const GemmParams &p0, int pnl0, int nregs, int *red)
+__device__ __forceinline__ void skinny_body(const GemmParams &p0, int pnl0, int nwaves, int *red)
 {
     GemmParams p = p0;
     if (ROWSUM_IN) {
@@ -3127,8 +3214,7 @@ __device__ __forceinline__ void skinny_body(const GemmParams &p0, int pnl0, int 
     }
     constexpr int BATCH = P >= 4 ? 2 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nwaves = blockDim.x >> 6;
-    const int nslices = p.Kp / 32;
+    const int nregs = 4 * ((p.M + 7) / 8), nslices = p.Kp / 32;
     const int mine = nslices > wave ? (nslices - wave + nwaves - 1) / nwaves : 0;   // fragments of this wavefront
 
     const int row = lane & 31;
@@ -3258,20 +3344,20 @@ __device__ __forceinline__ void skinny_body(const GemmParams &p0, int pnl0, int 
 }
 
 template <bool REQUANT, int P>
-__global__ __launch_bounds__(512) void gemm_skinny_kernel(const GemmParams p, int nregs)
+__global__ __launch_bounds__(512) void gemm_skinny_kernel(const GemmArgs a)
 {
     extern __shared__ int red[];                       // [nwaves][nregs][64]
-    skinny_body<REQUANT, P, true>(p, blockIdx.x * P, nregs, red);     // row sums formed here: no pass before it
+    skinny_body<REQUANT, P, true>(params_of<1, 32, 32>(a), blockIdx.x * P, count_of(a), red);     // row sums formed here: no pass before it
 }
 
-// Grouped form: unit = one 32-column panel of one problem; always 8 wavefronts and room for 16
+// Grouped form: unit = one 32-column panel of one problem; g.nwaves wavefronts and room for 16
 // accumulator registers per wavefront in LDS.
 __global__ __launch_bounds__(512) void gemm_group_skinny_kernel(const GroupParams g)
 {
     extern __shared__ int red[];
     const int q = group_find(g, blockIdx.x);
     const GemmParams p = group_member_params<64, 64>(g.prob[q], g.nxcd);
-    skinny_body<false, 1, true>(p, blockIdx.x - g.unit_start[q], 4 * ((p.M + 7) / 8), red);
+    skinny_body<false, 1, true>(p, blockIdx.x - g.unit_start[q], g.nwaves, red);
 }
 
 // Both kinds of member in one grid (see GroupParams): four wavefronts; a skinny member's panel is
@@ -3286,7 +3372,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_group_kernel(const GroupP
     const int q = group_find(g, blockIdx.x);
     const GemmParams p = group_member_params<BM, BN>(g.prob[q], g.nxcd);
     const int unit = blockIdx.x - g.unit_start[q];
-    if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, 4 * ((p.M + 7) / 8), (int *)lds);
+    if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, WGM * WGN, (int *)lds);
     else tile_body_staged<BM, BN, WGM, WGN, BK, false, true, kGroupRing>(p, unit, lds);
 }
 
@@ -3496,9 +3582,11 @@ __device__ __forceinline__ void stream_body(const GemmParams &p0, int pnl_first,
 
 // Single problem: `chunk` panels per workgroup.
 template <bool REQUANT>
-__global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_skinny_kernel(const GemmParams p, int chunk, int lds_bytes)
+__global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_skinny_kernel(const GemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const GemmParams p = params_of<1, 32, 32>(a);
+    const int chunk = a.kchunk, lds_bytes = a.ksplit;    // (no K split here)
     const int first = blockIdx.x * chunk;
     const int count = p.npanels - first < chunk ? p.npanels - first : chunk;
     stream_body<REQUANT>(p, first, count, chunk, lds_bytes, lds);

@@ -545,10 +545,10 @@ __device__ __forceinline__ void mid_body(const GemmParams &p, int tile, uint8_t 
 }
 
 template <class C, bool REQUANT, bool ROWS, bool AREG>
-__global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_kernel(const GemmParams p)
+__global__ __launch_bounds__(C::kThreads, C::NW / 4 * C::kPerCu) void gemm_mid_kernel(const GemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    mid_body<C, REQUANT, ROWS, AREG>(p, blockIdx.x, lds);
+    mid_body<C, REQUANT, ROWS, AREG>(params_of<1, C::BM, C::BN>(a), blockIdx.x, lds);
 }
 
 // Grouped launches (see GroupParams): the panels of the skinny members, four wavefronts each, then the tiles of the others, whose rows
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(256, C::kPerCu) void gemm_group_mid_kernel(const Gr
     const int q = group_find(g, blockIdx.x);
     const GemmParams p = group_member_params<C::BM, C::BN>(g.prob[q], g.nxcd);
     const int unit = blockIdx.x - g.unit_start[q];
-    if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, 4 * ((p.M + 7) / 8), (int *)lds);
+    if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, C::NW, (int *)lds);
     else mid_body<C, false, true, true>(p, unit, lds);
 }
 
