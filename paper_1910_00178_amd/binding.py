@@ -1,12 +1,14 @@
-"""ctypes binding of the C ABI in include/ngemm.h.  Argument marshalling only.
+"""Binding of the C ABI in include/ngemm.h: argument marshalling only, by ctypes; the calls of every product also
+natively (csrc/calls.c), for arguments of the usual types.
 
 Every function has the name and argument order of its C counterpart.  Device
 pointers may be given as integers or as torch tensors (their data_ptr() is
 taken); a stream may be an integer hipStream_t, a torch.cuda.Stream or None
-(torch's current stream).  There is no CPU fallback: if the library is missing
-or cannot be loaded, importing this module raises.
+(torch's current stream).  There is no CPU fallback: if the library or the native
+calls are missing or cannot be loaded, importing this module raises.
 """
 import ctypes
+import importlib
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -48,6 +50,10 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_1910_00178_amd.build` "
                       "(there is no fallback path)")
 _lib = ctypes.CDLL(LIB_PATH)
+try:
+    _calls = importlib.import_module("._calls", __package__)
+except ImportError as e:
+    raise ImportError(f"the native calls of the binding: {e}; build them with `python -m paper_1910_00178_amd.build`") from e
 
 _i64, _i32, _p, _sz, _f32, _int = (ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_size_t,
                                    ctypes.c_float, ctypes.c_int)
@@ -141,6 +147,7 @@ def _bind_current_stream():
         return raw(device()) if ready() else _slow_current_stream()
 
     _current_stream = fast
+    _calls.streams(raw, device, ready)
 
 
 def _stream(s):
@@ -322,3 +329,16 @@ def ngemm_run_batched_u8s8s32(ctx, problems, workspace_dev=None, workspace_bytes
     _check(_lib.ngemm_run_batched_u8s8s32(ctx, len(problems), problems, _dev(workspace_dev),
                                           int(workspace_bytes), _stream(hip_stream)),
            "ngemm_run_batched_u8s8s32")
+
+
+# The calls above that a program makes per product, weight or batch: natively where all arguments are of the usual types,
+# else through the functions above.
+_calls.setup(_p, ngemm_problem, ctypes.sizeof(ngemm_problem), _check)
+for _name, _kind in (("ngemm_run_u8s8s32", "run"), ("ngemm_run_s8s8s32", "run"), ("ngemm_run_u8u8s32", "run"), ("ngemm_run_s16s16s32", "run"),
+                     ("ngemm_run_u8s8s32_static", "static"), ("ngemm_run_u8s8u8_requant", "requant"),
+                     ("ngemm_run_u8s8u8_requant_channel", "channel"), ("ngemm_run_u8s8s32_unpacked", "unpacked"),
+                     ("ngemm_run_batched_u8s8s32", "batched"), ("ngemm_pack_b", "pack"), ("ngemm_pack_b_u8", "pack"),
+                     ("ngemm_pack_b_s16", "pack"), ("ngemm_packed_b_free", "free")):
+    _slow = globals()[_name]
+    globals()[_name] = _calls.Call(_slow, _kind, ctypes.cast(getattr(_lib, _name), _p).value)
+    globals()[_name].__dict__.update(__doc__=_slow.__doc__, __module__=_slow.__module__, __qualname__=_slow.__qualname__)

@@ -1,12 +1,15 @@
-"""Compile the HIP library (hipcc, gfx950) in-tree.  `python -m paper_1910_00178_amd.build`."""
+"""Compile the HIP library (hipcc, gfx950) and the binding's native calls in-tree.  `python -m paper_1910_00178_amd.build`."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "ngemm.hip")
 LIB = os.path.join(HERE, "libngemm.so")
+CALLS_SRC = os.path.join(HERE, "csrc", "calls.c")
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -19,21 +22,28 @@ FLAGS = [
 ]
 
 
-def _compile(src, lib, verbose):
-    cmd = [HIPCC, *FLAGS, "-o", lib, src]
+CC = os.environ.get("CC", "gcc")
+CALLS_FLAGS = ["-O2", "-std=gnu11", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-cast-function-type", "-Wno-missing-field-initializers",
+               "-I" + sysconfig.get_path("include")]
+
+
+def _compile(cmd, src, lib, verbose):
+    cmd = [*cmd, "-o", lib, src]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(cmd[0] + " failed:\n" + out)
     if verbose and out.strip():
         print(out)
     return lib
 
 
 def build_library(verbose=False):
-    return _compile(SRC, LIB, verbose)
+    """The HIP library, and the binding's native calls beside it."""
+    _compile([CC, *CALLS_FLAGS], CALLS_SRC, CALLS, verbose)
+    return _compile([HIPCC, *FLAGS], SRC, LIB, verbose)
 
 
 if __name__ == "__main__":

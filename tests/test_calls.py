@@ -1,0 +1,164 @@
+"""The binding's native calls: what reaches the C function, and which arguments are left to the Python function."""
+import copy
+import ctypes
+import inspect
+import pickle
+
+import pytest
+
+L, I, P, Z, F, INT = ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float, ctypes.c_int
+RUN = [P, L, P, L, I, P, I, P, L]
+WS = [P, Z, P]
+KINDS = {                                                # the C functions' arguments as include/ngemm.h declares them
+    "run": RUN + WS, "static": RUN + [P], "requant": RUN[:7] + [F, I, P, L] + WS,
+    "channel": RUN[:7] + [P, P, P, I, I, P, L] + WS, "unpacked": [P, L, L, L, P, L, I, P, L, I, P, L] + WS,
+    "batched": [P, INT, P] + WS, "pack": [P, L, L, P, L, P, Z, P, ctypes.POINTER(P)], "free": [P],
+}
+NAMES = {"run": "ngemm_run_u8s8s32", "static": "ngemm_run_u8s8s32_static", "requant": "ngemm_run_u8s8u8_requant",
+         "channel": "ngemm_run_u8s8u8_requant_channel", "unpacked": "ngemm_run_u8s8s32_unpacked",
+         "batched": "ngemm_run_batched_u8s8s32", "pack": "ngemm_pack_b", "free": "ngemm_packed_b_free"}
+
+
+class Tensor:
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+class Stream:
+    cuda_stream = 0x5eed
+
+
+@pytest.fixture()
+def both():
+    """both(kind, status) -> (native call, what the C function saw, what the Python function was given)"""
+    from paper_1910_00178_amd import binding
+    keep = []
+
+    def make(kind, status=0):
+        seen, given = [], []
+
+        def c(*a):
+            seen.append(a)
+            if kind == "pack":
+                a[-1][0] = 0x1234
+            return status
+
+        def slow(*a, **kw):
+            given.append((a, kw))
+            return "slow"
+        slow.__name__ = NAMES[kind]
+        fn = ctypes.CFUNCTYPE(INT, *KINDS[kind])(c)
+        keep.append(fn)
+        return binding._calls.Call(slow, kind, ctypes.cast(fn, P).value), seen, given
+    yield make
+    binding._calls.streams(None, None, None)
+
+
+def usual(kind):
+    """Arguments of the usual types for every parameter of the Python function, and what the C function has to see."""
+    from paper_1910_00178_amd import binding
+    fn = getattr(binding, NAMES[kind])
+    problems = binding.make_problems([(1, 2, 3, 4, 5, 6, 7, 8)] * 3)
+    args, want = [], []
+    for n, name in enumerate(inspect.signature(fn).parameters):
+        at = 0x1000 * (n + 1)
+        if name in ("ctx", "B", "b"): a, w = P(at), at
+        elif name == "problems":
+            a, w = problems, ctypes.addressof(problems)
+            want.append(3)
+        elif name == "hip_stream": a, w = Stream(), 0x5eed
+        elif name == "scale": a, w = 0.1, F(0.1).value
+        elif name == "relu": a, w = True, 1
+        elif name.endswith("_zero_point"): a, w = -3 - n, -3 - n
+        elif name.endswith(("_dev",)): a, w = Tensor(at), at
+        else: a, w = (1 << 40) + n, (1 << 40) + n
+        args.append(a)
+        want.append(w)
+    return args, want
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_native_call(both, kind):
+    call, seen, given = both(kind)
+    args, want = usual(kind)
+    out = call(*args)
+    assert not given and len(seen) == 1 and list(seen[0])[:len(want)] == want
+    if kind == "pack":
+        assert type(out) is P and out.value == 0x1234
+    else:
+        assert out is None
+    # handles as integers, empty pointers
+    call(*[a.value if type(a) is P else None if isinstance(a, Tensor) else a for a in args])
+    assert not given and list(seen[1])[:len(want)] == [None if isinstance(a, Tensor) else w for a, w in
+                                                       zip(args if kind != "batched" else [None] + args, want)]
+    # every other way of saying it goes to the Python function untouched, nothing having been called
+    others = {P: ("0", 1.5, -1), Tensor: ("0", 1.5, -1, object()), Stream: ("0", 1.5, -1), float: (1, "x"), bool: ("x", None), int: (1.0, "1", 1 << 70, True)}
+    for n, a in enumerate(args):
+        for other in others.get(type(a), (None, 1, object(), (ctypes.c_int * 3)())):
+            bad = args[:n] + [other] + args[n + 1:]
+            assert call(*bad) == "slow" and given.pop()[0] == tuple(bad)
+    if kind != "free":
+        params = list(inspect.signature(call).parameters)
+        assert params == list(inspect.signature(call.__wrapped__).parameters)
+        assert call(*args[:1], **{"x": 1}) == "slow" and given.pop()[1] == {"x": 1}
+    assert call() == "slow" and call(*args, 1) == "slow"
+    assert len(seen) == 2
+
+
+def test_defaults_and_stream(both):
+    from paper_1910_00178_amd import binding
+    call, seen, given = both("run")
+    args, _ = usual("run")
+    assert call(*args[:9]) == "slow"                      # the current stream is not known yet: the Python function finds it
+    up = [True]
+    binding._calls.streams(lambda d: 0x100 + d, lambda: 7, lambda: up[0])
+    assert call(*args[:9]) is None and seen[-1][9:] == (None, 0, 0x107)
+    assert call(*args[:11], None) is None and seen[-1][11] == 0x107
+    assert call(*args[:11], 0) is None and seen[-1][11] is None
+    up[0] = False                                         # not initialised, or a forked child
+    n = len(seen)
+    assert call(*args[:9]) == "slow" and len(seen) == n
+    assert len(given) == 2
+
+
+def test_whole_numbers_at_their_ends(both):
+    call, seen, given = both("run")
+    args, _ = usual("run")
+    for n, lo, hi in ((1, -2**63, 2**63 - 1), (4, -2**31, 2**31 - 1), (10, 0, 2**63 - 1)):
+        for v in (lo, hi):
+            call(*args[:n], v, *args[n + 1:])
+            assert not given and seen[-1][n] == v
+        for v in (lo - 1, hi + 1):
+            assert call(*args[:n], v, *args[n + 1:]) == "slow" and given.pop()
+
+
+def test_errors_and_interrupts(both):
+    from paper_1910_00178_amd import binding
+    call, _, _ = both("run", status=-2)
+    args, _ = usual("run")
+    with pytest.raises(binding.NgemmError, match="ngemm_run_u8s8s32: bad shape") as e:
+        call(*args)
+    assert e.value.status == -2
+
+    class Interrupted:
+        def data_ptr(self):
+            raise KeyboardInterrupt
+    with pytest.raises(KeyboardInterrupt):
+        call(*args[:2], Interrupted(), *args[3:])
+
+
+def test_binding_holds_them():
+    import paper_1910_00178_amd as ng
+    from paper_1910_00178_amd import binding
+    for kind, name in NAMES.items():
+        fn = getattr(ng, name)
+        assert type(fn) is binding._calls.Call and fn.__name__ == name and inspect.signature(fn) == inspect.signature(fn.__wrapped__)
+        assert fn.__module__ == binding.__name__ and copy.copy(fn) is fn
+        assert pickle.loads(pickle.dumps(fn)) is fn
+    with pytest.raises(TypeError):
+        ng.ngemm_run_u8s8s32(None)
+    with pytest.raises(ValueError):
+        binding._calls.Call(print, "nothing", 1)
