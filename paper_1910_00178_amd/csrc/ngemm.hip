@@ -69,6 +69,14 @@ inline bool x64_offsets_fit(int64_t rows, int64_t pitch, int64_t extent)
     return pitch < (1ll << 32) && (rows - 1) * pitch + extent + 4096 < (1ll << 32);
 }
 
+// gemm_wavek_kernel counts in 31 bits, from a row of at most 64 of A and from one of at most four panels of 32 columns of B
+// (unpacked: rows of it)
+inline bool wavek_offsets_fit(int64_t lda_bytes, int64_t kbytes, int64_t Kp, int64_t ldb = 0)
+{
+    constexpr int64_t most = (1ll << 31) - 8192;
+    return lda_bytes < most / 64 && 64 * lda_bytes + kbytes < most && Kp < most / 128 && ldb < most / 128 && 128 * ldb + kbytes < most;
+}
+
 struct DeviceGuard {
     int prev = -1;
     bool ok = false;
@@ -682,8 +690,9 @@ bool wavek_fits(int form, int64_t M, int64_t N, int64_t budget, int64_t cus)
 
 // The form that takes the place of `kernel` (the streaming kernel, 64 x 64 tiles, 128 x 128 tiles with aligned rows), or 0.
 // budget: workgroups that the caller allows (the kernels for unaligned rows launch one per tile whichever runs).
-int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, int64_t cus, int64_t budget)
+int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, int64_t cus, int64_t budget)
 {
+    if (!wavek_offsets_fit(lda, K, round_up(K, 64))) return 0;
     const bool small = kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64;
     if (!aligned) return small ? wavek_areg_form(M, N, K, cus) : 0;
     const int form = small || kernel == NGEMM_KERNEL_TILE_128 ? wavek_form(M, N, K, rows, cus) : 0;
@@ -939,7 +948,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 r = Route{t.kernel, false};
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
-                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0 ||
+                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0 ||
                                 mid_form(NGEMM_KERNEL_AUTO, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus,
                                          workgroup_budget(ctx)) != 0))
                     r = Route{small, true, true};
@@ -1015,7 +1024,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
     // outputs of few tiles: K split over the wavefronts of a workgroup; of many: the kernel of tiles between those of the others
     if (route.wavek) {
-        const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, device_cus, num_cus);
+        const int form = wavek_form_of(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, device_cus, num_cus);
         if (form != 0) {
             const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
@@ -1264,7 +1273,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
             if (!dma_ok || splitk_parts(M, B->N, B->K, workgroup_budget(ctx), &kchunk) < 2) continue;
         }
         const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, cus, workgroup_budget(ctx)) == 0 &&
+        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, cus, workgroup_budget(ctx)) == 0 &&
             mid_form(NGEMM_KERNEL_AUTO, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
@@ -1567,7 +1576,8 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     // the looping form walk several tiles per workgroup.
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256, budget = workgroup_budget(ctx);
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((B->N + bn - 1) / bn); };
-    auto fits = [&](int64_t n) { return budget >= cus || n <= budget; };
+    const bool near = wavek_offsets_fit(p.lda, 2 * B->K, B->Kp);       // else the looping form, with addresses of 64 bits, in its place
+    auto fits = [&](int64_t n) { return near && (budget >= cus || n <= budget); };
     hipError_t e;
     if (tiles(32, 32) <= cus && fits(tiles(32, 32))) {
         e = launch_wavek<WaveK11, 2, false, true>(p, st);
@@ -1576,8 +1586,9 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     } else if (B->K < S16Cfg::kMinK && !fits(tiles(64, 64))) {
         p.tiles_m = (int)((M + 63) / 64);
         p.tiles_n = (int)((B->N + 63) / 64);
-        hipLaunchKernelGGL((gemm_wavek_kernel<2, 2, 2, WaveK22::NW, WaveK22::RING, false, true, false, false, false, true>), dim3((unsigned)budget),
-                           dim3(WaveK22::NW * 64), (WaveKCfg<2, 2, WaveK22::NW, WaveK22::RING>::kLdsBytes), st, args_of(p, (int)budget));
+        const int64_t nwg = tiles(64, 64) < budget ? tiles(64, 64) : budget;
+        hipLaunchKernelGGL((gemm_wavek_kernel<2, 2, 2, WaveK22::NW, WaveK22::RING, false, true, false, false, false, true>), dim3((unsigned)nwg),
+                           dim3(WaveK22::NW * 64), (WaveKCfg<2, 2, WaveK22::NW, WaveK22::RING>::kLdsBytes), st, args_of(p, (int)nwg));
         e = hipGetLastError();
     } else if (B->K < S16Cfg::kMinK || (tiles(64, 64) <= 2 * cus && tiles(128, 128) * 2 <= cus && fits(tiles(64, 64)))) {
         e = launch_wavek<WaveK22, 2, false, true>(p, st);
@@ -1632,7 +1643,8 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128 || kernel == NGEMM_KERNEL_SKINNY;
     // the kernel that splits K over a workgroup's wavefronts: of the automatic choice only
     int form = aligned && K > 0 && small_kernel && ctx->force_kernel == NGEMM_KERNEL_AUTO ? wavek_raw_form(M, N, K, cus) : 0;
-    if ((kernel == NGEMM_KERNEL_TILE_128 && form != 24) || !wavek_fits(form, M, N, workgroup_budget(ctx), cus)) form = 0;
+    if ((kernel == NGEMM_KERNEL_TILE_128 && form != 24) || !wavek_fits(form, M, N, workgroup_budget(ctx), cus) ||
+        !wavek_offsets_fit(lda, K, 0, ldb)) form = 0;
     if (aligned && K > 0 && (form != 0 || kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return NGEMM_ERR_DEVICE;

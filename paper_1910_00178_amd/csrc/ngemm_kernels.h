@@ -536,18 +536,32 @@ struct TileCfg {
 // share A row-panels and B column-panels.
 __device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int nxcd, int &tm, int &tn)
 {
-    const int nb = tiles_m * tiles_n;
-    const int q = nb / nxcd, r = nb - q * nxcd;
-    const int local = bid / nxcd, xcd = bid - local * nxcd;
-    const int logical = xcd * q + (xcd < r ? xcd : r) + local;
-    constexpr int GM = 4;
-    const int per_group = GM * tiles_n;
-    const int group = logical / per_group;
-    const int first_m = group * GM;
-    const int gsize = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
-    const int in_group = logical - group * per_group;
-    tm = first_m + in_group % gsize;
-    tn = in_group / gsize;
+    // (a division by a number that only the launch knows is 25 dependent instructions ahead of a workgroup's first load, some 50 ns: a
+    // power of two of XCDs, up to GM tile rows and the last division, by at most GM, do without)
+    const unsigned nb = (unsigned)tiles_m * (unsigned)tiles_n, n = (unsigned)nxcd, ubid = (unsigned)bid;
+    unsigned q, local;
+    if ((n & (n - 1)) == 0) {
+        const int sh = __builtin_ctz(n);
+        q = nb >> sh;
+        local = ubid >> sh;
+    } else {
+        q = nb / n;
+        local = ubid / n;
+    }
+    const unsigned r = nb - q * n, xcd = ubid - local * n;
+    const unsigned logical = xcd * q + (xcd < r ? xcd : r) + local;
+    constexpr unsigned GM = 4;
+    unsigned group = 0, in_group = logical;
+    if ((unsigned)tiles_m > GM) {
+        const unsigned per_group = GM * (unsigned)tiles_n;
+        group = logical / per_group;
+        in_group = logical - group * per_group;
+    }
+    const unsigned first_m = group * GM, left = (unsigned)tiles_m - first_m, gsize = left < GM ? left : GM;
+    const unsigned third = (unsigned)(((uint64_t)in_group * 0xaaaaaaabu) >> 33), shifted = in_group >> (gsize >> 1);       // 1, 2, 4: by 0, 1, 2
+    const unsigned col = gsize == 3 ? third : shifted;
+    tm = (int)(first_m + in_group - col * gsize);
+    tn = (int)col;
 }
 
 // Workgroup barrier that orders LDS traffic only: outstanding global loads (the prefetch of a
@@ -2784,6 +2798,12 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmArgs a)
 // AREG: rows of A with any alignment, which copies into LDS cannot fetch: A comes through registers (two steps on
 // their way, written into the ring two steps before they are read); everything else stays (64 x 4096 x 4097
 // 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).
+// Calls of 3 to 5 us are a launch (2.1 us) and what every wavefront does one after the other, so that is kept short: the copies go out
+// first, from lane offsets that stay (a step adds a scalar), the column terms behind them (they were waited for ahead of the first copy: a trip to
+// memory); the step that K ends in is one of the ring (it was fetched behind the others: another trip); the last steps, with fewer and
+// fewer copies on their way, are laid out one by one instead of copying once more what nobody reads.  us in a graph, three inputs in turn,
+// before / so: 1 x 4096 x 1024 3.80 / 3.26, 16 x 1088 x 384 3.42 / 3.00, 64 x 4096 x 4096 z 7.07 / 6.47, 256 x 320 x 260 u8 z 4.40 / 3.69, 16-bit
+// 512 x 768 x 768 6.11 / 5.37, 64 x 94 x 186 4.46 / 3.93, unaligned 54 x 2556 x 331 u8 5.03 / 3.62; 13000 drawn calls 1.10 x.
 // NT: non-temporal copies of B, for weights that are read once (the rule that chooses it has the figures).
 // LOOP: fewer workgroups than tiles, for a caller that caps them (the others launch a workgroup per tile).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
@@ -2800,114 +2820,272 @@ struct WaveKCfg {
     static constexpr int kPartBytes = TM * 32 * kPitch * 4;
     static constexpr int kEpiBytes = NW * (kPartBytes + (TM + TN) * 32 * 4);
     static constexpr int kLdsBytes = NW * kWaveBytes > kEpiBytes ? NW * kWaveBytes : kEpiBytes;
+    static constexpr int kPerCu = 160 * 1024 / kLdsBytes;  // workgroups that share a compute unit: their registers have to fit as well
+    static constexpr int kWavesPerSimd = NW * kPerCu >= 4 ? NW * kPerCu / 4 : 1;
     static_assert((RING - 1) * kLoadsPerStep <= 63, "vmcnt range");
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
     static_assert(RING >= 3, "copies in flight");
 };
 
 // p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
-// count tiles of 32 TM x 32 TN.
+// count tiles of 32 TM x 32 TN.  Offsets from a tile's first row and panel have to stay below 2 GiB, but for LOOP.
 template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
           bool LOOP = false>
-__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmArgs args)
+__device__ __forceinline__ void wavek_body(const GemmArgs &args)
 {
-    const GemmParams p = params_of<ELEM, TM * 32, TN * 32, BRAW>(args);
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
+    static_assert(!NT || (!BRAW && !AREG), "packed B, aligned rows of A");
+    static_assert(!AREG || (RING == 4 && !LOOP), "register sets and places of the ring in step");
     using Cfg = WaveKCfg<TM, TN, NW, RING>;
     constexpr int LPS = Cfg::kLoadsPerStep, NTHREADS = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
+    constexpr int AL = 2 * TM, BL = 2 * TN, NB = BRAW ? BL : TN;     // copies of A and of B per step, B's row blocks or panels
+    constexpr bool BREG = BRAW && AREG;                  // rows of either operand with any alignment
+    const GemmParams p = params_of<ELEM, TM * 32, TN * 32, BRAW>(args);
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nfrag = p.Kp / 32;                         // fragments per panel
     const int kbytes = p.K * ELEM;
-    const int nfull = kbytes / 64;                       // full steps, all wavefronts together
-    const int cnt = nfull > wave ? (nfull - wave + NW - 1) / NW : 0;      // this wavefront's: wave, wave + NW, ...
+    const int nsteps = (int)((unsigned)(kbytes + 63) / 64);          // all wavefronts together
+    const int cnt = nsteps > wave ? (int)((unsigned)(nsteps - wave + NW - 1) / NW) : 0;       // this wavefront's: wave, wave + NW, ...
+    // The last step may reach past K.  The pack is zero there, so what A holds does not matter (but for the row sums, which leave it out).
+    // t_end: which of this wavefront's steps it is, -1: none of them; the `full` others are copied as they lie.
+    const int kend = (nsteps - 1) * 64;
+    const int t_end = (kbytes & 63) != 0 && cnt > 0 && (cnt - 1) * NW + wave == nsteps - 1 ? cnt - 1 : -1, full = t_end >= 0 ? t_end : cnt;
     int tile = blockIdx.x;
     do {                                                 // (one pass but for LOOP; to the end of the kernel)
     int tm, tn;
     tile_of_block(tile, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
     const int m0 = tm * (TM * 32), n0 = tn * (TN * 32);
 
-    // copies of a step: 16-row blocks of A (row t of the block, chunk c in slot 4 t + (c + t / 4) % 4), then
-    // the two fragments of each panel of B as they lie in the pack
+    // ---- copies ----
+    // Of a step: 16-row blocks of A (row t of the block, chunk c in slot 4 t + (c + t / 4) % 4), then the two fragments of each panel of B
+    // as they lie in the pack.  A lane's offsets from the tile's first row and panel stay, the step is added as a scalar; up to four copies
+    // share the LDS base (M0) and carry 1024 * i as immediate offset, which counts for the memory address as well (the lane offsets
+    // take it back, + kBias, never negative; the descriptors' bases start kBias early, an address only).
+    constexpr uint32_t kBias = 3 * 1024, kExtent = 0x80000000u;      // an offset of kExtent and more: not read
     const int t16 = lane >> 2, a_chunk = ((lane & 3) - (t16 >> 2)) & 3;
-    constexpr int NB = BRAW ? 2 * TN : TN;
-    const uint8_t *a_src[2 * TM], *b_src[NB];
+    const uint8_t *a_tile = p.A + (int64_t)m0 * p.lda;
+    const uint8_t *b_tile = BRAW ? p.Bp + (int64_t)n0 * args.ldb : p.Bp + (int64_t)(n0 / 32) * nfrag * kFragBytes;
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)a_tile - kBias), (short)0, (int)kExtent, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)b_tile - kBias), (short)0, (int)kExtent, 0x00020000);
+    auto row_of = [&](int i) { return 16 * i + t16 < p.M - m0 ? 16 * i + t16 : p.M - 1 - m0; };     // rows past M: a valid one, never stored
+    auto col_of = [&](int j) { return 16 * j + t16 < p.N - n0 ? 16 * j + t16 : p.N - 1 - n0; };     // (unpacked B)
+    uint32_t a_off[AL], b_off[NB];
 #pragma unroll
-    for (int i = 0; i < 2 * TM; ++i) {
-        int grow = m0 + 16 * i + t16;
-        grow = grow < p.M ? grow : p.M - 1;              // rows past M: read a valid row, never stored
-        a_src[i] = p.A + (int64_t)grow * p.lda + a_chunk * 16;
+    for (int i = 0; i < AL; ++i) {
+        a_off[i] = (uint32_t)row_of(i) * (uint32_t)p.lda + (uint32_t)(a_chunk * 16) + (AREG ? 0u : kBias - 1024u * i);
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        if (BRAW) {
-            int gcol = n0 + 16 * j + t16;
-            gcol = gcol < p.N ? gcol : p.N - 1;          // columns past N: read a valid one, never stored
-            b_src[j] = p.Bp + (int64_t)gcol * args.ldb + a_chunk * 16;
-        } else {
-            int pnl = n0 / 32 + j;
-            pnl = pnl < p.npanels ? pnl : p.npanels - 1; // panels past N: read a valid panel, never stored
-            b_src[j] = p.Bp + ((int64_t)pnl * nfrag) * kFragBytes + lane * 16;
+        const int pnl = n0 / 32 + j < p.npanels ? j : p.npanels - 1 - n0 / 32;       // panels past N: a valid one, never stored
+        if constexpr (BRAW) b_off[j] = (uint32_t)col_of(j) * (uint32_t)args.ldb + (uint32_t)(a_chunk * 16) + (BREG ? 0u : kBias - 1024u * (j & 3));
+        else b_off[j] = (uint32_t)pnl * (uint32_t)(nfrag * kFragBytes) + (uint32_t)(lane * 16) + kBias - 2048u * (j & 1);
+    }
+    uint8_t *ring = lds + wave * Cfg::kWaveBytes;
+    // In the step that K ends in, a lane whose 16 bytes of a row lie past K reads nothing; one whose 16 bytes reach past the end of
+    // the operand (fix) fetches the row's last 16 instead, behind the first copies, and puts those that exist in place at the end.
+    const int vend = kbytes - (kend + a_chunk * 16);     // bytes of this lane's 16 that exist
+    constexpr int NFB = BRAW ? BL : 1;
+    bool fix_a[AL], fix_b[NFB];
+    v4i fixv_a[AL], fixv_b[NFB];
+#pragma unroll
+    for (int i = 0; i < AL; ++i) fix_a[i] = false;
+#pragma unroll
+    for (int j = 0; j < NFB; ++j) fix_b[j] = false;
+    // (rows shorter than 16 bytes: more than the last one reach past the end)
+    const bool fixes = t_end >= 0 && (kbytes & 15) != 0 && (m0 + TM * 32 + 15 >= p.M || (BRAW && n0 + TN * 32 + 15 >= p.N));
+    if (fixes && vend > 0 && vend < 16) {
+#pragma unroll
+        for (int i = 0; i < AL; ++i) fix_a[i] = (int64_t)(p.M - 1 - m0 - row_of(i)) * p.lda + vend < 16;
+        if constexpr (BRAW) {
+#pragma unroll
+            for (int j = 0; j < BL; ++j) fix_b[j] = (int64_t)(p.N - 1 - n0 - col_of(j)) * args.ldb + vend < 16;
         }
     }
-    // memory of copy j (0 .. 2 TN - 1) of B's part of full step g
-    auto b_mem = [&](int j, int g) {
-        if constexpr (BRAW) return b_src[j] + (int64_t)g * 64;
-        else return b_src[j >> 1] + (int64_t)g * (2 * kFragBytes) + (j & 1) * kFragBytes;
+    auto fix_of = [&](const uint8_t *chunk) {            // (a row of less than 16 bytes has no others before its end)
+        return kbytes < 16 ? load16_partial(chunk, vend) : load16_any(chunk + vend - 16);
     };
-    uint8_t *ring = lds + wave * Cfg::kWaveBytes;
-    auto step_of = [&](int t) { return (t < cnt ? t : cnt - 1) * NW + wave; };       // past the end: copies nobody reads
-    auto dma_a = [&](int t, int slot) {
-        const int g = step_of(t);
+    auto load_fix = [&]() {
+        if (vend <= 0 || vend >= 16) return;
 #pragma unroll
-        for (int i = 0; i < 2 * TM; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + (int64_t)g * 64),
-                                             (lptr_t)(ring + slot * Cfg::kStepBytes + i * 1024), 16, 0, 0);
-    };
-    auto dma_b = [&](int t, int slot) {
-        const int g = step_of(t);
+        for (int i = 0; i < AL; ++i)
+            if (fix_a[i]) fixv_a[i] = fix_of(a_tile + (int64_t)row_of(i) * p.lda + a_chunk * 16 + kend);
+        if constexpr (BRAW) {
 #pragma unroll
-        for (int j = 0; j < 2 * TN; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)b_mem(j, g), (lptr_t)(ring + slot * Cfg::kStepBytes + (2 * TM + j) * 1024), 16, 0, NT ? kCopyNT : 0);
+            for (int j = 0; j < BL; ++j)
+                if (fix_b[j]) fixv_b[j] = fix_of(b_tile + (int64_t)col_of(j) * args.ldb + a_chunk * 16 + kend);
+        }
     };
-    // AREG: A of step t waits in register set t % 2
-    static_assert(!AREG || RING == 4, "a step's register set is free again when the step four on is requested");
-    v4i va[2][2 * TM];
-    auto load_a = [&](auto set, int t) {
+    // Step t to ring offset `slot`.  From the step that K ends in on (AREG: what is requested past the last step is counted, but not read)
+    // the offsets are others.
+    auto turn = [&](int t) {
+        if constexpr (!AREG) {                           // (rows through registers keep their offsets)
+#pragma unroll
+            for (int i = 0; i < AL; ++i) a_off[i] = vend > 0 && !fix_a[i] ? a_off[i] : kExtent;
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if constexpr (BRAW) b_off[j] = vend > 0 && !fix_b[j] ? b_off[j] : kExtent;
+            else if constexpr (AREG) b_off[j] = t == t_end ? b_off[j] : kExtent;
+        }
+    };
+    auto copies_a = [&](int t, int slot) {
+        static_for<0, AL>([&](auto n) {
+            constexpr int I = decltype(n)::value;
+            if constexpr (LOOP) {
+                const uint8_t *src = a_tile + (int64_t)row_of(I) * p.lda + a_chunk * 16 + (int64_t)(t * NW + wave) * 64;
+                if (t >= full && (vend <= 0 || fix_a[I])) src = p.Bp;
+                __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(ring + slot + I * 1024), 16, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lptr_t)(ring + slot), 16, a_off[I], (t * NW + wave) * 64, I * 1024, 0);
+            }
+        });
+    };
+    auto copies_b = [&](int t, int slot) {
+        static_for<0, BL>([&](auto n) {
+            constexpr int J = decltype(n)::value;
+            if constexpr (LOOP) {
+                const int pnl = n0 / 32 + (J >> 1) < p.npanels ? n0 / 32 + (J >> 1) : p.npanels - 1;
+                const uint8_t *src = p.Bp + ((int64_t)pnl * nfrag + 2 * (t * NW + wave) + (J & 1)) * kFragBytes + lane * 16;
+                __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(ring + slot + (AL + J) * 1024), 16, 0, 0);
+            } else
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lptr_t)(ring + slot + (AL + (J & ~3)) * 1024), 16, b_off[BRAW ? J : J >> 1],
+                                                         (t * NW + wave) * (BRAW ? 64 : 2 * kFragBytes), (J & 3) * 1024, NT ? kCopyNT : 0);
+        });
+    };
+    auto request = [&](int t, int slot) {
+        if (!LOOP && !BREG && __builtin_expect(t >= full, 0)) turn(t);
+        if constexpr (!AREG) copies_a(t, slot);
+        if constexpr (!BREG) copies_b(t, slot);
+    };
+    auto apply_fix = [&](int slot) {
+        auto put = [&](const v4i &v, int block) {        // the row's last 16 bytes, down by those that lie before this lane's
+            const uint64_t lo = (uint64_t)(uint32_t)v.x | (uint64_t)(uint32_t)v.y << 32, hi = (uint64_t)(uint32_t)v.z | (uint64_t)(uint32_t)v.w << 32;
+            const int by = kbytes < 16 ? 0 : 8 * (16 - vend);        // 0 .. 120 bits
+            const uint64_t l = by == 0 ? lo : by < 64 ? lo >> by | hi << (64 - by) : hi >> (by - 64), h = by < 64 ? hi >> by : 0;
+            *(v4i *)(ring + slot + block * 1024 + lane * 16) = v4i{(int)(uint32_t)l, (int)(uint32_t)(l >> 32), (int)(uint32_t)h, (int)(uint32_t)(h >> 32)};
+        };
+#pragma unroll
+        for (int i = 0; i < AL; ++i)
+            if (fix_a[i]) put(fixv_a[i], i);
+        if constexpr (BRAW) {
+#pragma unroll
+            for (int j = 0; j < BL; ++j)
+                if (fix_b[j]) put(fixv_b[j], AL + j);
+        }
+    };
+    // AREG: the rows come through registers, step t through set t % 4
+    v4i va[4][AL], vb[4][BL];
+    auto load_regs = [&](auto set, int t, auto is_full) {            // (past the end: the last full step once more)
         constexpr int S = decltype(set)::value;
-        const int g = step_of(t);
+        if (decltype(is_full)::value == 0 && t >= full) {
+            const bool end = t == t_end;
+            const int at = end ? kend : full > 0 ? ((full - 1) * NW + wave) * 64 : 0;
 #pragma unroll
-        for (int i = 0; i < 2 * TM; ++i) va[S][i] = load16_any(a_src[i] + (int64_t)g * 64);
+            for (int i = 0; i < AL; ++i)                 // (no row, or not all 16 bytes of it: others that exist)
+                va[S][i] = load16_any((end ? vend <= 0 || fix_a[i] : full == 0) ? (const uint8_t *)p.colsum : a_tile + at + a_off[i]);
+            if constexpr (BREG) {
+#pragma unroll
+                for (int j = 0; j < BL; ++j)
+                    vb[S][j] = load16_any((end ? vend <= 0 || fix_b[j] : full == 0) ? (const uint8_t *)p.colsum : b_tile + at + b_off[j]);
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < AL; ++i) va[S][i] = load16_any(a_tile + (int64_t)(t * NW + wave) * 64 + a_off[i]);
+        if constexpr (BREG) {
+#pragma unroll
+            for (int j = 0; j < BL; ++j) vb[S][j] = load16_any(b_tile + (int64_t)(t * NW + wave) * 64 + b_off[j]);
+        }
     };
-    auto write_a = [&](auto set, int slot) {
+    auto write_regs = [&](auto set, int slot) {
         constexpr int S = decltype(set)::value;
 #pragma unroll
-        for (int i = 0; i < 2 * TM; ++i) *(v4i *)(ring + slot * Cfg::kStepBytes + i * 1024 + lane * 16) = va[S][i];
+        for (int i = 0; i < AL; ++i) *(v4i *)(ring + slot + i * 1024 + lane * 16) = va[S][i];
+        if constexpr (BREG) {
+#pragma unroll
+            for (int j = 0; j < BL; ++j) *(v4i *)(ring + slot + (AL + j) * 1024 + lane * 16) = vb[S][j];
+        }
     };
-    // fragments of a step: A block i, part x (8-bit: 32-byte half x of the step; 16-bit: chunk x of the lane's
+    // the first copies, ahead of all that they need not wait for
+    __builtin_amdgcn_sched_barrier(0);
+    const bool brief = AREG && cnt <= 4;                 // all of it is asked for at once, nothing later
+    if (cnt > 0) {
+        auto first_regs = [&](auto u) {
+            if (!brief || decltype(u)::value < cnt) load_regs(u, decltype(u)::value, IntC<0>{});
+        };
+        if constexpr (AREG) static_for<0, 2>(first_regs);
+#pragma unroll
+        for (int t = 0; t < RING; ++t)
+            if ((AREG && !brief) || t < cnt) request(t, t * Cfg::kStepBytes);
+        if constexpr (AREG) static_for<2, 4>(first_regs);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // The column terms of this thread's four output columns: asked for now, needed after the loop.
+    constexpr int CG = TN * 8;                           // groups of four columns per row
+    static_assert(NTHREADS % CG == 0, "a thread keeps its columns");
+    const int col = n0 + 4 * (tid % CG);
+    int4 cs = {0, 0, 0, 0}, bias = {0, 0, 0, 0}, zbs = {(int)p.zb, (int)p.zb, (int)p.zb, (int)p.zb};
+    float4 scs = {p.scale, p.scale, p.scale, p.scale};
+    if (col < p.N) {
+        if (!BRAW) cs = *(const int4 *)(p.colsum + col);             // colsum is padded to 32 columns
+        if (REQUANT && col + 4 <= p.N) {
+            if (p.bias_vec) __builtin_memcpy(&bias, p.bias_vec + col, 16);
+            if (p.zb_vec) __builtin_memcpy(&zbs, p.zb_vec + col, 16);
+            if (p.scale_vec) __builtin_memcpy(&scs, p.scale_vec + col, 16);
+        } else if (REQUANT) {                            // the last one to three columns
+            const int c1 = col + 1 < p.N ? col + 1 : col, c2 = col + 2 < p.N ? col + 2 : col;
+            if (p.bias_vec) bias = int4{p.bias_vec[col], p.bias_vec[c1], p.bias_vec[c2], 0};
+            if (p.zb_vec) zbs = int4{p.zb_vec[col], p.zb_vec[c1], p.zb_vec[c2], 0};
+            if (p.scale_vec) scs = float4{p.scale_vec[col], p.scale_vec[c1], p.scale_vec[c2], 1.0f};
+        }
+    }
+    if (__builtin_expect(fixes, 0)) load_fix();
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- fragments ----
+    // of a step: A block i, part x (8-bit: 32-byte half x of the step; 16-bit: chunk x of the lane's
     // 32 bytes), B panel j, part x (half / plane)
     v4i fa[2][TM][2], fb[2][TN][2];
-    int a_off[2];
+    int f_off[2];
     {
         const int r = lane & 31, t = r & 15, h = lane >> 5;
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
             const int c = ELEM == 1 ? 2 * x + h : 2 * h + x;
-            a_off[x] = (r >> 4) * 1024 + (4 * t + ((c + (t >> 2)) & 3)) * 16;
+            f_off[x] = (r >> 4) * 1024 + (4 * t + ((c + (t >> 2)) & 3)) * 16;
         }
     }
     auto read_frags = [&](auto set, int slot) {
         constexpr int S = decltype(set)::value;
-        const uint8_t *base = ring + slot * Cfg::kStepBytes;
+        const uint8_t *base = ring + slot;
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[S][i][x] = *(const v4i *)(base + i * 2048 + a_off[x]);
+            for (int i = 0; i < TM; ++i) fa[S][i][x] = *(const v4i *)(base + i * 2048 + f_off[x]);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                fb[S][j][x] = BRAW ? *(const v4i *)(base + (TM + j) * 2048 + a_off[x])
-                                   : *(const v4i *)(base + (2 * TM + 2 * j + x) * 1024 + lane * 16);
+                fb[S][j][x] = BRAW ? *(const v4i *)(base + (TM + j) * 2048 + f_off[x])
+                                   : *(const v4i *)(base + (AL + 2 * j + x) * 1024 + lane * 16);
+        }
+    };
+    // what the last step holds past K: out of the row sums (there zero, as the shift then counts it), and out of an unpacked B
+    auto mask_end = [&](auto set) {
+        constexpr int S = decltype(set)::value;
+        const int h = lane >> 5;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const v4i e = ~bytes_from(kbytes - (kend + (ELEM == 1 ? 2 * x + h : 2 * h + x) * 16));
+            if (ROWS) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fa[S][i][x] &= e;
+            }
+            if (BRAW) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fb[S][j][x] &= e;
+            }
         }
     };
     v16i acc[NACC][TM][TN];
@@ -2977,114 +3155,107 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmArgs args
         }
     };
 
-    // The column terms of this thread's four output columns: asked for now, needed after the loop.
-    constexpr int CG = TN * 8;                           // groups of four columns per row
-    static_assert(NTHREADS % CG == 0, "a thread keeps its columns");
-    const int col = n0 + 4 * (tid % CG);
-    uint32_t ct[4] = {0u, 0u, 0u, 0u}, zbv[4] = {p.zb, p.zb, p.zb, p.zb};
-    float sc[4] = {p.scale, p.scale, p.scale, p.scale};
-    if (!BRAW && col < p.N) {
-        const int4 cs = *(const int4 *)(p.colsum + col);             // colsum is padded to 32 columns
-        ct[0] = p.za_term * (uint32_t)cs.x; ct[1] = p.za_term * (uint32_t)cs.y;
-        ct[2] = p.za_term * (uint32_t)cs.z; ct[3] = p.za_term * (uint32_t)cs.w;
-        if (REQUANT) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (col + q < p.N) {
-                    if (p.bias_vec) ct[q] += (uint32_t)p.bias_vec[col + q];
-                    if (p.zb_vec) zbv[q] = (uint32_t)p.zb_vec[col + q];
-                    if (p.scale_vec) sc[q] = p.scale_vec[col + q];
-                }
+    // ---- main loop: step t in place t % RING of the ring (offset `cur`), its fragments in set t % 2 ----
+    // Its fragments are in registers, so its place is free: step t + RING is requested into it; the fragments of step t + 1 are read
+    // while its matrix ops run.  AREG: A of step t + 2 is written, the set of step t filled again with step t + RING.
+    int t = 0, cur = 0;
+    // W: steps that may be on their way still when step t + 1 has to be there, -1: no step t + 1; asks: whether it requests
+    // step t + RING, 2: which is a full one (AREG: with A through registers; two steps further ahead K of 5000 and more takes 8 % longer, its lines
+    // leave the vector cache before the next wavefront wants their other half)
+    auto step = [&](auto v, auto w, auto asks) {
+        constexpr int V = decltype(v)::value, X = V & 1, W = decltype(w)::value;
+        constexpr bool ASKS = decltype(asks)::value != 0;
+        const int nxt = cur + Cfg::kStepBytes == Cfg::kWaveBytes ? 0 : cur + Cfg::kStepBytes;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): the fragments of step t are in registers
+        if constexpr (W >= 0 && !BREG) wait_vmcnt<(W >= 0 ? W : 0) * LPS>();
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (W >= 0) read_frags(IntC<X ^ 1>{}, nxt);
+        if constexpr (AREG) {
+            if (!brief) write_regs(IntC<(V + 2) % 4>{}, nxt + Cfg::kStepBytes == Cfg::kWaveBytes ? 0 : nxt + Cfg::kStepBytes);
+            if constexpr (ASKS) load_regs(IntC<V % 4>{}, t + RING, IntC<(decltype(asks)::value > 1)>{});
         }
-    }
-    // The partial step at the end of K belongs to one wavefront.  Its part of B (the pack is zero padded to whole
-    // steps): with NT, a weight that comes from memory, asked for behind the ring's first copies, because after the loop it
-    // would be one more trip there (1 x 4096 x 1000 5.07 -> 4.77 us; loads younger than a step's copies only make its wait
-    // longer).  From cache that costs 0.05 us more than it saves.
-    static_assert(!NT || (!BRAW && !AREG), "packed B, aligned rows of A");
-    v4i tail_b[2 * TN];
-    auto load_tail = [&]() {
-        if (nfull * 64 < kbytes && wave == nfull % NW) {
-#pragma unroll
-            for (int j = 0; j < 2 * TN; ++j) tail_b[j] = *(const v4i *)b_mem(j, nfull);
+        if constexpr (AREG && decltype(asks)::value > 1) {
+            if constexpr (!BREG) copies_b(t + RING, cur);
+        } else if constexpr (ASKS) {
+            request(t + RING, cur);
+        }
+        compute(IntC<X>{});
+        cur = nxt;
+        ++t;
+    };
+    // the step that K ends in: what its copies left out, in place; what lies past K, out of the sums
+    auto finish_end = [&](auto set) {
+        if (__builtin_expect(fixes && !brief, 0)) {
+            wait_vmcnt<0>();
+            apply_fix(cur);
+            read_frags(set, cur);
+        }
+        if (ROWS || BRAW) {
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            mask_end(set);
         }
     };
     if (cnt > 0) {
-        __builtin_amdgcn_sched_barrier(0);
         if constexpr (AREG) {
-            load_a(IntC<0>{}, 0);
-            load_a(IntC<1>{}, 1);
-#pragma unroll
-            for (int t = 0; t < RING; ++t) dma_b(t, t);
-            write_a(IntC<0>{}, 0);
-            write_a(IntC<1>{}, 1);
-            load_a(IntC<0>{}, 2);
-            load_a(IntC<1>{}, 3);
-            wait_vmcnt<(RING - 1) * 2 * TN + 4 * TM>();  // step 0 has landed: younger are B of steps 1 .. 3, A of 2 and 3
-        } else {
-#pragma unroll
-            for (int t = 0; t < RING; ++t) {
-                dma_a(t, t);
-                dma_b(t, t);
-            }
-            if constexpr (NT) load_tail();
-            wait_vmcnt<(RING - 1) * LPS>();              // step 0 has landed
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(IntC<0>{}, 0);
-        // Step t: its fragments are in register set t % 2 (waited for, so its slot is free); the fragments of
-        // step t + 1 are read while its matrix ops run, step t + RING is requested into its slot.
-        auto body = [&](auto set, auto other, int t) {
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0): the fragments of step t are in registers
-            wait_vmcnt<(RING - 2) * LPS>();              // step t + 1 has landed
-            __builtin_amdgcn_sched_barrier(0);
-            read_frags(other, (t + 1) % RING);
-            if constexpr (AREG) {
-                write_a(set, (t + 2) % RING);            // A of step t + 2, requested two steps ago
-                load_a(set, t + RING);
+            if (brief) {
+                static_for<0, 4>([&](auto u) {
+                    if (decltype(u)::value < cnt) write_regs(u, decltype(u)::value * Cfg::kStepBytes);
+                });
+                wait_vmcnt<0>();
+                if (__builtin_expect(fixes, 0)) apply_fix(t_end * Cfg::kStepBytes);
+                __builtin_amdgcn_sched_barrier(0);
+                read_frags(IntC<0>{}, 0);
             } else {
-                dma_a(t + RING, t % RING);
+                write_regs(IntC<0>{}, 0);
+                write_regs(IntC<1>{}, Cfg::kStepBytes);
+                if constexpr (!BREG) wait_vmcnt<3 * BL + 2 * AL>();      // step 0 has landed
+                __builtin_amdgcn_sched_barrier(0);
+                read_frags(IntC<0>{}, 0);
+                while (t + 3 + RING < full) static_for<0, 4>([&](auto u) { step(u, IntC<RING - 2>{}, IntC<2>{}); });
+                static_for<0, 4>([&](auto u) { step(u, IntC<RING - 2>{}, IntC<1>{}); });     // (4 to 7 full ones are left)
             }
-            dma_b(t + RING, t % RING);
-            compute(set);
-        };
-        int t = 0;
-        for (; t + 1 < cnt; t += 2) {
-            body(IntC<0>{}, IntC<1>{}, t);
-            body(IntC<1>{}, IntC<0>{}, t + 1);
+            // The last ones, all asked for.  (What would be loaded here nobody reads: the compiler would leave it out, and the count of what
+            // is on its way would be another.)
+            static_for<0, 4>([&](auto u) {
+                constexpr int V = decltype(u)::value;
+                if (t < full) step(u, IntC<(V < 2 ? 2 - V : 0)>{}, IntC<0>{});
+            });
+            if (t_end >= 0) {                            // (its fragments are in set t % 2)
+                if ((t & 1) == 0) {
+                    finish_end(IntC<0>{});
+                    compute(IntC<0>{});
+                } else {
+                    finish_end(IntC<1>{});
+                    compute(IntC<1>{});
+                }
+            }
+            wait_vmcnt<0>();                             // what was requested past the end has come to nothing
+        } else {
+            if (cnt >= RING) wait_vmcnt<(RING - 1) * LPS>();             // step 0 has landed
+            else if (cnt == 1) wait_vmcnt<0>();
+            else if (cnt == 2) wait_vmcnt<LPS>();
+            else wait_vmcnt<(RING > 3 ? 2 : 0) * LPS>();
+            __builtin_amdgcn_sched_barrier(0);
+            // The last RING steps, with nothing to request and fewer and fewer on their way, are laid out one by one: the set that the first
+            // fragments go to is the one from which they end up in the right ones.
+            if (((cnt ^ RING) & 1) == 0) {
+                read_frags(IntC<0>{}, 0);
+            } else {
+                read_frags(IntC<1>{}, 0);
+                if (cnt > RING) step(IntC<1>{}, IntC<RING - 2>{}, IntC<1>{});
+            }
+            while (cnt - t > RING) static_for<0, 2>([&](auto u) { step(u, IntC<RING - 2>{}, IntC<1>{}); });
+            static_for<0, RING - 1>([&](auto u) {
+                constexpr int R = RING - decltype(u)::value;             // steps left
+                if (cnt - t >= R) step(u, IntC<R - 2>{}, IntC<0>{});
+            });
+            if (t_end >= 0) finish_end(IntC<(RING - 1) & 1>{});
+            step(IntC<RING - 1>{}, IntC<-1>{}, IntC<0>{});
         }
-        if (t < cnt) body(IntC<0>{}, IntC<1>{}, t);
-    } else if constexpr (NT) {
-        load_tail();
     }
-    wait_vmcnt<0>();                                     // drain the copies nobody reads
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_sched_barrier(0);
-    // the partial step at the end of K: guarded register loads into slot 0 by the wavefront whose turn it is
-    // (the pack is zero padded to whole steps)
-    if (nfull * 64 < kbytes && wave == nfull % NW) {
-        const int kbase = nfull * 64;
-#pragma unroll
-        for (int i = 0; i < 2 * TM; ++i) {
-            const int valid = kbytes - (kbase + a_chunk * 16);
-            const uint8_t *src = a_src[i] + kbase;
-            *(v4i *)(ring + i * 1024 + lane * 16) = valid >= 16 ? load16_any(src) : load16_partial(src, valid < 0 ? 0 : valid);
-        }
-#pragma unroll
-        for (int j = 0; j < 2 * TN; ++j) {
-            v4i v;
-            if (BRAW) {
-                const int valid = kbytes - (kbase + a_chunk * 16);
-                v = valid >= 16 ? load16_any(b_mem(j, nfull)) : load16_partial(b_mem(j, nfull), valid < 0 ? 0 : valid);
-            } else {
-                v = NT ? tail_b[j] : *(const v4i *)b_mem(j, nfull);
-            }
-            *(v4i *)(ring + (2 * TM + j) * 1024 + lane * 16) = v;
-        }
-        read_frags(IntC<0>{}, 0);
-        compute(IntC<0>{});
-    }
 
     __syncthreads();                                     // every wavefront is done with its ring
     int *part = (int *)(lds + wave * Cfg::kPartBytes);
@@ -3119,12 +3290,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmArgs args
         }
     }
     __syncthreads();
+    uint32_t ct[4] = {p.za_term * (uint32_t)cs.x + (uint32_t)bias.x, p.za_term * (uint32_t)cs.y + (uint32_t)bias.y,
+                      p.za_term * (uint32_t)cs.z + (uint32_t)bias.z, p.za_term * (uint32_t)cs.w + (uint32_t)bias.w};
+    const uint32_t zbv[4] = {(uint32_t)zbs.x, (uint32_t)zbs.y, (uint32_t)zbs.z, (uint32_t)zbs.w};
     if (BRAW) {                                          // columns past N: never stored
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const int4 cs = *(const int4 *)(csx + w * (TN * 32) + 4 * (tid % CG));
-            ct[0] += p.za_term * (uint32_t)cs.x; ct[1] += p.za_term * (uint32_t)cs.y;
-            ct[2] += p.za_term * (uint32_t)cs.z; ct[3] += p.za_term * (uint32_t)cs.w;
+            const int4 cw = *(const int4 *)(csx + w * (TN * 32) + 4 * (tid % CG));
+            ct[0] += p.za_term * (uint32_t)cw.x; ct[1] += p.za_term * (uint32_t)cw.y;
+            ct[2] += p.za_term * (uint32_t)cw.z; ct[3] += p.za_term * (uint32_t)cw.w;
         }
     }
     // the zero fill of the partial step counts as -128 per element of a shifted operand: taken out again
@@ -3153,10 +3327,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmArgs args
             uint32_t bw;
             if (small_zc) {
                 const float zcf = (float)p.zc;
-                bw = requant4_u8_small_zc(c, float4{sc[0], sc[1], sc[2], sc[3]}, zcf, p.relu ? zcf : -3.402823466e38f);
+                bw = requant4_u8_small_zc(c, scs, zcf, p.relu ? zcf : -3.402823466e38f);
             } else {
-                bw = (uint32_t)requant_u8(c[0], sc[0], p.zc, p.relu) | ((uint32_t)requant_u8(c[1], sc[1], p.zc, p.relu) << 8) |
-                     ((uint32_t)requant_u8(c[2], sc[2], p.zc, p.relu) << 16) | ((uint32_t)requant_u8(c[3], sc[3], p.zc, p.relu) << 24);
+                bw = (uint32_t)requant_u8(c[0], scs.x, p.zc, p.relu) | ((uint32_t)requant_u8(c[1], scs.y, p.zc, p.relu) << 8) |
+                     ((uint32_t)requant_u8(c[2], scs.z, p.zc, p.relu) << 16) | ((uint32_t)requant_u8(c[3], scs.w, p.zc, p.relu) << 24);
             }
             uint8_t *dst = (uint8_t *)p.C + (int64_t)row * p.ldc + col;
             if (col + 3 < p.N) {
@@ -3180,9 +3354,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(const GemmArgs args
                 if (col + 2 < p.N) dst[2] = o.z;
             }
         }
-    }    if (LOOP) __syncthreads();                           // the partial tiles are read: the next tile's copies may land
+    }
+    if (LOOP) __syncthreads();                           // the partial tiles are read: the next tile's copies may land
     tile += count_of(args);
     } while (LOOP && tile < p.tiles_m * p.tiles_n);
+}
+
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
+          bool LOOP = false>
+__global__ __launch_bounds__(NW * 64, (WaveKCfg<TM, TN, NW, RING>::kWavesPerSimd)) void gemm_wavek_kernel(const GemmArgs args)
+{
+    wavek_body<ELEM, TM, TN, NW, RING, REQUANT, ROWS, BRAW, AREG, NT, LOOP>(args);
 }
 
 // ---- skinny-M kernel (M <= 32) --------------------------------------------------------------

@@ -205,3 +205,63 @@ def test_forced_skinny_stays_refused_beyond_its_rows(runner):
             ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, A, K, 0, B, K, 0, C, N, ws, wsb)
     finally:
         runner.set_kernel(ng.NGEMM_KERNEL_AUTO)
+
+
+# Every number of steps of a wavefront around the ends of its ring (four or two wavefronts, 64 bytes a step): the steps that are laid out one by one,
+# the first that are asked for at once, K ending in any of them, within 16 bytes and not; rows of any alignment, whose A comes through registers,
+# and aligned ones.  The allocation ends with the last byte of A.
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "tight"])
+@pytest.mark.parametrize("M,N", [(40, 1100), (13, 8300)])
+def test_u8_every_number_of_steps(runner, M, N, pad):
+    import torch
+    rng = np.random.default_rng(M)
+    Kmax = 64 * (56 if N < 8192 else 30)
+    B = rng.integers(-128, 128, size=(N, Kmax), dtype=np.int8)
+    A = rng.integers(0, 256, size=(M, Kmax), dtype=np.uint8)
+    Bd = torch.from_numpy(B).cuda().double()
+    for k, K in enumerate(sorted({64 * q + r for q in range(Kmax // 64) for r in ((0, 9, 53) if q % 3 else (23, 32))} - {0})):
+        if k % (1 if N < 8192 else 2): continue
+        if pad and K % 16 == 0: K += 3
+        K = min(K, Kmax - 1)
+        za, zb = 131, (0, 5)[k % 2]
+        h, packed = runner.pack(np.ascontiguousarray(B[:, :K]))
+        got = runner.run(np.ascontiguousarray(A[:, :K]), h, N, za=za, zb=zb, lda_pad=0 if pad else -K % 16)
+        want = ((torch.from_numpy(A[:, :K]).cuda().double() - za) @ (Bd[:, :K] - zb).t()).long().int().cpu().numpy()
+        assert np.array_equal(got, want), (K, zb)
+        import paper_1910_00178_amd as ng
+        ng.ngemm_packed_b_free(h)
+
+
+# Pitches at which a tile's rows lie further apart than the kernel counts: the kernels before it, and for 16-bit operands the looping form, serve them.
+@pytest.mark.parametrize("op,M,K", [("u8", 3, 200), ("u8", 40, 200), ("s16", 3, 100), ("s16", 40, 300), ("raw", 5, 192), ("raw", 40, 192)])
+@pytest.mark.parametrize("far", [False, True])
+def test_rows_far_apart(runner, op, M, K, far):
+    import torch
+    import paper_1910_00178_amd as ng
+    N, size = 70, 2 if op == "s16" else 1
+    ld = ((1 << 31) // 64 - 8192 + (16384 if far else -16384)) // size       # (the line lies at 2^31 - 8192 bytes over 64 rows)
+    gen = torch.Generator(device="cuda").manual_seed(M + K)
+    ta, tb = (torch.int16, torch.int16) if op == "s16" else (torch.uint8, torch.int8)
+    ia, ib = torch.iinfo(ta), torch.iinfo(tb)
+    A = torch.randint(ia.min, ia.max + 1, (M, K), generator=gen, device="cuda", dtype=ta)
+    B = torch.randint(ib.min, ib.max + 1, (N, K), generator=gen, device="cuda", dtype=tb)
+    Abuf = torch.empty((M - 1) * ld + K, dtype=ta, device="cuda")
+    Abuf.as_strided((M, K), (ld, 1)).copy_(A)
+    C = torch.full((M + 1, N + 2), -7, dtype=torch.int32, device="cuda")
+    if op == "raw":
+        wsb = ng.ngemm_unpacked_workspace_bytes(M, N, K)
+        ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+        ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, Abuf, ld, 37, B, K, 3, C, N + 2, ws, wsb)
+    else:
+        size_of, pack, run = (ng.ngemm_packed_b_bytes_s16, ng.ngemm_pack_b_s16, ng.ngemm_run_s16s16s32) if op == "s16" else \
+            (ng.ngemm_packed_b_bytes, ng.ngemm_pack_b, ng.ngemm_run_u8s8s32)
+        nb = size_of(K, N)
+        packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        h = pack(runner.ctx, K, N, B, K, packed, nb)
+        wsb = ng.ngemm_workspace_bytes(M, N, K)
+        ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+        run(runner.ctx, M, Abuf, ld, 37, h, 3, C, N + 2, ws, wsb)
+        ng.ngemm_packed_b_free(h)
+    want = ((A.double() - 37) @ (B.double() - 3).t()).long()
+    want = ((want + 2**31) % 2**32 - 2**31).int()
+    assert torch.equal(C[:M, :N], want) and bool((C[M:] == -7).all()) and bool((C[:, N:] == -7).all())
