@@ -608,8 +608,17 @@ bool wavek_nt(int64_t M, int64_t N, int64_t K, int64_t cus)
 //  * 64 x 128 tiles, one per compute unit at most, and a long K, in the place of 128 x 128 tiles on half of the units or
 //    of two rounds of 64 x 64: 512 x 4096 x 4096 16.8 / 19.3 (z 18.0 / 21.9), 128 x 16384 x 4096 18.1 / 20.2 (z 20.4 /
 //    23.0); at K = 2048 it is a tie (1024 x 2048 x 2048 12.0 / 11.9);
-//  * 64 x 64 tiles with row sums and a long K: 256 x 4096 x 4096 z 11.8 / 13.7, 384 x 2048 x 2048 z 8.3 / 9.0.
-int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
+//  * 64 x 64 tiles, one per unit at most, and a long K: with row sums 256 x 4096 x 4096 z 11.8 / 13.7, 384 x 2048 x 2048 z 8.3 / 9.0.
+// The next three lines come from 9900 shapes of 257 to 760 tiles of 32 x 64 timed with these forms and with the kernels before, a third
+// of them with every byte of B from memory, where the gains are the same or larger (averages; z, u8: a zero-point of B, u8 outputs):
+//  * the same tiles without row sums: int32 1.08 x up to K = 2048, 1.05 up to 3072, 1.02 up to 4096, 1.00 beyond (480 x 2048 x 2369 9.0 / 8.1); u8
+//    1.04, 1.015 and 1.00 x;
+//  * 32 x 64 tiles where there are more than three of 32 x 32 per unit and a K of up to 1024: 1.04-1.14 x (661 x 1469 x 784
+//    6.8 / 5.7, 224 x 3904 x 819 z 6.6 / 5.6), only with row sums, int32 and K < 384 1.00;
+//  * 32 x 64 tiles, two per unit, in the place of two rounds of 64 x 64: 1.07-1.27 x (412 x 2492 x 1472 z 9.6 / 7.6, 160 x 5696 x 3008 13.5 / 11.8),
+//    beyond K = 6144 1.03 (from memory 1.00); plain int32 problems also in the place of 64 x 128 tiles (1.05-1.3 x).  With more tiles 0.80-1.02 x.
+//    From K = 1536 on the others are gemm_mid_kernel's (1.05-1.3 x is left there).
+int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, bool requant, int64_t cus)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const int64_t t32 = tiles(32, 32), t64 = tiles(64, 64);
@@ -617,7 +626,10 @@ int wavek_form(int64_t M, int64_t N, int64_t K, bool rows, int64_t cus)
     if (t32 <= cus) return 11;
     if (tiles(32, 64) <= cus) return 12;
     if (K >= 256 && K <= 1024 && t32 <= 3 * cus && t64 <= cus) return 1;
-    if (rows && K > 1024 && t64 <= cus) return 22;
+    if (K >= (rows && !requant ? 384 : 256) && K <= 1024 && t64 <= cus) return 12;
+    const bool plain = !rows && !requant && K % 64 == 0;
+    if (K >= 192 && K <= 6144 && t64 > cus && tiles(32, 64) <= 2 * cus && (K < 1536 || plain)) return 12;
+    if (K > 1024 && t64 <= cus && (rows || K <= (requant ? 3072 : 4096))) return 22;
     if (K >= 3072 && t64 > cus && tiles(64, 128) <= cus) return 24;
     return 0;
 }
@@ -690,12 +702,12 @@ bool wavek_fits(int form, int64_t M, int64_t N, int64_t budget, int64_t cus)
 
 // The form that takes the place of `kernel` (the streaming kernel, 64 x 64 tiles, 128 x 128 tiles with aligned rows), or 0.
 // budget: workgroups that the caller allows (the kernels for unaligned rows launch one per tile whichever runs).
-int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, int64_t cus, int64_t budget)
+int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
 {
     if (!wavek_offsets_fit(lda, K, round_up(K, 64))) return 0;
     const bool small = kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64;
     if (!aligned) return small ? wavek_areg_form(M, N, K, cus) : 0;
-    const int form = small || kernel == NGEMM_KERNEL_TILE_128 ? wavek_form(M, N, K, rows, cus) : 0;
+    const int form = small || kernel == NGEMM_KERNEL_TILE_128 ? wavek_form(M, N, K, rows, requant, cus) : 0;
     return (small || form == 24) && wavek_fits(form, M, N, budget, cus) ? form : 0;
 }
 
@@ -888,7 +900,7 @@ hipError_t launch_wavek_raw_form(int form, const GemmParams &p, bool rows, const
 // without row sums too (200 x 4096 x 4096 12.1 us against 17.4), and the other way for M <= 32 packs B first.
 int wavek_raw_form(int64_t M, int64_t N, int64_t K, int64_t cus)
 {
-    const int form = wavek_form(M, N, K, true, cus);
+    const int form = wavek_form(M, N, K, true, false, cus);
     return form == 0 && M <= kSkinnyMaxM ? 12 : form;
 }
 
@@ -948,7 +960,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 r = Route{t.kernel, false};
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
-                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), cus, workgroup_budget(ctx)) != 0 ||
+                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0 ||
                                 mid_form(NGEMM_KERNEL_AUTO, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus,
                                          workgroup_budget(ctx)) != 0))
                     r = Route{small, true, true};
@@ -1024,7 +1036,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
     // outputs of few tiles: K split over the wavefronts of a workgroup; of many: the kernel of tiles between those of the others
     if (route.wavek) {
-        const int form = wavek_form_of(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, device_cus, num_cus);
+        const int form = wavek_form_of(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
         if (form != 0) {
             const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
@@ -1200,7 +1212,7 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
                                 S16Cfg::kLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void *)gemm_s16_tile_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 S16Cfg::kLdsBytes) != hipSuccess ||
-            allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess ||
+            allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess || allow_big_lds_wavek<WaveK22Long, 2, false, true>() != hipSuccess ||
             allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_nt<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess ||
             allow_big_lds_mid<Mid256>() != hipSuccess || allow_big_lds_mid<Mid192>() != hipSuccess || allow_big_lds_mid<Mid128>() != hipSuccess ||
             allow_big_lds_mid<Mid64x192>() != hipSuccess || allow_big_lds_mid<Mid64x128>() != hipSuccess) {
@@ -1273,7 +1285,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
             if (!dma_ok || splitk_parts(M, B->N, B->K, workgroup_budget(ctx), &kchunk) < 2) continue;
         }
         const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, cus, workgroup_budget(ctx)) == 0 &&
+        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0 &&
             mid_form(NGEMM_KERNEL_AUTO, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
@@ -1571,7 +1583,8 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     // larger ones, and what a K of less than two stages leaves to them, the 128 x 128 kernel.  us, against the
     // 128 x 128 kernel: 16 x 4096 x 4096 8.5 / 45.6, 64 x 4096 x 4096 11.1 / 46.0, 512 x 768 x 768 5.8 / 15.0,
     // 1024^3 9.8 / 17.6, 512 x 3072 x 768 11.5 / 15.4, 1024 x 2048 x 1024 14.0 / 17.8, but 1024 x 3072 x 1024
-    // 24.8 / 19.6 and 1536^3 27 / 24.9.
+    // 24.8 / 19.6 and 1536^3 27 / 24.9.  From K = 2048 on 64 x 64 tiles of four wavefronts, one per unit at most, in the place of two of 32 x 64: 1.06 x up to
+    // K = 3072, 1.11 beyond (303 x 2046 x 3824 22.1 / 19.1), from memory the same; at 1536 0.97.
     // Under a caller's cap only those whose workgroups, one per tile, keep within it; the 128 x 128 kernel and, below its K,
     // the looping form walk several tiles per workgroup.
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256, budget = workgroup_budget(ctx);
@@ -1581,6 +1594,8 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     hipError_t e;
     if (tiles(32, 32) <= cus && fits(tiles(32, 32))) {
         e = launch_wavek<WaveK11, 2, false, true>(p, st);
+    } else if (tiles(32, 64) > cus && tiles(64, 64) <= cus && B->K >= 2048 && fits(tiles(64, 64))) {
+        e = launch_wavek<WaveK22Long, 2, false, true>(p, st);
     } else if (tiles(32, 64) <= 2 * cus && fits(tiles(32, 64))) {
         e = launch_wavek<WaveK12, 2, false, true>(p, st);
     } else if (B->K < S16Cfg::kMinK && !fits(tiles(64, 64))) {

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
+from test_gpu_routes import launches  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -265,3 +266,46 @@ def test_rows_far_apart(runner, op, M, K, far):
     want = ((A.double() - 37) @ (B.double() - 3).t()).long()
     want = ((want + 2**31) % 2**32 - 2**31).int()
     assert torch.equal(C[:M, :N], want) and bool((C[M:] == -7).all()) and bool((C[:, N:] == -7).all())
+
+
+# (M, N, K, zero-point, output, kernel): each line of the rules that give a call 32 x 64 or 64 x 64 tiles of four wavefronts, on both sides
+W12, W22 = "gemm_wavek_kernel<%d, 1, 2, 4, 3,", "gemm_wavek_kernel<%d, 2, 2, 4, 3,"
+FORMS = [(661, 1469, 784, 0, "s32", W12 % 1), (661, 1469, 1025, 0, "s32", W22 % 1), (480, 2048, 4096, 0, "s32", W22 % 1),
+         (480, 2048, 4097, 0, "s32", "gemm_tile_deep_kernel<1,"), (480, 2048, 3072, 0, "u8", W22 % 1), (480, 2048, 3073, 0, "u8", "gemm_tile_deep_kernel<1,"),
+         (224, 3904, 383, 3, "s32", "gemm_tile_dma_kernel<64, 64,"), (224, 3904, 384, 3, "s32", W12 % 1), (224, 3904, 256, 3, "u8", W12 % 1),
+         (412, 2492, 1472, 3, "s32", W12 % 1), (160, 5696, 3008, 0, "s32", W12 % 1), (160, 5696, 191, 0, "s32", "gemm_tile_dma_kernel<64, 64,"),
+         (303, 2046, 2047, 5, "s16", W12 % 2), (303, 2046, 2048, 5, "s16", W22 % 2), (640, 1664, 2500, 5, "s16", "gemm_wavek_kernel<2, 2, 2, 2, 4,")]
+
+
+@pytest.mark.parametrize("case", FORMS, ids=str)
+def test_forms_and_their_lines(runner, launches, case):  # noqa: F811
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N, K, zb, op, want = case
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    ta, tb = (torch.int16, torch.int16) if op == "s16" else (torch.uint8, torch.int8)
+    ia, ib, ld = torch.iinfo(ta), torch.iinfo(tb), (K + 15) // 16 * 16
+    A = torch.randint(ia.min, ia.max + 1, (M, ld), generator=gen, device="cuda", dtype=ta)
+    B = torch.randint(ib.min, ib.max + 1, (N, K), generator=gen, device="cuda", dtype=tb)
+    nb = (ng.ngemm_packed_b_bytes_s16 if op == "s16" else ng.ngemm_packed_b_bytes)(K, N)
+    packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    h = (ng.ngemm_pack_b_s16 if op == "s16" else ng.ngemm_pack_b)(runner.ctx, K, N, B, K, packed, nb)
+    wsb = ng.ngemm_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    C = torch.full((M + 1, N + 3), 77, dtype=torch.uint8 if op == "u8" else torch.int32, device="cuda")
+    scale = 2.0 ** -12
+
+    def call(stream):
+        if op == "u8":
+            ng.ngemm_run_u8s8u8_requant(runner.ctx, M, A, ld, 37, h, zb, scale, 128, C, N + 3, ws, wsb, stream)
+        else:
+            (ng.ngemm_run_s16s16s32 if op == "s16" else ng.ngemm_run_u8s8s32)(runner.ctx, M, A, ld, 37, h, zb, C, N + 3, ws, wsb, stream)
+    got = launches(call)
+    assert len(got) == 1 and got[0][0].startswith(want), got
+    call(0)
+    sums = ((A[:, :K].double() - 37) @ (B.double() - zb).t()).long()
+    sums = (sums + 2**31) % 2**32 - 2**31
+    exact = (torch.round(sums.float() * scale).double() + 128).clamp(0, 255).to(torch.uint8) if op == "u8" else sums.int()
+    torch.cuda.synchronize()
+    assert torch.equal(C[:M, :N], exact) and bool((C[M:] == 77).all()) and bool((C[:, N:] == 77).all())
+    ng.ngemm_packed_b_free(h)
