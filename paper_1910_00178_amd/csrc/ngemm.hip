@@ -1753,14 +1753,17 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
     grp.unit_start[0] = 0;
     const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     using TCfg = TileCfg<64, 64, 2, 2, 64>;
+    // small_tiles: every member by 32 x 32 tiles (below).
     // gemm_group_mid_kernel counts in 32 bits from a tile's first row and panel; a group with a member that has more keeps the kernel
     // with 64-bit addresses.
-    bool wide = false;
+    bool wide = false, small_tiles = false;
     auto flush = [&]() -> hipError_t {
         if (grp.count == 0) return hipSuccess;
         const unsigned grid = (unsigned)grp.unit_start[grp.count];
         if (grid > 0) {
-            if (grp.first_tile == grp.count) {
+            if (small_tiles) {
+                hipLaunchKernelGGL((gemm_group_kernel<32, 32, 1, 4, 64>), dim3(grid), dim3(256), (WaveKCfg<1, 1, 4, 4>::kLdsBytes), st, grp);
+            } else if (grp.first_tile == grp.count) {
                 // skinny members only.  Wavefronts per panel: eight hide latency when the panels are
                 // few; with several panels per compute unit anyway, fewer wavefronts with more
                 // fragments each spend less on the final sum across wavefronts
@@ -1862,6 +1865,26 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
         stream_members.clear();
     }
     auto longer_k = [](const Pending &x, const Pending &y) { return x.p.K > y.p.K; };
+    // Tiles of 32 x 32 for every member, K shared by four wavefronts, while the chip holds them all at once: two workgroups to a compute
+    // unit, and twice as many where the chains are long.  In a graph, on drawn batches with a member of M > 32, the other kernels' time over this
+    // one's: 1.02-1.05 on up to 512 tiles with a longest K of 65 to 256, 1.12 up to 512, 1.22 up to 1024, 1.27 up to 1536; 1.4-1.5 from 2048 on, up
+    // to 1024 tiles; on 513 to 1024 tiles with K up to 1024 0.9, and from 1025 tiles on 0.5-0.8 (K over 2048: 1.15).  Between 1536 and 2048 the 64 x 64
+    // tiles stay.  Groups of skinny members alone do not gain (0.9-1.0): their panels have eight wavefronts to a workgroup already.
+    int64_t tiles32 = 0, longest = 0;
+    bool near = true;
+    for (const std::vector<Pending> *v : {&tile_members, &skinny_members})
+        for (const Pending &m : *v) {
+            tiles32 += (int64_t)((m.p.M + 31) / 32) * m.p.npanels;
+            longest = std::max<int64_t>(longest, m.p.K);
+            near = near && wavek_offsets_fit(m.p.lda, m.p.K, m.p.Kp);
+        }
+    if (!tile_members.empty() && stream_members.empty() && near &&
+        ((longest > 256 && longest <= 1536 && tiles32 <= 2 * cus) || (longest >= 2048 && tiles32 <= 4 * cus))) {
+        small_tiles = true;
+        skinny_members.insert(skinny_members.end(), tile_members.begin(), tile_members.end());
+        tile_members.clear();
+        for (Pending &m : skinny_members) m.units = (int64_t)((m.p.M + 31) / 32) * m.p.npanels;
+    }
     std::stable_sort(tile_members.begin(), tile_members.end(), longer_k);
     std::stable_sort(skinny_members.begin(), skinny_members.end(), longer_k);
     // skinny members first: in a grid that also holds tiles they start with the launch (the longest

@@ -2830,8 +2830,8 @@ struct WaveKCfg {
 // p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
 // count tiles of 32 TM x 32 TN.  Offsets from a tile's first row and panel have to stay below 2 GiB, but for LOOP.
 template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
-          bool LOOP = false>
-__device__ __forceinline__ void wavek_body(const GemmArgs &args)
+          bool LOOP = false, bool GROUP = false>        // (GROUP: a function of its own, the host pass takes no second caller of one)
+__device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int tile, int stride)
 {
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
     static_assert(!NT || (!BRAW && !AREG), "packed B, aligned rows of A");
@@ -2840,7 +2840,6 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
     constexpr int LPS = Cfg::kLoadsPerStep, NTHREADS = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
     constexpr int AL = 2 * TM, BL = 2 * TN, NB = BRAW ? BL : TN;     // copies of A and of B per step, B's row blocks or panels
     constexpr bool BREG = BRAW && AREG;                  // rows of either operand with any alignment
-    const GemmParams p = params_of<ELEM, TM * 32, TN * 32, BRAW>(args);
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2852,7 +2851,6 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
     // t_end: which of this wavefront's steps it is, -1: none of them; the `full` others are copied as they lie.
     const int kend = (nsteps - 1) * 64;
     const int t_end = (kbytes & 63) != 0 && cnt > 0 && (cnt - 1) * NW + wave == nsteps - 1 ? cnt - 1 : -1, full = t_end >= 0 ? t_end : cnt;
-    int tile = blockIdx.x;
     do {                                                 // (one pass but for LOOP; to the end of the kernel)
     int tm, tn;
     tile_of_block(tile, p.tiles_m, p.tiles_n, p.nxcd, tm, tn);
@@ -2866,7 +2864,7 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
     constexpr uint32_t kBias = 3 * 1024, kExtent = 0x80000000u;      // an offset of kExtent and more: not read
     const int t16 = lane >> 2, a_chunk = ((lane & 3) - (t16 >> 2)) & 3;
     const uint8_t *a_tile = p.A + (int64_t)m0 * p.lda;
-    const uint8_t *b_tile = BRAW ? p.Bp + (int64_t)n0 * args.ldb : p.Bp + (int64_t)(n0 / 32) * nfrag * kFragBytes;
+    const uint8_t *b_tile = BRAW ? p.Bp + (int64_t)n0 * ldb : p.Bp + (int64_t)(n0 / 32) * nfrag * kFragBytes;
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)a_tile - kBias), (short)0, (int)kExtent, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)b_tile - kBias), (short)0, (int)kExtent, 0x00020000);
     auto row_of = [&](int i) { return 16 * i + t16 < p.M - m0 ? 16 * i + t16 : p.M - 1 - m0; };     // rows past M: a valid one, never stored
@@ -2879,7 +2877,7 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int pnl = n0 / 32 + j < p.npanels ? j : p.npanels - 1 - n0 / 32;       // panels past N: a valid one, never stored
-        if constexpr (BRAW) b_off[j] = (uint32_t)col_of(j) * (uint32_t)args.ldb + (uint32_t)(a_chunk * 16) + (BREG ? 0u : kBias - 1024u * (j & 3));
+        if constexpr (BRAW) b_off[j] = (uint32_t)col_of(j) * (uint32_t)ldb + (uint32_t)(a_chunk * 16) + (BREG ? 0u : kBias - 1024u * (j & 3));
         else b_off[j] = (uint32_t)pnl * (uint32_t)(nfrag * kFragBytes) + (uint32_t)(lane * 16) + kBias - 2048u * (j & 1);
     }
     uint8_t *ring = lds + wave * Cfg::kWaveBytes;
@@ -2900,7 +2898,7 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
         for (int i = 0; i < AL; ++i) fix_a[i] = (int64_t)(p.M - 1 - m0 - row_of(i)) * p.lda + vend < 16;
         if constexpr (BRAW) {
 #pragma unroll
-            for (int j = 0; j < BL; ++j) fix_b[j] = (int64_t)(p.N - 1 - n0 - col_of(j)) * args.ldb + vend < 16;
+            for (int j = 0; j < BL; ++j) fix_b[j] = (int64_t)(p.N - 1 - n0 - col_of(j)) * ldb + vend < 16;
         }
     }
     auto fix_of = [&](const uint8_t *chunk) {            // (a row of less than 16 bytes has no others before its end)
@@ -2914,7 +2912,7 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
         if constexpr (BRAW) {
 #pragma unroll
             for (int j = 0; j < BL; ++j)
-                if (fix_b[j]) fixv_b[j] = fix_of(b_tile + (int64_t)col_of(j) * args.ldb + a_chunk * 16 + kend);
+                if (fix_b[j]) fixv_b[j] = fix_of(b_tile + (int64_t)col_of(j) * ldb + a_chunk * 16 + kend);
         }
     };
     // Step t to ring offset `slot`.  From the step that K ends in on (AREG: what is requested past the last step is counted, but not read)
@@ -3356,7 +3354,7 @@ __device__ __forceinline__ void wavek_body(const GemmArgs &args)
         }
     }
     if (LOOP) __syncthreads();                           // the partial tiles are read: the next tile's copies may land
-    tile += count_of(args);
+    tile += stride;
     } while (LOOP && tile < p.tiles_m * p.tiles_n);
 }
 
@@ -3364,7 +3362,8 @@ template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, b
           bool LOOP = false>
 __global__ __launch_bounds__(NW * 64, (WaveKCfg<TM, TN, NW, RING>::kWavesPerSimd)) void gemm_wavek_kernel(const GemmArgs args)
 {
-    wavek_body<ELEM, TM, TN, NW, RING, REQUANT, ROWS, BRAW, AREG, NT, LOOP>(args);
+    wavek_body<ELEM, TM, TN, NW, RING, REQUANT, ROWS, BRAW, AREG, NT, LOOP>(params_of<ELEM, TM * 32, TN * 32, BRAW>(args), args.ldb, blockIdx.x,
+                                                                           count_of(args));
 }
 
 // ---- skinny-M kernel (M <= 32) --------------------------------------------------------------
@@ -3547,14 +3546,19 @@ __global__ __launch_bounds__(512) void gemm_group_skinny_kernel(const GroupParam
 // skinny members come first in the grid: the longest of them take as long as the whole launch and
 // have to start with it.  For groups with a member whose rows or panels lie too far apart for the 32-bit offsets of gemm_group_mid_kernel, and for
 // groups of few tiles with a short K, on which that one is slower (64 odd shapes in a graph: 16.9 us there, 18.3 here).
+//
+// The form with 32 x 32 tiles is for groups of few tiles, as many as the chip holds at once: such a launch lasts as long as its longest chain
+// over K, and WGM * WGN wavefronts that share K (wavek_body, every member's tiles, A by way of registers so that rows of any alignment
+// do) cut it to a quarter.  In a graph, 100 to 512 tiles of members with K up to 1024: 5.9 us on 64 x 64 tiles, 4.8 here; the launch says where the line lies.
 template <int BM, int BN, int WGM, int WGN, int BK>
-__global__ __launch_bounds__(WGM * WGN * 64) void gemm_group_kernel(const GroupParams g)
+__global__ __launch_bounds__(WGM * WGN * 64, (BM == 32 ? WaveKCfg<1, 1, WGM * WGN, 4>::kWavesPerSimd : 1)) void gemm_group_kernel(const GroupParams g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int q = group_find(g, blockIdx.x);
     const GemmParams p = group_member_params<BM, BN>(g.prob[q], g.nxcd);
     const int unit = blockIdx.x - g.unit_start[q];
-    if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, WGM * WGN, (int *)lds);
+    if constexpr (BM == 32) wavek_body<1, 1, 1, WGM * WGN, 4, false, true, false, true, false, false, true>(p, 0, unit, 0);
+    else if (q < g.first_tile) skinny_body<false, 1, true>(p, unit, WGM * WGN, (int *)lds);
     else tile_body_staged<BM, BN, WGM, WGN, BK, false, true, kGroupRing>(p, unit, lds);
 }
 

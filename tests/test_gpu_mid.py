@@ -274,6 +274,47 @@ def test_grouped_tiles_of_few_short_chains(runner, launches, shapes, want):  # n
         ng.ngemm_packed_b_free(h)
 
 
+@pytest.mark.parametrize("shapes,small", [
+    ([((33, 5, 64, 1, 65)[i % 5], (1, 31, 33, 64, 130)[i % 4 + i // 16], k) for i, k in enumerate([0, 1, 15, 16, 63, 64, 65, 127, 129, 192, 255, 256, 257, 320, 449, 513, 700, 1000, 1025, 1279, 1535, 1536])], True),
+    ([(40, 70, 4113), (3, 200, 3001), (97, 33, 2048), (65, 65, 0), (32, 32, 130), (33, 1, 2111)], True),
+    ([(40, 70, 4113), (35, 40, 16)], "far apart"),                                            # the second one's rows
+    ([(64, 8192, 300)], True), ([(64, 8193, 300)], False), ([(33, 100, 257)], True), ([(33, 100, 256)], False), ([(33, 100, 1537)], False),
+    ([(33, 100, 2047)], False), ([(512, 2048, 2048)], True), ([(512, 2049, 2048)], False), ([(32, 100, 700)] * 3, False),
+    ([(33, 40, 300 + i) for i in range(80)], True)], ids=lambda s: str(s) if isinstance(s, (bool, str)) else "%dx%s" % (len(s), s[0]))
+def test_grouped_small_tiles(runner, launches, shapes, small):  # noqa: F811
+    """Batches of few tiles: 32 x 32 tiles with K shared by four wavefronts.  K of every remainder of a step, of fewer steps than wavefronts, none at all;
+    rows of any alignment, members with M <= 32 among the others, more members than one launch holds, both sides of the lines of the rule."""
+    import torch
+    import paper_1910_00178_amd as ng
+    rng = np.random.default_rng(len(shapes))
+    items, want, outs, keep, handles = [], [], [], [], []
+    for t, (M, N, K) in enumerate(shapes):
+        pitch = (1 << 25) if small == "far apart" and t else max(1, K + (0, 3, 16)[t % 3])
+        A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(N, K), dtype=np.int8)
+        za, zb = int(rng.integers(0, 256)), 0 if t % 3 == 0 else int(rng.integers(-128, 128))
+        h, packed = runner.pack(B)
+        flat = torch.empty(max(16, (M - 1) * pitch + K), dtype=torch.uint8, device="cuda")          # ends with the last row
+        if K:
+            flat.as_strided((M, K), (pitch, 1)).copy_(torch.from_numpy(A))
+        C = torch.full((M + 1, N + 1), -9, dtype=torch.int32, device="cuda")
+        items.append((M, flat, pitch, za, zb, h, C, N + 1))
+        want.append(oracle.gemm_u8s8s32(A, B, za, zb))
+        outs.append(C)
+        keep += [flat, packed]
+        handles.append(h)
+    problems = ng.make_problems(items)
+    got = launches(lambda stream: ng.ngemm_run_batched_u8s8s32(runner.ctx, problems, None, 0, stream.cuda_stream))
+    assert all(("gemm_group_kernel<32" in name) == (small is True) for name, _ in got), got
+    ng.ngemm_run_batched_u8s8s32(runner.ctx, problems)
+    torch.cuda.synchronize()
+    for shape, C, w in zip(shapes, outs, want):
+        c = C.cpu().numpy()
+        assert np.array_equal(c[:-1, :-1], w), shape
+        assert (c[-1] == -9).all() and (c[:, -1] == -9).all(), shape
+    for h in handles:
+        ng.ngemm_packed_b_free(h)
+
+
 @pytest.mark.parametrize("M,N,K,in_kernel", [(1541, 1500, 128, True), (1665, 1409, 133, True), (1537, 1537, 191, True), (2047, 2050, 192, True),
                                              (1600, 1600, 333, True), (1541, 1500, 2560, True), (1541, 1500, 2561, False), (4097, 2049, 1344, False)])
 def test_s16_row_sums(ctx, launches, M, N, K, in_kernel):  # noqa: F811
