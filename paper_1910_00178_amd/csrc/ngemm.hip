@@ -879,14 +879,15 @@ int mid_form(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool alig
 }
 
 // The forms that read B from the caller's storage.
-template <class F>
+template <class F, bool ANY = false>                    // ANY: rows of any alignment
 hipError_t launch_wavek_raw(const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
 {
-    return rows ? launch_wavek<F, 1, false, true, true>(p, st, &rawb) : launch_wavek<F, 1, false, false, true>(p, st, &rawb);
+    return rows ? launch_wavek<F, 1, false, true, true, ANY>(p, st, &rawb) : launch_wavek<F, 1, false, false, true, ANY>(p, st, &rawb);
 }
 
-hipError_t launch_wavek_raw_form(int form, const GemmParams &p, bool rows, const RawB &rawb, hipStream_t st)
+hipError_t launch_wavek_raw_form(int form, const GemmParams &p, bool rows, const RawB &rawb, bool aligned, hipStream_t st)
 {
+    if (!aligned) return form == 11 ? launch_wavek_raw<WaveK11, true>(p, rows, rawb, st) : launch_wavek_raw<WaveK12Short, true>(p, rows, rawb, st);
     switch (form) {
     case 1: return launch_wavek_raw<WaveK11Short>(p, rows, rawb, st);
     case 11: return launch_wavek_raw<WaveK11>(p, rows, rawb, st);
@@ -902,6 +903,24 @@ int wavek_raw_form(int64_t M, int64_t N, int64_t K, int64_t cus)
 {
     const int form = wavek_form(M, N, K, true, false, cus);
     return form == 0 && M <= kSkinnyMaxM ? 12 : form;
+}
+
+// The same with rows of any alignment, both operands through registers; 0: a pack pass first, then the kernels for packed B.  us in a graph, packed
+// first / so: 1 x 996 x 909 8.3 / 4.9, 16 x 2846 x 4103 19.9 / 11.7, 64 x 2126 x 1729 14.6 / 7.2,
+// 221 x 314 x 328 9.4 / 4.4, 896 x 960 x 319 9.9 / 6.0.  Averages over 12400 drawn shapes with rows of an odd pitch: 2.1 x with K of up to 512,
+// 2.0 up to 1024, 1.9 up to 2048, 1.6 beyond, and 1.6 to 3.1 for M <= 32 with many panels.  Where the lines lie:
+//  * 32 x 32 tiles up to one per compute unit, and up to two with K <= 1024 (32 x 64 tiles there 1.6-1.9 x, these 1.9-2.2; with a longer K the former lead);
+//  * more tiles than four of 32 x 32 per unit lose the pack pass's price to reading B once per 32 rows: K of up to 256 1.23 x, 512 1.09 (some 0.95),
+//    then 0.9 and less; from three on K of up to 3072 1.2-1.5 x, beyond it 0.87-1.3;
+//  * up to eight rows on a few tiles, K over 6144: 0.83-1.1 x, the K split over workgroups is worth the pass; over 8192 it was not measured for others.
+int wavek_raw_any_form(int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const int64_t t32 = tiles(32, 32), t64 = tiles(32, 64);
+    if (K > 8192 || (K > 6144 && M <= 8 && t32 <= 16)) return 0;
+    if (t32 <= cus || (K <= 1024 && t32 <= 2 * cus)) return 11;
+    if (M <= kSkinnyMaxM || t64 <= cus || (K <= 3072 && t64 <= 2 * cus) || (K <= 256 && t64 <= 4 * cus)) return 12;
+    return 0;
 }
 
 struct RunArgs {
@@ -1649,7 +1668,8 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     if (!workspace_dev || ((uintptr_t)workspace_dev & 15u) != 0) return NGEMM_ERR_INVALID_ARG;
     if (workspace_bytes < ngemm_unpacked_workspace_bytes(M, N, K)) return NGEMM_ERR_BUFFER_TOO_SMALL;
     // Rows of both operands 16-byte aligned: no pack pass.  The kernels read B from the caller's storage with the
-    // same copies as A; all but the 256 x 256 ones form the sums of its columns themselves.
+    // same copies as A; all but the 256 x 256 ones form the sums of its columns themselves.  Other rows: none either for
+    // small outputs, where one kernel takes both operands through registers.
     int kernel = ctx->force_kernel == NGEMM_KERNEL_AUTO ? choose_kernel(ctx, M, N, K, rows_aligned(A_dev, lda), false) : ctx->force_kernel;
     if (kernel == NGEMM_KERNEL_SPLIT_K)                                     // the K split reads a packed B only
         kernel = M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
@@ -1657,10 +1677,11 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     const bool small_kernel = kernel == NGEMM_KERNEL_TILE_64 || kernel == NGEMM_KERNEL_TILE_128 || kernel == NGEMM_KERNEL_SKINNY;
     // the kernel that splits K over a workgroup's wavefronts: of the automatic choice only
-    int form = aligned && K > 0 && small_kernel && ctx->force_kernel == NGEMM_KERNEL_AUTO ? wavek_raw_form(M, N, K, cus) : 0;
+    int form = K == 0 || !small_kernel || ctx->force_kernel != NGEMM_KERNEL_AUTO ? 0
+               : aligned ? wavek_raw_form(M, N, K, cus) : wavek_raw_any_form(M, N, K, cus);
     if ((kernel == NGEMM_KERNEL_TILE_128 && form != 24) || !wavek_fits(form, M, N, workgroup_budget(ctx), cus) ||
         !wavek_offsets_fit(lda, K, 0, ldb)) form = 0;
-    if (aligned && K > 0 && (form != 0 || kernel != NGEMM_KERNEL_SKINNY)) {
+    if (form != 0 || (aligned && K > 0 && kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return NGEMM_ERR_DEVICE;
         hipStream_t st = (hipStream_t)hip_stream;
@@ -1676,7 +1697,7 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
         p.colsum = colsum;
         const RawB rawb{(const uint8_t *)B_dev, ldb};
         if (form != 0)
-            return launch_wavek_raw_form(form, p, b_zero_point != 0, rawb, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+            return launch_wavek_raw_form(form, p, b_zero_point != 0, rawb, aligned, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         // The sums of B's columns (without weight at a_zero_point = 128) and of A's rows (at b_zero_point = 0): the
         // 64 x 64 and 128 x 128 kernels form them, the larger ones read them from passes of their own.
         const bool sums = p.za_term != 0 || b_zero_point != 0;

@@ -2797,7 +2797,7 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmArgs a)
 // 9.0 -> 4.0 and, every byte of B from memory, 12.2 -> 4.3, 18.8 -> 8.4, 12.0 -> 5.8).
 // AREG: rows of A with any alignment, which copies into LDS cannot fetch: A comes through registers (two steps on
 // their way, written into the ring two steps before they are read); everything else stays (64 x 4096 x 4097
-// 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).
+// 23.7 -> 9.9 us, rows padded to 16 bytes 7.3).  With BRAW the rows of B go the same way, instead of a pack pass and a second launch.
 // Calls of 3 to 5 us are a launch (2.1 us) and what every wavefront does one after the other, so that is kept short: the copies go out
 // first, from lane offsets that stay (a step adds a scalar), the column terms behind them (they were waited for ahead of the first copy: a trip to
 // memory); the step that K ends in is one of the ring (it was fetched behind the others: another trip); the last steps, with fewer and

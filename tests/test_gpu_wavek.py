@@ -309,3 +309,56 @@ def test_forms_and_their_lines(runner, launches, case):  # noqa: F811
     torch.cuda.synchronize()
     assert torch.equal(C[:M, :N], exact) and bool((C[M:] == 77).all()) and bool((C[:, N:] == 77).all())
     ng.ngemm_packed_b_free(h)
+
+
+RAW11, RAW12 = "gemm_wavek_kernel<1, 1, 1, 4, 4, false, %s, true, true,", "gemm_wavek_kernel<1, 1, 2, 2, 4, false, %s, true, true,"
+# (M, N, K, kernel or None: B is packed first), both sides of the lines of the rule
+RAW_ANY = [(1, 1, 1, RAW11), (33, 65, 15, RAW11), (512, 512, 77, RAW11), (512, 1024, 1024, RAW11), (512, 1024, 1025, RAW12), (512, 1025, 1024, RAW12),
+           (30, 17000, 190, RAW12), (1024, 1024, 1030, RAW12), (1024, 1024, 3072, RAW12), (1024, 1024, 3073, None), (1024, 1056, 255, RAW12),
+           (1024, 1056, 257, None), (2048, 1024, 250, RAW12), (2048, 1030, 250, None), (8, 512, 6144, RAW11), (8, 512, 6145, None), (9, 512, 6145, RAW11),
+           (8, 513, 6145, RAW11), (40, 70, 8192, RAW11), (40, 70, 8193, None)]
+
+
+@pytest.mark.parametrize("M,N,K,kernel", RAW_ANY)
+def test_unpacked_rows_of_any_alignment(runner, launches, M, N, K, kernel):  # noqa: F811
+    import torch
+    import paper_1910_00178_amd as ng
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, K)
+    ws = torch.full((wsb,), 0xC3, dtype=torch.uint8, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    for pa, pb, za, zb in ((K + K % 2 + 1, K + 5, 128, 0), (K + K % 2 + 1, (K + 15) // 16 * 16, 37, -7)):      # the second: only A's rows are unaligned
+        A = torch.randint(0, 256, (M, pa), generator=gen, device="cuda", dtype=torch.uint8).reshape(-1)[:(M - 1) * pa + K].clone()
+        B = torch.randint(-128, 128, (N, pb), generator=gen, device="cuda", dtype=torch.int8).reshape(-1)[:(N - 1) * pb + K].clone()
+        C = torch.full((M + 1, N + 1), -7, dtype=torch.int32, device="cuda")
+        call = lambda stream: ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, A, pa, za, B, pb, zb, C, N + 1, ws, wsb, stream)
+        names = [name for name, _ in launches(lambda stream: call(stream.cuda_stream))]
+        if kernel:
+            assert len(names) == 1 and kernel % ("true" if zb else "false") in names[0], names
+        else:
+            assert len(names) > 1, names
+        call(None)
+        _check(A.as_strided((M, K), (pa, 1)), B.as_strided((N, K), (pb, 1)), za, zb, C)
+
+
+@pytest.mark.parametrize("M,N", [(1, 70), (35, 33), (100, 66)])
+def test_unpacked_every_number_of_steps(runner, M, N):
+    """K from one byte to past every number of steps that the kernel treats by itself, either operand ending with its last row."""
+    import torch
+    import paper_1910_00178_amd as ng
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, 4000)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    for K in list(range(1, 40)) + [64 * s + d for s in range(1, 46) for d in (-1, 0, 1, 17)]:
+        A = torch.randint(0, 256, (M * K,), generator=gen, device="cuda", dtype=torch.uint8)
+        B = torch.randint(-128, 128, (N * K + 1,), generator=gen, device="cuda", dtype=torch.int8)[1:]          # (unaligned for every K)
+        C = torch.full((M + 1, N + 1), -7, dtype=torch.int32, device="cuda")
+        ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, A, K, 3, B, K, (0, 5)[K & 1], C, N + 1, ws, wsb)
+        _check(A.view(M, K), B.view(N, K), 3, (0, 5)[K & 1], C)
+
+
+def _check(A, B, za, zb, C):
+    import torch
+    M, N = A.shape[0], B.shape[0]
+    want = ((A.double() - za) @ (B.double() - zb).t()).long()
+    want = ((want + 2**31) % 2**32 - 2**31).int()
+    assert torch.equal(C[:M, :N], want) and bool((C[M:] == -7).all()) and bool((C[:, N:] == -7).all()), (A.shape, B.shape)
