@@ -1,4 +1,4 @@
-"""MI355X (gfx950) u8 x s8 -> s32 GEMM: thin ctypes binding over the C-ABI HIP library.
+"""MI355X (gfx950) u8 x s8 -> s32 GEMM: thin binding over the C-ABI HIP library.
 
 The binding (and with it the shared library) is loaded on first use of any of its names, so
 that `paper_1910_00178_amd.build` can (re)compile the library without loading a stale one.

@@ -1795,7 +1795,8 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
                 const size_t lds = std::max((size_t)TCfg::kLdsBytes, (size_t)(4 * 16 * 64 * 4));
                 // Few tiles and a K around the 11 stages from which gemm_group_mid_kernel has a steady loop: a workgroup alone on its unit waits longer
                 // per stage there (in a graph, gemm_group_kernel is 1.12 x as fast on up to 64 tiles with K = 512 .. 640, 1.04 x with 1280, 1.05 x on up
-                // to 256 tiles with K = 640 .. 1024; outside of these lines the other one, 1.0-1.3 x).  The members with the longest K come first.
+                // to 256 tiles with K = 640 .. 1024; outside of these lines the other one, 1.0-1.3 x).  Most such groups take the 32 x 32 tiles (below).  The
+                // members with the longest K come first.
                 const int tiles = grp.unit_start[grp.count] - grp.unit_start[grp.first_tile], longest = grp.prob[grp.first_tile].K;
                 const bool short_chains = (tiles <= cus / 4 && longest > 192 && longest <= 1536) || (tiles <= cus && longest > 256 && longest <= 1024);
                 if (wide || short_chains) hipLaunchKernelGGL((gemm_group_kernel<64, 64, 2, 2, 64>), dim3(grid), dim3(256), lds, st, grp);
