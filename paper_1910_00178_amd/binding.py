@@ -147,7 +147,8 @@ def _bind_current_stream():
         return raw(device()) if ready() else _slow_current_stream()
 
     _current_stream = fast
-    _calls.streams(raw, device, ready)
+    if _native:
+        _calls.streams(raw, device, ready, fast)
 
 
 def _stream(s):
@@ -332,13 +333,16 @@ def ngemm_run_batched_u8s8s32(ctx, problems, workspace_dev=None, workspace_bytes
 
 
 # The calls above that a program makes per product, weight or batch: natively where all arguments are of the usual types,
-# else through the functions above.
-_calls.setup(_p, ngemm_problem, ctypes.sizeof(ngemm_problem), _check)
-for _name, _kind in (("ngemm_run_u8s8s32", "run"), ("ngemm_run_s8s8s32", "run"), ("ngemm_run_u8u8s32", "run"), ("ngemm_run_s16s16s32", "run"),
-                     ("ngemm_run_u8s8s32_static", "static"), ("ngemm_run_u8s8u8_requant", "requant"),
-                     ("ngemm_run_u8s8u8_requant_channel", "channel"), ("ngemm_run_u8s8s32_unpacked", "unpacked"),
-                     ("ngemm_run_batched_u8s8s32", "batched"), ("ngemm_pack_b", "pack"), ("ngemm_pack_b_u8", "pack"),
-                     ("ngemm_pack_b_s16", "pack"), ("ngemm_packed_b_free", "free")):
-    _slow = globals()[_name]
-    globals()[_name] = _calls.Call(_slow, _kind, ctypes.cast(getattr(_lib, _name), _p).value)
-    globals()[_name].__dict__.update(__doc__=_slow.__doc__, __module__=_slow.__module__, __qualname__=_slow.__qualname__)
+# else as above.
+_kinds = {"ngemm_run_u8s8s32": "run", "ngemm_run_s8s8s32": "run", "ngemm_run_u8u8s32": "run", "ngemm_run_s16s16s32": "run",
+          "ngemm_run_u8s8s32_static": "static", "ngemm_run_u8s8u8_requant": "requant", "ngemm_run_u8s8u8_requant_channel": "channel",
+          "ngemm_run_u8s8s32_unpacked": "unpacked", "ngemm_run_batched_u8s8s32": "batched", "ngemm_pack_b": "pack", "ngemm_pack_b_u8": "pack",
+          "ngemm_pack_b_s16": "pack", "ngemm_packed_b_free": "free"}
+_native = hasattr(_calls, "Call")
+if _native:
+    for _name in _kinds:
+        getattr(_lib, _name)
+    _calls.setup(_p, ngemm_problem, ctypes.sizeof(ngemm_problem), _check, globals(), ("_check", "_dev", "_lib", "_p", "_stream"),
+                 _lib.__dict__, tuple(_kinds))
+    for _name, _kind in _kinds.items():
+        globals()[_name] = _calls.Call(globals()[_name], _kind, ctypes.cast(getattr(_lib, _name), _p).value)

@@ -2,15 +2,18 @@
  * the C function is called through its address.  Through ctypes a call of the smallest product spends 2.1 of its 5.2 us on that, here
  * 1.0 of 4.2 (1 x 4096 x 1024, pass after pass).
  *
- * A Call wraps one Python function of the binding (its `slow` one) and takes over only where every argument has the type that programs
- * pass: exact ints in range, None, floats, objects with data_ptr(), c_void_p handles, streams.  Whatever else it meets, keywords among
- * it, it hands the call on to the Python function before anything is launched, which converts or refuses it as ever.
+ * A Call is one Python function of the binding over again: a function object in all but its vectorcall, so that what programs do with
+ * functions (weak references, binding in a class, inspection, mocks) stays.  The vectorcall takes over only where every argument has the
+ * type that programs pass: exact ints in range, None, floats, objects with data_ptr(), c_void_p handles, streams.  Whatever else it meets,
+ * keywords among it, it runs the function's own code before anything is launched, which converts or refuses it as ever; so it
+ * does under a tracer or profiler and while any name that this code looks up, or the code itself, is not the binding's own.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stddef.h>
 #include <stdint.h>
-#include <structmember.h>
+
+#if PY_VERSION_HEX >= 0x030A0000 && PY_VERSION_HEX < 0x030B0000      /* (other versions' functions are laid out otherwise: all calls by ctypes there) */
 
 enum { KIND_RUN, KIND_STATIC, KIND_REQUANT, KIND_CHANNEL, KIND_UNPACKED, KIND_BATCHED, KIND_PACK, KIND_FREE, KIND_COUNT };
 
@@ -27,11 +30,10 @@ static const struct { const char *name, *spec; int need; } kinds[KIND_COUNT] = {
 typedef union { int64_t l; int32_t i; size_t z; float f; void *p; } Value;
 
 typedef struct {
-    PyObject_HEAD
-    PyObject *dict, *slow, *name;
+    PyFunctionObject f;
+    PyObject *code, *defaults;                                   /* as they were */
     void *fn;
     int kind, nargs;
-    vectorcallfunc vectorcall;
 } Call;
 
 /* set once by the binding: ctypes.c_void_p, the problem structure, the function that raises for a status */
@@ -39,7 +41,36 @@ static PyObject *handle_type, *problem_type, *check;
 static Py_ssize_t problem_bytes;
 /* torch's: the raw handle of a device's current stream, the current device, whether the runtime is up (and not a forked child's) */
 static PyObject *raw_stream, *current_device, *ready;
-static PyObject *s_data_ptr, *s_cuda_stream, *s_type;
+static PyObject *s_data_ptr, *s_cuda_stream, *s_type, *s_current_stream;
+/* What the Python functions look up: (dict, names, values) for the binding's names and for the library's.  A dict's version tells whether it was
+ * written to since `intact` was found, so that a call costs two comparisons.  bound_stream: the binding's _current_stream that calls
+ * raw_stream; another one is asked itself. */
+enum { WATCHED = 2 };
+static PyObject *watched[WATCHED][3], *bound_stream;
+static uint64_t version[WATCHED];
+static int intact, stream_intact;
+
+static int look_again(void)
+{
+    intact = stream_intact = 1;
+    for (int w = 0; w < WATCHED; ++w) {
+        PyObject *dict = watched[w][0];
+        if (!dict) return intact = 0;
+        version[w] = ((PyDictObject *)dict)->ma_version_tag;
+        for (Py_ssize_t k = 0; k < PyTuple_GET_SIZE(watched[w][1]); ++k)
+            if (PyDict_GetItem(dict, PyTuple_GET_ITEM(watched[w][1], k)) != PyTuple_GET_ITEM(watched[w][2], k)) intact = 0;
+    }
+    if (bound_stream && PyDict_GetItem(watched[0][0], s_current_stream) != bound_stream) stream_intact = 0;
+    return intact;
+}
+
+static int as_it_was(const Call *c)
+{
+    if (c->f.func_code != c->code || c->f.func_defaults != c->defaults || PyThreadState_Get()->cframe->use_tracing) return 0;
+    for (int w = 0; w < WATCHED; ++w)
+        if (!watched[w][0] || ((PyDictObject *)watched[w][0])->ma_version_tag != version[w]) return look_again();
+    return intact;
+}
 
 /* a failed attempt: the Python function will meet (and raise) the same, but an interrupt goes through */
 static int give_up(void)
@@ -108,7 +139,7 @@ static int problems_of(PyObject *o, void **p, int64_t *count)
 static int stream_of(PyObject *o, void **p)
 {
     if (o && o != Py_None) return PyLong_CheckExact(o) ? address_of(o, p) : address_in(PyObject_GetAttr(o, s_cuda_stream), p);
-    if (!raw_stream) return 0;                                   /* (the first call finds them) */
+    if (!raw_stream || !stream_intact) return 0;                 /* (the first call finds them) */
     PyObject *up = PyObject_CallNoArgs(ready);
     const int is_up = up == Py_True;
     Py_XDECREF(up);
@@ -168,7 +199,7 @@ static PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyOb
     const char *spec = kinds[c->kind].spec;
     Value v[MAX_ARGS];
     int64_t count = 0;
-    if ((kwnames && PyTuple_GET_SIZE(kwnames) != 0) || n < kinds[c->kind].need || n > c->nargs) goto slow;
+    if ((kwnames && PyTuple_GET_SIZE(kwnames) != 0) || n < kinds[c->kind].need || n > c->nargs || !as_it_was(c)) goto slow;
     for (int k = 0; k < c->nargs; ++k)
         if (!convert(spec[k], k < n ? args[k] : NULL, &v[k], &count)) goto slow;
     {
@@ -207,13 +238,13 @@ static PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyOb
             break;
         }
         Py_END_ALLOW_THREADS
-        if (status != 0) return PyObject_CallFunction(check, "iO", status, c->name);
+        if (status != 0) return PyObject_CallFunction(check, "iO", status, c->f.func_name);
         if (c->kind == KIND_PACK) return PyObject_CallFunction(handle_type, "N", PyLong_FromVoidPtr(handle));
         Py_RETURN_NONE;
     }
 slow:
     if (PyErr_Occurred()) return NULL;
-    return PyObject_Vectorcall(c->slow, args, nargsf, kwnames);
+    return _PyFunction_Vectorcall(self, args, nargsf, kwnames);
 }
 
 static PyObject *new_call(PyTypeObject *type, PyObject *args, PyObject *kw)
@@ -226,82 +257,62 @@ static PyObject *new_call(PyTypeObject *type, PyObject *args, PyObject *kw)
     int k = 0;
     while (k < KIND_COUNT && strcmp(kinds[k].name, kind) != 0) ++k;
     if (k == KIND_COUNT || fn == 0 || !handle_type) return PyErr_Format(PyExc_ValueError, "Call: kind '%s'", kind);
-    Call *c = (Call *)type->tp_alloc(type, 0);
-    if (!c) return NULL;
-    c->name = PyObject_GetAttrString(slow, "__name__");
-    if (!c->name) {
-        Py_DECREF(c);
+    if (!PyFunction_Check(slow)) return PyErr_Format(PyExc_TypeError, "Call: a Python function");
+    PyObject *dict = PyDict_New();
+    if (!dict || PyDict_SetItemString(dict, "__wrapped__", slow) != 0) {
+        Py_XDECREF(dict);
         return NULL;
     }
-    Py_INCREF(slow);
-    c->slow = slow;
+    Call *c = PyObject_GC_New(Call, type);
+    if (!c) {
+        Py_DECREF(dict);
+        return NULL;
+    }
+    const PyFunctionObject *s = (PyFunctionObject *)slow;
+    PyFunctionObject *f = &c->f;
+    memcpy((char *)f + sizeof(PyObject), (const char *)s + sizeof(PyObject), sizeof(*f) - sizeof(PyObject));
+    PyObject *shared[] = {f->func_globals, f->func_builtins, f->func_name, f->func_qualname, f->func_code, f->func_defaults, f->func_kwdefaults,
+                          f->func_closure, f->func_doc, f->func_module, f->func_annotations, f->func_code, f->func_defaults};
+    for (size_t k = 0; k < sizeof(shared) / sizeof(shared[0]); ++k) Py_XINCREF(shared[k]);
+    f->func_dict = dict;
+    f->func_weakreflist = NULL;
+    f->vectorcall = call;
+    c->code = f->func_code;
+    c->defaults = f->func_defaults;
     c->fn = (void *)(uintptr_t)fn;
     c->kind = k;
     c->nargs = (int)strlen(kinds[k].spec);
-    c->vectorcall = call;
+    PyObject_GC_Track(c);
     return (PyObject *)c;
-}
-
-static int traverse(PyObject *self, visitproc visit, void *arg)
-{
-    Call *c = (Call *)self;
-    Py_VISIT(c->dict);
-    Py_VISIT(c->slow);
-    Py_VISIT(c->name);
-    return 0;
-}
-
-static int clear(PyObject *self)
-{
-    Call *c = (Call *)self;
-    Py_CLEAR(c->dict);
-    return 0;                                                    /* (the rest stays: a call may still come) */
 }
 
 static void dealloc(PyObject *self)
 {
-    PyObject_GC_UnTrack(self);
-    clear(self);
-    Py_CLEAR(((Call *)self)->slow);
-    Py_CLEAR(((Call *)self)->name);
-    Py_TYPE(self)->tp_free(self);
+    PyObject *code = ((Call *)self)->code, *defaults = ((Call *)self)->defaults;
+    PyFunction_Type.tp_dealloc(self);
+    Py_DECREF(code);
+    Py_XDECREF(defaults);
 }
 
 static PyObject *reduce(PyObject *self, PyObject *unused)       /* pickled by name, as the function is */
 {
     (void)unused;
-    Py_INCREF(((Call *)self)->name);
-    return ((Call *)self)->name;
+    Py_INCREF(((Call *)self)->f.func_name);
+    return ((Call *)self)->f.func_name;
 }
 
 static PyMethodDef call_methods[] = {{"__reduce__", reduce, METH_NOARGS, NULL}, {NULL, NULL, 0, NULL}};
 
-static PyMemberDef members[] = {
-    {"__wrapped__", T_OBJECT, offsetof(Call, slow), READONLY, "the Python function that takes what this one hands on"},
-    {"__name__", T_OBJECT, offsetof(Call, name), READONLY, NULL},
-    {NULL, 0, 0, 0, NULL},
-};
-
-static PyGetSetDef getset[] = {
-    {"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, NULL, NULL},
-    {NULL, NULL, NULL, NULL, NULL},
-};
-
-static PyTypeObject CallType = {
+static PyTypeObject CallType = {                                 /* (what is not here is the function type's, its collector's entries among it) */
     PyVarObject_HEAD_INIT(NULL, 0)
     .tp_name = "paper_1910_00178_amd._calls.Call",
     .tp_basicsize = sizeof(Call),
-    .tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_GC | Py_TPFLAGS_HAVE_VECTORCALL,
-    .tp_vectorcall_offset = offsetof(Call, vectorcall),
+    .tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL,
+    .tp_vectorcall_offset = offsetof(PyFunctionObject, vectorcall),
     .tp_call = PyVectorcall_Call,
     .tp_new = new_call,
     .tp_dealloc = dealloc,
-    .tp_traverse = traverse,
-    .tp_clear = clear,
-    .tp_dictoffset = offsetof(Call, dict),
     .tp_methods = call_methods,
-    .tp_members = members,
-    .tp_getset = getset,
 };
 
 static void keep(PyObject **where, PyObject *o)
@@ -313,30 +324,53 @@ static void keep(PyObject **where, PyObject *o)
 
 static PyObject *setup(PyObject *m, PyObject *args)
 {
-    PyObject *h, *p, *c;
+    PyObject *h, *p, *c, *of[WATCHED], *names[WATCHED];
     (void)m;
-    if (!PyArg_ParseTuple(args, "OOnO", &h, &p, &problem_bytes, &c)) return NULL;
+    if (!PyArg_ParseTuple(args, "OOnOO!O!O!O!", &h, &p, &problem_bytes, &c, &PyDict_Type, &of[0], &PyTuple_Type, &names[0], &PyDict_Type, &of[1],
+                          &PyTuple_Type, &names[1])) return NULL;
+    for (int w = 0; w < WATCHED; ++w) {
+        const Py_ssize_t n = PyTuple_GET_SIZE(names[w]);
+        PyObject *values = PyTuple_New(n);
+        if (!values) return NULL;
+        for (Py_ssize_t k = 0; k < n; ++k) {
+            PyObject *v = PyDict_GetItemWithError(of[w], PyTuple_GET_ITEM(names[w], k));
+            if (!v) {
+                Py_DECREF(values);
+                return PyErr_Format(PyExc_KeyError, "setup: %R", PyTuple_GET_ITEM(names[w], k));
+            }
+            Py_INCREF(v);
+            PyTuple_SET_ITEM(values, k, v);
+        }
+        keep(&watched[w][0], of[w]);
+        keep(&watched[w][1], names[w]);
+        keep(&watched[w][2], values);
+        Py_DECREF(values);
+        version[w] = 0;
+    }
     keep(&handle_type, h);
     keep(&problem_type, p);
     keep(&check, c);
     keep(&raw_stream, NULL);
+    keep(&bound_stream, NULL);
     Py_RETURN_NONE;
 }
 
 static PyObject *streams(PyObject *m, PyObject *args)
 {
-    PyObject *r, *d, *u;
+    PyObject *r, *d, *u, *b = NULL;
     (void)m;
-    if (!PyArg_ParseTuple(args, "OOO", &r, &d, &u)) return NULL;
+    if (!PyArg_ParseTuple(args, "OOO|O", &r, &d, &u, &b)) return NULL;
     keep(&current_device, d);
     keep(&ready, u);
     keep(&raw_stream, r);
+    keep(&bound_stream, b);
+    version[0] = 0;                                              /* (no dict has it) */
     Py_RETURN_NONE;
 }
 
 static PyMethodDef methods[] = {
-    {"setup", setup, METH_VARARGS, "setup(c_void_p, problem structure, its size, check(status, name))"},
-    {"streams", streams, METH_VARARGS, "streams(raw handle of a device's stream, current device, runtime is up)"},
+    {"setup", setup, METH_VARARGS, "setup(c_void_p, problem structure, its size, check(status, name), the binding's names, those to watch, the library's, those to watch)"},
+    {"streams", streams, METH_VARARGS, "streams(raw handle of a device's stream, current device, runtime is up[, the binding's _current_stream that asks them])"},
     {NULL, NULL, 0, NULL},
 };
 
@@ -347,7 +381,9 @@ PyMODINIT_FUNC PyInit__calls(void)
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
     s_type = PyUnicode_InternFromString("_type_");
-    if (!s_data_ptr || !s_cuda_stream || !s_type || PyType_Ready(&CallType) < 0) return NULL;
+    s_current_stream = PyUnicode_InternFromString("_current_stream");
+    CallType.tp_base = &PyFunction_Type;
+    if (!s_data_ptr || !s_cuda_stream || !s_type || !s_current_stream || PyType_Ready(&CallType) < 0) return NULL;
     PyObject *m = PyModule_Create(&module);
     if (!m) return NULL;
     Py_INCREF(&CallType);
@@ -358,3 +394,11 @@ PyMODINIT_FUNC PyInit__calls(void)
     }
     return m;
 }
+
+#else
+
+static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", NULL, -1, NULL, NULL, NULL, NULL, NULL};
+
+PyMODINIT_FUNC PyInit__calls(void) { return PyModule_Create(&module); }
+
+#endif

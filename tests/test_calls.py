@@ -162,3 +162,105 @@ def test_binding_holds_them():
         ng.ngemm_run_u8s8s32(None)
     with pytest.raises(ValueError):
         binding._calls.Call(print, "nothing", 1)
+
+
+def test_they_are_functions():
+    import types
+    import weakref
+    import paper_1910_00178_amd as ng
+    from paper_1910_00178_amd import binding
+    fn, plain = ng.ngemm_run_u8s8s32, ng.ngemm_run_u8s8s32.__wrapped__
+    assert type(plain) is types.FunctionType and inspect.isfunction(fn) and weakref.ref(fn)() is fn
+    assert repr(fn).startswith("<function ngemm_run_u8s8s32 at ")
+    for name in ("__code__", "__defaults__", "__globals__", "__kwdefaults__", "__closure__", "__annotations__", "__doc__", "__qualname__", "__module__"):
+        assert getattr(fn, name) == getattr(plain, name), name
+    assert ng.ngemm_tune_u8s8s32.__doc__ and inspect.getsource(fn) == inspect.getsource(plain)
+
+    class Holder:
+        run = fn
+    holder = Holder()
+    assert inspect.ismethod(holder.run) and holder.run.__self__ is holder and holder.run.__func__ is fn
+    with pytest.raises(TypeError):
+        holder.run(1, 2)
+    fn.note = 5
+    assert fn.__dict__.pop("note") == 5
+    assert {type(getattr(binding, name)) for name in binding._kinds} == {binding._calls.Call}
+
+
+def test_collected(both):
+    import gc
+    import weakref
+    call, _, _ = both("run")
+    call.itself = call
+    gone = weakref.ref(call)
+    del call
+    gc.collect()
+    assert gone() is None
+
+
+@pytest.mark.parametrize("name", ["_dev", "_stream", "_check"])
+def test_a_replaced_name_is_used(both, monkeypatch, name):
+    from paper_1910_00178_amd import binding
+    call, seen, given = both("run")
+    args, _ = usual("run")
+    assert call(*args) is None and not given
+    with monkeypatch.context() as m:
+        m.setattr(binding, name, lambda *a: None)
+        assert call(*args) == "slow" and call(*args) == "slow"
+    assert call(*args) is None and len(seen) == 2 and len(given) == 2
+
+
+def test_a_replaced_library_function_is_used(monkeypatch):
+    import paper_1910_00178_amd as ng
+    from paper_1910_00178_amd import binding
+    args, want = usual("run")
+    seen = []
+
+    def status(*a):
+        seen.append(a)
+        return 0
+    monkeypatch.setattr(binding._lib, "ngemm_run_u8s8s32", status)
+    assert ng.ngemm_run_u8s8s32(*args) is None
+    assert [a.value if type(a) is P else a for a in seen[0]] == want
+    fake = type("Lib", (), {"ngemm_run_u8u8s32": staticmethod(status)})
+    monkeypatch.setattr(binding, "_lib", fake)
+    assert ng.ngemm_run_u8u8s32(*args) is None and len(seen) == 2
+
+
+def test_other_code_defaults_and_stream_lookup(both, monkeypatch):
+    from paper_1910_00178_amd import binding
+    call, seen, given = both("run")
+    args, _ = usual("run")
+    monkeypatch.setattr(binding, "_current_stream", lambda: 9)
+    binding._calls.streams(lambda d: 0x100 + d, lambda: 7, lambda: True, binding._current_stream)
+    assert call(*args[:9]) is None and seen[-1][11] == 0x107
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_current_stream", lambda: 8)           # asked itself
+        assert call(*args[:9]) == "slow" and call(*args) is None
+    assert call(*args[:9]) is None
+    call.__defaults__ = (1,)
+    assert call(*args) == "slow"
+    call.__defaults__ = None
+    assert call(*args) is None
+    code = call.__code__
+
+    def other(*a, **kw):
+        return given, "other"
+    call.__code__ = other.__code__.replace(co_freevars=code.co_freevars)
+    assert call(*args)[1] == "other"
+    call.__code__ = code
+    assert call(*args) is None
+
+
+def test_a_profiler_sees_them(both):
+    import sys
+    call, seen, given = both("run")
+    args, _ = usual("run")
+    events = []
+    sys.setprofile(lambda frame, event, arg: events.append((event, frame.f_code.co_name)))
+    try:
+        call(*args)
+    finally:
+        sys.setprofile(None)
+    assert ("call", "slow") in events and len(given) == 1 and not seen
+    assert call(*args) is None and len(seen) == 1
