@@ -31,10 +31,17 @@ class Stream:
     cuda_stream = 0x5eed
 
 
-@pytest.fixture()
-def both():
+def forget_streams():
+    """What the binding knows of the current stream: nothing, so that the next call without a stream looks for it."""
+    from paper_1910_00178_amd import binding
+    binding._calls.streams(None, None, None)
+    binding._current_stream = binding._slow_current_stream
+
+
+def watched_calls():
     """both(kind, status) -> (native call, what the C function saw, what the Python function was given)"""
     from paper_1910_00178_amd import binding
+    forget_streams()
     keep = []
 
     def make(kind, status=0):
@@ -54,7 +61,10 @@ def both():
         keep.append(fn)
         return binding._calls.Call(slow, kind, ctypes.cast(fn, P).value), seen, given
     yield make
-    binding._calls.streams(None, None, None)
+    forget_streams()
+
+
+both = pytest.fixture(watched_calls, name="both")
 
 
 def usual(kind):
@@ -122,6 +132,16 @@ def test_defaults_and_stream(both):
     n = len(seen)
     assert call(*args[:9]) == "slow" and len(seen) == n
     assert len(given) == 2
+
+
+def test_these_tests_leave_the_stream_to_be_found():
+    from paper_1910_00178_amd import binding
+    steps = watched_calls()
+    next(steps)
+    binding._calls.streams(lambda d: 1, lambda: 2, lambda: True)
+    binding._current_stream = lambda: 4                   # as a call that has found it leaves them
+    next(steps, None)
+    assert binding._current_stream is binding._slow_current_stream
 
 
 def test_whole_numbers_at_their_ends(both):
