@@ -233,26 +233,84 @@ def test_u8_every_number_of_steps(runner, M, N, pad):
         ng.ngemm_packed_b_free(h)
 
 
-# Pitches at which a tile's rows lie further apart than the kernel counts: the kernels before it, and for 16-bit operands the looping form, serve them.
-@pytest.mark.parametrize("op,M,K", [("u8", 3, 200), ("u8", 40, 200), ("s16", 3, 100), ("s16", 40, 300), ("raw", 5, 192), ("raw", 40, 192)])
-@pytest.mark.parametrize("far", [False, True])
-def test_rows_far_apart(runner, op, M, K, far):
+# The same for the forms with a ring of three (32 x 64, 64 x 64 and 64 x 128 tiles of four wavefronts, aligned rows): other steps laid out, another first wait.
+# From the smallest K that the rules give them over all that the last steps, the parity of the first fragments and the ring can meet; packed B and the
+# caller's.  The allocations end with the last byte.
+THREE = [(600, 700, 1, "gemm_wavek_kernel<1, 1, 2, 4, 3,"), (700, 1400, 1025, "gemm_wavek_kernel<1, 2, 2, 4, 3,"), (200, 6000, 3072, "gemm_wavek_kernel<1, 2, 4, 4, 3,")]
+
+
+@pytest.mark.parametrize("M,N,first,kernel", THREE)
+@pytest.mark.parametrize("raw", [False, True], ids=["packed", "unpacked"])
+def test_u8_every_number_of_steps_of_a_ring_of_three(runner, launches, M, N, first, kernel, raw):  # noqa: F811
     import torch
     import paper_1910_00178_amd as ng
-    N, size = 70, 2 if op == "s16" else 1
-    ld = ((1 << 31) // 64 - 8192 + (16384 if far else -16384)) // size       # (the line lies at 2^31 - 8192 bytes over 64 rows)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    most = first + 64 * 37
+    Aall = torch.randint(0, 256, (M, most), generator=gen, device="cuda", dtype=torch.uint8)
+    Ball = torch.randint(-128, 128, (N, most), generator=gen, device="cuda", dtype=torch.int8)
+    Ad, Bd = Aall.double(), Ball.double()
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, most) + ng.ngemm_workspace_bytes(M, N, most)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    for n, K in enumerate(first + 64 * q + r for q in range(36) for r in ((0, 9, 53) if q % 3 else (23, 32))):
+        za, zb, ld = 131, (0, 5)[n % 2], (K + 15) // 16 * 16
+        A, B = (torch.zeros((X.shape[0], ld), dtype=X.dtype, device="cuda") for X in (Aall, Ball))
+        A[:, :K], B[:, :K] = Aall[:, :K], Ball[:, :K]
+        A, B = A.view(-1)[:(M - 1) * ld + K].clone(), B.view(-1)[:(N - 1) * ld + K].clone()
+        C = torch.full((M + 1, N + 1), -7, dtype=torch.int32, device="cuda")
+        if not raw:
+            nb = ng.ngemm_packed_b_bytes(K, N)
+            packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+            h = ng.ngemm_pack_b(runner.ctx, K, N, B, ld, packed, nb)
+
+        def call(stream):
+            if raw:
+                ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, A, ld, za, B, ld, zb, C, N + 1, ws, wsb, stream)
+            else:
+                ng.ngemm_run_u8s8s32(runner.ctx, M, A, ld, za, h, zb, C, N + 1, ws, wsb, stream)
+        if n % 16 == 0:
+            torch.cuda.synchronize()
+            names = [name for name, _ in launches(call)]
+            assert len(names) == 1 and names[0].startswith(kernel), (K, names)
+        call(None)
+        want = ((Ad[:, :K] - za) @ (Bd[:, :K] - zb).t()).int()
+        assert torch.equal(C[:M, :N], want) and bool((C[M:] == -7).all()) and bool((C[:, N:] == -7).all()), (K, zb)
+        if not raw: ng.ngemm_packed_b_free(h)
+
+
+# Pitches at which a tile's rows lie further apart than the kernel counts: the kernels before it, and for 16-bit operands below two stages of the 128 x 128
+# kernel the looping form, serve them.  "line": 16 KiB to either side of where the rule lies (2^31 - 8192 bytes over 64 rows of A, 128 of an unpacked
+# B); "far": the last row is 4 GiB and more from the first, so that an offset of 32 bits would name another one.
+FAR = [("u8", 3, 70, 200), ("u8", 40, 70, 200), ("u8 any", 40, 70, 201), ("s16", 3, 70, 100), ("s16", 40, 70, 100), ("s16", 40, 70, 300), ("raw", 5, 70, 192),
+       ("raw", 40, 70, 192), ("raw B", 40, 5, 192), ("raw B", 40, 70, 192), ("raw any", 40, 70, 191)]
+
+
+@pytest.mark.parametrize("op,M,N,K", FAR)
+@pytest.mark.parametrize("where", ["near the line", "past the line", "far"])
+def test_rows_far_apart(runner, launches, op, M, N, K, where):  # noqa: F811
+    import torch
+    import paper_1910_00178_amd as ng
+    size, of_b = 2 if op == "s16" else 1, op == "raw B"
+    rows = N if of_b else M
+    line = ((1 << 31) - 8192) // (128 if of_b else 64)
+    ld = {"near the line": line - 16384, "past the line": line + 16384, "far": max((1 << 32) // (rows - 1) // 16 * 16 + 16, line + 16384)}[where] // 16 * 16 // size
+    if op.endswith("any"): ld += 3
+    assert where != "far" or (rows - 1) * ld * size >= 1 << 32
     gen = torch.Generator(device="cuda").manual_seed(M + K)
     ta, tb = (torch.int16, torch.int16) if op == "s16" else (torch.uint8, torch.int8)
     ia, ib = torch.iinfo(ta), torch.iinfo(tb)
     A = torch.randint(ia.min, ia.max + 1, (M, K), generator=gen, device="cuda", dtype=ta)
     B = torch.randint(ib.min, ib.max + 1, (N, K), generator=gen, device="cuda", dtype=tb)
-    Abuf = torch.empty((M - 1) * ld + K, dtype=ta, device="cuda")
-    Abuf.as_strided((M, K), (ld, 1)).copy_(A)
+    far = torch.empty((rows - 1) * ld + K, dtype=tb if of_b else ta, device="cuda")
+    far.as_strided((rows, K), (ld, 1)).copy_(B if of_b else A)
     C = torch.full((M + 1, N + 2), -7, dtype=torch.int32, device="cuda")
-    if op == "raw":
+    h = None
+    if op.startswith("raw"):
         wsb = ng.ngemm_unpacked_workspace_bytes(M, N, K)
         ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
-        ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, Abuf, ld, 37, B, K, 3, C, N + 2, ws, wsb)
+        Ad, lda, Bd, ldb = (A, K, far, ld) if of_b else (far, ld, B, K)
+
+        def call(stream):
+            ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, Ad, lda, 37, Bd, ldb, 3, C, N + 2, ws, wsb, stream)
     else:
         size_of, pack, run = (ng.ngemm_packed_b_bytes_s16, ng.ngemm_pack_b_s16, ng.ngemm_run_s16s16s32) if op == "s16" else \
             (ng.ngemm_packed_b_bytes, ng.ngemm_pack_b, ng.ngemm_run_u8s8s32)
@@ -261,11 +319,58 @@ def test_rows_far_apart(runner, op, M, K, far):
         h = pack(runner.ctx, K, N, B, K, packed, nb)
         wsb = ng.ngemm_workspace_bytes(M, N, K)
         ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
-        run(runner.ctx, M, Abuf, ld, 37, h, 3, C, N + 2, ws, wsb)
+
+        def call(stream):
+            run(runner.ctx, M, far, ld, 37, h, 3, C, N + 2, ws, wsb, stream)
+    names = [name for name, _ in launches(call)]
+    wavek = [name for name in names if name.startswith("gemm_wavek_kernel<")]
+    if where == "near the line":
+        assert len(names) == len(wavek) == 1, names
+    elif op == "s16" and K < 128:
+        assert len(names) == 1 and names[0].endswith(", true>") and wavek, names       # the looping form
+    else:
+        assert not wavek, names
+    torch.cuda.synchronize()
+    call(0)
+    torch.cuda.synchronize()
+    if h is not None:
         ng.ngemm_packed_b_free(h)
     want = ((A.double() - 37) @ (B.double() - 3).t()).long()
     want = ((want + 2**31) % 2**32 - 2**31).int()
     assert torch.equal(C[:M, :N], want) and bool((C[M:] == -7).all()) and bool((C[:, N:] == -7).all())
+
+
+# Panels: a K of 2^24 - 64 is the first whose columns are too long (u8 outputs with a zero-point per column, which the K split over workgroups does not serve).
+@pytest.mark.parametrize("K,near", [((1 << 24) - 192, True), ((1 << 24) - 64, False)])
+def test_panels_far_apart(runner, launches, K, near):  # noqa: F811
+    import torch
+    import paper_1910_00178_amd as ng
+    M, N = 33, 40
+    A = torch.randint(0, 256, (M, K), device="cuda", dtype=torch.uint8)
+    B = torch.randint(-128, 128, (N, K), device="cuda", dtype=torch.int8)
+    zb = torch.randint(-9, 9, (N,), device="cuda", dtype=torch.int32)
+    scales = torch.full((N,), 2.0 ** -24, device="cuda")
+    nb = ng.ngemm_packed_b_bytes(K, N)
+    packed = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    h = ng.ngemm_pack_b(runner.ctx, K, N, B, K, packed, nb)
+    wsb = ng.ngemm_workspace_bytes(M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    C = torch.full((M + 1, N), 77, dtype=torch.uint8, device="cuda")
+
+    def call(stream):
+        ng.ngemm_run_u8s8u8_requant_channel(runner.ctx, M, A, K, 37, h, 0, zb, scales, None, False, 128, C, N, ws, wsb, stream)
+    names = [name for name, _ in launches(call)]
+    assert len(names) == 1 and names[0].startswith("gemm_wavek_kernel<") == near, names
+    torch.cuda.synchronize()
+    call(0)
+    sums = torch.zeros((M, N), dtype=torch.float64, device="cuda")           # (whole numbers below 2^53: exact)
+    for k in range(0, K, 1 << 20):
+        sums += (A[:, k:k + (1 << 20)].double() - 37) @ (B[:, k:k + (1 << 20)].double() - zb[:, None]).t()
+    sums = (sums.long() + 2**31) % 2**32 - 2**31
+    want = (torch.round(sums.float() * 2.0 ** -24).double() + 128).clamp(0, 255).to(torch.uint8)
+    torch.cuda.synchronize()
+    assert torch.equal(C[:M], want) and bool((C[M:] == 77).all())
+    ng.ngemm_packed_b_free(h)
 
 
 # (M, N, K, zero-point, output, kernel): each line of the rules that give a call 32 x 64 or 64 x 64 tiles of four wavefronts, on both sides
