@@ -1002,8 +1002,6 @@ GemmParams make_params(const RunArgs &a, int nxcd)
     p.A = a.A;
     p.lda = a.lda;
     p.Bp = B->data;
-    p.colsum = (const int32_t *)(B->data + B->Kp * B->Np);
-    p.rowsum = nullptr;
     p.C = a.C;
     p.ldc = a.ldc;
     p.M = (int)a.M;
@@ -1015,13 +1013,11 @@ GemmParams make_params(const RunArgs &a, int nxcd)
     p.a_xor = a.a_signed ? 0u : 0x80808080u;
     p.za_term = (uint32_t)(shift - a.za);
     p.zb = (uint32_t)a.zb;
-    p.kconst = 0u - (uint32_t)a.zb * (uint32_t)(shift - a.za) * (uint32_t)B->K;
     p.scale = a.scale;
     p.zc = a.zc;
     p.scale_vec = a.scale_vec;
     p.bias_vec = a.bias_vec;
     p.zb_vec = a.zb_vec;
-    p.rconst = (uint32_t)(shift - a.za) * (uint32_t)B->K;
     p.relu = a.relu;
     p.ksplit = 1;
     p.kchunk = 0;
@@ -1586,7 +1582,6 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     p.A = (const uint8_t *)A_dev;
     p.lda = lda * 2;
     p.Bp = B->data;
-    p.colsum = (const int32_t *)(B->data + B->Kp * B->Np);
     p.C = C_dev;
     p.ldc = ldc;
     p.M = (int)M; p.N = (int)B->N; p.K = (int)B->K; p.Kp = (int)B->Kp;
@@ -1594,7 +1589,6 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     // sum (a-za)(b-zb) = sum (a-128)(b-128) + (128-za) colsum'[j] - (zb-128) rowsum'[i] - (zb-128)(128-za) K
     p.za_term = (uint32_t)(128 - a_zero_point);
     p.zb = (uint32_t)(b_zero_point - 128);
-    p.kconst = 0u - (uint32_t)(b_zero_point - 128) * (uint32_t)(128 - a_zero_point) * (uint32_t)B->K;
     p.nxcd = ctx->num_xcd;
     // Small outputs run the kernel that splits K over a workgroup's wavefronts (no row-sum launch, tiles small
     // enough to spread over the compute units): 32 x 32 tiles while there is a compute unit for each, 32 x 64 up

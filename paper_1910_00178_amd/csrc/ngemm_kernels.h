@@ -26,6 +26,8 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kFragBytes = 1024;   // 32 columns x 32 k-values
 
+// What a kernel works from.  The host fills in what GemmArgs carries, and with it the tile counts, which it needs for the grid; on the device params_of
+// and group_member_params derive the others, colsum of a packed B, kconst and rconst among them, which the host leaves empty.
 struct GemmParams {
     const uint8_t *A;       // row-major u8
     int64_t lda;
