@@ -225,6 +225,18 @@ __device__ __forceinline__ v4i bytes_from(int n)
     return m;
 }
 
+// Mask of 16 packed bytes with ones in the bytes < n, in half the instructions: for where they stand between a wavefront's data and its matrix ops.
+__device__ __forceinline__ v4i bytes_below(int n)
+{
+    v4i m;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int half = 4 * n - 16 * q, s = half < 0 ? 0 : half > 16 ? 16 : half;       // (two shifts, of up to 16 each: one by 32 would shift by none)
+        m[q] = (int)~((0xffffffffu << s) << s);
+    }
+    return m;
+}
+
 // u8 -> s8 shift of 16 packed bytes: a xor 0x80 == a - 128 read as signed (mask 0x80808080);
 // a signed A operand passes with mask 0.
 __device__ __forceinline__ v4i shift_u8_to_s8(v4i v, uint32_t mask)
@@ -3072,20 +3084,16 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
         }
     };
     // what the last step holds past K: out of the row sums (there zero, as the shift then counts it), and out of an unpacked B
-    auto mask_end = [&](auto set) {
+    auto exist_of = [&](int x) { return bytes_below(kbytes - (kend + (ELEM == 1 ? 2 * x + (lane >> 5) : 2 * (lane >> 5) + x) * 16)); };
+    auto mask_end = [&](auto set, int x, v4i exist) {
         constexpr int S = decltype(set)::value;
-        const int h = lane >> 5;
+        if (ROWS) {
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            const v4i e = ~bytes_from(kbytes - (kend + (ELEM == 1 ? 2 * x + h : 2 * h + x) * 16));
-            if (ROWS) {
+            for (int i = 0; i < TM; ++i) fa[S][i][x] &= exist;
+        }
+        if (BRAW) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i) fa[S][i][x] &= e;
-            }
-            if (BRAW) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j) fb[S][j][x] &= e;
-            }
+            for (int j = 0; j < TN; ++j) fb[S][j][x] &= exist;
         }
     };
     v16i acc[NACC][TM][TN];
@@ -3193,7 +3201,8 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
         }
         if (ROWS || BRAW) {
             __builtin_amdgcn_s_waitcnt(0xc07f);
-            mask_end(set);
+            mask_end(set, 0, exist_of(0));
+            mask_end(set, 1, exist_of(1));
         }
     };
     if (cnt > 0) {
@@ -3231,9 +3240,8 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
                 }
             }
             wait_vmcnt<0>();                             // what was requested past the end has come to nothing
-        } else {
+        } else if (__builtin_expect(cnt > 1, 1)) {
             if (cnt >= RING) wait_vmcnt<(RING - 1) * LPS>();             // step 0 has landed
-            else if (cnt == 1) wait_vmcnt<0>();
             else if (cnt == 2) wait_vmcnt<LPS>();
             else wait_vmcnt<(RING > 3 ? 2 : 0) * LPS>();
             __builtin_amdgcn_sched_barrier(0);
@@ -3252,6 +3260,23 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
             });
             if (t_end >= 0) finish_end(IntC<(RING - 1) & 1>{});
             step(IntC<RING - 1>{}, IntC<-1>{}, IntC<0>{});
+        } else {
+            // One step and nothing to overlap: the masks while it is on its way, what its copies left out before its fragments are read, and code
+            // of its own (with the masks formed behind the reads and the fragments read once more behind the repair, K = 65 to 127 with
+            // a zero-point took 0.05 us more than the kernel before and 0.15 more than so).
+            v4i exist[2];
+            if (ROWS || BRAW) {
+                exist[0] = t_end < 0 ? v4i{-1, -1, -1, -1} : exist_of(0);
+                exist[1] = t_end < 0 ? v4i{-1, -1, -1, -1} : exist_of(1);
+            }
+            wait_vmcnt<0>();
+            if (__builtin_expect(fixes, 0)) apply_fix(0);
+            read_frags(IntC<0>{}, 0);
+            if (ROWS || BRAW) {
+                mask_end(IntC<0>{}, 0, exist[0]);
+                mask_end(IntC<0>{}, 1, exist[1]);
+            }
+            compute(IntC<0>{});
         }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);

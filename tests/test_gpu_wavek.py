@@ -233,6 +233,36 @@ def test_u8_every_number_of_steps(runner, M, N, pad):
         ng.ngemm_packed_b_free(h)
 
 
+# At most one step per wavefront, aligned rows: a branch of its own, in which K ends in any byte of the step or not at all.  The allocations end with
+# the last byte of the last row.
+@pytest.mark.parametrize("op", ["u8", "s16", "unpacked"])
+@pytest.mark.parametrize("M,N", [(1, 70), (17, 33), (40, 96)])
+def test_one_step_per_wavefront(runner, op, M, N):
+    import torch
+    import paper_1910_00178_amd as ng
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    ta, tb, elems = (torch.int16, torch.int16, 8) if op == "s16" else (torch.uint8, torch.int8, 16)
+    ia, ib = torch.iinfo(ta), torch.iinfo(tb)
+    size, pack, run = (ng.ngemm_packed_b_bytes_s16, ng.ngemm_pack_b_s16, ng.ngemm_run_s16s16s32) if op == "s16" else \
+        (ng.ngemm_packed_b_bytes, ng.ngemm_pack_b, ng.ngemm_run_u8s8s32)
+    wsb = ng.ngemm_unpacked_workspace_bytes(M, N, 300) + ng.ngemm_workspace_bytes(M, N, 300)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    for K in range(1, 17 * elems + 1):
+        ld = (K + elems - 1) // elems * elems
+        A = torch.randint(ia.min, ia.max + 1, ((M - 1) * ld + K,), generator=gen, device="cuda", dtype=ta)
+        B = torch.randint(ib.min, ib.max + 1, ((N - 1) * ld + K,), generator=gen, device="cuda", dtype=tb)
+        C = torch.full((M + 1, N + 1), -7, dtype=torch.int32, device="cuda")
+        za, zb = ((131, 0), (131, 5), (128, -3))[K % 3]
+        if op == "unpacked":
+            ng.ngemm_run_u8s8s32_unpacked(runner.ctx, M, N, K, A, ld, za, B, ld, zb, C, N + 1, ws, wsb)
+        else:
+            packed = torch.empty(size(K, N), dtype=torch.uint8, device="cuda")
+            h = pack(runner.ctx, K, N, B, ld, packed, packed.numel())
+            run(runner.ctx, M, A, ld, za, h, zb, C, N + 1, ws, wsb)
+            ng.ngemm_packed_b_free(h)
+        _check(A.as_strided((M, K), (ld, 1)), B.as_strided((N, K), (ld, 1)), za, zb, C)
+
+
 # The same for the forms with a ring of three (32 x 64, 64 x 64 and 64 x 128 tiles of four wavefronts, aligned rows): other steps laid out, another first wait.
 # From the smallest K that the rules give them over all that the last steps, the parity of the first fragments and the ring can meet; packed B and the
 # caller's.  The allocations end with the last byte.
