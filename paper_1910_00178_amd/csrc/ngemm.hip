@@ -686,9 +686,34 @@ hipError_t launch_wavek_areg(const GemmParams &p, bool requant, bool rows, hipSt
     return rows ? launch_wavek<F, 1, false, true, false, true>(p, st) : launch_wavek<F, 1, false, false, false, true>(p, st);
 }
 
-hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, bool rows, hipStream_t st)
+// Whether the 32 x 64 tiles wait for all of their loads in every other step.  A's steps are halves of 128-byte lines, and the other half is wanted by
+// the tile's other wavefront a step later.  With two or three tiles to a unit and four steps of each on their way the vector cache has lost the line by then,
+// and calls with a long K took up to 8 % longer than with half as many.  With one tile to a unit, and with a fourth of a unit's tiles in a round
+// of their own, the deeper pipeline is worth more.  Averages of 6500 drawn calls, the kernel before this pipeline over (deep / waiting):
+// 257 to 512 tiles, M <= 32: K = 2000 .. 3000 1.03 / 1.07, 4000 .. 8000 0.98 / 1.04, M > 32: 1.08 / 1.12, 1.01 / 1.07; 513 to 768: K = 2000 .. 3000
+// 1.06 / 1.06, 3000 .. 4500 1.04 / 1.05; up to 256: 1.2-1.37 / 1.08-1.14; 769 to 1023: 1.17-1.22 / 1.12-1.15.  Below K = 2048 it is a tie.
+bool wavek_areg_drains(int64_t M, int64_t N, int64_t K, int64_t cus)
 {
-    return form == 11 ? launch_wavek_areg<WaveK11>(p, requant, rows, st) : launch_wavek_areg<WaveK12Short>(p, requant, rows, st);
+    const int64_t t64 = ((M + 31) / 32) * ((N + 63) / 64);
+    return t64 > cus && t64 <= 3 * cus && K >= 2048;
+}
+
+template <class F>
+hipError_t launch_wavek_drain(const GemmParams &p, bool requant, bool rows, hipStream_t st)
+{
+    auto go = [&](auto kernel) {
+        const int64_t tiles = ((int64_t)(p.M + F::TM * 32 - 1) / (F::TM * 32)) * ((p.N + F::TN * 32 - 1) / (F::TN * 32));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(F::NW * 64), (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, args_of(p));
+        return hipGetLastError();
+    };
+    if (requant) return rows ? go(gemm_wavek_drain_kernel<F::TM, F::TN, F::NW, F::RING, true, true>) : go(gemm_wavek_drain_kernel<F::TM, F::TN, F::NW, F::RING, true, false>);
+    return rows ? go(gemm_wavek_drain_kernel<F::TM, F::TN, F::NW, F::RING, false, true>) : go(gemm_wavek_drain_kernel<F::TM, F::TN, F::NW, F::RING, false, false>);
+}
+
+hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, bool rows, int64_t cus, hipStream_t st)
+{
+    if (form == 11) return launch_wavek_areg<WaveK11>(p, requant, rows, st);
+    return wavek_areg_drains(p.M, p.N, p.K, cus) ? launch_wavek_drain<WaveK12Short>(p, requant, rows, st) : launch_wavek_areg<WaveK12Short>(p, requant, rows, st);
 }
 
 // Whether a form's workgroups, one per tile, keep within a caller's cap (budget < cus).  Up to 32 rows they need not: the
@@ -1054,7 +1079,7 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
         const int form = wavek_form_of(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
         if (form != 0) {
             const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
-                                         : launch_wavek_areg_form(form, p, a.requant, rows_needed, st);
+                                         : launch_wavek_areg_form(form, p, a.requant, rows_needed, device_cus, st);
             return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
         const int mid = kernel == NGEMM_KERNEL_SPLIT_K ? 0 : mid_form(route.measured ? NGEMM_KERNEL_AUTO : kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed,

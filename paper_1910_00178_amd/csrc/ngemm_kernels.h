@@ -2819,6 +2819,8 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmArgs a)
 // before / so: 1 x 4096 x 1024 3.80 / 3.26, 16 x 1088 x 384 3.42 / 3.00, 64 x 4096 x 4096 z 7.07 / 6.47, 256 x 320 x 260 u8 z 4.40 / 3.69, 16-bit
 // 512 x 768 x 768 6.11 / 5.37, 64 x 94 x 186 4.46 / 3.93, unaligned 54 x 2556 x 331 u8 5.03 / 3.62; 13000 drawn calls 1.10 x.
 // NT: non-temporal copies of B, for weights that are read once (the rule that chooses it has the figures).
+// DRAIN (with AREG): every other step waits for all that has been asked for, half of the four steps' lead (gemm_wavek_drain_kernel; the rule that
+// chooses it has the figures; as a branch in the one kernel it cost the calls that do not wait 1 %).
 // LOOP: fewer workgroups than tiles, for a caller that caps them (the others launch a workgroup per tile).
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
 // 4096 45.6 -> 8.5 (3.9 TB/s of B's planes), 64 x 4096 x 4096 46.0 -> 11.1, 512 x 768 x 768 15.0 -> 5.8, 1024^3
@@ -2844,7 +2846,7 @@ struct WaveKCfg {
 // p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
 // count tiles of 32 TM x 32 TN.  Offsets from a tile's first row and panel have to stay below 2 GiB, but for LOOP.
 template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
-          bool LOOP = false, bool GROUP = false>        // (GROUP: a function of its own, the host pass takes no second caller of one)
+          bool LOOP = false, bool GROUP = false, bool DRAIN = false>    // (GROUP: a function of its own, the host pass takes no second caller of one)
 __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int tile, int stride)
 {
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
@@ -3180,6 +3182,7 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (W >= 0) read_frags(IntC<X ^ 1>{}, nxt);
         if constexpr (AREG) {
+            if constexpr (DRAIN && decltype(asks)::value > 1 && (V & 1) == 0) wait_vmcnt<0>();
             if (!brief) write_regs(IntC<(V + 2) % 4>{}, nxt + Cfg::kStepBytes == Cfg::kWaveBytes ? 0 : nxt + Cfg::kStepBytes);
             if constexpr (ASKS) load_regs(IntC<V % 4>{}, t + RING, IntC<(decltype(asks)::value > 1)>{});
         }
@@ -3263,7 +3266,7 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
         } else {
             // One step and nothing to overlap: the masks while it is on its way, what its copies left out before its fragments are read, and code
             // of its own (with the masks formed behind the reads and the fragments read once more behind the repair, K = 65 to 127 with
-            // a zero-point took 0.05 us more than the kernel before and 0.15 more than so).
+            // a zero-point took 3.45 us at one row, so 3.29).
             v4i exist[2];
             if (ROWS || BRAW) {
                 exist[0] = t_end < 0 ? v4i{-1, -1, -1, -1} : exist_of(0);
@@ -3391,6 +3394,12 @@ __global__ __launch_bounds__(NW * 64, (WaveKCfg<TM, TN, NW, RING>::kWavesPerSimd
 {
     wavek_body<ELEM, TM, TN, NW, RING, REQUANT, ROWS, BRAW, AREG, NT, LOOP>(params_of<ELEM, TM * 32, TN * 32, BRAW>(args), args.ldb, blockIdx.x,
                                                                            count_of(args));
+}
+
+template <int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS>
+__global__ __launch_bounds__(NW * 64, (WaveKCfg<TM, TN, NW, RING>::kWavesPerSimd)) void gemm_wavek_drain_kernel(const GemmArgs args)
+{
+    wavek_body<1, TM, TN, NW, RING, REQUANT, ROWS, false, true, false, false, false, true>(params_of<1, TM * 32, TN * 32>(args), 0, blockIdx.x, 0);
 }
 
 // ---- skinny-M kernel (M <= 32) --------------------------------------------------------------

@@ -307,6 +307,32 @@ def test_u8_every_number_of_steps_of_a_ring_of_three(runner, launches, M, N, fir
         if not raw: ng.ngemm_packed_b_free(h)
 
 
+# Rows of any alignment, long, two 32 x 64 tiles to a unit: from K = 2048 on every other step waits for all of its loads.  Every number of steps
+# modulo the four that are laid out, on both sides of the line, the first and last number of tiles that it holds for.
+@pytest.mark.parametrize("M,N", [(13, 16384), (13, 16385), (12, 49152), (300, 3000)])
+def test_long_unaligned_rows_two_tiles_to_a_unit(runner, launches, M, N):  # noqa: F811
+    import torch
+    import paper_1910_00178_amd as ng
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    wsb = ng.ngemm_workspace_bytes(M, N, 2700)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    for K in (2047, 2049, 2111, 2175, 2241, 2300, 2367, 2431, 2497, 2570, 2625):
+        A = torch.randint(0, 256, (M * K,), generator=gen, device="cuda", dtype=torch.uint8)
+        B = torch.randint(-128, 128, (N, K), generator=gen, device="cuda", dtype=torch.int8)
+        packed = torch.empty(ng.ngemm_packed_b_bytes(K, N), dtype=torch.uint8, device="cuda")
+        h = ng.ngemm_pack_b(runner.ctx, K, N, B, K, packed, packed.numel())
+        C = torch.full((M + 1, N + 1), -7, dtype=torch.int32, device="cuda")
+        zb = (0, 5)[K & 2 and 1]
+        call = lambda stream: ng.ngemm_run_u8s8s32(runner.ctx, M, A, K, 131, h, zb, C, N + 1, ws, wsb, stream)
+        torch.cuda.synchronize()
+        names = [name for name, _ in launches(call)]
+        kernel = "gemm_wavek_drain_kernel<1, 2, 2, 4," if N != 16384 and K >= 2048 else "gemm_wavek_kernel<1, 1, 2, 2, 4," if M <= 32 else "gemm_"
+        assert len(names) == 1 and names[0].startswith(kernel), (K, names)
+        call(None)
+        _check(A.view(M, K), B, 131, zb, C)
+        ng.ngemm_packed_b_free(h)
+
+
 # Pitches at which a tile's rows lie further apart than the kernel counts: the kernels before it, and for 16-bit operands below two stages of the 128 x 128
 # kernel the looping form, serve them.  "line": 16 KiB to either side of where the rule lies (2^31 - 8192 bytes over 64 rows of A, 128 of an unpacked
 # B); "far": the last row is 4 GiB and more from the first, so that an offset of 32 bits would name another one.
