@@ -1910,17 +1910,20 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
     // unit, and twice as many where the chains are long.  In a graph, on drawn batches with a member of M > 32, the other kernels' time over this
     // one's: 1.02-1.05 on up to 512 tiles with a longest K of 65 to 256, 1.12 up to 512, 1.22 up to 1024, 1.27 up to 1536; 1.4-1.5 from 2048 on, up
     // to 1024 tiles; on 513 to 1024 tiles with K up to 1024 0.9, and from 1025 tiles on 0.5-0.8 (K over 2048: 1.15).  Between 1536 and 2048 the 64 x 64
-    // tiles stay.  Groups of skinny members alone do not gain (0.9-1.0): their panels have eight wavefronts to a workgroup already.
-    int64_t tiles32 = 0, longest = 0;
+    // tiles stay.  Groups of skinny members alone do not gain (0.9-1.0): their panels have eight wavefronts to a workgroup already.  Up to K = 1024 a
+    // member of up to eight rows is no long chain: as a panel it takes no longer than here, so the line is drawn by the others.  (Batches whose only K over
+    // 256 was such a member's ran at 0.89-1.15 x, 1.01 on average; with a longer K, or more rows, at 1.0-1.3.)
+    int64_t tiles32 = 0, longest = 0, chain = 0;
     bool near = true;
     for (const std::vector<Pending> *v : {&tile_members, &skinny_members})
         for (const Pending &m : *v) {
             tiles32 += (int64_t)((m.p.M + 31) / 32) * m.p.npanels;
             longest = std::max<int64_t>(longest, m.p.K);
+            if (m.p.M > 8 || m.p.K > 1024) chain = std::max<int64_t>(chain, m.p.K);
             near = near && wavek_offsets_fit(m.p.lda, m.p.K, m.p.Kp);
         }
     if (!tile_members.empty() && stream_members.empty() && near &&
-        ((longest > 256 && longest <= 1536 && tiles32 <= 2 * cus) || (longest >= 2048 && tiles32 <= 4 * cus))) {
+        ((chain > 256 && longest <= 1536 && tiles32 <= 2 * cus) || (longest >= 2048 && tiles32 <= 4 * cus))) {
         small_tiles = true;
         skinny_members.insert(skinny_members.end(), tile_members.begin(), tile_members.end());
         tile_members.clear();

@@ -225,7 +225,7 @@ def test_grouped_tiles(runner, launches, wide):  # noqa: F811
     rng = np.random.default_rng(31)
     ks = [0, 1, 15, 16, 17, 63, 64, 65, 80, 127, 128, 129, 191, 257, 320, 383, 449, 513, 640, 705, 769, 1000, 1100, 1663]
     shapes = [((33, 64, 65, 129)[i % 4], (1, 31, 64, 65, 130)[i % 5], k, k + (0, 3, 16)[i % 3]) for i, k in enumerate(ks)]
-    shapes += [(7, 100, 700, 701)] + ([(35, 40, 16, (1 << 24) + 256 * 1024)] if wide else [])
+    shapes += [(7, 100, 700, 701)] + ([(35, 40, 16, 1 << 27)] if wide else [])
     items, want, outs, keep, handles = [], [], [], [], []
     for t, (M, N, K, pitch) in enumerate(shapes):
         A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(N, K), dtype=np.int8)
@@ -280,7 +280,10 @@ def test_grouped_tiles_of_few_short_chains(runner, launches, shapes, want):  # n
     ([(40, 70, 4113), (35, 40, 16)], "far apart"),                                            # the second one's rows
     ([(64, 8192, 300)], True), ([(64, 8193, 300)], False), ([(33, 100, 257)], True), ([(33, 100, 256)], False), ([(33, 100, 1537)], False),
     ([(33, 100, 2047)], False), ([(512, 2048, 2048)], True), ([(512, 2049, 2048)], False), ([(32, 100, 700)] * 3, False),
-    ([(33, 40, 300 + i) for i in range(80)], True)], ids=lambda s: str(s) if isinstance(s, (bool, str)) else "%dx%s" % (len(s), s[0]))
+    ([(33, 40, 300 + i) for i in range(80)], True),
+    # members of up to eight rows and up to K = 1024 do not count as long
+    ([(33, 100, 256), (8, 40, 1024)], False), ([(33, 100, 256), (9, 40, 300)], True), ([(33, 100, 64), (8, 40, 1025)], True),
+    ([(33, 100, 64), (1, 300, 2048)], True)], ids=lambda s: str(s) if isinstance(s, (bool, str)) else "%dx%s" % (len(s), s[0]))
 def test_grouped_small_tiles(runner, launches, shapes, small):  # noqa: F811
     """Batches of few tiles: 32 x 32 tiles with K shared by four wavefronts.  K of every remainder of a step, of fewer steps than wavefronts, none at all;
     rows of any alignment, members with M <= 32 among the others, more members than one launch holds, both sides of the lines of the rule."""
@@ -289,7 +292,7 @@ def test_grouped_small_tiles(runner, launches, shapes, small):  # noqa: F811
     rng = np.random.default_rng(len(shapes))
     items, want, outs, keep, handles = [], [], [], [], []
     for t, (M, N, K) in enumerate(shapes):
-        pitch = (1 << 25) if small == "far apart" and t else max(1, K + (0, 3, 16)[t % 3])
+        pitch = (1 << 27) if small == "far apart" and t else max(1, K + (0, 3, 16)[t % 3])
         A, B = rng.integers(0, 256, size=(M, K), dtype=np.uint8), rng.integers(-128, 128, size=(N, K), dtype=np.int8)
         za, zb = int(rng.integers(0, 256)), 0 if t % 3 == 0 else int(rng.integers(-128, 128))
         h, packed = runner.pack(B)
