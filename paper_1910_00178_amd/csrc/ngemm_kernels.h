@@ -3432,7 +3432,7 @@ __device__ __forceinline__ void skinny_body(const GemmParams &p0, int pnl0, int 
     constexpr int BATCH = P >= 4 ? 2 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nregs = 4 * ((p.M + 7) / 8), nslices = p.Kp / 32;
-    const int mine = nslices > wave ? (nslices - wave + nwaves - 1) / nwaves : 0;   // fragments of this wavefront
+    const int mine = nslices > wave ? (int)((unsigned)(nslices - wave + nwaves - 1) / (unsigned)nwaves) : 0;   // fragments of this wavefront
 
     const int row = lane & 31;
     const bool row_ok = row < p.M;
