@@ -70,7 +70,7 @@ inline bool x64_offsets_fit(int64_t rows, int64_t pitch, int64_t extent)
 }
 
 // gemm_wavek_kernel counts in 31 bits, from a row of at most 64 of A and from one of at most four panels of 32 columns of B
-// (unpacked: rows of it)
+// (unpacked: rows of it); what lies further apart takes the same forms with addresses of 64 bits (launch_wavek_far_form)
 inline bool wavek_offsets_fit(int64_t lda_bytes, int64_t kbytes, int64_t Kp, int64_t ldb = 0)
 {
     constexpr int64_t most = (1ll << 31) - 8192;
@@ -716,6 +716,37 @@ hipError_t launch_wavek_areg_form(int form, const GemmParams &p, bool requant, b
     return wavek_areg_drains(p.M, p.N, p.K, cus) ? launch_wavek_drain<WaveK12Short>(p, requant, rows, st) : launch_wavek_areg<WaveK12Short>(p, requant, rows, st);
 }
 
+// The forms with addresses of 64 bits: 32 x 32 and 32 x 64 tiles of four wavefronts (rows of any alignment: of two), which serve forms 1 and 22 as well; they
+// form the row sums whether a zero-point needs them or not.  Instead of 64 x 128 tiles the kernels before run.
+template <class F, int ELEM, bool REQUANT, bool BRAW = false, bool AREG = false>
+hipError_t launch_wavek_far(const GemmParams &p, hipStream_t st, const RawB *rawb = nullptr)
+{
+    const int64_t tiles = ((int64_t)(p.M + F::TM * 32 - 1) / (F::TM * 32)) * ((p.N + F::TN * 32 - 1) / (F::TN * 32));
+    hipLaunchKernelGGL((gemm_wavek_far_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, BRAW, AREG>), dim3((unsigned)tiles), dim3(F::NW * 64),
+                       (WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes), st, rawb ? args_of_raw(p, *rawb) : args_of(p));
+    return hipGetLastError();
+}
+
+template <class F, int ELEM, bool REQUANT, bool BRAW = false>
+hipError_t allow_big_lds_wavek_far()
+{
+    return hipFuncSetAttribute((const void *)gemm_wavek_far_kernel<ELEM, F::TM, F::TN, F::NW, F::RING, REQUANT, BRAW, false>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, WaveKCfg<F::TM, F::TN, F::NW, F::RING>::kLdsBytes);
+}
+
+template <bool REQUANT, bool BRAW = false>
+hipError_t launch_wavek_far_aligned(int form, const GemmParams &p, hipStream_t st, const RawB *rawb = nullptr)
+{
+    return form == 11 ? launch_wavek_far<WaveK11, 1, REQUANT, BRAW>(p, st, rawb) : launch_wavek_far<WaveK12, 1, REQUANT, BRAW>(p, st, rawb);
+}
+
+hipError_t launch_wavek_far_form(int form, const GemmParams &p, bool requant, bool aligned, hipStream_t st)
+{
+    if (aligned) return requant ? launch_wavek_far_aligned<true>(form, p, st) : launch_wavek_far_aligned<false>(form, p, st);
+    if (form == 11) return requant ? launch_wavek_far<WaveK11, 1, true, false, true>(p, st) : launch_wavek_far<WaveK11, 1, false, false, true>(p, st);
+    return requant ? launch_wavek_far<WaveK12Short, 1, true, false, true>(p, st) : launch_wavek_far<WaveK12Short, 1, false, false, true>(p, st);
+}
+
 // Whether a form's workgroups, one per tile, keep within a caller's cap (budget < cus).  Up to 32 rows they need not: the
 // streaming kernels, in whose place they run there, launch a workgroup per panel as well.  (Form 0, none, has no tiles to count.)
 bool wavek_fits(int form, int64_t M, int64_t N, int64_t budget, int64_t cus)
@@ -727,9 +758,8 @@ bool wavek_fits(int form, int64_t M, int64_t N, int64_t budget, int64_t cus)
 
 // The form that takes the place of `kernel` (the streaming kernel, 64 x 64 tiles, 128 x 128 tiles with aligned rows), or 0.
 // budget: workgroups that the caller allows (the kernels for unaligned rows launch one per tile whichever runs).
-int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, int64_t lda, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
+int wavek_form_of(int kernel, int64_t M, int64_t N, int64_t K, bool aligned, bool rows, bool requant, int64_t cus, int64_t budget)
 {
-    if (!wavek_offsets_fit(lda, K, round_up(K, 64))) return 0;
     const bool small = kernel == NGEMM_KERNEL_SKINNY || kernel == NGEMM_KERNEL_TILE_64;
     if (!aligned) return small ? wavek_areg_form(M, N, K, cus) : 0;
     const int form = small || kernel == NGEMM_KERNEL_TILE_128 ? wavek_form(M, N, K, rows, requant, cus) : 0;
@@ -1004,7 +1034,7 @@ ngemm_status validate_run(const ngemm_ctx *ctx, const RunArgs &a, Route *route)
                 r = Route{t.kernel, false};
                 const int small = a.M <= kSkinnyMaxM ? NGEMM_KERNEL_SKINNY : NGEMM_KERNEL_TILE_64;
                 // (its rules look at the rows' alignment and at the zero-point, which another call may have otherwise)
-                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0 ||
+                if (t.wavek && (wavek_form_of(small, a.M, a.B->N, a.B->K, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus, workgroup_budget(ctx)) != 0 ||
                                 mid_form(NGEMM_KERNEL_AUTO, a.M, a.B->N, a.B->K, a.lda, rows_aligned(a.A, a.lda), a.needs_rowsum(), a.requant, cus,
                                          workgroup_budget(ctx)) != 0))
                     r = Route{small, true, true};
@@ -1076,9 +1106,11 @@ ngemm_status launch_run(const RunArgs &a, Route route, int num_cus, int device_c
     const bool rows_needed = a.needs_rowsum() && B->K > 0;
     // outputs of few tiles: K split over the wavefronts of a workgroup; of many: the kernel of tiles between those of the others
     if (route.wavek) {
-        const int form = wavek_form_of(kernel, a.M, B->N, B->K, a.lda, dma_ok, rows_needed, a.requant, device_cus, num_cus);
-        if (form != 0) {
-            const hipError_t we = dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
+        const int form = wavek_form_of(kernel, a.M, B->N, B->K, dma_ok, rows_needed, a.requant, device_cus, num_cus);
+        const bool far = !wavek_offsets_fit(a.lda, B->K, B->Kp);
+        if (form != 0 && !(far && form == 24)) {
+            const hipError_t we = far ? launch_wavek_far_form(form, p, a.requant, dma_ok, st)
+                                : dma_ok ? launch_wavek_form(form, p, a.requant, rows_needed, wavek_nt(a.M, B->N, B->K, device_cus), st)
                                          : launch_wavek_areg_form(form, p, a.requant, rows_needed, device_cus, st);
             return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
         }
@@ -1254,6 +1286,8 @@ ngemm_status ngemm_create(ngemm_ctx **out, int device_ordinal)
                                 S16Cfg::kLdsBytes) != hipSuccess ||
             allow_big_lds_wavek<WaveK12, 2, false, true>() != hipSuccess || allow_big_lds_wavek<WaveK22Long, 2, false, true>() != hipSuccess ||
             allow_big_lds_wavek_u8<WaveK12>() != hipSuccess || allow_big_lds_wavek_nt<WaveK12>() != hipSuccess || allow_big_lds_wavek_u8<WaveK22Long>() != hipSuccess || allow_big_lds_wavek_u8<WaveK24>() != hipSuccess ||
+            allow_big_lds_wavek_far<WaveK12, 2, false>() != hipSuccess || allow_big_lds_wavek_far<WaveK12, 1, false>() != hipSuccess ||
+            allow_big_lds_wavek_far<WaveK12, 1, true>() != hipSuccess || allow_big_lds_wavek_far<WaveK12, 1, false, true>() != hipSuccess ||
             allow_big_lds_mid<Mid256>() != hipSuccess || allow_big_lds_mid<Mid192>() != hipSuccess || allow_big_lds_mid<Mid128>() != hipSuccess ||
             allow_big_lds_mid<Mid64x192>() != hipSuccess || allow_big_lds_mid<Mid64x128>() != hipSuccess) {
             delete c;
@@ -1325,7 +1359,7 @@ ngemm_status ngemm_tune_u8s8s32(ngemm_ctx *ctx, int64_t M, const uint8_t *A_dev,
             if (!dma_ok || splitk_parts(M, B->N, B->K, workgroup_budget(ctx), &kchunk) < 2) continue;
         }
         const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0 &&
+        if (candidates[c].wavek && wavek_form_of(k, M, B->N, B->K, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0 &&
             mid_form(NGEMM_KERNEL_AUTO, M, B->N, B->K, lda, dma_ok, b_zero_point != 0, false, cus, workgroup_budget(ctx)) == 0) continue;
         // three rounds of 50 launches after a warm-up, the fastest round counts: short kernels are
         // within the noise of one another otherwise (clock ramp, first-touch effects)
@@ -1627,19 +1661,20 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M, const int16_t *A_dev
     // the looping form walk several tiles per workgroup.
     const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 256, budget = workgroup_budget(ctx);
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((B->N + bn - 1) / bn); };
-    const bool near = wavek_offsets_fit(p.lda, 2 * B->K, B->Kp);       // else the looping form, with addresses of 64 bits, in its place
-    auto fits = [&](int64_t n) { return near && (budget >= cus || n <= budget); };
+    const bool near = wavek_offsets_fit(p.lda, 2 * B->K, B->Kp);       // else the forms with addresses of 64 bits, the looping one for 64 x 64 tiles
+    auto fits = [&](int64_t n) { return budget >= cus || n <= budget; };
     hipError_t e;
     if (tiles(32, 32) <= cus && fits(tiles(32, 32))) {
-        e = launch_wavek<WaveK11, 2, false, true>(p, st);
-    } else if (tiles(32, 64) > cus && tiles(64, 64) <= cus && B->K >= 2048 && fits(tiles(64, 64))) {
+        e = near ? launch_wavek<WaveK11, 2, false, true>(p, st) : launch_wavek_far<WaveK11, 2, false>(p, st);
+    } else if (near && tiles(32, 64) > cus && tiles(64, 64) <= cus && B->K >= 2048 && fits(tiles(64, 64))) {
         e = launch_wavek<WaveK22Long, 2, false, true>(p, st);
     } else if (tiles(32, 64) <= 2 * cus && fits(tiles(32, 64))) {
-        e = launch_wavek<WaveK12, 2, false, true>(p, st);
-    } else if (B->K < S16Cfg::kMinK && !fits(tiles(64, 64))) {
+        e = near ? launch_wavek<WaveK12, 2, false, true>(p, st) : launch_wavek_far<WaveK12, 2, false>(p, st);
+    } else if ((B->K < S16Cfg::kMinK && (!near || !fits(tiles(64, 64)))) ||
+               (!near && tiles(64, 64) <= 2 * cus && tiles(128, 128) * 2 <= cus && fits(tiles(64, 64)))) {
         p.tiles_m = (int)((M + 63) / 64);
         p.tiles_n = (int)((B->N + 63) / 64);
-        const int64_t nwg = tiles(64, 64) < budget ? tiles(64, 64) : budget;
+        const int64_t most = budget >= cus ? 2 * cus : budget, nwg = tiles(64, 64) < most ? tiles(64, 64) : most;      // (two to a unit)
         hipLaunchKernelGGL((gemm_wavek_kernel<2, 2, 2, WaveK22::NW, WaveK22::RING, false, true, false, false, false, true>), dim3((unsigned)nwg),
                            dim3(WaveK22::NW * 64), (WaveKCfg<2, 2, WaveK22::NW, WaveK22::RING>::kLdsBytes), st, args_of(p, (int)nwg));
         e = hipGetLastError();
@@ -1698,8 +1733,8 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
     // the kernel that splits K over a workgroup's wavefronts: of the automatic choice only
     int form = K == 0 || !small_kernel || ctx->force_kernel != NGEMM_KERNEL_AUTO ? 0
                : aligned ? wavek_raw_form(M, N, K, cus) : wavek_raw_any_form(M, N, K, cus);
-    if ((kernel == NGEMM_KERNEL_TILE_128 && form != 24) || !wavek_fits(form, M, N, workgroup_budget(ctx), cus) ||
-        !wavek_offsets_fit(lda, K, 0, ldb)) form = 0;
+    const bool near = wavek_offsets_fit(lda, K, 0, ldb);
+    if ((kernel == NGEMM_KERNEL_TILE_128 && form != 24) || !wavek_fits(form, M, N, workgroup_budget(ctx), cus) || (!near && (!aligned || form == 24))) form = 0;
     if (form != 0 || (aligned && K > 0 && kernel != NGEMM_KERNEL_SKINNY)) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return NGEMM_ERR_DEVICE;
@@ -1715,8 +1750,11 @@ ngemm_status ngemm_run_u8s8s32_unpacked(ngemm_ctx *ctx, int64_t M, int64_t N, in
         p.Bp = nullptr;
         p.colsum = colsum;
         const RawB rawb{(const uint8_t *)B_dev, ldb};
-        if (form != 0)
-            return launch_wavek_raw_form(form, p, b_zero_point != 0, rawb, aligned, st) == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+        if (form != 0) {
+            const hipError_t we = near ? launch_wavek_raw_form(form, p, b_zero_point != 0, rawb, aligned, st)
+                                       : launch_wavek_far_aligned<false, true>(form, p, st, &rawb);
+            return we == hipSuccess ? NGEMM_OK : NGEMM_ERR_DEVICE;
+        }
         // The sums of B's columns (without weight at a_zero_point = 128) and of A's rows (at b_zero_point = 0): the
         // 64 x 64 and 128 x 128 kernels form them, the larger ones read them from passes of their own.
         const bool sums = p.za_term != 0 || b_zero_point != 0;

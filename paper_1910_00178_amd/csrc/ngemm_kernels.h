@@ -17,6 +17,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace ngemm {
 
@@ -2822,6 +2823,9 @@ __global__ __launch_bounds__(256) void gemm_s16_tile_kernel(const GemmArgs a)
 // DRAIN (with AREG): every other step waits for all that has been asked for, half of the four steps' lead (gemm_wavek_drain_kernel; the rule that
 // chooses it has the figures; as a branch in the one kernel it cost the calls that do not wait 1 %).
 // LOOP: fewer workgroups than tiles, for a caller that caps them (the others launch a workgroup per tile).
+// FAR: rows or panels too far apart for 31 bits, addresses of 64 bits (LOOP has them too; gemm_wavek_far_kernel, in the forms of the rules, row sums always).
+// us in a graph, rows 32 MiB apart, the other kernels / so: 16 x 4096 x 4096 8.2 / 5.5, 64 x 4096 x 4096 11.3 / 5.8, unpacked 16 x 4096 x 4096 20.1 / 6.1,
+// 16-bit 16 x 4096 x 4096 45 / 9.0, 1 x 4096 x 1024 16.1 / 4.6.
 // Measured (us per call in a graph, 16-bit operands, against 128 x 128 tiles and a row-sum launch): 16 x 4096 x
 // 4096 45.6 -> 8.5 (3.9 TB/s of B's planes), 64 x 4096 x 4096 46.0 -> 11.1, 512 x 768 x 768 15.0 -> 5.8, 1024^3
 // 17.6 -> 9.8.  A form with 32 x 32 wavefront tiles of a shared 64 x 64 tile and a barrier per stage took 22.9
@@ -2844,9 +2848,9 @@ struct WaveKCfg {
 };
 
 // p.A / p.lda in bytes, rows 16-byte aligned unless AREG; p.K in elements; p.Kp bytes of a packed column; p.tiles_m / n
-// count tiles of 32 TM x 32 TN.  Offsets from a tile's first row and panel have to stay below 2 GiB, but for LOOP.
+// count tiles of 32 TM x 32 TN.  Offsets from a tile's first row and panel have to stay below 2 GiB, but for LOOP and FAR.
 template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS, bool BRAW = false, bool AREG = false, bool NT = false,
-          bool LOOP = false, bool GROUP = false, bool DRAIN = false>    // (GROUP: a function of its own, the host pass takes no second caller of one)
+          bool LOOP = false, bool GROUP = false, bool DRAIN = false, bool FAR = false>  // (GROUP: a function of its own, the host pass takes no second caller)
 __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int tile, int stride)
 {
     static_assert(!BRAW || (ELEM == 1 && !REQUANT), "unpacked B: 8-bit operands, int32 output");
@@ -2856,6 +2860,8 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
     constexpr int LPS = Cfg::kLoadsPerStep, NTHREADS = Cfg::kThreads, NACC = ELEM == 1 ? 1 : 3;
     constexpr int AL = 2 * TM, BL = 2 * TN, NB = BRAW ? BL : TN;     // copies of A and of B per step, B's row blocks or panels
     constexpr bool BREG = BRAW && AREG;                  // rows of either operand with any alignment
+    constexpr bool WIDE = LOOP || FAR;                   // addresses of 64 bits
+    static_assert(!(FAR && BREG), "packed first");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2885,10 +2891,12 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
     const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)b_tile - kBias), (short)0, (int)kExtent, 0x00020000);
     auto row_of = [&](int i) { return 16 * i + t16 < p.M - m0 ? 16 * i + t16 : p.M - 1 - m0; };     // rows past M: a valid one, never stored
     auto col_of = [&](int j) { return 16 * j + t16 < p.N - n0 ? 16 * j + t16 : p.N - 1 - n0; };     // (unpacked B)
-    uint32_t a_off[AL], b_off[NB];
+    using Offset = std::conditional_t<FAR && AREG, int64_t, uint32_t>;
+    Offset a_off[AL];
+    uint32_t b_off[NB];
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
-        a_off[i] = (uint32_t)row_of(i) * (uint32_t)p.lda + (uint32_t)(a_chunk * 16) + (AREG ? 0u : kBias - 1024u * i);
+        a_off[i] = (Offset)row_of(i) * (Offset)p.lda + (Offset)(a_chunk * 16) + (AREG ? 0u : kBias - 1024u * i);
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -2947,9 +2955,9 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
     auto copies_a = [&](int t, int slot) {
         static_for<0, AL>([&](auto n) {
             constexpr int I = decltype(n)::value;
-            if constexpr (LOOP) {
+            if constexpr (WIDE) {                        // (no row, or not all 16 bytes of it: others that exist)
                 const uint8_t *src = a_tile + (int64_t)row_of(I) * p.lda + a_chunk * 16 + (int64_t)(t * NW + wave) * 64;
-                if (t >= full && (vend <= 0 || fix_a[I])) src = p.Bp;
+                if (t >= full && (vend <= 0 || fix_a[I])) src = (const uint8_t *)p.colsum;
                 __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(ring + slot + I * 1024), 16, 0, 0);
             } else {
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lptr_t)(ring + slot), 16, a_off[I], (t * NW + wave) * 64, I * 1024, 0);
@@ -2959,9 +2967,16 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
     auto copies_b = [&](int t, int slot) {
         static_for<0, BL>([&](auto n) {
             constexpr int J = decltype(n)::value;
-            if constexpr (LOOP) {
-                const int pnl = n0 / 32 + (J >> 1) < p.npanels ? n0 / 32 + (J >> 1) : p.npanels - 1;
-                const uint8_t *src = p.Bp + ((int64_t)pnl * nfrag + 2 * (t * NW + wave) + (J & 1)) * kFragBytes + lane * 16;
+            if constexpr (WIDE) {
+                const uint8_t *src;
+                if constexpr (BRAW) {
+                    src = b_tile + (int64_t)col_of(J) * ldb + a_chunk * 16 + (int64_t)(t * NW + wave) * 64;
+                    if (t >= full && (vend <= 0 || fix_b[J])) src = (const uint8_t *)p.colsum;
+                } else {                                 // (AREG requests past the last step too: the panel's first fragment, which nobody reads)
+                    const int pnl = n0 / 32 + (J >> 1) < p.npanels ? n0 / 32 + (J >> 1) : p.npanels - 1;
+                    const int step = AREG && t >= full && t != t_end ? 0 : t * NW + wave;
+                    src = p.Bp + ((int64_t)pnl * nfrag + 2 * step + (J & 1)) * kFragBytes + lane * 16;
+                }
                 __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(ring + slot + (AL + J) * 1024), 16, 0, 0);
             } else
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lptr_t)(ring + slot + (AL + (J & ~3)) * 1024), 16, b_off[BRAW ? J : J >> 1],
@@ -2969,7 +2984,7 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
         });
     };
     auto request = [&](int t, int slot) {
-        if (!LOOP && !BREG && __builtin_expect(t >= full, 0)) turn(t);
+        if (!WIDE && !BREG && __builtin_expect(t >= full, 0)) turn(t);
         if constexpr (!AREG) copies_a(t, slot);
         if constexpr (!BREG) copies_b(t, slot);
     };
@@ -3400,6 +3415,13 @@ template <int TM, int TN, int NW, int RING, bool REQUANT, bool ROWS>
 __global__ __launch_bounds__(NW * 64, (WaveKCfg<TM, TN, NW, RING>::kWavesPerSimd)) void gemm_wavek_drain_kernel(const GemmArgs args)
 {
     wavek_body<1, TM, TN, NW, RING, REQUANT, ROWS, false, true, false, false, false, true>(params_of<1, TM * 32, TN * 32>(args), 0, blockIdx.x, 0);
+}
+
+template <int ELEM, int TM, int TN, int NW, int RING, bool REQUANT, bool BRAW, bool AREG>
+__global__ __launch_bounds__(NW * 64, (WaveKCfg<TM, TN, NW, RING>::kWavesPerSimd)) void gemm_wavek_far_kernel(const GemmArgs args)
+{
+    wavek_body<ELEM, TM, TN, NW, RING, REQUANT, true, BRAW, AREG, false, false, false, false, true>(params_of<ELEM, TM * 32, TN * 32, BRAW>(args), args.ldb,
+                                                                                                  blockIdx.x, 0);
 }
 
 // ---- skinny-M kernel (M <= 32) --------------------------------------------------------------

@@ -333,10 +333,11 @@ def test_long_unaligned_rows_two_tiles_to_a_unit(runner, launches, M, N):  # noq
         ng.ngemm_packed_b_free(h)
 
 
-# Pitches at which a tile's rows lie further apart than the kernel counts: the kernels before it, and for 16-bit operands below two stages of the 128 x 128
-# kernel the looping form, serve them.  "line": 16 KiB to either side of where the rule lies (2^31 - 8192 bytes over 64 rows of A, 128 of an unpacked
+# Pitches at which a tile's rows lie further apart than the kernel counts: its forms with addresses of 64 bits serve them, for 64 x 64 tiles of 16-bit
+# operands the looping one; unpacked rows of any alignment are packed first.  "line": 16 KiB to either side of where the rule lies (2^31 - 8192 bytes over 64 rows of A, 128 of an unpacked
 # B); "far": the last row is 4 GiB and more from the first, so that an offset of 32 bits would name another one.
-FAR = [("u8", 3, 70, 200), ("u8", 40, 70, 200), ("u8 any", 40, 70, 201), ("s16", 3, 70, 100), ("s16", 40, 70, 100), ("s16", 40, 70, 300), ("raw", 5, 70, 192),
+FAR = [("u8", 3, 70, 200), ("u8", 40, 70, 200), ("u8 any", 40, 70, 201), ("s16", 3, 70, 100), ("s16", 40, 70, 100), ("s16", 40, 70, 300), ("s16", 70, 10944, 100), ("s16", 70, 10944, 300), ("u8", 40, 12000, 300),
+       ("u8", 100, 8000, 1400), ("raw", 5, 70, 192),
        ("raw", 40, 70, 192), ("raw B", 40, 5, 192), ("raw B", 40, 70, 192), ("raw any", 40, 70, 191)]
 
 
@@ -379,13 +380,11 @@ def test_rows_far_apart(runner, launches, op, M, N, K, where):  # noqa: F811
         def call(stream):
             run(runner.ctx, M, far, ld, 37, h, 3, C, N + 2, ws, wsb, stream)
     names = [name for name, _ in launches(call)]
-    wavek = [name for name in names if name.startswith("gemm_wavek_kernel<")]
-    if where == "near the line":
-        assert len(names) == len(wavek) == 1, names
-    elif op == "s16" and K < 128:
-        assert len(names) == 1 and names[0].endswith(", true>") and wavek, names       # the looping form
-    else:
-        assert not wavek, names
+    near = where == "near the line"
+    looping = op == "s16" and N > 10000 and not near
+    assert names[-1].startswith("gemm_wavek_kernel<" if near or looping else "gemm_wavek_far_kernel<"), names
+    assert names[-1].endswith(", true>") or not looping, names
+    assert (len(names) > 1) == (op == "raw any" and not near), names
     torch.cuda.synchronize()
     call(0)
     torch.cuda.synchronize()
@@ -416,7 +415,7 @@ def test_panels_far_apart(runner, launches, K, near):  # noqa: F811
     def call(stream):
         ng.ngemm_run_u8s8u8_requant_channel(runner.ctx, M, A, K, 37, h, 0, zb, scales, None, False, 128, C, N, ws, wsb, stream)
     names = [name for name, _ in launches(call)]
-    assert len(names) == 1 and names[0].startswith("gemm_wavek_kernel<") == near, names
+    assert len(names) == 1 and names[0].startswith("gemm_wavek_kernel<" if near else "gemm_wavek_far_kernel<"), names
     torch.cuda.synchronize()
     call(0)
     sums = torch.zeros((M, N), dtype=torch.float64, device="cuda")           # (whole numbers below 2^53: exact)
