@@ -3258,6 +3258,14 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
                 }
             }
             wait_vmcnt<0>();                             // what was requested past the end has come to nothing
+            // The waits above count every load of the loops among what is on its way.  A load whose step is not there is read by nobody, and the compiler would be
+            // free to leave it out (and a wait would then let a copy pass that has not landed): here all of them are.
+            if (!BREG && !brief) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int i = 0; i < AL; ++i) asm volatile("" ::"v"(va[u][i]));
+            }
         } else if (__builtin_expect(cnt > 1, 1)) {
             if (cnt >= RING) wait_vmcnt<(RING - 1) * LPS>();             // step 0 has landed
             else if (cnt == 2) wait_vmcnt<LPS>();
