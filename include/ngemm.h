@@ -333,7 +333,8 @@ ngemm_status ngemm_run_s16s16s32(ngemm_ctx *ctx, int64_t M,
  * column-major form (N rows of K contiguous int8, pitch ldb).  When the rows of A and of B are
  * 16-byte aligned (pointers and pitches multiples of 16), nothing is packed at all: the kernels copy
  * B's tiles from the caller's storage as they copy A's, and form the column sums from them (the 256 x 256
- * tiles read them from a pass of their own).  Otherwise B is packed into the workspace on the stream
+ * tiles read them from a pass of their own).  With other rows, small outputs are served without a pack pass
+ * too, by a kernel that takes both operands through registers; otherwise B is packed into the workspace on the stream
  * and multiplied at once.  The workspace must hold ngemm_unpacked_workspace_bytes(M, N, K)
  * bytes (16-byte aligned) for either way.  Result identical to ngemm_pack_b followed by
  * ngemm_run_u8s8s32.

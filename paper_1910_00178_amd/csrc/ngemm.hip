@@ -1944,11 +1944,11 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
         stream_members.clear();
     }
     auto longer_k = [](const Pending &x, const Pending &y) { return x.p.K > y.p.K; };
-    // Tiles of 32 x 32 for every member, K shared by four wavefronts, while the chip holds them all at once: two workgroups to a compute
-    // unit, and twice as many where the chains are long.  In a graph, on drawn batches with a member of M > 32, the other kernels' time over this
+    // Tiles of 32 x 32 for every member, K shared by four wavefronts, while the chip holds them all at once, two workgroups to a compute
+    // unit, and up to twice as many, in two rounds, where the chains are long.  In a graph, on drawn batches with a member of M > 32, the other kernels' time over this
     // one's: 1.02-1.05 on up to 512 tiles with a longest K of 65 to 256, 1.12 up to 512, 1.22 up to 1024, 1.27 up to 1536; 1.4-1.5 from 2048 on, up
     // to 1024 tiles; on 513 to 1024 tiles with K up to 1024 0.9, and from 1025 tiles on 0.5-0.8 (K over 2048: 1.15).  Between 1536 and 2048 the 64 x 64
-    // tiles stay.  Groups of skinny members alone do not gain (0.9-1.0): their panels have eight wavefronts to a workgroup already.  Up to K = 1024 a
+    // tiles stay (on 1460 drawn batches 1.35 x on up to 512 tiles, 1.2 up to 768 and 1.1 up to 1024, one in eight of those slower: left there).  Groups of skinny members alone do not gain (0.9-1.0): their panels have eight wavefronts to a workgroup already.  Up to K = 1024 a
     // member of up to eight rows is no long chain: as a panel it takes no longer than here, so the line is drawn by the others.  (Batches whose only K over
     // 256 was such a member's ran at 0.89-1.15 x, 1.01 on average; with a longer K, or more rows, at 1.0-1.3.)
     int64_t tiles32 = 0, longest = 0, chain = 0;

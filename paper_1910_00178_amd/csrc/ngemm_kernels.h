@@ -552,7 +552,7 @@ struct TileCfg {
 __device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int nxcd, int &tm, int &tn)
 {
     // (a division by a number that only the launch knows is 25 dependent instructions ahead of a workgroup's first load, some 50 ns: a
-    // power of two of XCDs, up to GM tile rows and the last division, by at most GM, do without)
+    // power of two of XCDs, up to GM tile rows and the last division, by at most GM, do without; 4600 drawn small outputs 1.02-1.03 x, by this alone)
     const unsigned nb = (unsigned)tiles_m * (unsigned)tiles_n, n = (unsigned)nxcd, ubid = (unsigned)bid;
     unsigned q, local;
     if ((n & (n - 1)) == 0) {
@@ -2840,7 +2840,9 @@ struct WaveKCfg {
     static constexpr int kPartBytes = TM * 32 * kPitch * 4;
     static constexpr int kEpiBytes = NW * (kPartBytes + (TM + TN) * 32 * 4);
     static constexpr int kLdsBytes = NW * kWaveBytes > kEpiBytes ? NW * kWaveBytes : kEpiBytes;
-    static constexpr int kPerCu = 160 * 1024 / kLdsBytes;  // workgroups that share a compute unit: their registers have to fit as well
+    static constexpr int kPerCu = 160 * 1024 / kLdsBytes;  // workgroups that share a compute unit by their LDS
+    // What the compiler keeps registers free for: all of them but for five workgroups of two wavefronts, of which it is four (those kernels take up to 94
+    // registers, with which the fifth fits as well), and for forms with both operands through registers (two workgroups of 32 x 64 tiles in the place of three).
     static constexpr int kWavesPerSimd = NW * kPerCu >= 4 ? NW * kPerCu / 4 : 1;
     static_assert((RING - 1) * kLoadsPerStep <= 63, "vmcnt range");
     static_assert(kLdsBytes <= 160 * 1024, "LDS of a compute unit");
@@ -3613,8 +3615,8 @@ __global__ __launch_bounds__(512) void gemm_group_skinny_kernel(const GroupParam
 // have to start with it.  For groups with a member whose rows or panels lie too far apart for the 32-bit offsets of gemm_group_mid_kernel, and for
 // groups of few tiles with a short K, on which that one is slower (64 odd shapes in a graph: 16.9 us there, 18.3 here).
 //
-// The form with 32 x 32 tiles is for groups of few tiles, as many as the chip holds at once: such a launch lasts as long as its longest chain
-// over K, and WGM * WGN wavefronts that share K (wavek_body, every member's tiles, A by way of registers so that rows of any alignment
+// The form with 32 x 32 tiles is for groups of few tiles, as many as the chip holds at once or, with a long K, twice that: such a launch lasts as long as its
+// longest chain over K, and WGM * WGN wavefronts that share K (wavek_body, every member's tiles, A by way of registers so that rows of any alignment
 // do) cut it to a quarter.  In a graph, 100 to 512 tiles of members with K up to 1024: 5.9 us on 64 x 64 tiles, 4.8 here; the launch says where the line lies.
 template <int BM, int BN, int WGM, int WGN, int BK>
 __global__ __launch_bounds__(WGM * WGN * 64, (BM == 32 ? WaveKCfg<1, 1, WGM * WGN, 4>::kWavesPerSimd : 1)) void gemm_group_kernel(const GroupParams g)
