@@ -1951,7 +1951,9 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
     // tiles stay (on 1460 drawn batches 1.35 x on up to 512 tiles, 1.2 up to 768 and 1.1 up to 1024, one in eight of those slower: left there).  Groups of skinny members alone do not gain (0.9-1.0): their panels have eight wavefronts to a workgroup already.  Up to K = 1024 a
     // member of up to eight rows is no long chain: as a panel it takes no longer than here, so the line is drawn by the others.  (Batches whose only K over
     // 256 was such a member's ran at 0.89-1.15 x, 1.01 on average; with a longer K, or more rows, at 1.0-1.3.)
-    int64_t tiles32 = 0, longest = 0, chain = 0;
+    // In two rounds they lead only while the second one is short, that is while the tiles with more than a third of the longest K fit the first: of 5100 drawn
+    // batches with a K of 2048 and more on 513 to 1024 tiles, those 1.22 x, the others 0.92 (512 x 2048 x 2048 alone 0.75).
+    int64_t tiles32 = 0, longest = 0, chain = 0, long32 = 0;
     bool near = true;
     for (const std::vector<Pending> *v : {&tile_members, &skinny_members})
         for (const Pending &m : *v) {
@@ -1960,8 +1962,11 @@ ngemm_status ngemm_run_batched_u8s8s32(ngemm_ctx *ctx, int count, const ngemm_pr
             if (m.p.M > 8 || m.p.K > 1024) chain = std::max<int64_t>(chain, m.p.K);
             near = near && wavek_offsets_fit(m.p.lda, m.p.K, m.p.Kp);
         }
+    for (const std::vector<Pending> *v : {&tile_members, &skinny_members})
+        for (const Pending &m : *v)
+            if (3 * (int64_t)m.p.K > longest) long32 += (int64_t)((m.p.M + 31) / 32) * m.p.npanels;
     if (!tile_members.empty() && stream_members.empty() && near &&
-        ((chain > 256 && longest <= 1536 && tiles32 <= 2 * cus) || (longest >= 2048 && tiles32 <= 4 * cus))) {
+        ((chain > 256 && longest <= 1536 && tiles32 <= 2 * cus) || (longest >= 2048 && tiles32 <= 4 * cus && long32 <= 2 * cus))) {
         small_tiles = true;
         skinny_members.insert(skinny_members.end(), tile_members.begin(), tile_members.end());
         tile_members.clear();

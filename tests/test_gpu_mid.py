@@ -279,7 +279,10 @@ def test_grouped_tiles_of_few_short_chains(runner, launches, shapes, want):  # n
     ([(40, 70, 4113), (3, 200, 3001), (97, 33, 2048), (65, 65, 0), (32, 32, 130), (33, 1, 2111)], True),
     ([(40, 70, 4113), (35, 40, 16)], "far apart"),                                            # the second one's rows
     ([(64, 8192, 300)], True), ([(64, 8193, 300)], False), ([(33, 100, 257)], True), ([(33, 100, 256)], False), ([(33, 100, 1537)], False),
-    ([(33, 100, 2047)], False), ([(512, 2048, 2048)], True), ([(512, 2049, 2048)], False), ([(32, 100, 700)] * 3, False),
+    ([(33, 100, 2047)], False), ([(32, 100, 700)] * 3, False),
+    # two rounds: the tiles with more than a third of the longest K have to fit the first
+    ([(512, 1024, 2048)], True), ([(512, 1025, 2048)], False), ([(512, 2048, 2048)], False), ([(512, 1024, 2048), (512, 1024, 682)], True),
+    ([(512, 1024, 2048), (512, 1024, 683)], False), ([(512, 1024, 2048), (512, 1025, 682)], False),
     ([(33, 40, 300 + i) for i in range(80)], True),
     # members of up to eight rows and up to K = 1024 do not count as long
     ([(33, 100, 256), (8, 40, 1024)], False), ([(33, 100, 256), (9, 40, 300)], True), ([(33, 100, 64), (8, 40, 1025)], True),
