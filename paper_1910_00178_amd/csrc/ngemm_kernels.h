@@ -2863,6 +2863,7 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
     constexpr int AL = 2 * TM, BL = 2 * TN, NB = BRAW ? BL : TN;     // copies of A and of B per step, B's row blocks or panels
     constexpr bool BREG = BRAW && AREG;                  // rows of either operand with any alignment
     constexpr bool WIDE = LOOP || FAR;                   // addresses of 64 bits
+    constexpr bool SHORT = TM == 1 || NW == 2;           // calls of one step per wavefront are among this form's
     static_assert(!(FAR && BREG), "packed first");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -3268,8 +3269,9 @@ __device__ __forceinline__ void wavek_body(const GemmParams &p, int64_t ldb, int
 #pragma unroll
                     for (int i = 0; i < AL; ++i) asm volatile("" ::"v"(va[u][i]));
             }
-        } else if (__builtin_expect(cnt > 1, 1)) {
+        } else if (!SHORT || __builtin_expect(cnt > 1, 1)) {
             if (cnt >= RING) wait_vmcnt<(RING - 1) * LPS>();             // step 0 has landed
+            else if (!SHORT && cnt == 1) wait_vmcnt<0>();
             else if (cnt == 2) wait_vmcnt<LPS>();
             else wait_vmcnt<(RING > 3 ? 2 : 0) * LPS>();
             __builtin_amdgcn_sched_barrier(0);
